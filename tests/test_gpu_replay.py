@@ -60,6 +60,21 @@ def test_random_small(g10, seed):
     h.close()
 
 
+@pytest.mark.parametrize("seed", range(12))
+def test_many_waits(g10, seed):
+    """Kernels far faster than profiled: nearly every use waits, several times within 64 events and on both sides of
+    each 64-event boundary; and slow ones beside them, so that runs without a wait cross the boundaries too."""
+    w = traces.random_small(9500 + seed, K=30 + 3 * seed, N=16 + 5 * seed, max_uses=6)
+    h, v, args = run_both(g10, w)
+    args = dict(args, gpu_cap=int(v.peak) // 4, host_cap=int(v.peak), bw_out=(400, 900), bw_in=(500, 800))
+    p = v.plan(**args)
+    assert_plan_equal(h.plan(**args), p)
+    tr = w.trace
+    mixed = np.where(np.arange(tr.K) % 7 < 2, tr.dur_ns * np.uint64(9), np.uint64(1))
+    both(h, p, [np.ones(tr.K, np.uint64), mixed.astype(np.uint64), np.maximum(tr.dur_ns // 100, 1).astype(np.uint64)])
+    h.close()
+
+
 @pytest.mark.parametrize("cfg", [1, 2, 3, 4])
 def test_configs(g10, cfg):
     w = traces.config(cfg)
