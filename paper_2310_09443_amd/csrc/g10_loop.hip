@@ -460,7 +460,12 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   // bits over the pass's migrations: for a transfer-window job, A = the migrations of that
   // destination whose window meets the chunk; for a pressure job, A = those whose absent window
   // cuts the chunk, B = those that cover it whole.  (Host occupancy has no such job: see J_HQ.) --
+  // Slot s0 + 256 st + 64 i + lane belongs to lane `lane` (i = 0..3): every load and store of a job
+  // covers 64 neighbouring slots.  A workgroup has one texture unit, about one cache line per clock,
+  // and up to eight jobs run at once: with four neighbouring slots per lane and one 64-byte record
+  // per slot a rewrite touched 64 lines per instruction, now 8 (see the tables of px).
   auto run_jobs = [&]() {
+    ulonglong2* const px = reinterpret_cast<ulonglong2*>(tl.px);
     const u32 nj = S->njobs;
     for (u32 jb = wave; jb < nj; jb += LW) {
       const u64 jw = jobs[jb];
@@ -472,62 +477,57 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         // slots after the first window slot is rewritten from a scan of the new values
         const bool out = type < J_FI0;
         const u32 d = (type - J_FO0) & 1u;
-        const u32 arr = (out ? A_FO : A_FI) + d, w = out ? w_fo(d) : w_fi(d);
+        const u32 arr = (out ? A_FO : A_FI) + d;
         u64* fr = tl.fre + (u64)((out ? 0u : 2u) + d) * tl.Kp;
+        ulonglong2* tab = px + (u64)((out ? T_FO : T_FI) + d) * tl.Kp;
         const u64 bc = base[(u64)arr * nb1 + c], ball = base[(u64)arr * nb1 + nch];
         const u32 mask = ma_;                            // the migrations of this destination whose window meets the chunk
         u32 first = NONE32;
-        for (u32 pb = mask; pb; pb &= pb - 1) {
-          const Winner& W = S->mem[__builtin_ctz(pb)];
-          const u32 f = first_covered(s0, s1, K, out ? W.L1 : W.b + 1, out ? W.a - 1 : W.R - 1);
-          first = f < first ? f : first;
-        }
         u64 carry = 0;
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane * 4u;
-          u64 f[4], old[4], tau[4], ref[4];
-          u32 jj[4];
+          const u32 j0 = s0 + st * 256u + lane;
+          u64 f[4], old[4];
+          bool took[4];
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i;
+            const u32 j = j0 + i * 64u;
             f[i] = j < K ? fr[j] : 0ull;
-            jj[i] = NONE32; tau[i] = 0; ref[i] = 0;
-            if (j < K)
-              for (u32 pb = mask; pb; pb &= pb - 1) {
-                const Winner& W = S->mem[__builtin_ctz(pb)];
-                const u32 p = in_doubled(j, K, out ? W.L1 : W.b + 1, out ? W.a - 1 : W.R - 1);
-                if (p != NONE32) { jj[i] = p; tau[i] = out ? W.tau_o : W.tau_i; ref[i] = out ? W.fo_base : W.fi_end; }
-              }
-            old[i] = jj[i] != NONE32 ? tl.px[(u64)j * PX + w] : 0ull;       // free time of the chunk before the slot
+            old[i] = j < K ? tab[j].x : 0ull;            // free time of the chunk before the slot
+            took[i] = false;
           }
-          u64 lsum = 0;
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i) {
-            if (jj[i] != NONE32) {
-              const u64 before_slot = (jj[i] >= K ? ball : 0ull) + bc + old[i];  // free time before slot jj
-              u64 take;
-              if (out) {                           // eviction: earliest free time of the window first
-                const u64 before = before_slot - ref[i];
-                const u64 used = before < tau[i] ? before : tau[i];
-                take = f[i] < tau[i] - used ? f[i] : tau[i] - used;
-              } else {                             // prefetch: latest free time first
-                const u64 after = ref[i] - (before_slot + f[i]);
-                const u64 used = after < tau[i] ? after : tau[i];
-                take = f[i] < tau[i] - used ? f[i] : tau[i] - used;
-              }
-              if (take) { f[i] -= take; fr[j0 + i] = f[i]; }
+          for (u32 pb = mask; pb; pb &= pb - 1) {
+            const Winner& W = S->mem[__builtin_ctz(pb)];
+            const u32 x = out ? W.L1 : W.b + 1, y = out ? W.a - 1 : W.R - 1;
+            const u64 tau = out ? W.tau_o : W.tau_i, ref = out ? W.fo_base : W.fi_end;
+            if (st == 0) {
+              const u32 fc = first_covered(s0, s1, K, x, y);
+              first = fc < first ? fc : first;
             }
-            lsum += f[i];
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u32 j = j0 + i * 64u;
+              const u32 jj = j < K ? in_doubled(j, K, x, y) : NONE32;
+              if (jj != NONE32) {
+                const u64 before_slot = (jj >= K ? ball : 0ull) + bc + old[i];  // free time before slot jj
+                // eviction: earliest free time of the window first; prefetch: latest free time first
+                const u64 gone = out ? before_slot - ref : ref - (before_slot + f[i]);
+                const u64 used = gone < tau ? gone : tau;
+                const u64 take = f[i] < tau - used ? f[i] : tau - used;
+                f[i] -= take;
+                took[i] = take != 0;
+              }
+            }
           }
-          const u64 inc = wave_scan_incl(lsum);
-          u64 run = carry + inc - lsum;
+          u64 inc[4];
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i) inc[i] = wave_scan_incl(f[i]);
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i;
-            if (j < K && j > first) tl.px[(u64)j * PX + w] = run;
-            run += f[i];
+            const u32 j = j0 + i * 64u;
+            if (took[i]) fr[j] = f[i];
+            if (j < K && j > first) tab[j].x = carry + inc[i] - f[i];
+            carry += wave_last(inc[i]);
           }
-          carry += wave_last(inc);
         }
         if (lane == 0) tot[(u64)arr * nch + c] = carry;
       } else if (type == J_P) {
@@ -538,62 +538,68 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u64 lz0 = lazyP[c];                        // the lazy add before this pass
         u64 lz_full = 0;
         const u32 part = ma_;                            // migrations whose window cuts the chunk; mb_: those that cover it whole
-        for (u32 pb = mb_; pb; pb &= pb - 1) lz_full += S->mem[__builtin_ctz(pb)].s;
-        const u64 lz = lz0 + lz_full;
-        u64 mn = NONE64;
+        u64 mn = NONE64, carry = 0;
         u32 first = NONE32;                              // first slot that dropped under the capacity
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane * 4u;
+          const u32 j0 = s0 + st * 256u + lane;
+          u64 p[4], v[4], sub[4];
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i) {
+            const u32 j = j0 + i * 64u;
+            p[i] = j < K ? tl.P[j] : 0ull;
+            v[i] = j < K ? tl.dur[j] : 0ull;
+            sub[i] = 0;
+          }
+          if (st == 0) for (u32 pb = mb_; pb; pb &= pb - 1) lz_full += S->mem[__builtin_ctz(pb)].s;
+          const u64 lz = lz0 + lz_full;
+          for (u32 pb = part; pb; pb &= pb - 1) {
+            const Winner& W = S->mem[__builtin_ctz(pb)];
+            const u32 x = W.a, y = W.b;
+            const u64 s = W.s;
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u32 j = j0 + i * 64u;
+              if (j < K && in_doubled(j, K, x, y) != NONE32) sub[i] += s;
+            }
+          }
           u32 myfirst = NONE32;
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i;
+            const u32 j = j0 + i * 64u;
+            bool over = false;
             if (j < K) {
-              u64 p = tl.P[j];
-              const u64 before = p - lz0;                // pressure before this pass
-              u64 sub = 0;
-              for (u32 pb = part; pb; pb &= pb - 1) {
-                const Winner& W = S->mem[__builtin_ctz(pb)];
-                if (in_doubled(j, K, W.a, W.b) != NONE32) sub += W.s;
-              }
-              if (sub) { p -= sub; tl.P[j] = p; }
-              const u64 act = p - lz;
-              if (act > cap) mn = act < mn ? act : mn;
+              const u64 before = p[i] - lz0, act = p[i] - sub[i] - lz;     // pressure before and after this pass
+              if (sub[i]) tl.P[j] = p[i] - sub[i];
+              over = act > cap;
+              if (over) mn = act < mn ? act : mn;
               else if (before > cap && myfirst == NONE32) myfirst = j;
             }
+            if (!over) v[i] = 0;
           }
-          const u32 stfirst = wave_min(myfirst);
-          if (first == NONE32) first = stfirst;
+          if (first == NONE32) {
+            first = wave_min(myfirst);
+            if (first != NONE32 && st) carry = px[s0 + st * 256u].y;   // (nothing before this slot changes)
+          }
+          if (first != NONE32) {                         // rewrite the prefix of the slots after it
+            u64 inc[4];
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) inc[i] = wave_scan_incl(v[i]);
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u32 j = j0 + i * 64u;
+              if (j < K && j > first) {
+                const u64 run = carry + inc[i] - v[i];
+#pragma unroll
+                for (u32 t = 0; t < 4; ++t) px[(u64)t * tl.Kp + j].y = run;      // the four copies of OT
+              }
+              carry += wave_last(inc[i]);
+            }
+          }
         }
         mn = wave_min(mn);
-        if (lane == 0) { minOver[c] = mn; lazyP[c] = lz; }
-        if (first != NONE32) {                           // rewrite the prefix of the slots after it
-          u64 carry = 0;
-          for (u32 st = 0; st < tl.spt; ++st) {
-            const u32 j0 = s0 + st * 256u + lane * 4u;
-            u64 v[4];
-            u64 lsum = 0;
-#pragma unroll
-            for (u32 i = 0; i < 4; ++i) {
-              const u32 j = j0 + i;
-              v[i] = 0;
-              if (j < K && tl.P[j] - lz > cap) v[i] = tl.dur[j];
-              lsum += v[i];
-            }
-            const u64 inc = wave_scan_incl(lsum);
-            u64 run = carry + inc - lsum;
-#pragma unroll
-            for (u32 i = 0; i < 4; ++i) {
-              const u32 j = j0 + i;
-              if (j < K && j > first) {
-                ulonglong2* rec = reinterpret_cast<ulonglong2*>(tl.px + (u64)j * PX);
-                rec[0].y = run; rec[1].y = run; rec[2].y = run; rec[3].y = run;   // the four copies of OT
-              }
-              run += v[i];
-            }
-            carry += wave_last(inc);
-          }
-          if (lane == 0) { tot[(u64)A_OT * nch + c] = carry; S->ot_changed = 1; }
+        if (lane == 0) {
+          minOver[c] = mn; lazyP[c] = lz0 + lz_full;
+          if (first != NONE32) { tot[(u64)A_OT * nch + c] = carry; S->ot_changed = 1; }
         }
       } else if (type == J_CLIP) {
         // clipped area of the winner's absent window inside this chunk: per slot over the
@@ -603,10 +609,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u64 lz = lazyP[c];
         u64 alo = 0, ahi = 0;
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane * 4u;
+          const u32 j0 = s0 + st * 256u + lane;
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i;
+            const u32 j = j0 + i * 64u;
             if (j < K && in_doubled(j, K, wa, wb) != NONE32) {
               const u64 act = tl.P[j] - lz;
               if (act > cap) {
@@ -637,10 +643,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u32 from = hmat[c], to = (u32)S->n_mig;
         u64 m_cov = 0, m_all = 0;
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane * 4u;
+          const u32 j0 = s0 + st * 256u + lane;
           u64 h[4];
 #pragma unroll
-          for (u32 i = 0; i < 4; ++i) h[i] = j0 + i < K ? tl.H[j0 + i] : 0ull;
+          for (u32 i = 0; i < 4; ++i) h[i] = j0 + i * 64u < K ? tl.H[j0 + i * 64u] : 0ull;
           if (bring) {
             for (u32 r0 = from; r0 < to; r0 += 64u) {
               const u32 r = r0 + lane;
@@ -656,15 +662,15 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
                 const u64 sz = read_lane64(qs, l);
 #pragma unroll
                 for (u32 i = 0; i < 4; ++i)
-                  if (j0 + i < K && in_doubled(j0 + i, K, x, y - 1) != NONE32) h[i] += sz;
+                  if (j0 + i * 64u < K && in_doubled(j0 + i * 64u, K, x, y - 1) != NONE32) h[i] += sz;
               }
             }
 #pragma unroll
-            for (u32 i = 0; i < 4; ++i) if (j0 + i < K) tl.H[j0 + i] = h[i];
+            for (u32 i = 0; i < 4; ++i) if (j0 + i * 64u < K) tl.H[j0 + i * 64u] = h[i];
           }
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i;
+            const u32 j = j0 + i * 64u;
             if (j < K) {
               const u64 act = h[i] + lz;
               m_all = act > m_all ? act : m_all;

@@ -32,12 +32,12 @@
 //                         2 flash-in, 3 host-in)
 //   H[K], lazyH[nch]      host bytes parked in slot j = H[j] + lazyH[chunk(j)]
 //   hmax[nch]             maximum of that over the chunk
-//   px[K][8]              chunk-local exclusive prefix sums, one 64-byte record
-//                         per slot: {FO0, OT, FO1, OT, FI0, OT, FI1, OT} with
+//   px[4][Kp]             chunk-local exclusive prefix sums, four tables of 16-byte
+//                         pairs: {FO0, OT}, {FO1, OT}, {FI0, OT}, {FI1, OT} with
 //                         OT over-capacity time dur*[pressure > cap], FOd / FId
-//                         free out / in channel time of destination d.  The
-//                         pairs a candidate needs at one slot are 16-byte
-//                         aligned neighbours.
+//                         free out / in channel time of destination d.  What a
+//                         candidate needs at one slot is one 16-byte load, and a
+//                         chunk's rewrite of one table touches whole lines.
 //   tot[5][nch], base[5][nch+1]   chunk totals and their exclusive prefix
 //                         (arrays: 0 OT, 1+d FOd, 3+d FId); a prefix up to
 //                         slot j is base[chunk(j)] + px[j].
@@ -171,9 +171,7 @@ __global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, cons
   for (u32 i = 0; i < tl.spt; ++i) {
     const u32 j = j0 + i;
     if (j >= K) break;
-    u64* rec = tl.px + (u64)j * PX;
-    rec[0] = run_d; rec[2] = run_d; rec[4] = run_d; rec[6] = run_d;
-    rec[1] = run_o; rec[3] = run_o; rec[5] = run_o; rec[7] = run_o;
+    for (u32 t = 0; t < 4; ++t) reinterpret_cast<ulonglong2*>(tl.px)[(u64)t * tl.Kp + j] = ulonglong2{run_d, run_o};
     tl.otc[j] = run_o;
     const u64 d = tl.dur[j];
     run_d += d;
@@ -470,7 +468,7 @@ static void work_layout(PlanWork* w, Arena& ar) {
     if (w->has_cache) { ar.take(&w->cd[i].cv, w->cap_pad); ar.take(&w->cd[i].ce, w->cap_pad); }
   }
   ar.take(&w->P, K); ar.take(&w->fre, (u64)4 * w->Kp); ar.take(&w->H, K);
-  ar.take(&w->px, (u64)PX * K); ar.take(&w->otc, (u64)K + 1);
+  ar.take(&w->px, (u64)PX * w->Kp); ar.take(&w->otc, (u64)K + 1);
   ar.take(&w->base0, (u64)w->nch + 1);
   ar.take(&w->g_base, (u64)N_ARR * (w->nch + 1));
   ar.take(&w->g_tot, (u64)N_ARR * w->nch);
@@ -502,7 +500,7 @@ static int work_alloc(g10_plan_s* h, u32 max_chunks, bool cache, PlanWork** slot
   const u64 C = h->n_periods;
   w->K = K; w->C = C;
   w->device = h->device;
-  w->Kp = (K + 3u) & ~3u;
+  w->Kp = slots_padded(K);
   w->spt = 1; w->shift_ch = 8;
   w->max_chunks = max_chunks;
   w->has_cache = cache;

@@ -23,8 +23,10 @@ constexpr u32 GUESS_SHIFT_MAX = 24;            // the keys resolve no finer step
 constexpr u64 NONE64 = ~0ull;
 constexpr u32 NONE32 = 0xffffffffu;
 
-__device__ __forceinline__ u32 w_fo(u32 d) { return 2 * d; }          // word of FOd in a slot record (OT follows)
-__device__ __forceinline__ u32 w_fi(u32 d) { return 4 + 2 * d; }      // word of FId (OT follows)
+// The chunk-local prefixes of the slots: four tables of 16-byte pairs, {FOd, OT} for d = 0, 1 and {FId, OT} for
+// d = 0, 1, Kp pairs each.
+enum { T_FO = 0, T_FI = 2 };                                          // table of destination d: T_FO + d, T_FI + d
+__host__ __device__ __forceinline__ u32 slots_padded(u32 K) { return (K + 3u) & ~3u; }
 
 struct Ctl {
   // parameters
@@ -63,7 +65,7 @@ struct Timelines {
   u64* P;
   u64* fre;                   // [4][Kp]
   u64* H;
-  u64* px;                    // [K][PX]
+  u64* px;                    // [4][Kp] pairs: chunk-local prefixes, a table per channel (T_FO, T_FI)
   u64* otc;                   // [K + 1] over-capacity time before every slot, before any eviction
   u32 K, Kp, nch, spt, shift_ch;   // chunk = 256 * spt = 1 << shift_ch slots
 };
@@ -177,7 +179,7 @@ __device__ __forceinline__ void costs_of(const Machine& mc, u64 s, u64& c0, u64&
   c1 = ceil_div_x1000(s, mc.bwo1, mc.ivo1) + ceil_div_x1000(s, mc.bwi1, mc.ivi1);
 }
 
-struct PrefixView {           // slot records in HBM / L2, level 1 in LDS
+struct PrefixView {           // slot tables in HBM / L2, level 1 in LDS
   const u64* px;
   const u64* base;            // [5][nch + 1]
   u32 K, nch, shift_ch;
@@ -190,7 +192,9 @@ struct Score {
   bool strike0, strike1;      // the destination can never count again
 };
 
-__device__ __forceinline__ ulonglong2 ld2(const u64* p) { return *reinterpret_cast<const ulonglong2*>(p); }
+__device__ __forceinline__ ulonglong2 ld_pair(const PrefixView& pv, u32 table, u32 j) {
+  return reinterpret_cast<const ulonglong2*>(pv.px)[(u64)table * slots_padded(pv.K) + j];
+}
 
 // Both destinations' record pairs are gathered before anything is used.  A
 // destination is struck when its channel cannot carry the transfer any more
@@ -217,15 +221,15 @@ __device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Mac
     sa0 = A.z >= K; sb0 = A.w + 1 >= K;
     const u32 ja = sa0 ? A.z - K : A.z, jb = sb0 ? A.w + 1 - K : A.w + 1;
     ca0 = ja >> pv.shift_ch; cb0 = jb >> pv.shift_ch;
-    qL0 = ld2(pv.px + (u64)jL * PX + 0); qR0 = ld2(pv.px + (u64)jR * PX + 4);      // {FO0, OT} {FI0, OT}
-    qa0 = ld2(pv.px + (u64)ja * PX + 0); qb0 = ld2(pv.px + (u64)jb * PX + 4);
+    qL0 = ld_pair(pv, T_FO + 0, jL); qR0 = ld_pair(pv, T_FI + 0, jR);      // {FO0, OT} {FI0, OT}
+    qa0 = ld_pair(pv, T_FO + 0, ja); qb0 = ld_pair(pv, T_FI + 0, jb);
   }
   if (v1) {
     sa1 = B.x >= K; sb1 = B.y + 1 >= K;
     const u32 ja = sa1 ? B.x - K : B.x, jb = sb1 ? B.y + 1 - K : B.y + 1;
     ca1 = ja >> pv.shift_ch; cb1 = jb >> pv.shift_ch;
-    qL1 = ld2(pv.px + (u64)jL * PX + 2); qR1 = ld2(pv.px + (u64)jR * PX + 6);      // {FO1, OT} {FI1, OT}
-    qa1 = ld2(pv.px + (u64)ja * PX + 2); qb1 = ld2(pv.px + (u64)jb * PX + 6);
+    qL1 = ld_pair(pv, T_FO + 1, jL); qR1 = ld_pair(pv, T_FI + 1, jR);      // {FO1, OT} {FI1, OT}
+    qa1 = ld_pair(pv, T_FO + 1, ja); qb1 = ld_pair(pv, T_FI + 1, jb);
   }
   u64 fo0_L = 0, fi0_R = 0, fo1_L = 0, fi1_R = 0;
   if (v0) {
