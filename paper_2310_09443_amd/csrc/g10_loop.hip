@@ -9,7 +9,7 @@ using namespace g10;
 
 namespace {
 
-struct Winner {               // what a commit needs of the winning candidate
+struct alignas(16) Winner {   // what a commit needs of the winning candidate
   u64 hi, lo;                 // benefit
   u64 cost;                   // eviction + prefetch time (ranking by benefit / cost only)
   u64 s, fo_base, fi_end;     // size; free out-channel time before L1; free in-channel time before R
@@ -20,7 +20,7 @@ struct Winner {               // what a commit needs of the winning candidate
   u32 kr;                     // kU if the policy sends the candidate to flash while host could take it too (a flash
                               // reservation in its transfer windows would move it to host, where its benefit may be
                               // larger), else 0
-  u32 pad;
+  u32 slot;                   // its entry in the list of the pass (NONE32: it has none)
 };
 
 // Ranking by benefit / cost keeps a bound per candidate that holds whichever destination the
@@ -62,19 +62,20 @@ static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid o
 constexpr u32 MC_GUESS_SHIFT_MIN = 4;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
 constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the second and later migrations
 
-struct Shared {               // small per-pass state of the loop workgroup
+struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
   Winner wave_win[LW];        // best of every wavefront
-  Winner list[LIST_MAX];      // the other candidates whose bound exceeds every bound not looked at one by one
+  Winner list[LIST_MAX];      // the candidates whose bound exceeds every bound not looked at one by one
+  uint4 listA[LIST_MAX], listB[LIST_MAX];   // ... their periods and windows as in Cands; a committed one has no window left
   u32 wave_f2[LW];            // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
                               // host-capacity test needs the exact per-slot maximum
   u32 by_floor, touched;      // the selection ended because the next candidate did not clear the floor; timelines (a bit
                               // per array of level 1) whose chunk totals change in this pass
+  u32 fast, pad1;             // the pass's migrations were picked from the list without an arg-max over all threads
   u32 Fkeep, more;            // the floor of the pass; another round of commits follows from the same list
   u64 more_rounds, list_rescored;   // such rounds made; list entries scored again for them (statistics)
-  u32 sel[MAXM];              // list entries picked, in order
   u64 hq;                     // host-capacity query: maximum over the period
   u64 acc[3];                 // clipped area being summed: bits 0..31, 32..63 and 64.. of the terms, added apart
   u64 evals, refused;         // clipped areas computed; of those, how many came out below the bound
@@ -161,7 +162,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   const LoopArgs a = plans[blockIdx.x];        // one workgroup per plan
   const Timelines tl = a.tl;
   const u32 nch = tl.nch, nb1 = nch + 1, K = tl.K, CH = 1u << tl.shift_ch, nt = a.nt, ns = (nt + 63) / 64;
-  u64* base = (u64*)smem;                               // [5][nch + 1]
+  Shared* S = (Shared*)smem;
+  u64* base = (u64*)(S + 1);                            // [5][nch + 1]
   u64* tot = base + (u64)N_ARR * nb1;                   // [5][nch]
   u64* lazyP = tot + (u64)N_ARR * nch;
   u64* minOver = lazyP + nch;
@@ -170,8 +172,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   u64* smark = hmax + nch;                              // [ns] tiles of a group of 64 scored in this pass
   u64* scr = smark + ns;                                // [4 * LW]
   u64* jobs = scr + 4 * LW;                             // [8 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
-  Shared* S = (Shared*)(jobs + 8 * nch + 8);
-  u32* keys = (u32*)(S + 1);                            // [nt]  bound of every tile
+  u32* keys = (u32*)(jobs + 8 * nch + 8);               // [nt]  bound of every tile
   u32* skeys = keys + nt;                               // [ns]  largest bound of every group of 64 tiles
   u32* hmat = skeys + ns;                               // [nch] host occupancy: migrations (by index) already added to the chunk's slots
   u32* hpend = hmat + nch;                              // [nch] ... and whether a later one that cuts the chunk is still missing
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   u32 pass_units = 0;           // units of 256 candidates scored in the current pass (the same in every thread)
   // this thread's best candidate of the pass
   Winner mine;
-  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.pad = 0;
+  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   u32 floor2 = 0;               // largest bound among the candidates this thread scored in the pass other than `mine`
   u32 cur_iter = 0;             // number of the current pass (the stamp of the values computed in it)
 
@@ -385,6 +386,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       const bool ok_any = rr.ok0 || rr.ok1;
       const u32 d = rr.ok0 ? 0u : 1u;
       const u64 hi = ok_any ? (d ? rr.h1 : rr.h0) : 0ull, lo = ok_any ? (d ? rr.l1 : rr.l0) : 0ull, cost = d ? c1 : c0;
+      u32 listed = NONE32;                       // the candidate's entry in the list of the pass
       if (MC) {
         // every candidate whose bound reaches the round's threshold goes on the list of the pass
         // with all a commit needs; the others count with their bound only (floor2)
@@ -399,17 +401,19 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           slot = off + (u32)__popcll(pm & ((1ull << lane) - 1ull));
         }
         if (pub && slot < LIST_MAX) {
+          listed = slot;
+          S->listA[slot] = A; S->listB[slot] = B;
           Winner& e = S->list[slot];
           e.hi = hi; e.lo = lo; e.cost = cost; e.cand = cur.id.x; e.tensor = cur.id.y; e.pos = cur.p; e.dest = d;
           e.L1 = A.x; e.R = A.y; e.a = d ? B.x : A.z; e.b = d ? B.y : A.w; e.s = ((u64)B.w << 32) | B.z;
-          e.fo_base = rr.fo_L; e.fi_end = rr.fi_R; e.exact = 0; e.kU = kc; e.kr = (rr.ok0 && rr.ok1) ? kc : 0u;
+          e.fo_base = rr.fo_L; e.fi_end = rr.fi_R; e.exact = 0; e.kU = kc; e.kr = (rr.ok0 && rr.ok1) ? kc : 0u; e.slot = slot;
         } else if (kc > floor2) floor2 = kc;
       }
       if ((hi | lo) != 0 && (RATIO ? better_ratio(hi, lo, cost, cur.id.x, mine.hi, mine.lo, mine.cost, mine.cand)
                                    : better(hi, lo, cur.id.x, mine.hi, mine.lo, mine.cand))) {
         mine.hi = hi; mine.lo = lo; mine.cost = cost; mine.cand = cur.id.x; mine.tensor = cur.id.y; mine.pos = cur.p; mine.dest = d;
         mine.L1 = A.x; mine.R = A.y; mine.a = d ? B.x : A.z; mine.b = d ? B.y : A.w; mine.s = ((u64)B.w << 32) | B.z;
-        mine.fo_base = rr.fo_L; mine.fi_end = rr.fi_R; mine.exact = exact;
+        mine.fo_base = rr.fo_L; mine.fi_end = rr.fi_R; mine.exact = exact; mine.slot = listed;
       }
       u = un;
       cur = nxt;
@@ -443,13 +447,9 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u32 f2 = wave_max(lane < LW ? S->wave_f2[lane] : 0u);
         if (lane == 0) S->F2 = f2;
       }
-      if (w == NONE32) { if (lane == 0) { S->mem[0].hi = 0; S->mem[0].lo = 0; } }
-      else {
-        if (lane == 0) {
-          S->mem[0] = S->wave_win[w];
-          S->mem[0].tau_o = ceil_div_x1000(S->wave_win[w].s, S->wave_win[w].dest ? bwo1 : bwo0, S->wave_win[w].dest ? ivo1 : ivo0);
-        }
-        if (lane == 1) S->mem[0].tau_i = ceil_div_x1000(S->wave_win[w].s, S->wave_win[w].dest ? bwi1 : bwi0, S->wave_win[w].dest ? ivi1 : ivi0);
+      if (lane == 0) {
+        if (w == NONE32) { S->mem[0].hi = 0; S->mem[0].lo = 0; }
+        else S->mem[0] = S->wave_win[w];
       }
     }
     __syncthreads();
@@ -689,6 +689,52 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     if (tid == 0) S->jobs += nj;
   };
 
+  // The next best entries of the list of the pass, a list entry per lane of one wavefront: entry by
+  // entry in the order of their benefit, as far as it is certain that each wins Algorithm 1's next
+  // pass (see "more migrations of the same pass" below).  F bounds every candidate that is not on
+  // the list; `m` migrations of the round stand already (0, or 1: the one in mem[0], `picked` by
+  // its lane if it is on the list); at most `allowed` are made.  Picked entries go to mem[]; the
+  // number of migrations is returned.
+  auto pick = [&](const Winner& e, const bool have, bool picked, const u32 F, u32 m, const u32 allowed, u32& by_floor) -> u32 {
+    u32 kB = (have && !picked) ? upkey(e.hi, e.lo) : 0u;           // (0: cannot be picked)
+    const u32 eE0 = e.L1, eE1 = e.a - 1, eW0 = e.b + 1, eW1 = e.R - 1, ed = e.dest;
+    const u32 kr = ed == 0u ? e.kr : 0u;
+    u32 at = NONE32;                               // which migration this lane's entry becomes
+    bool ov = false;                               // a transfer window meets one of a picked migration on the same channel
+    auto meet = [&](u32 wd, u32 wL1, u32 wa, u32 wb, u32 wR) {
+      const bool hit = cyc_overlap32(eE0, eE1, wL1, wa - 1, K) || cyc_overlap32(eW0, eW1, wb + 1, wR - 1, K);
+      ov = ov || (hit && ed == wd && !picked);
+    };
+    if (m) { const Winner& W1 = S->mem[0]; meet(W1.dest, W1.L1, W1.a, W1.b, W1.R); }
+    by_floor = 0;
+    while (m < allowed) {
+      const u32 kmax = wave_max(kB);
+      if (kmax <= F) { by_floor = 1; break; }      // (also when nothing is left)
+      u64 mk = __ballot(kB == kmax);
+      if (mk & (mk - 1)) {                         // equal keys: high word, low word, lowest index
+        const bool in1 = kB == kmax;
+        const u64 hmx = wave_max(in1 ? e.hi : 0ull);
+        const bool in2 = in1 && e.hi == hmx;
+        const u64 lmx = wave_max(in2 ? e.lo : 0ull);
+        const bool in3 = in2 && e.lo == lmx;
+        const u32 cmin = wave_min(in3 ? e.cand : NONE32);
+        mk = __ballot(in3 && e.cand == cmin);
+      }
+      const u32 bl = (u32)__builtin_ctzll(mk);
+      const u64 ovm = __ballot(ov);
+      if ((ovm >> bl) & 1ull) break;               // its own windows are not what they were
+      if (ovm && wave_max(ov ? kr : 0u) >= kmax) break;   // a candidate at risk might rise above it
+      if (lane == bl) { kB = 0u; picked = true; ov = false; at = m; }
+      ++m;
+      if (m == allowed) break;
+      meet((u32)__builtin_amdgcn_readlane((int)ed, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.L1, (int)bl),
+           (u32)__builtin_amdgcn_readlane((int)e.a, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.b, (int)bl),
+           (u32)__builtin_amdgcn_readlane((int)e.R, (int)bl));
+    }
+    if (at != NONE32) S->mem[at] = e;
+    return m;
+  };
+
   // Clipped-area benefit: the ranking went by bounds (the tensor's band, or a value computed
   // in an earlier pass: both can only be too large).  The best by bound stands only with a
   // value computed in this pass.  Otherwise its area is computed here - whole chunks of its
@@ -784,7 +830,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       else { S->n_iter += 1; S->n_evals += C - S->n_mig - S->n_drop; }
       S->hq = 0; S->njobs = 0; S->ot_changed = 0;
       S->mem[0].hi = 0; S->mem[0].lo = 0;
-      S->nlist = 0; S->F2 = 0; S->cut = MAXM; S->need_exact = 0; S->m0 = 1; S->by_floor = 0; S->touched = 0;
+      S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->m0 = 1; S->by_floor = 0; S->touched = 0;
       if (S->stale_hot) { S->restL = NONE32; S->stale_hot = 0; }
       if (a.tick_budget && wall_clock64() - S->t_start > a.tick_budget) S->stop = 1;
     }
@@ -860,8 +906,38 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           resume = 0;
           if (tid == 0) wv.ctx->pending = 0;
         }
-        reduce_best();
         ++rounds;
+        if (MC && K < (1u << 30)) {
+          // The winner is the best entry of the list if that clears every bound of what is not on the
+          // list: then one wavefront takes it from there, and the next ones with it, while the others
+          // bring the group bounds up to date, and no arg-max over the threads is needed (2.5 us a
+          // pass: two stages of wavefront reductions over 128-bit values with a barrier between them).
+          const u32 f2 = wave_max(floor2);
+          if (lane == 0 && f2) atomicMax(&S->F2, f2);
+          __syncthreads();
+          if (wave == LW - 1) {
+            const u32 nl_ = S->nlist, n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
+            const u32 F = rest > S->F2 ? rest : S->F2;
+            const bool have = lane < n;
+            Winner e;
+            if (have) e = S->list[lane];
+            else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
+            u32 allowed = MAXM, by_floor;                // passes of Algorithm 1 this round may stand for
+            if (max_iter && max_iter - S->n_iter + 1 < allowed) allowed = (u32)(max_iter - S->n_iter + 1);   // (n_iter counts this pass already)
+            const u32 m = pick(e, have, false, F, 0u, allowed, by_floor);
+            if (lane == 0) { S->m0 = m ? m : 1u; S->by_floor = by_floor; S->Fkeep = F; S->fast = m ? 1u : 0u; }
+          } else {
+            const u32 ntl = S->ntl;
+            for (u32 i = wave; i < ntl; i += LW - 1) {   // bounds of the groups that hold re-scored tiles
+              const u32 g = alist[i] >> 6, t = g * 64 + lane;
+              const u32 k = wave_max(t < nt ? keys[t] : 0u);
+              if (lane == 0) skeys[g] = k;
+            }
+          }
+          __syncthreads();
+          if (S->fast) { rest_final = rest; break; }
+        }
+        reduce_best();
         const u32 kb = key_dn_of<RATIO>(S->mem[0].hi, S->mem[0].lo, S->mem[0].cost);
         const u32 need = kb ? kb : 1u;
         if (rest < need) decided = true;                 // every tile left out is below the best found
@@ -900,32 +976,32 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // entries still on the list that might clear the floor, the steps are taken again from here
     // (cround > 0) instead of from a new ranking.
     for (u32 cround = 0;; ++cround) {
-    if (MC && wave == LW - 1 && S->nlist > 1u && K < (1u << 30)) {
+    const bool from_list = MC && !(cround == 0u && S->fast);       // (else: the ranking has done this step)
+    if (from_list && wave == LW - 1 && S->nlist > 1u && K < (1u << 30)) {
       const u32 nl_ = S->nlist, n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
       const bool have = lane < n;
       Winner e;
       if (have) e = S->list[lane];
-      else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; }
-      u32 F = rest_final > S->F2 ? rest_final : S->F2;
-      u32 allowed = MAXM;                              // passes of Algorithm 1 this round may stand for
-      bool picked;
+      else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
+      u32 allowed = MAXM, m, by_floor;                 // passes of Algorithm 1 this round may stand for
       if (cround == 0u) {
-        picked = have && e.cand == S->mem[0].cand;     // a migration of this pass already
+        const u32 F = rest_final > S->F2 ? rest_final : S->F2;
         if (max_iter && max_iter - S->n_iter + 1 < allowed) allowed = (u32)(max_iter - S->n_iter + 1);   // (n_iter counts this pass already)
         if (lane == 0) S->Fkeep = F;
+        m = pick(e, have, have && e.cand == S->mem[0].cand, F, 1u, allowed, by_floor);
       } else {
         // Another round from the same list: its entries are scored again against the timelines as
         // the earlier rounds left them (a committed candidate has no window any more and scores
         // nothing), and the best of them wins the next pass of Algorithm 1 if its key clears the
         // floor - every candidate not on the list is still bounded by it, since bounds only fall.
-        F = S->Fkeep;
+        const u32 F = S->Fkeep;
         if (max_iter && max_iter - S->n_iter < allowed) allowed = (u32)(max_iter - S->n_iter);
         if (lane == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->touched = 0; S->ot_changed = 0; S->hq = 0; S->list_rescored += n; }
         PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
         Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
         mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
         if (have) {
-          const uint4 A = a.cd.A[e.pos], B = a.cd.B[e.pos];
+          const uint4 A = S->listA[lane], B = S->listB[lane];
           const Score r = score_candidate(pv, mc, A, B);
           const bool ok_any = r.ok0 || r.ok1;
           const u32 d = r.ok0 ? 0u : 1u;
@@ -934,66 +1010,13 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           e.hi = ok_any ? (d ? r.h1 : r.h0) : 0ull; e.lo = ok_any ? (d ? r.l1 : r.l0) : 0ull;
           e.dest = d; e.a = d ? B.x : A.z; e.b = d ? B.y : A.w;
           e.fo_base = r.fo_L; e.fi_end = r.fi_R; e.kU = kc; e.kr = (r.ok0 && r.ok1) ? kc : 0u;
-          S->list[lane] = e;
         }
-        const u32 b1 = wave_best_lane(e.hi, e.lo, e.cand);
-        const u32 k1 = b1 == NONE32 ? 0u : upkey(read_lane64(e.hi, b1), read_lane64(e.lo, b1));
-        if (allowed == 0u || k1 <= F) allowed = 0u;    // nothing on the list clears the floor: the pass is over
-        else if (lane == b1) {
-          e.tau_o = ceil_div_x1000(e.s, e.dest ? bwo1 : bwo0, e.dest ? ivo1 : ivo0);
-          e.tau_i = ceil_div_x1000(e.s, e.dest ? bwi1 : bwi0, e.dest ? ivi1 : ivi0);
-          S->mem[0] = e;
-        }
-        picked = allowed != 0u && lane == b1;
-      }
-      u32 m = 0, by_floor = 0;
-      if (allowed) {
-        const Winner& W1 = S->mem[0];
-        u32 kB = (have && !picked) ? upkey(e.hi, e.lo) : 0u;       // (0: cannot be picked)
-        const u32 eE0 = e.L1, eE1 = e.a - 1, eW0 = e.b + 1, eW1 = e.R - 1, ed = e.dest;
-        const u32 kr = ed == 0u ? e.kr : 0u;
-        bool ov = false;                               // a transfer window meets one of a committed migration on the same channel
-        auto meet = [&](u32 wd, u32 wL1, u32 wa, u32 wb, u32 wR) {
-          const bool hit = cyc_overlap32(eE0, eE1, wL1, wa - 1, K) || cyc_overlap32(eW0, eW1, wb + 1, wR - 1, K);
-          ov = ov || (hit && ed == wd && !picked);
-        };
-        meet(W1.dest, W1.L1, W1.a, W1.b, W1.R);
-        const u32 mmax = allowed;
-        m = 1;
-        while (m < mmax) {
-          const u32 kmax = wave_max(kB);
-          if (kmax <= F) { by_floor = 1; break; }      // (also when nothing is left)
-          u64 mk = __ballot(kB == kmax);
-          if (mk & (mk - 1)) {                         // equal keys: high word, low word, lowest index
-            const bool in1 = kB == kmax;
-            const u64 hmx = wave_max(in1 ? e.hi : 0ull);
-            const bool in2 = in1 && e.hi == hmx;
-            const u64 lmx = wave_max(in2 ? e.lo : 0ull);
-            const bool in3 = in2 && e.lo == lmx;
-            const u32 cmin = wave_min(in3 ? e.cand : NONE32);
-            mk = __ballot(in3 && e.cand == cmin);
-          }
-          const u32 bl = (u32)__builtin_ctzll(mk);
-          const u64 ovm = __ballot(ov);
-          if ((ovm >> bl) & 1ull) break;               // its own windows are not what they were
-          if (ovm && wave_max(ov ? kr : 0u) >= kmax) break;   // a candidate at risk might rise above it
-          if (lane == 0) S->sel[m] = bl;
-          if (lane == bl) { kB = 0u; picked = true; ov = false; }
-          meet((u32)__builtin_amdgcn_readlane((int)ed, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.L1, (int)bl),
-               (u32)__builtin_amdgcn_readlane((int)e.a, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.b, (int)bl),
-               (u32)__builtin_amdgcn_readlane((int)e.R, (int)bl));
-          ++m;
-        }
-        if (lane >= 1 && lane < m) {                   // the picked entries become migrations 1 .. m - 1
-          Winner x = S->list[S->sel[lane]];
-          x.tau_o = ceil_div_x1000(x.s, x.dest ? bwo1 : bwo0, x.dest ? ivo1 : ivo0);
-          x.tau_i = ceil_div_x1000(x.s, x.dest ? bwi1 : bwi0, x.dest ? ivi1 : ivi0);
-          S->mem[lane] = x;
-        }
+        // (nothing on the list clears the floor: the pass is over)
+        m = pick(e, have, false, F, 0u, allowed, by_floor);
       }
       if (lane == 0) { S->m0 = m; S->by_floor = by_floor; }
-    } else if (MC && wave == LW - 1 && lane == 0) S->by_floor = 1;     // (nothing else on the list)
-    __syncthreads();
+    } else if (from_list && wave == LW - 1 && lane == 0) S->by_floor = 1;     // (nothing else on the list)
+    if (from_list) __syncthreads();
 
     // Step 2, chunk by chunk: what every picked migration does to the chunk (kept in `fl`, six bits
     // each), and how many of them can go together: the first that might let a slot drop under the
@@ -1004,6 +1027,11 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     const u32 m0 = S->m0;
     if (MC && m0 == 0u) break;                           // (a later round found nothing above the floor)
     u64 fl[MAXM / 8] = {};
+    if (wave == LW - 1 && lane < m0) {                   // transfer times (needed from step 3 on)
+      Winner& M = S->mem[lane];
+      M.tau_o = ceil_div_x1000(M.s, M.dest ? bwo1 : bwo0, M.dest ? ivo1 : ivo0);
+      M.tau_i = ceil_div_x1000(M.s, M.dest ? bwi1 : bwi0, M.dest ? ivi1 : ivi0);
+    }
     if (tid < ((nch + 63u) & ~63u)) {
       u32 cut = MAXM;
       bool ex0 = false;
@@ -1068,6 +1096,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u64 ms = M.s;
         a.cd.A[M.pos] = make_uint4(mL1, mR, 1u, 0u);       // the candidate leaves the live set
         a.cd.B[M.pos] = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
+        if (MC && M.slot != NONE32) {                      // (and has nothing left to win on the list of the pass)
+          S->listA[M.slot] = make_uint4(mL1, mR, 1u, 0u);
+          S->listB[M.slot] = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
+        }
         if (!room) {
           g10_dropped dr; dr.iteration = S->n_iter - 1; dr.cand = M.cand; dr.reserved = 0;
           a.dropped[nd] = dr;
@@ -1225,7 +1257,7 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
   Machine mc; mc.bwo0 = ctl->bw_out[0]; mc.bwo1 = ctl->bw_out[1]; mc.bwi0 = ctl->bw_in[0]; mc.bwi1 = ctl->bw_in[1];
   mc.ivo0 = ctl->inv_out[0]; mc.ivo1 = ctl->inv_out[1]; mc.ivi0 = ctl->inv_in[0]; mc.ivi1 = ctl->inv_in[1];
   Winner mine;
-  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.pad = 0;
+  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   mine.s = 0; mine.fo_base = 0; mine.fi_end = 0; mine.tensor = 0; mine.pos = 0; mine.dest = 0; mine.L1 = 0; mine.R = 0; mine.a = 1; mine.b = 0;
   const u32 nunits = wv.ctx->ntl << a.tshift;
   for (u32 u = blockIdx.x; u < nunits; u += nwg) {

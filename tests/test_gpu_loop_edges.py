@@ -1,0 +1,60 @@
+"""The greedy loop at the sizes where its chunk jobs, its list of a pass and its 32-bit sums can go wrong, against the
+oracle through the C ABI.  Integer work: every comparison is exact."""
+import numpy as np
+import pytest
+
+from paper_2310_09443_amd import traces
+from paper_2310_09443_amd.traces import Trace, Workload
+from test_gpu_parity import assert_plan_equal, assert_prefetch_equal, g10, run_both  # noqa: F401  (g10 is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("max_chunks", [0, 1, 2])
+@pytest.mark.parametrize("K", [8, 63, 64, 65, 255, 256, 257, 321, 512, 513, 767])
+def test_ragged_chunks(g10, K, max_chunks):
+    """A chunk's slots go to the lanes 64 apart: last chunks of one slot, of one and of several rounds of lanes."""
+    w = traces.stress(K=K, N=12 * K, seed=K)
+    h, v, args = run_both(g10, w)
+    for cap, host in ((0.25, 0.25), (0.6, 0.02), (0.9, 2.0)):
+        a = dict(args, gpu_cap=int(v.peak * cap), host_cap=int(v.peak * host))
+        p = v.plan(**a)
+        assert_plan_equal(h.plan(max_chunks=max_chunks, **a), p)
+    assert_prefetch_equal(h.prefetch(), p.prefetch())
+    h.close()
+
+
+def _equal_tensors(n, K, dur):
+    """n tensors of one size, used at the same two kernels of their group: every ranking ends in ties."""
+    g = np.arange(n, dtype=np.int64) % 3
+    first, last = 1 + g, K - 2 - g
+    uk = np.concatenate([first, last]).astype(np.uint32)
+    ut = np.concatenate([np.arange(n), np.arange(n)]).astype(np.uint32)
+    tr = Trace(f"equal{n}", np.full(K, dur, np.uint64), np.full(n, 64_000, np.uint64), np.zeros(n, np.uint8), uk, ut)
+    return Workload(tr, cap_frac=0.1, host_cap_frac=0.3)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130, 700])
+def test_list_of_equal_candidates(g10, n):
+    """Ties by the dozen: the list of a pass is full of them, or overflows (64 entries)."""
+    h, v, args = run_both(g10, _equal_tensors(n, 300, 5000))
+    for host in (0.3, 1.0):
+        a = dict(args, host_cap=int(v.peak * host))
+        assert_plan_equal(h.plan(**a), v.plan(**a))
+        assert_plan_equal(h.plan(max_iters=n // 2 + 1, **a), v.plan(max_iters=n // 2 + 1, **a))
+    h.close()
+
+
+@pytest.mark.parametrize("dur", [16_777_215, 16_777_216, 16_777_217, 1 << 33, 1 << 45])
+def test_long_kernels(g10, dur):
+    """Chunk totals (256 slots) just below, at and above 2^32 ns, and far above."""
+    w = traces.stress(K=600, N=6000, seed=9)
+    tr = w.trace
+    d = np.where(np.arange(tr.K) % 2 == 0, np.uint64(dur), np.uint64(max(dur - 3, 1))).astype(np.uint64)
+    d[300:] = np.uint64(dur)
+    w = Workload(traces.with_durations(tr, d), cap_frac=0.3, host_cap_frac=0.1, bw_out_Bpus=(1, 3), bw_in_Bpus=(1, 2))
+    h, v, args = run_both(g10, w)
+    for bw in ((1, 3), (700, 2000), (6000, 25000)):
+        a = dict(args, bw_out=bw, bw_in=bw)
+        assert_plan_equal(h.plan(**a), v.plan(**a))
+    h.close()
