@@ -81,7 +81,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u64 evals, refused;         // clipped areas computed; of those, how many came out below the bound
   u32 nl, restL;              // hot list: length; bound of the tiles outside it
   u32 ntl, filt;              // current round: tiles to score; bound of the hot tiles left out
-  u32 njobs, ot_changed, stale_hot;
+  u32 njobs, jnext, ot_changed, stale_hot;   // jobs listed; the next one that a wavefront takes after its first
   u32 no_wide;                // this launch may not leave a round to the scoring kernel (none is queued behind it)
   // progress (mirrors Ctl)
   u64 n_iter, n_mig, n_drop, n_evals, units, second, jobs;
@@ -460,18 +460,28 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   // bits over the pass's migrations: for a transfer-window job, A = the migrations of that
   // destination whose window meets the chunk; for a pressure job, A = those whose absent window
   // cuts the chunk, B = those that cover it whole.  (Host occupancy has no such job: see J_HQ.) --
+  // Jobs begin .. end - 1 of the list, about the migrations in `keep`: a job for each wavefront but
+  // the last, then whoever is done takes the next one (the last wavefront comes late to a round's
+  // jobs, from writing its plan records); jnext counts from LW - 1.
   // Slot s0 + 256 st + 64 i + lane belongs to lane `lane` (i = 0..3): every load and store of a job
   // covers 64 neighbouring slots.  A workgroup has one texture unit, about one cache line per clock,
   // and up to eight jobs run at once: with four neighbouring slots per lane and one 64-byte record
   // per slot a rewrite touched 64 lines per instruction, now 8 (see the tables of px).
-  auto run_jobs = [&]() {
+  auto run_jobs = [&](const u32 begin, const u32 end, const u32 keep) {
     ulonglong2* const px = reinterpret_cast<ulonglong2*>(tl.px);
-    const u32 nj = S->njobs;
-    for (u32 jb = wave; jb < nj; jb += LW) {
+    auto take = [&]() -> u32 {
+      u32 x = 0;
+      if (lane == 0) x = atomicAdd(&S->jnext, 1u);
+      return x;                                          // (in lane 0)
+    };
+    u32 jb = begin + (wave < LW - 1 ? wave : (u32)__builtin_amdgcn_readfirstlane((int)take()));
+    while (jb < end) {
       const u64 jw = jobs[jb];
-      const u32 type = (u32)(jw >> 16) & 0xffu, c = (u32)jw & 0xffffu, ma_ = (u32)(jw >> 24) & 0xffffu, mb_ = (u32)(jw >> 40) & 0xffffu;
+      const u32 after = take();                            // (known by the time this job is done)
+      const u32 type = (u32)(jw >> 16) & 0xffu, c = (u32)jw & 0xffffu, ma_ = (u32)(jw >> 24) & keep, mb_ = (u32)(jw >> 40) & keep;
       const u32 s0 = c * CH, s1 = (s0 + CH - 1 < K - 1) ? s0 + CH - 1 : K - 1;
       if (type >= J_FO0 && type <= J_FI1) {
+        if (ma_) {
         // channel time of the transfer windows of this destination that meet the chunk is taken
         // from its slots (the windows of one pass are disjoint); the free-time prefix of the
         // slots after the first window slot is rewritten from a scan of the new values
@@ -530,6 +540,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           }
         }
         if (lane == 0) tot[(u64)arr * nch + c] = carry;
+        }
       } else if (type == J_P) {
         // pressure of the chunk's slots: the migrations whose absent window cuts the chunk are
         // taken off slot by slot, the ones that cover it whole go into the chunk's lazy add
@@ -685,8 +696,9 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         }
         if (lane == 0) atomicMax((unsigned long long*)&S->hq, (unsigned long long)m_cov);
       }
+      jb = begin + (u32)__builtin_amdgcn_readfirstlane((int)after);
     }
-    if (tid == 0) S->jobs += nj;
+    if (tid == 0) S->jobs += end - begin;
   };
 
   // The next best entries of the list of the pass, a list entry per lane of one wavefront: entry by
@@ -748,7 +760,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     if ((S->mem[0].hi | S->mem[0].lo) == 0 || S->mem[0].exact) return true;
     const u32 wa = S->mem[0].a, wb = S->mem[0].b;
     const u64 s = S->mem[0].s;
-    if (tid == 0) { S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0; S->njobs = 0; }
+    if (tid == 0) { S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0; S->njobs = 0; S->jnext = LW - 1; }
     __syncthreads();
     if (tid < nch) {
       u32 len = 0;
@@ -768,7 +780,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       }
     }
     __syncthreads();
-    run_jobs();
+    run_jobs(0u, S->njobs, 0xffffu);
     __syncthreads();
     const u64 a0 = S->acc[0], a1 = S->acc[1], a2 = S->acc[2];
     const u64 vlo = a0 + (a1 << 32), vhi = a2 + (a1 >> 32) + (vlo < a0 ? 1ull : 0ull);
@@ -1018,76 +1030,129 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     } else if (from_list && wave == LW - 1 && lane == 0) S->by_floor = 1;     // (nothing else on the list)
     if (from_list) __syncthreads();
 
-    // Step 2, chunk by chunk: what every picked migration does to the chunk (kept in `fl`, six bits
-    // each), and how many of them can go together: the first that might let a slot drop under the
-    // capacity, or that host memory might not hold on top of the earlier ones, ends the set (it
-    // is ranked again in the next pass).  For the winner itself the two tests only decide how it
-    // is committed: alone, and with the exact host-capacity test.
-    enum { F_E = 1, F_W = 2, F_ACUT = 4, F_AALL = 8, F_PCUT = 16, F_PALL = 32 };
+    // Step 2, chunk by chunk: what every picked migration does to the chunk (sets of migrations, a
+    // bit each), the jobs that follow - for a chunk that is cut, that holds a transfer window, or
+    // in which a slot drops under the capacity - and how many migrations can go together: the first
+    // that might let a slot drop under the capacity, or that host memory might not hold on top of
+    // the earlier ones, ends the set (it is ranked again in the next pass, and the jobs leave it
+    // out).  For the winner itself the two tests only decide how it is committed: alone, and with
+    // the exact host-capacity test.
     const u32 m0 = S->m0;
     if (MC && m0 == 0u) break;                           // (a later round found nothing above the floor)
-    u64 fl[MAXM / 8] = {};
-    if (wave == LW - 1 && lane < m0) {                   // transfer times (needed from step 3 on)
+    u32 cutP = 0, allP = 0, cutH = 0, allH = 0, eF = 0, eH = 0, wF = 0, wH = 0;   // absent window / period cuts, covers the chunk whole;
+                                                         // eviction and prefetch windows meet it, to flash and to host
+    u64 lzP = 0, lzH = 0, cutHs = 0;                     // sizes of allP, allH, cutH
+    bool jobP = false;
+    if (wave == LW - 1 && lane < m0) {                   // transfer times (needed by the jobs and the records)
       Winner& M = S->mem[lane];
       M.tau_o = ceil_div_x1000(M.s, M.dest ? bwo1 : bwo0, M.dest ? ivo1 : ivo0);
       M.tau_i = ceil_div_x1000(M.s, M.dest ? bwi1 : bwi0, M.dest ? ivi1 : ivi0);
     }
+    if (tid == 0) S->jnext = LW - 1;
     if (tid < ((nch + 63u) & ~63u)) {
+      // migration i lies in lane i of every wavefront and is read from there into scalars: with a trip to
+      // LDS for every migration this loop took 2.1 us a round on the stress trace
+      u32 gL = 0, gR = 0, ga = 1, gb = 0, gd = 0;
+      u64 gs = 0;
+      if (lane < m0) { const Winner& M = S->mem[lane]; gL = M.L1; gR = M.R; ga = M.a; gb = M.b; gd = M.dest; gs = M.s; }
+      const bool in = tid < nch;
+      const u64 mo = in ? minOver[tid] : NONE64, hm = in ? hmax[tid] : 0ull;
+      const u32 c0 = in ? tid * CH : 0u, c1 = in ? (c0 + CH < K ? c0 + CH : K) : 0u, len = c1 - c0;
       u32 cut = MAXM;
       bool ex0 = false;
-      if (tid < nch) {
-        const u64 mo = minOver[tid], hm = hmax[tid];
-        u64 runP = 0, runH = 0;
-        for (u32 i = 0; i < m0; ++i) {
-          const Winner& M = S->mem[i];
-          const u32 mL1 = M.L1, mR = M.R, ma = M.a, mb = M.b, md = M.dest;
-          const u64 ms = M.s;
-          u32 len = 0;
-          const u32 cP = cover(tid, CH, K, mL1, mR - 1, len);       // the period: eviction window, absent window, prefetch window
-          if (!cP) continue;                                        // (most migrations do not touch most chunks)
-          const u32 cE = cover(tid, CH, K, mL1, ma - 1, len), cA = cover(tid, CH, K, ma, mb, len), cW = cP - cE - cA;
-          u32 f = (cE ? F_E : 0u) | (cW ? F_W : 0u) | (cA == len ? F_AALL : cA ? F_ACUT : 0u);
-          if (cA) {
-            runP += ms;
-            if (mo != NONE64 && mo - cap <= runP) { const u32 lim = i ? i : 1u; cut = lim < cut ? lim : cut; }
-          }
-          if (md == G10_HOST && cP) {
-            f |= cP == len ? F_PALL : F_PCUT;
-            if (ms > host_cap || hm + runH > host_cap - ms) { if (i == 0) ex0 = true; else cut = i < cut ? i : cut; }
-            runH += ms;
-          }
-          fl[i >> 3] |= (u64)f << (8 * (i & 7u));
+      u64 runP = 0, runH = 0;
+      for (u32 i = 0; i < m0; ++i) {
+        const u32 mL1 = (u32)__builtin_amdgcn_readlane((int)gL, (int)i), mR = (u32)__builtin_amdgcn_readlane((int)gR, (int)i);
+        const u32 ma = (u32)__builtin_amdgcn_readlane((int)ga, (int)i), mb = (u32)__builtin_amdgcn_readlane((int)gb, (int)i);
+        const u32 md = (u32)__builtin_amdgcn_readlane((int)gd, (int)i), bit = 1u << i;
+        const u64 ms = read_lane64(gs, i);
+        const u32 nP = covered(c0, c1, K, mL1, mR);      // the period: eviction window, absent window, prefetch window
+        if (!nP) continue;                               // (most migrations do not touch most chunks)
+        const u32 nE = covered(c0, c1, K, mL1, ma), nA = covered(c0, c1, K, ma, mb + 1);
+        if (nA) {
+          runP += ms;
+          if (mo != NONE64 && mo - cap <= runP) { const u32 lim = i ? i : 1u; cut = lim < cut ? lim : cut; }
+          if (nA == len) { allP |= bit; lzP += ms; }
+          else cutP |= bit;
+        }
+        if (md == G10_HOST) {
+          if (nE) eH |= bit;
+          if (nE + nA != nP) wH |= bit;
+          if (ms > host_cap || hm + runH > host_cap - ms) { if (i == 0) ex0 = true; else cut = i < cut ? i : cut; }
+          runH += ms;
+          if (nP == len) { allH |= bit; lzH += ms; }
+          else { cutH |= bit; cutHs += ms; }
+        } else {
+          if (nE) eF |= bit;
+          if (nE + nA != nP) wF |= bit;
         }
       }
-      cut = wave_min(cut);
-      if (lane == 0 && cut < MAXM) atomicMin(&S->cut, cut);
+      if (__any(cut < MAXM)) {
+        cut = wave_min(cut);
+        if (lane == 0) atomicMin(&S->cut, cut);
+      }
       if (ex0) S->need_exact = 1;
+      // (a job adds the sizes of the migrations that cover its chunk whole itself)
+      jobP = cutP != 0 || (lzP != 0 && mo != NONE64 && mo - cap <= lzP);
+      const u64 b0 = __ballot(jobP), b1 = __ballot(eF != 0), b2 = __ballot(eH != 0), b3 = __ballot(wF != 0), b4 = __ballot(wH != 0);
+      const u32 n0 = (u32)__popcll(b0), n1 = n0 + (u32)__popcll(b1), n2 = n1 + (u32)__popcll(b2), n3 = n2 + (u32)__popcll(b3), n4 = n3 + (u32)__popcll(b4);
+      if (n4) {
+        u32 off = 0;
+        if (lane == 0) off = atomicAdd(&S->njobs, n4);
+        off = (u32)__builtin_amdgcn_readfirstlane((int)off);
+        const u64 lt = (1ull << lane) - 1ull;
+        if (jobP) jobs[off + (u32)__popcll(b0 & lt)] = ((u64)allP << 40) | ((u64)cutP << 24) | ((u64)J_P << 16) | tid;
+        if (eF) jobs[off + n0 + (u32)__popcll(b1 & lt)] = ((u64)eF << 24) | ((u64)J_FO0 << 16) | tid;
+        if (eH) jobs[off + n1 + (u32)__popcll(b2 & lt)] = ((u64)eH << 24) | ((u64)J_FO1 << 16) | tid;
+        if (wF) jobs[off + n2 + (u32)__popcll(b3 & lt)] = ((u64)wF << 24) | ((u64)J_FI0 << 16) | tid;
+        if (wH) jobs[off + n3 + (u32)__popcll(b4 & lt)] = ((u64)wH << 24) | ((u64)J_FI1 << 16) | tid;
+      }
     }
     __syncthreads();
+    const u32 nj = S->njobs;                             // the jobs of the round
     u32 m = m0 < S->cut ? m0 : S->cut;
     bool room = true;
     if (MC && cround && S->need_exact) break;            // (the exact host-memory test is left to the next ranking pass)
     if (S->need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
-      const u32 f0 = (u32)fl[0] & 0xffu;
       if (tid == 0) S->hq = 0;
       __syncthreads();
-      if ((f0 & F_PCUT) || ((f0 & F_PALL) && hpend[tid])) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_HQ << 16) | tid;
-      else if (f0 & F_PALL) atomicMax((unsigned long long*)&S->hq, (unsigned long long)hmax[tid]);   // (exact: nothing is missing there)
+      if ((cutH & 1u) || ((allH & 1u) && hpend[tid])) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_HQ << 16) | tid;   // (behind the round's jobs)
+      else if (allH & 1u) atomicMax((unsigned long long*)&S->hq, (unsigned long long)hmax[tid]);   // (exact: nothing is missing there)
       __syncthreads();
-      run_jobs();
+      run_jobs(nj, S->njobs, 0xffffu);
       __syncthreads();
       room = s <= host_cap && S->hq <= host_cap - s;
-      __syncthreads();
-      if (tid == 0) S->njobs = 0;
+      if (tid == 0) S->jnext = LW - 1;
       __syncthreads();
     }
 
-    // Step 3: the plan records, the counters and the next pass's first threshold (the last
-    // wavefront, lane i takes migration i) beside the commit chunk by chunk: a chunk a migration
-    // covers whole takes a lazy add; a chunk that is cut, that holds a transfer window, or in
-    // which a slot drops under the capacity gets a job (with the migrations it is about)
+    // Step 3: the commit.  A chunk a migration covers whole takes a lazy add, unless it has a job
+    // that makes it; the jobs; and beside the first of them, in the last wavefront (lane i takes
+    // migration i), the plan records, the counters and the next pass's first threshold.
+    if (room && tid < nch) {
+      const u32 c = tid;
+      if (m != m0) {                                     // the migrations left out
+        const u32 keep = (1u << m) - 1u;
+        allP &= keep; allH &= keep; cutH &= keep;
+        lzP = 0; lzH = 0; cutHs = 0;
+        for (u32 i = 0; i < m; ++i) {
+          const u64 ms = S->mem[i].s;
+          if ((allP >> i) & 1u) lzP += ms;
+          if ((allH >> i) & 1u) lzH += ms;
+          if ((cutH >> i) & 1u) cutHs += ms;
+        }
+      }
+      if (!jobP && lzP) {
+        lazyP[c] += lzP;
+        const u64 mo = minOver[c];
+        if (mo != NONE64) minOver[c] = mo - lzP;
+      }
+      // host occupancy: whole covers into the lazy add; cuts only into the chunk's bound, the slots follow on demand (J_HQ)
+      if (lzH | cutHs) { lazyH[c] += lzH; hmax[c] += lzH + cutHs; }
+      if (cutH) hpend[c] = 1u;
+    }
     if (wave == LW - 1) {
       const u64 nm = S->n_mig, nd = S->n_drop;
       if (lane < m) {
@@ -1154,40 +1219,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       }
     }
     if (!room) { __syncthreads(); break; }
-    if (tid < nch) {
-      const u32 c = tid;
-      u64 lzP = 0, lzH = 0, cutHs = 0;
-      u32 cutP = 0, allP = 0, cutH = 0, fo[2] = {0, 0}, fi[2] = {0, 0};
-      for (u32 i = 0; i < m; ++i) {
-        const u32 f = (u32)(fl[i >> 3] >> (8 * (i & 7u))) & 0xffu;
-        if (!f) continue;
-        const u64 ms = S->mem[i].s;
-        const u32 md = S->mem[i].dest;
-        if (f & F_AALL) { lzP += ms; allP |= 1u << i; }
-        if (f & F_ACUT) cutP |= 1u << i;
-        if (f & F_PALL) lzH += ms;
-        if (f & F_PCUT) { cutH |= 1u << i; cutHs += ms; }
-        if (f & F_E) fo[md] |= 1u << i;
-        if (f & F_W) fi[md] |= 1u << i;
-      }
-      bool jobP = cutP != 0;
-      if (lzP) {
-        const u64 mo = minOver[c];
-        if (mo != NONE64 && mo - cap <= lzP) jobP = true;       // a slot drops under the capacity
-        if (!jobP) { lazyP[c] += lzP; if (mo != NONE64) minOver[c] = mo - lzP; }
-      }
-      // host occupancy: whole covers into the lazy add; cuts only into the chunk's bound, the slots follow on demand (J_HQ)
-      if (lzH | cutHs) { lazyH[c] += lzH; hmax[c] += lzH + cutHs; }
-      if (cutH) hpend[c] = 1u;
-      // (a job adds the sizes of the migrations that cover its chunk whole itself)
-      if (jobP) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)allP << 40) | ((u64)cutP << 24) | ((u64)J_P << 16) | c;
-      if (fo[0]) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)fo[0] << 24) | ((u64)J_FO0 << 16) | c;
-      if (fo[1]) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)fo[1] << 24) | ((u64)J_FO1 << 16) | c;
-      if (fi[0]) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)fi[0] << 24) | ((u64)J_FI0 << 16) | c;
-      if (fi[1]) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)fi[1] << 24) | ((u64)J_FI1 << 16) | c;
-    }
-    __syncthreads();
-    run_jobs();
+    run_jobs(0u, nj, (1u << m) - 1u);
     __syncthreads();
     // level 1: the bases of the timelines whose chunk totals changed, one wavefront per timeline
     {

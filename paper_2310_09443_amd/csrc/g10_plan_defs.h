@@ -317,6 +317,12 @@ __device__ __forceinline__ u32 cover(u32 c, u32 ch, u32 K, u32 x, u32 y, u32& le
   return n;
 }
 
+// the same count for the plain slots [c0, c1) and the doubled range [x, y), ends excluded
+__device__ __forceinline__ u32 covered(u32 c0, u32 c1, u32 K, u32 x, u32 y) {
+  const u32 h0 = c1 < y ? c1 : y, l0 = c0 > x ? c0 : x, h1 = c1 + K < y ? c1 + K : y, l1 = c0 + K > x ? c0 + K : x;
+  return __builtin_elementwise_sub_sat(h0, l0) + __builtin_elementwise_sub_sat(h1, l1);
+}
+
 // first plain slot of [s0, s1] inside the doubled range [x, y] (y - x < K), or NONE32
 __device__ __forceinline__ u32 first_covered(u32 s0, u32 s1, u32 K, u32 x, u32 y) {
   u32 first = NONE32;
