@@ -41,6 +41,14 @@ void mem_trim();
 __device__ __forceinline__ u32 lane_id() { return threadIdx.x & (G10_WAVE - 1); }
 __device__ __forceinline__ u32 wave_id() { return threadIdx.x / G10_WAVE; }
 
+// A pointer that a kernel reads from memory (a job, a plan's arguments) is a generic one to the
+// compiler, and a flat access counts as an LDS access too: every wait for an LDS read then waits for
+// the memory accesses in flight as well.  This says that it points to device memory.
+template <class T>
+__device__ __forceinline__ T* in_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
 // Cross-lane steps run on the DPP path of the vector ALU (row shifts inside
 // rows of 16 lanes, then the row broadcasts 15 and 31 of the 64-wide wavefront)
 // instead of ds_bpermute: a few cycles per step, no LDS crossbar.  Lanes a step

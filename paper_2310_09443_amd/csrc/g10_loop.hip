@@ -159,7 +159,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   constexpr bool MC = !RATIO && !CLIP;
   constexpr bool WIDE = RATIO && !CLIP;        // long scoring rounds may be left to the scoring kernel (see WideCtx)
   extern __shared__ __align__(16) unsigned char smem[];
-  const LoopArgs a = plans[blockIdx.x];        // one workgroup per plan
+  const LoopArgs a = in_global(plans[blockIdx.x]);   // one workgroup per plan
   const Timelines tl = a.tl;
   const u32 nch = tl.nch, nb1 = nch + 1, K = tl.K, CH = 1u << tl.shift_ch, nt = a.nt, ns = (nt + 63) / 64;
   Shared* S = (Shared*)smem;
@@ -1274,7 +1274,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
 // raises the bounds of their tiles in device memory and leaves its best candidate in win[b].
 __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict__ plans) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const LoopArgs a = plans[0];
+  const LoopArgs a = in_global(plans[0]);
   if (!a.wide) return;
   const WideView wv = wide_view(a.wide);
   const u32 nwg = wv.ctx->nwg;

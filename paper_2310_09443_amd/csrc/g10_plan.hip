@@ -363,8 +363,15 @@ struct TileJob {
   u32 K, nch, shift_ch, pad;
 };
 
+__device__ __forceinline__ TileJob in_global(TileJob j) {
+  j.src = g10::in_global(j.src); j.dst = g10::in_global(j.dst);
+  j.sortkeys = ::in_global(j.sortkeys); j.sorted = ::in_global(j.sorted); j.from = ::in_global(j.from); j.tkeys = ::in_global(j.tkeys);
+  j.px = ::in_global(j.px); j.g_base = ::in_global(j.g_base); j.ctl = ::in_global(j.ctl);
+  return j;
+}
+
 __global__ __launch_bounds__(G10_BLOCK) void k_retile_begin_jobs(const TileJob* __restrict__ jobs) {
-  const TileJob& j = jobs[blockIdx.y];
+  const TileJob j = in_global(jobs[blockIdx.y]);
   for (u32 i = threadIdx.x; i < NT_MAX; i += G10_BLOCK) j.tkeys[i] = 0u;
   if (threadIdx.x == 0) j.ctl->n_live = 0u;
 }
@@ -372,14 +379,14 @@ __global__ __launch_bounds__(G10_BLOCK) void k_retile_begin_jobs(const TileJob* 
 __global__ __launch_bounds__(G10_BLOCK) void k_rescore_jobs(const TileJob* __restrict__ jobs) {
   extern __shared__ u64 lb[];                  // [5][nch + 1], the largest nch of the jobs
   __shared__ u32 tmp[G10_WAVES + 1];
-  const TileJob j = jobs[blockIdx.y];
+  const TileJob j = in_global(jobs[blockIdx.y]);
   if (blockIdx.x * G10_BLOCK >= j.n) return;
   if (j.rank == G10_RANK_RATIO) rescore_block<true>(j.src, j.n, j.px, j.g_base, j.K, j.nch, j.shift_ch, j.ctl, j.sortkeys, &j.ctl->n_live, lb, tmp);
   else rescore_block<false>(j.src, j.n, j.px, j.g_base, j.K, j.nch, j.shift_ch, j.ctl, j.sortkeys, &j.ctl->n_live, lb, tmp);
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_tile_gather_jobs(const TileJob* __restrict__ jobs) {
-  const TileJob j = jobs[blockIdx.y];
+  const TileJob j = in_global(jobs[blockIdx.y]);
   tile_gather_at(blockIdx.x * G10_BLOCK + threadIdx.x, j.sorted, j.from, j.n, j.n_pad, j.src, j.dst, j.tile_shift, j.tkeys);
 }
 

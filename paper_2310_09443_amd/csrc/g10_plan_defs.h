@@ -288,10 +288,21 @@ struct LoopArgs {
   u32 wide_last_seq;          // the launch of the loop kernel (counted from 1 over the plan) behind which no scoring kernel is queued
 };
 
-struct Best {
-  u64 hi, lo;
-  u32 cand;
-};
+__device__ __forceinline__ Cands in_global(const Cands& c) {
+  return Cands{::in_global(c.A), ::in_global(c.B), ::in_global(c.id), ::in_global(c.cv), ::in_global(c.ce)};
+}
+__device__ __forceinline__ LoopArgs in_global(LoopArgs a) {
+  a.cd = in_global(a.cd);
+  a.tl.dur = ::in_global(a.tl.dur); a.tl.P = ::in_global(a.tl.P); a.tl.fre = ::in_global(a.tl.fre); a.tl.H = ::in_global(a.tl.H);
+  a.tl.px = ::in_global(a.tl.px); a.tl.otc = ::in_global(a.tl.otc);
+  a.g_tot = ::in_global(a.g_tot); a.g_lazyP = ::in_global(a.g_lazyP); a.g_minOver = ::in_global(a.g_minOver);
+  a.g_lazyH = ::in_global(a.g_lazyH); a.g_hmax = ::in_global(a.g_hmax); a.g_base = ::in_global(a.g_base);
+  a.g_hmat = ::in_global(a.g_hmat); a.g_hpend = ::in_global(a.g_hpend); a.g_keys = ::in_global(a.g_keys);
+  a.ctl = ::in_global(a.ctl); a.records = ::in_global(a.records); a.rec_ab = ::in_global(a.rec_ab); a.rec_h = ::in_global(a.rec_h);
+  a.dropped = ::in_global(a.dropped);
+  a.wide = (void*)::in_global((char*)a.wide);
+  return a;
+}
 
 __device__ __forceinline__ bool better(u64 hi, u64 lo, u32 cand, u64 bhi, u64 blo, u32 bcand) {
   if (hi != bhi) return hi > bhi;

@@ -242,9 +242,13 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter(const KT* __restric
 }
 
 // ---- many sorts of (32-bit key, 32-bit value) pairs at once: job = blockIdx.y -------------------------
+__device__ __forceinline__ SortJob in_global(SortJob j) {
+  j.keys = ::in_global(j.keys); j.alt = ::in_global(j.alt); j.vals = ::in_global(j.vals); j.valt = ::in_global(j.valt); j.hist = ::in_global(j.hist);
+  return j;
+}
 __global__ __launch_bounds__(G10_BLOCK) void k_radix_hist_jobs(const SortJob* __restrict__ jobs, u32 shift, u32 flip) {
   __shared__ u32 cnt[256];
-  const SortJob j = jobs[blockIdx.y];
+  const SortJob j = in_global(jobs[blockIdx.y]);
   if (blockIdx.x >= j.nb) return;
   radix_hist_tile<u32>(flip ? j.alt : j.keys, j.n, shift, j.hist, j.nb, cnt);
 }
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_hist_jobs(const SortJob* __
 __global__ __launch_bounds__(1024) void k_radix_scan_jobs(const SortJob* __restrict__ jobs) {
   __shared__ u32 wsum[16];
   __shared__ u32 carry_s;
-  const SortJob j = jobs[blockIdx.y];
+  const SortJob j = in_global(jobs[blockIdx.y]);
   const u32 total = 256u * j.nb, w = threadIdx.x >> 6, l = threadIdx.x & 63u;
   u32* h = j.hist;
   u32 carry = 0;
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(1024) void k_radix_scan_jobs(const SortJob* __restr
 __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter_jobs(const SortJob* __restrict__ jobs, u32 shift, u32 flip, u32 iota) {
   __shared__ u32 cnt[G10_WAVES][256];
   __shared__ u32 gbase[256];
-  const SortJob j = jobs[blockIdx.y];
+  const SortJob j = in_global(jobs[blockIdx.y]);
   if (blockIdx.x >= j.nb) return;
   radix_scatter_tile<u32, true>(flip ? j.alt : j.keys, flip ? j.keys : j.alt, iota ? (const u32*)nullptr : (const u32*)(flip ? j.valt : j.vals),
                                 flip ? j.vals : j.valt, j.n, shift, j.hist, j.nb, cnt, gbase);
