@@ -59,8 +59,12 @@ static_assert(sizeof(WideCtx) % 16 == 0 && sizeof(Winner) % 8 == 0, "the arrays 
 constexpr u32 MAXM = 16;      // migrations committed in one ranking pass at most (a multiple of 8, at most 16: the job words hold two sets of 16)
 static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid out for 8 or 16");
 
-constexpr u32 MC_GUESS_SHIFT_MIN = 4;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
+constexpr u32 MC_GUESS_SHIFT_MIN = 3;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
 constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the second and later migrations
+// How far under the round's threshold a scored candidate's bound may lie to go on the list, in key steps (2^24 are a
+// factor of two).  Entries under the bound of the tiles left out cannot be picked, so that is the lowest; within that the
+// margin follows the list: it doubles while the list stays short and shrinks when it overflows.
+constexpr u32 PUB_START = 1u << 22, PUB_MIN = 1u << 12, PUB_MAX = 1u << 30;
 
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
@@ -86,7 +90,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   // progress (mirrors Ctl)
   u64 n_iter, n_mig, n_drop, n_evals, units, second, jobs;
   u32 thr_key, status, done, stop;
-  u32 gshift, pad2;
+  u32 gshift, pub;            // margins of the first threshold and of the list under it
   u64 t_start;
 };
 
@@ -212,6 +216,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     S->units = 0; S->second = 0; S->jobs = 0; S->evals = 0; S->refused = 0; S->more_rounds = 0; S->more = 0; S->list_rescored = 0;
     S->thr_key = ctl->thr_key; S->status = ctl->status; S->done = ctl->done;
     S->gshift = ctl->gshift ? ctl->gshift : GUESS_SHIFT;
+    S->pub = ctl->pub ? ctl->pub : PUB_START;
     S->nl = 0; S->restL = NONE32; S->stale_hot = 0;
     S->stop = 0; S->t_start = wall_clock64();
     S->mem[0].hi = 0; S->mem[0].lo = 0;
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       const u64 hi = ok_any ? (d ? rr.h1 : rr.h0) : 0ull, lo = ok_any ? (d ? rr.l1 : rr.l0) : 0ull, cost = d ? c1 : c0;
       u32 listed = NONE32;                       // the candidate's entry in the list of the pass
       if (MC) {
-        // every candidate whose bound reaches the round's threshold goes on the list of the pass
+        // every candidate whose bound reaches the list's threshold goes on the list of the pass
         // with all a commit needs; the others count with their bound only (floor2)
         const bool pub = kc >= thr_pub && kc != 0u;
         const u64 pm = __ballot(pub);
@@ -913,7 +918,14 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           const u32 nu = S->ntl << a.tshift;
           if (tid == 0) S->units += nu;
           pass_units += nu;
-        } else score_list(thr);
+        } else {
+          u32 low = thr;                           // the list's threshold
+          if (MC) {
+            low = thr > S->pub ? thr - S->pub : 1u;
+            low = low > rest ? low : rest + 1u;
+          }
+          score_list(low);
+        }
         if (WIDE && resume) {
           resume = 0;
           if (tid == 0) wv.ctx->pending = 0;
@@ -1197,6 +1209,11 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 4u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
+        if (MC && cround == 0u) {
+          const u32 nl_ = S->nlist, pub = S->pub;
+          if (nl_ > LIST_MAX) S->pub = pub / 4u > PUB_MIN ? pub / 4u : PUB_MIN;
+          else if (nl_ < LIST_MAX / 2u) S->pub = pub * 2u < PUB_MAX ? pub * 2u : PUB_MAX;
+        }
         const Winner& Z = S->mem[m - 1];
         u64 ghi = Z.hi, glo = Z.lo;
         const u64 dlo = (glo >> gs) | (ghi << (64 - gs)), dhi = ghi >> gs;
@@ -1260,7 +1277,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   if (tid == 0) {
     ctl->n_iter = S->n_iter; ctl->n_mig = S->n_mig; ctl->n_drop = S->n_drop; ctl->n_evals = S->n_evals;
     ctl->thr_key = S->thr_key; ctl->status = S->status; ctl->done = S->done;
-    ctl->gshift = S->gshift;
+    ctl->gshift = S->gshift; ctl->pub = S->pub;
     ctl->overtime_after = base[(u64)A_OT * nb1 + nch];
     ctl->units_scored += S->units; ctl->second_rounds += S->second; ctl->jobs_run += S->jobs; ctl->launches += 1;
     ctl->passes += passes;
