@@ -78,6 +78,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 by_floor, touched;      // the selection ended because the next candidate did not clear the floor; timelines (a bit
                               // per array of level 1) whose chunk totals change in this pass
   u32 fast, pad1;             // the pass's migrations were picked from the list without an arg-max over all threads
+  u32 lim, pad3;              // the plan has made as many passes as it may
   u32 Fkeep, more;            // the floor of the pass; another round of commits follows from the same list
   u64 more_rounds, list_rescored;   // such rounds made; list entries scored again for them (statistics)
   u64 hq;                     // host-capacity query: maximum over the period
@@ -296,9 +297,12 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
 
   // The tiles of the hot list whose bound reaches `thr` and that were not scored in this pass
   // -> alist (marked, bound cleared: the scoring rebuilds it); filt bounds the others.
-  auto activate = [&](u32 thr) {
-    if (tid == 0) { S->ntl = 0; S->filt = 0; }
-    __syncthreads();
+  // (`fresh`: the counters are cleared already)
+  auto activate = [&](u32 thr, bool fresh) {
+    if (!fresh) {
+      if (tid == 0) { S->ntl = 0; S->filt = 0; }
+      __syncthreads();
+    }
     const u32 nl = S->nl;
     u32 fm = 0;
     for (u32 i0 = 0; i0 < nl; i0 += LB) {
@@ -331,7 +335,6 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   Winner mine;
   mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   u32 floor2 = 0;               // largest bound among the candidates this thread scored in the pass other than `mine`
-  u32 cur_iter = 0;             // number of the current pass (the stamp of the values computed in it)
 
   struct CandV { uint4 A, B; uint2 id; u32 p, t; };
   auto load_cand = [&](u32 u) -> CandV {
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           const u32 vd = (e.y >> 1) & 1u, pd = rr.ok0 ? 0u : 1u;
           if (vd == 0u && rr.ok0 && gt128(rr.h0, rr.l0, vhi, vlo)) { rr.h0 = vhi; rr.l0 = vlo; }
           if (vd == 1u && rr.ok1 && gt128(rr.h1, rr.l1, vhi, vlo)) { rr.h1 = vhi; rr.l1 = vlo; }
-          exact = (vd == pd && e.x == cur_iter) ? 1u : 0u;
+          exact = (vd == pd && e.x == (u32)S->n_iter) ? 1u : 0u;   // (the number of the pass stamps the values computed in it)
         }
       }
       u64 c0 = 1, c1 = 1;
@@ -798,7 +801,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       else {
         S->refused += 1;
         a.cd.cv[S->mem[0].pos] = make_uint4((u32)vlo, (u32)(vlo >> 32), (u32)vhi, (u32)(vhi >> 32));
-        a.cd.ce[S->mem[0].pos] = make_uint2(cur_iter, 1u | (S->mem[0].dest << 1));
+        a.cd.ce[S->mem[0].pos] = make_uint2((u32)S->n_iter, 1u | (S->mem[0].dest << 1));
         S->ntl = 0;
       }
     }
@@ -817,42 +820,55 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     return false;
   };
 
+  // What the next ranking pass finds: made by the last wavefront at the end of the pass before,
+  // beside the level-1 update, so that a pass begins without a barrier of its own.
+  auto open_pass = [&]() {
+    for (u32 i = lane; i < ns; i += 64u) smark[i] = 0;   // no tile scored yet
+    if (lane == 0) {
+      S->hq = 0; S->njobs = 0; S->ntl = 0; S->filt = 0;
+      S->mem[0].hi = 0; S->mem[0].lo = 0;
+      S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->by_floor = 0;
+      if (S->stale_hot) { S->restL = NONE32; S->stale_hot = 0; }
+      S->lim = max_iter && S->n_iter >= max_iter ? 1u : 0u;
+      if (a.tick_budget && wall_clock64() - S->t_start > a.tick_budget) S->stop = 1;
+    }
+  };
+  __syncthreads();
+  if (wave == LW - 1) open_pass();
+  if (tid == 0) S->m0 = 1;
   __syncthreads();
   // ---- passes ------------------------------------------------------------------------
   u32 passes = 0, used = 0;                          // ranking passes of this launch; with the further rounds of commits: what the budget counts
   bool wide_exit = false;
   while (true) {
+    u32 thr = S->thr_key;
     if (!resume) {                                   // (a pass taken up again has passed these tests)
-      if (S->done) break;
-      if (base[(u64)A_OT * nb1 + nch] == 0) { if (tid == 0) { S->done = 1; S->status = G10_FITS; } break; }
-      if (max_iter && S->n_iter >= max_iter) { if (tid == 0) { S->done = 1; S->status = G10_TRUNCATED; } break; }
-      if (used >= a.pass_budget || S->stop || (a.pass_stop && passes_before + passes >= a.pass_stop)) break;
+      const u32 done = S->done, lim = S->lim, stop = S->stop;
+      const u64 over = base[(u64)A_OT * nb1 + nch];
+      if (done) break;
+      if (over == 0) { if (tid == 0) { S->done = 1; S->status = G10_FITS; } break; }
+      if (lim) { if (tid == 0) { S->done = 1; S->status = G10_TRUNCATED; } break; }
+      if (used >= a.pass_budget || stop || (a.pass_stop && passes_before + passes >= a.pass_stop)) break;
       if (WIDE && S->no_wide) break;               // (the last launch of a round only ends the pass left open)
       ++passes; ++used;
     }
     mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0;
     floor2 = 0;
     pass_units = 0;
-    u32 thr = S->thr_key ? S->thr_key : NONE32;
-    if (WIDE && resume) thr = wv.ctx->thr;
-    __syncthreads();                               // the loop conditions and thr are read
+    if (!thr) thr = NONE32;
+    bool fresh = true;
     if (WIDE && resume) {                          // the tiles the open pass has scored, and the list of its open round
+      thr = wv.ctx->thr;
       for (u32 i = tid; i < ns; i += LB) smark[i] = wv.smark[i];
       for (u32 i = tid; i < wv.ctx->ntl; i += LB) alist[i] = wv.alist[i];
-    } else {
-      for (u32 i = tid; i < ns; i += LB) smark[i] = 0;   // no tile scored in this pass yet
+      if (tid == 0) { S->ntl = wv.ctx->ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; }
+      fresh = false;
+      __syncthreads();
     }
-    if (tid == 0) {
-      if (WIDE && resume) { S->ntl = wv.ctx->ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; }
-      else { S->n_iter += 1; S->n_evals += C - S->n_mig - S->n_drop; }
-      S->hq = 0; S->njobs = 0; S->ot_changed = 0;
-      S->mem[0].hi = 0; S->mem[0].lo = 0;
-      S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->m0 = 1; S->by_floor = 0; S->touched = 0;
-      if (S->stale_hot) { S->restL = NONE32; S->stale_hot = 0; }
-      if (a.tick_budget && wall_clock64() - S->t_start > a.tick_budget) S->stop = 1;
+    if (tid == 0) {                                // (read again behind the next barrier only)
+      if (!(WIDE && resume)) { S->n_iter += 1; S->n_evals += C - S->n_mig - S->n_drop; }
+      S->touched = 0; S->ot_changed = 0;
     }
-    __syncthreads();
-    cur_iter = (u32)S->n_iter;
 
     // rank: score the hot tiles whose bound reaches a threshold (first a guess a little under
     // the last benefit), lower the threshold to the best benefit found, repeat until no tile
@@ -874,7 +890,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           build_hot(low);
           if (rounds && tid == 0) S->stale_hot = 1;  // built without the tiles already scored: not kept for the next pass
         }
-        activate(thr);
+        activate(thr, fresh);
+        fresh = false;
         const u32 ntl = S->ntl;
         rest = S->restL > S->filt ? S->restL : S->filt;
         if (ntl == 0) {
@@ -999,6 +1016,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // benefit, as far as (2) and the transfer windows allow.  Where a round of commits ends with
     // entries still on the list that might clear the floor, the steps are taken again from here
     // (cround > 0) instead of from a new ranking.
+    bool opened = false;                                 // the next pass's state is made
     for (u32 cround = 0;; ++cround) {
     const bool from_list = MC && !(cround == 0u && S->fast);       // (else: the ranking has done this step)
     if (from_list && wave == LW - 1 && S->nlist > 1u && K < (1u << 30)) {
@@ -1037,9 +1055,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         }
         // (nothing on the list clears the floor: the pass is over)
         m = pick(e, have, false, F, 0u, allowed, by_floor);
+        if (m == 0u) open_pass();
       }
       if (lane == 0) { S->m0 = m; S->by_floor = by_floor; }
-    } else if (from_list && wave == LW - 1 && lane == 0) S->by_floor = 1;     // (nothing else on the list)
+    } else if (from_list && wave == LW - 1 && lane == 0) { S->m0 = 1; S->by_floor = 1; }     // (nothing else on the list)
     if (from_list) __syncthreads();
 
     // Step 2, chunk by chunk: what every picked migration does to the chunk (sets of migrations, a
@@ -1050,15 +1069,17 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // out).  For the winner itself the two tests only decide how it is committed: alone, and with
     // the exact host-capacity test.
     const u32 m0 = S->m0;
-    if (MC && m0 == 0u) break;                           // (a later round found nothing above the floor)
+    if (MC && m0 == 0u) { opened = true; break; }        // (a later round found nothing above the floor)
     u32 cutP = 0, allP = 0, cutH = 0, allH = 0, eF = 0, eH = 0, wF = 0, wH = 0;   // absent window / period cuts, covers the chunk whole;
                                                          // eviction and prefetch windows meet it, to flash and to host
     u64 lzP = 0, lzH = 0, cutHs = 0;                     // sizes of allP, allH, cutH
     bool jobP = false;
-    if (wave == LW - 1 && lane < m0) {                   // transfer times (needed by the jobs and the records)
-      Winner& M = S->mem[lane];
-      M.tau_o = ceil_div_x1000(M.s, M.dest ? bwo1 : bwo0, M.dest ? ivo1 : ivo0);
-      M.tau_i = ceil_div_x1000(M.s, M.dest ? bwi1 : bwi0, M.dest ? ivi1 : ivi0);
+    if (wave == LW - 1 && (lane & 31u) < m0) {           // transfer times (needed by the jobs and the records): out in lane i, in in lane 32 + i
+      Winner& M = S->mem[lane & 31u];
+      const bool out = lane < 32u;
+      const u64 tau = ceil_div_x1000(M.s, out ? (M.dest ? bwo1 : bwo0) : (M.dest ? bwi1 : bwi0), out ? (M.dest ? ivo1 : ivo0) : (M.dest ? ivi1 : ivi0));
+      if (out) M.tau_o = tau;
+      else M.tau_i = tau;
     }
     if (tid == 0) S->jnext = LW - 1;
     if (tid < ((nch + 63u) & ~63u)) {
@@ -1243,6 +1264,12 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       const u32 touched = S->touched | (S->ot_changed ? 1u : 0u);
       if (wave < N_ARR && ((touched >> wave) & 1u)) {
         const u32 arr = wave;
+        if (nch <= G10_WAVE) {                           // (a chunk per lane)
+          const u64 v = lane < nch ? tot[(u64)arr * nch + lane] : 0ull;
+          const u64 inc = wave_scan_incl(v);
+          if (lane < nch) base[(u64)arr * nb1 + lane] = inc - v;
+          if (lane == G10_WAVE - 1) base[(u64)arr * nb1 + nch] = inc;
+        } else {
         constexpr u32 PER = (NCH_MAX + G10_WAVE - 1) / G10_WAVE;
         u64 v[PER], sum = 0;
 #pragma unroll
@@ -1260,12 +1287,20 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           run += v[k];
         }
         if (lane == G10_WAVE - 1) base[(u64)arr * nb1 + nch] = inc;
+        }
       }
+      opened = !MC || !S->more;
+      if (opened && wave == LW - 1) open_pass();
       __syncthreads();
     }
-    if (!MC || !S->more) break;
+    if (opened) break;
     ++used;
     }                                                    // (rounds of commits of one ranking pass)
+    if (!opened) {                                       // (a refused candidate, or a test left to the next pass)
+      __syncthreads();
+      if (wave == LW - 1) open_pass();
+      __syncthreads();
+    }
   }
   __syncthreads();
 
