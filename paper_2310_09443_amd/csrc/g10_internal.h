@@ -98,6 +98,11 @@ __device__ __forceinline__ T wave_last(T v) {                 // the value of la
   }
 }
 
+// A value that is the same in every lane (a counter read from LDS, say), in a scalar register: the
+// compiler cannot know, and would predicate what depends on it lane by lane.
+__device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ u64 uniform(u64 v) { return ((u64)uniform((u32)(v >> 32)) << 32) | uniform((u32)v); }
+
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) { return wave_last(wave_scan_dpp<OpAdd>(v, (T)0)); }
 

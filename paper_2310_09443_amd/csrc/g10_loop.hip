@@ -144,6 +144,21 @@ __device__ __forceinline__ u32 wave_best_lane_ratio(u64 hi, u64 lo, u64 cost, u3
   return p;
 }
 
+// Exclusive sums of four strips of 64 values (v[i] of lane l stands at 64 i + l) from `carry` on, which moves past
+// them.  T: the type that holds every sum.
+template <class T>
+__device__ __forceinline__ void scan_strips(const u64 (&v)[4], u64 (&run)[4], u64& carry) {
+  T inc[4], at = (T)carry;
+#pragma unroll
+  for (u32 i = 0; i < 4; ++i) inc[i] = wave_scan_incl((T)v[i]);
+#pragma unroll
+  for (u32 i = 0; i < 4; ++i) {
+    run[i] = (T)(at + inc[i] - (T)v[i]);
+    at += wave_last(inc[i]);
+  }
+  carry = at;
+}
+
 // Do the doubled slot ranges [x1, y1] and [x2, y2] (each shorter than K) share a kernel slot?  (K < 2^30)
 __device__ __forceinline__ bool cyc_overlap32(u32 x1, u32 y1, u32 x2, u32 y2, u32 K) {
   return (x1 <= y2 && x2 <= y1) || (x1 + K <= y2 && x2 <= y1 + K) || (x1 <= y2 + K && x2 + K <= y1);
@@ -184,7 +199,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   unsigned short* tlist = (unsigned short*)(hpend + nch);  // [nt]  the hot list
   unsigned short* alist = tlist + nt;                            // [nt]  tiles scored in the current round
 
-  const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const u32 tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
   Ctl* ctl = a.ctl;
   // A pass left open by the last launch: its list has been scored by the scoring kernel (1), or
   // has not (2: it is scored here).  Launches are queued ahead of what is known of the plan's
@@ -303,7 +318,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       if (tid == 0) { S->ntl = 0; S->filt = 0; }
       __syncthreads();
     }
-    const u32 nl = S->nl;
+    const u32 nl = uniform(S->nl);
     u32 fm = 0;
     for (u32 i0 = 0; i0 < nl; i0 += LB) {
       const u32 i = i0 + tid;
@@ -339,7 +354,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   struct CandV { uint4 A, B; uint2 id; u32 p, t; };
   auto load_cand = [&](u32 u) -> CandV {
     CandV c;
-    c.t = alist[u >> a.tshift];
+    c.t = uniform((u32)alist[u >> a.tshift]);
     c.p = (((c.t << a.tshift) + (u & ((1u << a.tshift) - 1u))) << 8) + (tid & 255u);
     c.A = a.cd.A[c.p]; c.B = a.cd.B[c.p]; c.id = a.cd.id[c.p];
     return c;
@@ -350,11 +365,11 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   // unit, about one cache line per clock: lanes whose candidate is dead load
   // nothing, and struck destinations are written back so later passes skip them.
   auto score_list = [&](const u32 thr_pub) {
-    const u32 nunits = S->ntl << a.tshift;
+    const u32 nunits = uniform(S->ntl) << a.tshift;
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
     mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
-    u32 u = tid >> 8;
+    u32 u = uniform(tid >> 8);
     CandV cur;
     if (u < nunits) cur = load_cand(u);
     while (u < nunits) {
@@ -482,9 +497,9 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       if (lane == 0) x = atomicAdd(&S->jnext, 1u);
       return x;                                          // (in lane 0)
     };
-    u32 jb = begin + (wave < LW - 1 ? wave : (u32)__builtin_amdgcn_readfirstlane((int)take()));
+    u32 jb = begin + (wave < LW - 1 ? wave : uniform(take()));
     while (jb < end) {
-      const u64 jw = jobs[jb];
+      const u64 jw = uniform(jobs[jb]);
       const u32 after = take();                            // (known by the time this job is done)
       const u32 type = (u32)(jw >> 16) & 0xffu, c = (u32)jw & 0xffffu, ma_ = (u32)(jw >> 24) & keep, mb_ = (u32)(jw >> 40) & keep;
       const u32 s0 = c * CH, s1 = (s0 + CH - 1 < K - 1) ? s0 + CH - 1 : K - 1;
@@ -500,6 +515,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         ulonglong2* tab = px + (u64)((out ? T_FO : T_FI) + d) * tl.Kp;
         const u64 bc = base[(u64)arr * nb1 + c], ball = base[(u64)arr * nb1 + nch];
         const u32 mask = ma_;                            // the migrations of this destination whose window meets the chunk
+        // (sums of free time inside the chunk stay under its old total: usually 32 bits hold them)
+        const bool narrow = uniform((u32)(tot[(u64)arr * nch + c] >> 32)) == 0u;
         u32 first = NONE32;
         u64 carry = 0;
         for (u32 st = 0; st < tl.spt; ++st) {
@@ -515,7 +532,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           }
           for (u32 pb = mask; pb; pb &= pb - 1) {
             const Winner& W = S->mem[__builtin_ctz(pb)];
-            const u32 x = out ? W.L1 : W.b + 1, y = out ? W.a - 1 : W.R - 1;
+            const u32 x = uniform(out ? W.L1 : W.b + 1), y = uniform(out ? W.a - 1 : W.R - 1);
             const u64 tau = out ? W.tau_o : W.tau_i, ref = out ? W.fo_base : W.fi_end;
             if (st == 0) {
               const u32 fc = first_covered(s0, s1, K, x, y);
@@ -536,15 +553,14 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
               }
             }
           }
-          u64 inc[4];
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i) inc[i] = wave_scan_incl(f[i]);
+          u64 run[4];
+          if (narrow) scan_strips<u32>(f, run, carry);
+          else scan_strips<u64>(f, run, carry);
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
             const u32 j = j0 + i * 64u;
             if (took[i]) fr[j] = f[i];
-            if (j < K && j > first) tab[j].x = carry + inc[i] - f[i];
-            carry += wave_last(inc[i]);
+            if (j < K && j > first) tab[j].x = run[i];
           }
         }
         if (lane == 0) tot[(u64)arr * nch + c] = carry;
@@ -559,6 +575,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         const u32 part = ma_;                            // migrations whose window cuts the chunk; mb_: those that cover it whole
         u64 mn = NONE64, carry = 0;
         u32 first = NONE32;                              // first slot that dropped under the capacity
+        const bool narrow = uniform((u32)(tot[(u64)A_OT * nch + c] >> 32)) == 0u;   // (the over-capacity time only falls)
         for (u32 st = 0; st < tl.spt; ++st) {
           const u32 j0 = s0 + st * 256u + lane;
           u64 p[4], v[4], sub[4];
@@ -573,7 +590,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           const u64 lz = lz0 + lz_full;
           for (u32 pb = part; pb; pb &= pb - 1) {
             const Winner& W = S->mem[__builtin_ctz(pb)];
-            const u32 x = W.a, y = W.b;
+            const u32 x = uniform(W.a), y = uniform(W.b);
             const u64 s = W.s;
 #pragma unroll
             for (u32 i = 0; i < 4; ++i) {
@@ -600,22 +617,23 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
             if (first != NONE32 && st) carry = px[s0 + st * 256u].y;   // (nothing before this slot changes)
           }
           if (first != NONE32) {                         // rewrite the prefix of the slots after it
-            u64 inc[4];
-#pragma unroll
-            for (u32 i = 0; i < 4; ++i) inc[i] = wave_scan_incl(v[i]);
+            u64 run[4];
+            if (narrow) scan_strips<u32>(v, run, carry);
+            else scan_strips<u64>(v, run, carry);
 #pragma unroll
             for (u32 i = 0; i < 4; ++i) {
               const u32 j = j0 + i * 64u;
               if (j < K && j > first) {
-                const u64 run = carry + inc[i] - v[i];
 #pragma unroll
-                for (u32 t = 0; t < 4; ++t) px[(u64)t * tl.Kp + j].y = run;      // the four copies of OT
+                for (u32 t = 0; t < 4; ++t) px[(u64)t * tl.Kp + j].y = run[i];   // the four copies of OT
               }
-              carry += wave_last(inc[i]);
             }
           }
         }
-        mn = wave_min(mn);
+        {                                                // the minimum: its high word, then the low one among those
+          const u32 hi = wave_min((u32)(mn >> 32)), lo = wave_min((u32)(mn >> 32) == hi ? (u32)mn : NONE32);
+          mn = ((u64)hi << 32) | lo;
+        }
         if (lane == 0) {
           minOver[c] = mn; lazyP[c] = lz0 + lz_full;
           if (first != NONE32) { tot[(u64)A_OT * nch + c] = carry; S->ot_changed = 1; }
@@ -704,7 +722,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         }
         if (lane == 0) atomicMax((unsigned long long*)&S->hq, (unsigned long long)m_cov);
       }
-      jb = begin + (u32)__builtin_amdgcn_readfirstlane((int)after);
+      jb = begin + uniform(after);
     }
     if (tid == 0) S->jobs += end - begin;
   };
@@ -788,7 +806,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       }
     }
     __syncthreads();
-    run_jobs(0u, S->njobs, 0xffffu);
+    run_jobs(0u, uniform(S->njobs), 0xffffu);
     __syncthreads();
     const u64 a0 = S->acc[0], a1 = S->acc[1], a2 = S->acc[2];
     const u64 vlo = a0 + (a1 << 32), vhi = a2 + (a1 >> 32) + (vlo < a0 ? 1ull : 0ull);
@@ -841,10 +859,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   u32 passes = 0, used = 0;                          // ranking passes of this launch; with the further rounds of commits: what the budget counts
   bool wide_exit = false;
   while (true) {
-    u32 thr = S->thr_key;
+    u32 thr = uniform(S->thr_key);
     if (!resume) {                                   // (a pass taken up again has passed these tests)
-      const u32 done = S->done, lim = S->lim, stop = S->stop;
-      const u64 over = base[(u64)A_OT * nb1 + nch];
+      const u32 done = uniform(S->done), lim = uniform(S->lim), stop = uniform(S->stop);
+      const u64 over = uniform(base[(u64)A_OT * nb1 + nch]);
       if (done) break;
       if (over == 0) { if (tid == 0) { S->done = 1; S->status = G10_FITS; } break; }
       if (lim) { if (tid == 0) { S->done = 1; S->status = G10_TRUNCATED; } break; }
@@ -884,7 +902,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         pass_units = wv.ctx->pass_units;
         if (tid == LB - 1 && rounds) mine = wv.win[WIDE_WG];    // the best of the rounds before
       } else if (!again) {
-        if (S->restL >= thr) {                     // the hot list may miss a tile that reaches thr: build it anew,
+        if (uniform(S->restL) >= thr) {                     // the hot list may miss a tile that reaches thr: build it anew,
           const u32 low = thr == NONE32 ? thr : (thr > (1u << 19) ? thr - (1u << 19) : 1u);   // a few percent lower to last a while
           __syncthreads();
           build_hot(low);
@@ -892,8 +910,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         }
         activate(thr, fresh);
         fresh = false;
-        const u32 ntl = S->ntl;
-        rest = S->restL > S->filt ? S->restL : S->filt;
+        const u32 ntl = uniform(S->ntl);
+        rest = uniform(S->restL > S->filt ? S->restL : S->filt);
         if (ntl == 0) {
           if ((rounds && (S->mem[0].hi | S->mem[0].lo) != 0) || rest == 0) decided = true;   // nothing left that could win
           else {
@@ -938,7 +956,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         } else {
           u32 low = thr;                           // the list's threshold
           if (MC) {
-            low = thr > S->pub ? thr - S->pub : 1u;
+            const u32 pub = uniform(S->pub);
+            low = thr > pub ? thr - pub : 1u;
             low = low > rest ? low : rest + 1u;
           }
           score_list(low);
@@ -957,18 +976,18 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           if (lane == 0 && f2) atomicMax(&S->F2, f2);
           __syncthreads();
           if (wave == LW - 1) {
-            const u32 nl_ = S->nlist, n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
-            const u32 F = rest > S->F2 ? rest : S->F2;
+            const u32 nl_ = uniform(S->nlist), n = nl_ < LIST_MAX ? nl_ : LIST_MAX, f2_ = uniform(S->F2);
+            const u32 F = rest > f2_ ? rest : f2_;
             const bool have = lane < n;
             Winner e;
             if (have) e = S->list[lane];
             else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
             u32 allowed = MAXM, by_floor;                // passes of Algorithm 1 this round may stand for
-            if (max_iter && max_iter - S->n_iter + 1 < allowed) allowed = (u32)(max_iter - S->n_iter + 1);   // (n_iter counts this pass already)
+            if (max_iter && max_iter - uniform(S->n_iter) + 1 < allowed) allowed = (u32)(max_iter - uniform(S->n_iter) + 1);   // (n_iter counts this pass already)
             const u32 m = pick(e, have, false, F, 0u, allowed, by_floor);
             if (lane == 0) { S->m0 = m ? m : 1u; S->by_floor = by_floor; S->Fkeep = F; S->fast = m ? 1u : 0u; }
           } else {
-            const u32 ntl = S->ntl;
+            const u32 ntl = uniform(S->ntl);
             for (u32 i = wave; i < ntl; i += LW - 1) {   // bounds of the groups that hold re-scored tiles
               const u32 g = alist[i] >> 6, t = g * 64 + lane;
               const u32 k = wave_max(t < nt ? keys[t] : 0u);
@@ -976,7 +995,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
             }
           }
           __syncthreads();
-          if (S->fast) { rest_final = rest; break; }
+          if (uniform(S->fast)) { rest_final = rest; break; }
         }
         reduce_best();
         const u32 kb = key_dn_of<RATIO>(S->mem[0].hi, S->mem[0].lo, S->mem[0].cost);
@@ -1017,18 +1036,21 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // entries still on the list that might clear the floor, the steps are taken again from here
     // (cround > 0) instead of from a new ranking.
     bool opened = false;                                 // the next pass's state is made
+    PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
+    uint4 nextA = make_uint4(0u, 0u, 1u, 0u), nextB = make_uint4(1u, 0u, 0u, 0u);   // (last wavefront) the list entries' windows and
+    Gathered next;                                       // what a further round needs of the slot tables for them
     for (u32 cround = 0;; ++cround) {
-    const bool from_list = MC && !(cround == 0u && S->fast);       // (else: the ranking has done this step)
-    if (from_list && wave == LW - 1 && S->nlist > 1u && K < (1u << 30)) {
-      const u32 nl_ = S->nlist, n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
+    const bool from_list = MC && !(cround == 0u && uniform(S->fast));       // (else: the ranking has done this step)
+    if (from_list && wave == LW - 1 && uniform(S->nlist) > 1u && K < (1u << 30)) {
+      const u32 nl_ = uniform(S->nlist), n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
       const bool have = lane < n;
       Winner e;
       if (have) e = S->list[lane];
       else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
       u32 allowed = MAXM, m, by_floor;                 // passes of Algorithm 1 this round may stand for
       if (cround == 0u) {
-        const u32 F = rest_final > S->F2 ? rest_final : S->F2;
-        if (max_iter && max_iter - S->n_iter + 1 < allowed) allowed = (u32)(max_iter - S->n_iter + 1);   // (n_iter counts this pass already)
+        const u32 f2_ = uniform(S->F2), F = rest_final > f2_ ? rest_final : f2_;
+        if (max_iter && max_iter - uniform(S->n_iter) + 1 < allowed) allowed = (u32)(max_iter - uniform(S->n_iter) + 1);   // (n_iter counts this pass already)
         if (lane == 0) S->Fkeep = F;
         m = pick(e, have, have && e.cand == S->mem[0].cand, F, 1u, allowed, by_floor);
       } else {
@@ -1036,15 +1058,14 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         // the earlier rounds left them (a committed candidate has no window any more and scores
         // nothing), and the best of them wins the next pass of Algorithm 1 if its key clears the
         // floor - every candidate not on the list is still bounded by it, since bounds only fall.
-        const u32 F = S->Fkeep;
-        if (max_iter && max_iter - S->n_iter < allowed) allowed = (u32)(max_iter - S->n_iter);
+        const u32 F = uniform(S->Fkeep);
+        if (max_iter && max_iter - uniform(S->n_iter) < allowed) allowed = (u32)(max_iter - uniform(S->n_iter));
         if (lane == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->touched = 0; S->ot_changed = 0; S->hq = 0; S->list_rescored += n; }
-        PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
         Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
         mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
         if (have) {
-          const uint4 A = S->listA[lane], B = S->listB[lane];
-          const Score r = score_candidate(pv, mc, A, B);
+          const uint4 A = nextA, B = nextB;
+          const Score r = score_gathered(pv, mc, A, B, next);
           const bool ok_any = r.ok0 || r.ok1;
           const u32 d = r.ok0 ? 0u : 1u;
           const bool one = gt128(r.h1, r.l1, r.h0, r.l0);
@@ -1068,7 +1089,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // the earlier ones, ends the set (it is ranked again in the next pass, and the jobs leave it
     // out).  For the winner itself the two tests only decide how it is committed: alone, and with
     // the exact host-capacity test.
-    const u32 m0 = S->m0;
+    const u32 m0 = uniform(S->m0);
     if (MC && m0 == 0u) { opened = true; break; }        // (a later round found nothing above the floor)
     u32 cutP = 0, allP = 0, cutH = 0, allH = 0, eF = 0, eH = 0, wF = 0, wH = 0;   // absent window / period cuts, covers the chunk whole;
                                                          // eviction and prefetch windows meet it, to flash and to host
@@ -1142,11 +1163,11 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       }
     }
     __syncthreads();
-    const u32 nj = S->njobs;                             // the jobs of the round
-    u32 m = m0 < S->cut ? m0 : S->cut;
+    const u32 nj = uniform(S->njobs), cut_ = uniform(S->cut), need_exact = uniform(S->need_exact);   // (nj: the jobs of the round)
+    u32 m = m0 < cut_ ? m0 : cut_;
     bool room = true;
-    if (MC && cround && S->need_exact) break;            // (the exact host-memory test is left to the next ranking pass)
-    if (S->need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
+    if (MC && cround && need_exact) break;               // (the exact host-memory test is left to the next ranking pass)
+    if (need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
       if (tid == 0) S->hq = 0;
@@ -1154,7 +1175,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       if ((cutH & 1u) || ((allH & 1u) && hpend[tid])) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_HQ << 16) | tid;   // (behind the round's jobs)
       else if (allH & 1u) atomicMax((unsigned long long*)&S->hq, (unsigned long long)hmax[tid]);   // (exact: nothing is missing there)
       __syncthreads();
-      run_jobs(nj, S->njobs, 0xffffu);
+      run_jobs(nj, uniform(S->njobs), 0xffffu);
       __syncthreads();
       room = s <= host_cap && S->hq <= host_cap - s;
       if (tid == 0) S->jnext = LW - 1;
@@ -1261,7 +1282,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     __syncthreads();
     // level 1: the bases of the timelines whose chunk totals changed, one wavefront per timeline
     {
-      const u32 touched = S->touched | (S->ot_changed ? 1u : 0u);
+      const u32 touched = uniform(S->touched | (S->ot_changed ? 1u : 0u));
       if (wave < N_ARR && ((touched >> wave) & 1u)) {
         const u32 arr = wave;
         if (nch <= G10_WAVE) {                           // (a chunk per lane)
@@ -1289,8 +1310,16 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         if (lane == G10_WAVE - 1) base[(u64)arr * nb1 + nch] = inc;
         }
       }
-      opened = !MC || !S->more;
-      if (opened && wave == LW - 1) open_pass();
+      opened = !MC || !uniform(S->more);
+      if (wave == LW - 1) {
+        if (opened) open_pass();
+        else {                                           // the jobs are done: the slot tables are read beside the level-1 update
+          const u32 nl_ = uniform(S->nlist);
+          nextA = make_uint4(0u, 0u, 1u, 0u); nextB = make_uint4(1u, 0u, 0u, 0u);
+          if (lane < nl_) { nextA = S->listA[lane]; nextB = S->listB[lane]; }
+          next = gather_candidate(pv, nextA, nextB);
+        }
+      }
       __syncthreads();
     }
     if (opened) break;

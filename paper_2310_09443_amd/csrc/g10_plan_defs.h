@@ -197,12 +197,32 @@ __device__ __forceinline__ ulonglong2 ld_pair(const PrefixView& pv, u32 table, u
   return reinterpret_cast<const ulonglong2*>(pv.px)[(u64)table * slots_padded(pv.K) + j];
 }
 
-// Both destinations' record pairs are gathered before anything is used.  A
-// destination is struck when its channel cannot carry the transfer any more
+// Both destinations' pairs at the ends of their windows: {FO, OT} at a and L, {FI, OT} at b + 1 and R.
+struct Gathered {
+  ulonglong2 a0, b0, L0, R0, a1, b1, L1, R1;
+};
+__device__ __forceinline__ Gathered gather_candidate(const PrefixView& pv, const uint4 A, const uint4 B) {
+  Gathered g;
+  const ulonglong2 z = {0, 0};
+  g.a0 = z; g.b0 = z; g.L0 = z; g.R0 = z; g.a1 = z; g.b1 = z; g.L1 = z; g.R1 = z;
+  const u32 K = pv.K;
+  const u32 jL = A.x >= K ? A.x - K : A.x, jR = A.y >= K ? A.y - K : A.y;
+  if (A.z <= A.w) {
+    g.L0 = ld_pair(pv, T_FO + 0, jL); g.R0 = ld_pair(pv, T_FI + 0, jR);
+    g.a0 = ld_pair(pv, T_FO + 0, A.z >= K ? A.z - K : A.z); g.b0 = ld_pair(pv, T_FI + 0, A.w + 1 >= K ? A.w + 1 - K : A.w + 1);
+  }
+  if (B.x <= B.y) {
+    g.L1 = ld_pair(pv, T_FO + 1, jL); g.R1 = ld_pair(pv, T_FI + 1, jR);
+    g.a1 = ld_pair(pv, T_FO + 1, B.x >= K ? B.x - K : B.x); g.b1 = ld_pair(pv, T_FI + 1, B.y + 1 >= K ? B.y + 1 - K : B.y + 1);
+  }
+  return g;
+}
+
+// A destination is struck when its channel cannot carry the transfer any more
 // (reservations only grow); host also when no over-capacity time is left in
 // its window (pressure only falls), flash then too if host is gone: while
 // host could still score, a feasible flash window keeps the policy on flash.
-__device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Machine& mc, const uint4 A, const uint4 B) {
+__device__ __forceinline__ Score score_gathered(const PrefixView& pv, const Machine& mc, const uint4 A, const uint4 B, const Gathered& g) {
   Score r;
   r.h0 = r.l0 = r.h1 = r.l1 = r.fo_L = r.fi_R = 0;
   r.ok0 = r.ok1 = r.strike0 = r.strike1 = false;
@@ -210,48 +230,33 @@ __device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Mac
   if (!(v0 || v1)) return r;
   const u32 K = pv.K, nb1 = pv.nch + 1;
   const u64 s = ((u64)B.w << 32) | B.z, x1000 = s * 1000ull;
-  const u32 L1 = A.x, R = A.y;
-  const bool sL = L1 >= K, sR = R >= K;
-  const u32 jL = sL ? L1 - K : L1, jR = sR ? R - K : R;
-  const u32 cL = jL >> pv.shift_ch, cR = jR >> pv.shift_ch;
+  const bool sL = A.x >= K, sR = A.y >= K;
+  const u32 cL = (sL ? A.x - K : A.x) >> pv.shift_ch, cR = (sR ? A.y - K : A.y) >> pv.shift_ch;
   const u64* bOT = pv.base + (u64)A_OT * nb1;
-  bool sa0 = false, sb0 = false, sa1 = false, sb1 = false;
-  u32 ca0 = 0, cb0 = 0, ca1 = 0, cb1 = 0;
-  ulonglong2 qa0 = {0, 0}, qb0 = {0, 0}, qL0 = {0, 0}, qR0 = {0, 0}, qa1 = {0, 0}, qb1 = {0, 0}, qL1 = {0, 0}, qR1 = {0, 0};
-  if (v0) {
-    sa0 = A.z >= K; sb0 = A.w + 1 >= K;
-    const u32 ja = sa0 ? A.z - K : A.z, jb = sb0 ? A.w + 1 - K : A.w + 1;
-    ca0 = ja >> pv.shift_ch; cb0 = jb >> pv.shift_ch;
-    qL0 = ld_pair(pv, T_FO + 0, jL); qR0 = ld_pair(pv, T_FI + 0, jR);      // {FO0, OT} {FI0, OT}
-    qa0 = ld_pair(pv, T_FO + 0, ja); qb0 = ld_pair(pv, T_FI + 0, jb);
-  }
-  if (v1) {
-    sa1 = B.x >= K; sb1 = B.y + 1 >= K;
-    const u32 ja = sa1 ? B.x - K : B.x, jb = sb1 ? B.y + 1 - K : B.y + 1;
-    ca1 = ja >> pv.shift_ch; cb1 = jb >> pv.shift_ch;
-    qL1 = ld_pair(pv, T_FO + 1, jL); qR1 = ld_pair(pv, T_FI + 1, jR);      // {FO1, OT} {FI1, OT}
-    qa1 = ld_pair(pv, T_FO + 1, ja); qb1 = ld_pair(pv, T_FI + 1, jb);
-  }
   u64 fo0_L = 0, fi0_R = 0, fo1_L = 0, fi1_R = 0;
   if (v0) {
+    const bool sa = A.z >= K, sb = A.w + 1 >= K;
+    const u32 ca = (sa ? A.z - K : A.z) >> pv.shift_ch, cb = (sb ? A.w + 1 - K : A.w + 1) >> pv.shift_ch;
     const u64 *bFO = pv.base + (u64)(A_FO + 0) * nb1, *bFI = pv.base + (u64)(A_FI + 0) * nb1;
     const u64 allFO = bFO[pv.nch], allFI = bFI[pv.nch], allOT = bOT[pv.nch];
-    fo0_L = (sL ? allFO : 0ull) + bFO[cL] + qL0.x; fi0_R = (sR ? allFI : 0ull) + bFI[cR] + qR0.x;
-    const u64 fo_a = (sa0 ? allFO : 0ull) + bFO[ca0] + qa0.x, fi_b = (sb0 ? allFI : 0ull) + bFI[cb0] + qb0.x;
+    fo0_L = (sL ? allFO : 0ull) + bFO[cL] + g.L0.x; fi0_R = (sR ? allFI : 0ull) + bFI[cR] + g.R0.x;
+    const u64 fo_a = (sa ? allFO : 0ull) + bFO[ca] + g.a0.x, fi_b = (sb ? allFI : 0ull) + bFI[cb] + g.b0.x;
     r.ok0 = carries(fo_a - fo0_L, mc.bwo0, x1000) && carries(fi0_R - fi_b, mc.bwi0, x1000);
     if (r.ok0) {
-      const u64 ot = ((sb0 ? allOT : 0ull) + bOT[cb0] + qb0.y) - ((sa0 ? allOT : 0ull) + bOT[ca0] + qa0.y);
+      const u64 ot = ((sb ? allOT : 0ull) + bOT[cb] + g.b0.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a0.y);
       r.h0 = __umul64hi(s, ot); r.l0 = s * ot;
     }
   }
   if (v1) {
+    const bool sa = B.x >= K, sb = B.y + 1 >= K;
+    const u32 ca = (sa ? B.x - K : B.x) >> pv.shift_ch, cb = (sb ? B.y + 1 - K : B.y + 1) >> pv.shift_ch;
     const u64 *bFO = pv.base + (u64)(A_FO + 1) * nb1, *bFI = pv.base + (u64)(A_FI + 1) * nb1;
     const u64 allFO = bFO[pv.nch], allFI = bFI[pv.nch], allOT = bOT[pv.nch];
-    fo1_L = (sL ? allFO : 0ull) + bFO[cL] + qL1.x; fi1_R = (sR ? allFI : 0ull) + bFI[cR] + qR1.x;
-    const u64 fo_a = (sa1 ? allFO : 0ull) + bFO[ca1] + qa1.x, fi_b = (sb1 ? allFI : 0ull) + bFI[cb1] + qb1.x;
+    fo1_L = (sL ? allFO : 0ull) + bFO[cL] + g.L1.x; fi1_R = (sR ? allFI : 0ull) + bFI[cR] + g.R1.x;
+    const u64 fo_a = (sa ? allFO : 0ull) + bFO[ca] + g.a1.x, fi_b = (sb ? allFI : 0ull) + bFI[cb] + g.b1.x;
     r.ok1 = carries(fo_a - fo1_L, mc.bwo1, x1000) && carries(fi1_R - fi_b, mc.bwi1, x1000);
     if (r.ok1) {
-      const u64 ot = ((sb1 ? allOT : 0ull) + bOT[cb1] + qb1.y) - ((sa1 ? allOT : 0ull) + bOT[ca1] + qa1.y);
+      const u64 ot = ((sb ? allOT : 0ull) + bOT[cb] + g.b1.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a1.y);
       r.h1 = __umul64hi(s, ot); r.l1 = s * ot;
     }
   }
@@ -261,6 +266,10 @@ __device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Mac
   r.strike1 = v1 && !keep1;
   r.fo_L = r.ok0 ? fo0_L : fo1_L; r.fi_R = r.ok0 ? fi0_R : fi1_R;
   return r;
+}
+// (everything is gathered before anything is used)
+__device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Machine& mc, const uint4 A, const uint4 B) {
+  return score_gathered(pv, mc, A, B, gather_candidate(pv, A, B));
 }
 
 // ---------------------------------------------------------------------------
