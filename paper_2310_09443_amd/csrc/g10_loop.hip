@@ -63,7 +63,9 @@ constexpr u32 MC_GUESS_SHIFT_MIN = 3;   // the widest margin of a pass's first t
 constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the second and later migrations
 // How far under the round's threshold a scored candidate's bound may lie to go on the list, in key steps (2^24 are a
 // factor of two).  Entries under the bound of the tiles left out cannot be picked, so that is the lowest; within that the
-// margin follows the list: it doubles while the list stays short and shrinks when it overflows.
+// margin follows the list towards 16 to 36 entries, in small steps near there: which entries an overflowing list takes
+// is left to chance, and a margin that doubled into an overflow every few passes gave stress plans between 400 and 1100
+// ranking passes (25.8 to 31.3 ms; 26.3 ms at the median with small steps, 28.5 without).
 constexpr u32 PUB_START = 1u << 22, PUB_MIN = 1u << 12, PUB_MAX = 1u << 30;
 
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
@@ -1248,13 +1250,17 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           if (rounds > 1u) { if (gs > 2u) --gs; }
           else if ((S->n_iter & 31u) == 0u && gs < GUESS_SHIFT) ++gs;
         } else if (pass_units > 8u && gs < GUESS_SHIFT_MAX) ++gs;
-        else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 4u && gs > MC_GUESS_SHIFT_MIN) --gs; }
+        else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 6u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
         if (MC && cround == 0u) {
           const u32 nl_ = S->nlist, pub = S->pub;
-          if (nl_ > LIST_MAX) S->pub = pub / 4u > PUB_MIN ? pub / 4u : PUB_MIN;
-          else if (nl_ < LIST_MAX / 2u) S->pub = pub * 2u < PUB_MAX ? pub * 2u : PUB_MAX;
+          u32 x = pub;
+          if (nl_ > LIST_MAX) x = pub / 2u;
+          else if (nl_ > 36u) x = pub - pub / 8u;
+          else if (nl_ < 6u) x = pub * 2u;
+          else if (nl_ < 16u) x = pub + pub / 4u;
+          S->pub = x < PUB_MIN ? PUB_MIN : x > PUB_MAX ? PUB_MAX : x;
         }
         const Winner& Z = S->mem[m - 1];
         u64 ghi = Z.hi, glo = Z.lo;
