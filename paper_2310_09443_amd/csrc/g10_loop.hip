@@ -38,23 +38,28 @@ struct WideCtx {
   u32 rounds, pass_units;     // of the pass left open: rounds finished, units scored in them
   u32 seq, pad[3];            // launches of the loop kernel on this plan so far
 };
+struct WideKey {              // the ranking of a winner on its own, for the arg-max over them
+  u64 hi, lo, cost, cand;
+};
 struct WideView {
   WideCtx* ctx;
+  WideKey* key;               // [WIDE_WG + 1] of win[]
   Winner* win;                // [WIDE_WG], then the best of the earlier rounds
   u64* smark;                 // [NT_MAX / 64]  tiles scored in the pass left open
   unsigned short* alist;      // [NT_MAX]       the list
 };
-constexpr size_t WIDE_BYTES = sizeof(WideCtx) + (WIDE_WG + 1) * sizeof(Winner) + (NT_MAX / 64) * 8 + (size_t)NT_MAX * 2;
+constexpr size_t WIDE_BYTES = sizeof(WideCtx) + (WIDE_WG + 1) * (sizeof(WideKey) + sizeof(Winner)) + (NT_MAX / 64) * 8 + (size_t)NT_MAX * 2;
 __host__ __device__ __forceinline__ WideView wide_view(void* blob) {
   WideView v;
   char* q = (char*)blob;
   v.ctx = (WideCtx*)q; q += sizeof(WideCtx);
+  v.key = (WideKey*)q; q += (WIDE_WG + 1) * sizeof(WideKey);
   v.win = (Winner*)q; q += (WIDE_WG + 1) * sizeof(Winner);
   v.smark = (u64*)q; q += (NT_MAX / 64) * 8;
   v.alist = (unsigned short*)q;
   return v;
 }
-static_assert(sizeof(WideCtx) % 16 == 0 && sizeof(Winner) % 8 == 0, "the arrays of the scoring kernel's block stay aligned");
+static_assert(sizeof(WideCtx) % 16 == 0 && sizeof(WideKey) % 16 == 0 && sizeof(Winner) % 16 == 0, "the arrays of the scoring kernel's block stay aligned");
 
 constexpr u32 MAXM = 16;      // migrations committed in one ranking pass at most (a multiple of 8, at most 16: the job words hold two sets of 16)
 static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid out for 8 or 16");
@@ -273,8 +278,13 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       for (u32 q = 0; q < na; ++q) base[(u64)arrs[q] * nb1 + tid] = scr[q * LW + wave] + inc[q] - v[q];
     __syncthreads();
   };
-  scan_bases(0, 1, 2, 3);
-  scan_bases(3, 4, 0, 2);
+  if (ctl->launches) {                                  // level 1 as the plan's last launch left it
+    for (u32 i = tid; i < N_ARR * nb1; i += LB) base[i] = a.g_base[i];
+    __syncthreads();
+  } else {
+    scan_bases(0, 1, 2, 3);
+    scan_bases(3, 4, 0, 2);
+  }
 
 
   // The hot list: every tile not scored in this pass whose bound reaches `thr`; restL bounds
@@ -447,6 +457,20 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     pass_units += nunits;
   };
 
+  // Bounds of the groups that hold tiles scored in the round, by LW - 1 wavefronts (this one is number w of
+  // them): tile by tile where they are few, else the groups with any mark (a round of 840 tiles in 70 groups
+  // spent 17 us here tile by tile).
+  auto group_bounds = [&](const u32 w) {
+    const u32 ntl = uniform(S->ntl);
+    const bool few = ntl <= 2 * (LW - 1);
+    for (u32 i = w; i < (few ? ntl : ns); i += LW - 1) {
+      const u32 g = few ? uniform((u32)alist[i]) >> 6 : i, t = g * 64 + lane;
+      if (!few && uniform(smark[g]) == 0ull) continue;
+      const u32 k = wave_max(t < nt ? keys[t] : 0u);
+      if (lane == 0) skeys[g] = k;
+    }
+  };
+
   // block-wide arg-max of the threads' best (two barriers); refreshes the group bounds in between
   auto reduce_best = [&]() {
     const u32 bl = best_lane<RATIO>(mine.hi, mine.lo, mine.cost, mine.cand);
@@ -457,12 +481,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
       if (lane == 0) S->wave_f2[wave] = f2;
     }
     __syncthreads();                               // all tile bounds and wavefront winners are in LDS
-    const u32 ntl = S->ntl;
-    for (u32 i = wave - 1; wave && i < ntl; i += LW - 1) {   // bounds of the groups that hold re-scored tiles
-      const u32 g = alist[i] >> 6, t = g * 64 + lane;
-      const u32 k = wave_max(t < nt ? keys[t] : 0u);
-      if (lane == 0) skeys[g] = k;
-    }
+    if (wave) group_bounds(wave - 1);
     if (wave == 0) {
       u64 h = 0, l = 0, cs = 1;
       u32 c = NONE32;
@@ -902,7 +921,10 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         rest = wv.ctx->rest;
         rounds = wv.ctx->rounds;
         pass_units = wv.ctx->pass_units;
-        if (tid == LB - 1 && rounds) mine = wv.win[WIDE_WG];    // the best of the rounds before
+        if (tid == LB - 1 && rounds) {                         // the best of the rounds before
+          if (resume == 1) { const WideKey k = wv.key[WIDE_WG]; mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = WIDE_WG; }
+          else mine = wv.win[WIDE_WG];
+        }
       } else if (!again) {
         if (uniform(S->restL) >= thr) {                     // the hot list may miss a tile that reaches thr: build it anew,
           const u32 low = thr == NONE32 ? thr : (thr > (1u << 19) ? thr - (1u << 19) : 1u);   // a few percent lower to last a while
@@ -936,6 +958,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           for (u32 i = tid; i < ntl; i += LB) wv.alist[i] = alist[i];
           if (tid == 0) {
             wv.win[WIDE_WG] = S->mem[0];         // (hi = lo = 0: none yet)
+            wv.key[WIDE_WG] = WideKey{S->mem[0].hi, S->mem[0].lo, S->mem[0].cost, S->mem[0].cand};
             wv.ctx->rounds = rounds; wv.ctx->pass_units = pass_units;
             wv.ctx->ntl = ntl; wv.ctx->thr = thr; wv.ctx->rest = rest;
             wv.ctx->nwg = nu < WIDE_WG ? nu : WIDE_WG; wv.ctx->done_wgs = 0;
@@ -945,12 +968,21 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
           wide_exit = true;
           break;
         }
-        if (WIDE && resume == 1) {                // the scoring kernel's winners, two per thread
+        bool from_wide = false;
+        if (WIDE && resume == 1) {
+          // the scoring kernel's winners, two per thread: their rankings only (the whole winners, 112 bytes
+          // each at 112-byte steps, kept this workgroup's texture unit busy for 18 us a pass)
+          from_wide = true;
           const u32 nw = wv.ctx->nwg;
-          if (tid < LB - 1 && tid < nw) mine = wv.win[tid];
-          if (tid < LB - 1 && tid + (LB - 1) < nw) {
-            const Winner o = wv.win[tid + (LB - 1)];
-            if ((o.hi | o.lo) != 0 && better_ratio(o.hi, o.lo, o.cost, o.cand, mine.hi, mine.lo, mine.cost, mine.cand)) mine = o;
+#pragma unroll
+          for (u32 q = 0; q < 2; ++q) {
+            const u32 i = tid + q * (LB - 1);
+            if (tid < LB - 1 && i < nw) {
+              const WideKey k = wv.key[i];
+              if ((k.hi | k.lo) != 0 && better_ratio(k.hi, k.lo, k.cost, (u32)k.cand, mine.hi, mine.lo, mine.cost, mine.cand)) {
+                mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = i;
+              }
+            }
           }
           const u32 nu = S->ntl << a.tshift;
           if (tid == 0) S->units += nu;
@@ -989,17 +1021,18 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
             const u32 m = pick(e, have, false, F, 0u, allowed, by_floor);
             if (lane == 0) { S->m0 = m ? m : 1u; S->by_floor = by_floor; S->Fkeep = F; S->fast = m ? 1u : 0u; }
           } else {
-            const u32 ntl = uniform(S->ntl);
-            for (u32 i = wave; i < ntl; i += LW - 1) {   // bounds of the groups that hold re-scored tiles
-              const u32 g = alist[i] >> 6, t = g * 64 + lane;
-              const u32 k = wave_max(t < nt ? keys[t] : 0u);
-              if (lane == 0) skeys[g] = k;
-            }
+            group_bounds(wave);
           }
           __syncthreads();
           if (uniform(S->fast)) { rest_final = rest; break; }
         }
         reduce_best();
+        if (WIDE && from_wide) {                  // the rest of the best one
+          const u32 i = S->mem[0].slot;
+          const bool any = (S->mem[0].hi | S->mem[0].lo) != 0;
+          if (wave == 0 && any && lane < sizeof(Winner) / 4) ((u32*)&S->mem[0])[lane] = ((const u32*)&wv.win[i])[lane];
+          __syncthreads();
+        }
         const u32 kb = key_dn_of<RATIO>(S->mem[0].hi, S->mem[0].lo, S->mem[0].cost);
         const u32 need = kb ? kb : 1u;
         if (rest < need) decided = true;                 // every tile left out is below the best found
@@ -1411,7 +1444,9 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
     if (lane < UNIT / 64) { h = wwin[lane].hi; l = wwin[lane].lo; cs = wwin[lane].cost; c = wwin[lane].cand; }
     const u32 w = wave_best_lane_ratio(h, l, cs, c);
     if (lane == 0) {
-      wv.win[blockIdx.x] = wwin[w == NONE32 ? 0u : w];  // (none: any of the four, all empty)
+      const Winner& b = wwin[w == NONE32 ? 0u : w];     // (none: any of the four, all empty)
+      wv.win[blockIdx.x] = b;
+      wv.key[blockIdx.x] = WideKey{b.hi, b.lo, b.cost, b.cand};
       __threadfence();
       atomicAdd(&wv.ctx->done_wgs, 1u);
     }
