@@ -312,7 +312,7 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
     hipLaunchKernelGGL(k_rp_events, dim3((n + G10_BLOCK - 1) / G10_BLOCK), dim3(G10_BLOCK), 0, s, (const g10_migration*)w->records,
                        (const uint2*)w->rec_ab, eager ? (const u32*)w->pf_gained : (const u32*)nullptr, n, K, rbits, keys, st);
     G10_HIP(hipGetLastError());
-    G10_TRY(radix_sort_u64(&keys, &alt, ne, bits_for(2ull * K) + 2 + rbits + 1, w->rp_hist, w->rp_scr, s));
+    G10_TRY(radix_sort_u64(&keys, &alt, ne, bits_for(2ull * K) + 2 + rbits + 1, w->rp_hist, s));
     hipLaunchKernelGGL(k_rp_index, dim3((u32)((ne + G10_BLOCK - 1) / G10_BLOCK)), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)ne, n, rbits,
                        w->rp_pos);
     G10_HIP(hipGetLastError());

@@ -12,6 +12,7 @@
 
 #include "g10_internal.h"
 
+#include <atomic>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -176,11 +177,39 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_hist(const KT* __restrict__
   radix_hist_tile<KT>(keys, P, shift, hist, nblocks, cnt);
 }
 
+// Exclusive scan of one digit's counts over the tiles, in place, by one workgroup; the digit's total goes
+// behind the counts (256 totals).  A row each for 256 workgroups and the digits' own scan in every scatter
+// workgroup take one launch where a scan over all 256 * nblocks counts took three; one workgroup
+// scanning all counts of a sort took about 100 us for a million keys.
+__device__ __forceinline__ void radix_row_scan(u32* __restrict__ hist, u32 nblocks, u32 d, u32* tmp) {
+  u32* row = hist + (u64)d * nblocks;
+  u32 carry = 0;
+  for (u32 b0 = 0; b0 < nblocks; b0 += TILE) {
+    const u32 i = b0 + threadIdx.x * ITEMS;
+    u32 v[ITEMS], sum = 0;
+#pragma unroll
+    for (u32 q = 0; q < ITEMS; ++q) { v[q] = i + q < nblocks ? row[i + q] : 0u; sum += v[q]; }
+    u32 total;
+    u32 run = carry + block_scan_excl(sum, tmp, total);
+#pragma unroll
+    for (u32 q = 0; q < ITEMS; ++q) {
+      if (i + q < nblocks) row[i + q] = run;
+      run += v[q];
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) hist[(u64)256 * nblocks + d] = carry;
+}
+__global__ __launch_bounds__(G10_BLOCK) void k_radix_rows(u32* __restrict__ hist, u32 nblocks) {
+  __shared__ u32 tmp[G10_WAVES + 1];
+  radix_row_scan(hist, nblocks, blockIdx.x, tmp);
+}
+
 template <class KT, bool PAIRS>
 __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, KT* __restrict__ out,
                                                    const u32* __restrict__ vals, u32* __restrict__ vout,
                                                    u64 P, u32 shift, const u32* __restrict__ offs,
-                                                   u32 nblocks, u32 (*cnt)[256], u32* gbase) {
+                                                   u32 nblocks, u32 (*cnt)[256], u32* gbase, u32* tmp) {
   for (u32 i = threadIdx.x; i < G10_WAVES * 256; i += G10_BLOCK) (&cnt[0][0])[i] = 0;
   __syncthreads();
   const u32 w = wave_id(), l = lane_id();
@@ -207,8 +236,10 @@ __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, 
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-  {                                           // one thread per digit: offsets of the wavefronts
+  {                                           // one thread per digit: offsets of the wavefronts, and where the tile's keys of the digit go
     const u32 d = threadIdx.x;
+    u32 all;
+    const u32 before = block_scan_excl(offs[(u64)256 * nblocks + d], tmp, all);      // keys of lower digits
     u32 run = 0;
 #pragma unroll
     for (u32 ww = 0; ww < G10_WAVES; ++ww) {
@@ -216,7 +247,7 @@ __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, 
       cnt[ww][d] = run;
       run += c;
     }
-    gbase[d] = offs[(u64)d * nblocks + blockIdx.x];
+    gbase[d] = before + offs[(u64)d * nblocks + blockIdx.x];
   }
   __syncthreads();
 #pragma unroll
@@ -238,7 +269,98 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter(const KT* __restric
                                                             u32 nblocks) {
   __shared__ u32 cnt[G10_WAVES][256];        // per wavefront: running count per digit
   __shared__ u32 gbase[256];
-  radix_scatter_tile<KT, PAIRS>(keys, out, vals, vout, P, shift, offs, nblocks, cnt, gbase);
+  __shared__ u32 tmp[G10_WAVES + 1];
+  radix_scatter_tile<KT, PAIRS>(keys, out, vals, vout, P, shift, offs, nblocks, cnt, gbase, tmp);
+}
+
+// ---- a sort of at most SMALL keys in one launch ---------------------------------------------------------
+// One workgroup of 16 wavefronts holds the keys in registers and orders them through LDS, all digits in
+// turn: the passes of a small sort are bound by their launches (three each, 3 to 4 us apiece), not by
+// their keys.  The limit is what LDS takes with 64-bit keys and values beside them.
+constexpr u32 SMALL_WAVES = 16, SMALL = SMALL_WAVES * G10_WAVE * ITEMS;      // 8192
+template <class KT, bool PAIRS>
+struct SmallSort {
+  KT key[SMALL];
+  u32 val[PAIRS ? SMALL : 1];
+  u32 cnt[SMALL_WAVES][256];
+  u32 tmp[SMALL_WAVES];
+};
+template <class KT, bool PAIRS>
+__global__ __launch_bounds__(SMALL_WAVES * G10_WAVE) void k_radix_small(const KT* __restrict__ keys, KT* __restrict__ out,
+                                                                       const u32* __restrict__ vals, u32* __restrict__ vout, u32 n,
+                                                                       u32 bits) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  SmallSort<KT, PAIRS>& S = *(SmallSort<KT, PAIRS>*)smem;
+  const u32 tid = threadIdx.x, w = tid >> 6, l = tid & 63u;
+  const u64 lt = (1ull << l) - 1ull;
+  const u32 rounds = (n + SMALL_WAVES * G10_WAVE - 1) / (SMALL_WAVES * G10_WAVE);   // keys per lane; a wavefront owns rounds * 64 neighbours
+  const u32 first = w * rounds * G10_WAVE + l;
+  KT key[ITEMS];
+  u32 val[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (u32 r = 0; r < ITEMS; ++r) {
+    const u32 i = first + r * G10_WAVE;
+    const bool ok = r < rounds && i < n;
+    key[r] = ok ? keys[i] : (KT)0;
+    val[r] = PAIRS && ok ? (vals ? vals[i] : i) : 0u;          // no values given: the positions themselves
+  }
+  for (u32 shift = 0; shift < bits; shift += 8) {
+    for (u32 i = tid; i < SMALL_WAVES * 256; i += SMALL_WAVES * G10_WAVE) (&S.cnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (u32 r = 0; r < ITEMS; ++r) {
+      if (r >= rounds) break;
+      const bool ok = first + r * G10_WAVE < n;
+      const u32 dig = (u32)(key[r] >> shift) & 255u;
+      u64 peers = __ballot(ok);
+#pragma unroll
+      for (u32 b = 0; b < 8; ++b) {
+        const u64 m = __ballot((dig >> b) & 1u);
+        peers &= ((dig >> b) & 1u) ? m : ~m;
+      }
+      const u32 before = S.cnt[w][dig];
+      rank[r] = before + (u32)__popcll(peers & lt);
+      __builtin_amdgcn_wave_barrier();
+      if (ok && (peers & lt) == 0) S.cnt[w][dig] = before + (u32)__popcll(peers);
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    u32 total = 0, inc = 0;
+    if (tid < 256) {                          // a digit per thread: its count, then where its keys begin
+      for (u32 x = 0; x < SMALL_WAVES; ++x) { const u32 c = S.cnt[x][tid]; S.cnt[x][tid] = total; total += c; }
+      inc = wave_scan_incl(total);
+      if (l == G10_WAVE - 1) S.tmp[w] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      u32 base = inc - total;
+      for (u32 x = 0; x < w; ++x) base += S.tmp[x];
+      for (u32 x = 0; x < SMALL_WAVES; ++x) S.cnt[x][tid] += base;
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 r = 0; r < ITEMS; ++r) {
+      if (r >= rounds) break;
+      if (first + r * G10_WAVE < n) {
+        const u32 pos = S.cnt[w][(u32)(key[r] >> shift) & 255u] + rank[r];
+        S.key[pos] = key[r];
+        if (PAIRS) S.val[pos] = val[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 r = 0; r < ITEMS; ++r) {
+      if (r >= rounds) break;
+      const u32 i = first + r * G10_WAVE;
+      if (i < n) { key[r] = S.key[i]; if (PAIRS) val[r] = S.val[i]; }
+    }
+    // (the next pass writes the keys behind three more barriers)
+  }
+#pragma unroll
+  for (u32 r = 0; r < ITEMS; ++r) {
+    const u32 i = first + r * G10_WAVE;
+    if (r < rounds && i < n) { out[i] = key[r]; if (PAIRS) vout[i] = val[r]; }
+  }
 }
 
 // ---- many sorts of (32-bit key, 32-bit value) pairs at once: job = blockIdx.y -------------------------
@@ -253,48 +375,20 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_hist_jobs(const SortJob* __
   radix_hist_tile<u32>(flip ? j.alt : j.keys, j.n, shift, j.hist, j.nb, cnt);
 }
 
-// exclusive scan of a job's 256 * nb counts in place, one workgroup of 1024 threads per job
-__global__ __launch_bounds__(1024) void k_radix_scan_jobs(const SortJob* __restrict__ jobs) {
-  __shared__ u32 wsum[16];
-  __shared__ u32 carry_s;
+__global__ __launch_bounds__(G10_BLOCK) void k_radix_rows_jobs(const SortJob* __restrict__ jobs) {
+  __shared__ u32 tmp[G10_WAVES + 1];
   const SortJob j = in_global(jobs[blockIdx.y]);
-  const u32 total = 256u * j.nb, w = threadIdx.x >> 6, l = threadIdx.x & 63u;
-  u32* h = j.hist;
-  u32 carry = 0;
-  for (u32 base = 0; base < total; base += 4096u) {
-    const u32 i = base + threadIdx.x * 4u;
-    u32 v[4];
-#pragma unroll
-    for (u32 q = 0; q < 4; ++q) v[q] = i + q < total ? h[i + q] : 0u;
-    const u32 mine = v[0] + v[1] + v[2] + v[3];
-    const u32 inc = wave_scan_incl(mine);
-    if (l == 63u) wsum[w] = inc;
-    __syncthreads();
-    if (w == 0) {
-      const u32 x = l < 16u ? wsum[l] : 0u;
-      const u32 xi = wave_scan_incl(x);
-      if (l < 16u) wsum[l] = xi - x;
-      if (l == 15u) carry_s = xi;
-    }
-    __syncthreads();
-    u32 run = carry + wsum[w] + inc - mine;
-#pragma unroll
-    for (u32 q = 0; q < 4; ++q) {
-      if (i + q < total) h[i + q] = run;
-      run += v[q];
-    }
-    carry += carry_s;
-    __syncthreads();                          // wsum and carry_s are read before the next round writes them
-  }
+  radix_row_scan(j.hist, j.nb, blockIdx.x, tmp);
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter_jobs(const SortJob* __restrict__ jobs, u32 shift, u32 flip, u32 iota) {
   __shared__ u32 cnt[G10_WAVES][256];
   __shared__ u32 gbase[256];
+  __shared__ u32 tmp[G10_WAVES + 1];
   const SortJob j = in_global(jobs[blockIdx.y]);
   if (blockIdx.x >= j.nb) return;
   radix_scatter_tile<u32, true>(flip ? j.alt : j.keys, flip ? j.keys : j.alt, iota ? (const u32*)nullptr : (const u32*)(flip ? j.valt : j.vals),
-                                flip ? j.vals : j.valt, j.n, shift, j.hist, j.nb, cnt, gbase);
+                                flip ? j.vals : j.valt, j.n, shift, j.hist, j.nb, cnt, gbase, tmp);
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_flag_distinct(const u64* __restrict__ keys, u64 P, u32* __restrict__ flag) {
@@ -505,58 +599,62 @@ int g10_hip_fail(hipError_t e, const char* file, int line) {
 }
 
 
-size_t radix_hist_elems(u64 n) { return (size_t)256 * ((n + TILE - 1) / TILE ? (n + TILE - 1) / TILE : 1) + 1; }
+size_t radix_hist_elems(u64 n) { return (size_t)256 * ((n + TILE - 1) / TILE ? (n + TILE - 1) / TILE : 1) + 256; }
 
-// LSD radix sort of the low `bits` bits of 64-bit keys, 8 bits per pass, stable.
-// On return *keys points at the sorted data and *alt at the other buffer.
-// hist: radix_hist_elems(n) words; scratch: scan_scratch_elems(radix_hist_elems(n)) words.
-int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, u32* scratch, hipStream_t s) {
+template <class KT, bool PAIRS>
+static int radix_small(const KT* keys, KT* out, const u32* vals, u32* vout, u64 n, u32 bits, hipStream_t s) {
+  constexpr size_t lds = sizeof(SmallSort<KT, PAIRS>);
+  static_assert(lds <= 160 * 1024, "the LDS of one workgroup");
+  static std::atomic<bool> allowed[64];           // (per device: the attribute belongs to the kernel)
+  int dev = 0;
+  G10_HIP(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64 || !allowed[dev].load(std::memory_order_acquire)) {
+    G10_HIP(hipFuncSetAttribute((const void*)k_radix_small<KT, PAIRS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (dev >= 0 && dev < 64) allowed[dev].store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((k_radix_small<KT, PAIRS>), dim3(1), dim3(SMALL_WAVES * G10_WAVE), lds, s, keys, out, vals, vout, (u32)n, bits);
+  G10_HIP(hipGetLastError());
+  return G10_OK;
+}
+
+// LSD radix sort of the low `bits` bits of KT keys, 8 bits per pass, stable; PAIRS: with a 32-bit value carried
+// along with every key (iota: the values are the positions 0..n-1 and *vals need not be filled).
+// On return *keys points at the sorted keys and *alt at the other buffer, *vals / *valt likewise.
+// hist: radix_hist_elems(n) words.
+template <class KT, bool PAIRS>
+static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota) {
   if (n == 0) return G10_OK;
+  auto swap = [&]() {
+    KT* t = *keys; *keys = *alt; *alt = t;
+    if (PAIRS) { u32* v = *vals; *vals = *valt; *valt = v; }
+  };
+  if (n <= SMALL) {
+    const u32* v = PAIRS && !iota ? *vals : nullptr;
+    G10_TRY((radix_small<KT, PAIRS>(*keys, *alt, v, PAIRS ? *valt : nullptr, n, bits, s)));
+    swap();
+    return G10_OK;
+  }
   const u32 nb = (u32)((n + TILE - 1) / TILE);
   for (u32 shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist<u64>, dim3(nb), dim3(G10_BLOCK), 0, s, *keys, n, shift, hist, nb);
-    G10_TRY(scan_excl_u32(hist, hist, (u64)256 * nb, scratch, s));
-    hipLaunchKernelGGL((k_radix_scatter<u64, false>), dim3(nb), dim3(G10_BLOCK), 0, s, *keys, *alt, (const u32*)nullptr, (u32*)nullptr, n,
+    hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, (const KT*)*keys, n, shift, hist, nb);
+    hipLaunchKernelGGL(k_radix_rows, dim3(256), dim3(G10_BLOCK), 0, s, hist, nb);
+    const u32* v = PAIRS && !(iota && shift == 0) ? *vals : nullptr;
+    hipLaunchKernelGGL((k_radix_scatter<KT, PAIRS>), dim3(nb), dim3(G10_BLOCK), 0, s, (const KT*)*keys, *alt, v, PAIRS ? *valt : nullptr, n,
                        shift, hist, nb);
-    u64* t = *keys; *keys = *alt; *alt = t;
+    swap();
   }
   G10_HIP(hipGetLastError());
   return G10_OK;
 }
-
-// The same with a 32-bit value carried along with every key; *vals / *valt swap like the keys.
-// iota: the values are the positions 0..n-1 (the first pass makes them; *vals need not be filled).
-int radix_sort_u64_pairs(u64** keys, u64** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, u32* scratch,
-                         hipStream_t s, bool iota) {
-  if (n == 0) return G10_OK;
-  const u32 nb = (u32)((n + TILE - 1) / TILE);
-  for (u32 shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist<u64>, dim3(nb), dim3(G10_BLOCK), 0, s, *keys, n, shift, hist, nb);
-    G10_TRY(scan_excl_u32(hist, hist, (u64)256 * nb, scratch, s));
-    hipLaunchKernelGGL((k_radix_scatter<u64, true>), dim3(nb), dim3(G10_BLOCK), 0, s, *keys, *alt,
-                       iota && shift == 0 ? (const u32*)nullptr : (const u32*)*vals, *valt, n, shift, hist, nb);
-    u64* t = *keys; *keys = *alt; *alt = t;
-    u32* v = *vals; *vals = *valt; *valt = v;
-  }
-  G10_HIP(hipGetLastError());
-  return G10_OK;
+int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, hipStream_t s) {
+  return radix_sort<u64, false>(keys, alt, nullptr, nullptr, n, bits, hist, s, false);
 }
-
-// 32-bit keys with a 32-bit value each (the score order of the planner's candidates).
-int radix_sort_u32_pairs(u32** keys, u32** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, u32* scratch,
-                         hipStream_t s, bool iota) {
-  if (n == 0) return G10_OK;
-  const u32 nb = (u32)((n + TILE - 1) / TILE);
-  for (u32 shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist<u32>, dim3(nb), dim3(G10_BLOCK), 0, s, (const u32*)*keys, n, shift, hist, nb);
-    G10_TRY(scan_excl_u32(hist, hist, (u64)256 * nb, scratch, s));
-    hipLaunchKernelGGL((k_radix_scatter<u32, true>), dim3(nb), dim3(G10_BLOCK), 0, s, (const u32*)*keys, *alt,
-                       iota && shift == 0 ? (const u32*)nullptr : (const u32*)*vals, *valt, n, shift, hist, nb);
-    u32* t = *keys; *keys = *alt; *alt = t;
-    u32* v = *vals; *vals = *valt; *valt = v;
-  }
-  G10_HIP(hipGetLastError());
-  return G10_OK;
+int radix_sort_u64_pairs(u64** keys, u64** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota) {
+  return radix_sort<u64, true>(keys, alt, vals, valt, n, bits, hist, s, iota);
+}
+// (the score order of the planner's candidates)
+int radix_sort_u32_pairs(u32** keys, u32** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota) {
+  return radix_sort<u32, true>(keys, alt, vals, valt, n, bits, hist, s, iota);
 }
 
 // `njobs` sorts of pairs in the same launches (jobs: device array; max_nb: the largest nb among them).  The
@@ -568,7 +666,7 @@ int radix_sort_u32_pairs_jobs(const SortJob* jobs, u32 njobs, u32 max_nb, u32 bi
   u32 flip = 0;
   for (u32 shift = 0; shift < bits; shift += 8, flip ^= 1u) {
     hipLaunchKernelGGL(k_radix_hist_jobs, dim3(max_nb, njobs), dim3(G10_BLOCK), 0, s, jobs, shift, flip);
-    hipLaunchKernelGGL(k_radix_scan_jobs, dim3(1, njobs), dim3(1024), 0, s, jobs);
+    hipLaunchKernelGGL(k_radix_rows_jobs, dim3(256, njobs), dim3(G10_BLOCK), 0, s, jobs);
     hipLaunchKernelGGL(k_radix_scatter_jobs, dim3(max_nb, njobs), dim3(G10_BLOCK), 0, s, jobs, shift, flip, iota && shift == 0 ? 1u : 0u);
   }
   G10_HIP(hipGetLastError());
@@ -666,7 +764,7 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
   G10_TRY(tmp.take(&scratch32, scan_scratch_elems(radix_hist_elems(P) > P ? radix_hist_elems(P) : P)));
   if (P) {
     hipLaunchKernelGGL(k_pack, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, tr->use_kernel, tr->use_tensor, P, K, N, h->kbits, keys, st);
-    G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, scratch32, s));
+    G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, s));
     hipLaunchKernelGGL(k_flag_distinct, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, keys, P, flag);
     G10_HIP(hipGetLastError());
   }
@@ -732,7 +830,7 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
     // (a stable sort of the starts alone, the position carried along: equal starts keep the order of the periods)
     u32 *k32 = (u32*)keys, *k32_alt = k32 + C, *ord = (u32*)alt, *ord_alt = ord + C;      // (C <= P: two arrays of C words in one of P keys)
     G10_HIP(hipMemcpyAsync(k32, h->per_L, C * 4, hipMemcpyDeviceToDevice, s));
-    G10_TRY(radix_sort_u32_pairs(&k32, &k32_alt, &ord, &ord_alt, C, h->kbits, hist, scratch32, s, true));
+    G10_TRY(radix_sort_u32_pairs(&k32, &k32_alt, &ord, &ord_alt, C, h->kbits, hist, s, true));
     hipLaunchKernelGGL(k_gather_periods, dim3(grid_for(C)), dim3(G10_BLOCK), 0, s, (const u32*)ord, C, h->per_t, h->per_L, h->per_R,
                        h->size, h->per_by_start, h->per_size);
     G10_HIP(hipGetLastError());                     // (still running when this function returns: see vitality_run)
