@@ -25,8 +25,29 @@ constexpr int TILE = G10_BLOCK * ITEMS;         // 2048
 // ===========================================================================
 // device-wide exclusive scan
 // ===========================================================================
+// What the tiles before this one sum up to, from the tiles' own sums; with `all`, the sum of all of them.
+// Up to DIRECT tiles every workgroup adds them up itself (8 loads a thread at most), so that no launch
+// is needed in between; above that the sums are scanned first (`scanned`).
+constexpr u32 DIRECT = 2048;
 template <class T>
-__global__ __launch_bounds__(G10_BLOCK) void k_scan_tiles(const T* __restrict__ in, T* out, u64 n, T* sums) {
+__device__ __forceinline__ T tile_base(const T* __restrict__ sums, u32 nb, bool scanned, T* tmp, T* all) {
+  if (scanned) {
+    if (all) *all = sums[nb];
+    return sums[blockIdx.x];
+  }
+  T before = 0, total = 0;
+  for (u32 i = threadIdx.x; i < nb; i += G10_BLOCK) {
+    const T x = sums[i];
+    if (i < blockIdx.x) before += x;
+    total += x;
+  }
+  if (all) *all = block_sum(total, tmp);
+  return block_sum(before, tmp);
+}
+
+// (max: where given, it is raised to the largest value of out[0..n])
+template <class T>
+__global__ __launch_bounds__(G10_BLOCK) void k_scan_tiles(const T* __restrict__ in, T* out, u64 n, T* sums, T* max) {
   __shared__ T tmp[G10_WAVES + 1];
   const u64 base = (u64)blockIdx.x * TILE + (u64)threadIdx.x * ITEMS;
   T v[ITEMS];
@@ -37,45 +58,58 @@ __global__ __launch_bounds__(G10_BLOCK) void k_scan_tiles(const T* __restrict__ 
     acc += v[i];
   }
   T total;
-  T run = block_scan_excl(acc, tmp, total);
+  T run = block_scan_excl(acc, tmp, total), top = total;
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    if (base + i < n) out[base + i] = run;
+    if (base + i < n) { out[base + i] = run; top = run > top ? run : top; }
     run += v[i];
   }
-  if (threadIdx.x == 0) {
-    if (sums) sums[blockIdx.x] = total;
-    else out[n] = total;                        // single tile: finished
+  if (sums) { if (threadIdx.x == 0) sums[blockIdx.x] = total; return; }
+  if (threadIdx.x == 0) out[n] = total;         // single tile: finished
+  if (max) {
+    top = block_max(top, tmp);
+    if (threadIdx.x == 0) *max = top;
   }
 }
 
 template <class T>
-__global__ __launch_bounds__(G10_BLOCK) void k_scan_add(T* out, u64 n, const T* __restrict__ sums, u32 nb) {
-  const T add = sums[blockIdx.x];
+__global__ __launch_bounds__(G10_BLOCK) void k_scan_add(T* out, u64 n, const T* __restrict__ sums, u32 nb, u32 scanned, T* max) {
+  __shared__ T tmp[G10_WAVES + 1];
+  T all;
+  const T add = tile_base<T>(sums, nb, scanned != 0, tmp, &all);
   const u64 base = (u64)blockIdx.x * TILE + (u64)threadIdx.x * ITEMS;
+  T top = 0;
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i)
-    if (base + i < n) out[base + i] += add;
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[nb];
+    if (base + i < n) {
+      const T x = out[base + i] + add;
+      out[base + i] = x;
+      top = x > top ? x : top;
+    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) { out[n] = all; top = all > top ? all : top; }
+  if (max) {
+    top = block_max(top, tmp);
+    if (threadIdx.x == 0) {
+      if constexpr (sizeof(T) == 8) atomicMax((unsigned long long*)max, (unsigned long long)top);
+      else atomicMax(max, top);
+    }
+  }
 }
 
+// max: device word (cleared) that takes the largest value of out[0..n], or null
 template <class T>
-int scan_excl(const T* in, T* out, u64 n, T* scratch, hipStream_t s) {
+int scan_excl(const T* in, T* out, u64 n, T* scratch, hipStream_t s, T* max = nullptr) {
   if (n == 0) {                                  // out[0] = 0
-    G10_HIP(hipMemsetAsync(out, 0, sizeof(T), s));
-    return G10_OK;
-  }
-  const u64 nb = (n + TILE - 1) / TILE;
-  if (nb == 1) {
-    hipLaunchKernelGGL(k_scan_tiles<T>, dim3(1), dim3(G10_BLOCK), 0, s, in, out, n, (T*)nullptr);
+    hipLaunchKernelGGL(k_scan_tiles<T>, dim3(1), dim3(G10_BLOCK), 0, s, in, out, n, (T*)nullptr, (T*)nullptr);
     G10_HIP(hipGetLastError());
     return G10_OK;
   }
-  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((u32)nb), dim3(G10_BLOCK), 0, s, in, out, n, scratch);
+  const u64 nb = (n + TILE - 1) / TILE;
+  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((u32)nb), dim3(G10_BLOCK), 0, s, in, out, n, nb == 1 ? (T*)nullptr : scratch, nb == 1 ? max : (T*)nullptr);
   G10_HIP(hipGetLastError());
-  int rc = scan_excl<T>(scratch, scratch, nb, scratch + nb + 1, s);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_scan_add<T>, dim3((u32)nb), dim3(G10_BLOCK), 0, s, out, n, scratch, (u32)nb);
+  if (nb == 1) return G10_OK;
+  if (nb > DIRECT) G10_TRY(scan_excl<T>(scratch, scratch, nb, scratch + nb + 1, s));
+  hipLaunchKernelGGL(k_scan_add<T>, dim3((u32)nb), dim3(G10_BLOCK), 0, s, out, n, scratch, (u32)nb, nb > DIRECT ? 1u : 0u, max);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }
@@ -111,35 +145,54 @@ __global__ __launch_bounds__(G10_BLOCK) void k_check_dur(const u64* __restrict__
   }
 }
 
-__global__ __launch_bounds__(G10_BLOCK) void k_check_size(const u64* __restrict__ size, u32 N, VitStats* st) {
-  u32 zero = 0, ovf = 0, big = 0;
-  u64 mx = 0;
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < N; i += (u64)gridDim.x * G10_BLOCK) {
-    u64 s = size[i];
-    mx = s > mx ? s : mx;
-    zero |= s == 0;
-    ovf |= s > 0xffffffffffffffffull / 1000ull;
-    big |= (s >> 43) != 0;
-  }
-  if (__any(zero) && lane_id() == 0) atomicOr(&st->zero_size, 1u);
-  if (__any(ovf) && lane_id() == 0) atomicOr(&st->size_overflow, 1u);
-  if (__any(big) && lane_id() == 0) atomicOr(&st->big_size, 1u);
-  // (atomics on one address queue up behind each other: one per workgroup, and only where it can still raise the maximum)
+// One pass over everything the caller gave: checks, own copies where planning follows (else dur_out is
+// null), and the sort keys (tensor, kernel) of the pairs.  A pair that names no kernel or no tensor of the
+// trace is reported and stands in as (0, 0): every later kernel then indexes inside its arrays, and the
+// host rejects the trace when it reads the report at the end of the analysis.
+__global__ __launch_bounds__(G10_BLOCK) void k_load(const u64* __restrict__ dur, const u64* __restrict__ size, const uint8_t* __restrict__ glob,
+                                                   const u32* __restrict__ uk, const u32* __restrict__ ut, u32 K, u32 N, u64 P, u32 kbits,
+                                                   u64* __restrict__ dur_out, u64* __restrict__ size_out, uint8_t* __restrict__ glob_out,
+                                                   u64* __restrict__ keys, VitStats* st) {
   __shared__ u64 tmp[G10_WAVES + 1];
-  mx = block_max(mx, tmp);
-  if (threadIdx.x == 0 && mx > *(volatile u64*)&st->max_size) atomicMax((unsigned long long*)&st->max_size, (unsigned long long)mx);
-}
-
-// ===========================================================================
-// use lists: key pack, radix sort, distinct
-// ===========================================================================
-// Sort keys (tensor, kernel) of the pairs.  A pair that names no kernel or no tensor of the trace is
-// reported and stands in as (0, 0): every later kernel then indexes inside its arrays, and the host
-// rejects the trace when it reads the report at the end of the analysis.
-__global__ __launch_bounds__(G10_BLOCK) void k_pack(const u32* __restrict__ uk, const u32* __restrict__ ut, u64 P,
-                                                   u32 K, u32 N, u32 kbits, u64* __restrict__ keys, VitStats* st) {
+  const u64 first = (u64)blockIdx.x * G10_BLOCK, step = (u64)gridDim.x * G10_BLOCK;
+  if (first < K) {
+    u64 lo = 0, hi = 0;
+    u32 zero = 0;
+    for (u64 i = first + threadIdx.x; i < K; i += step) {
+      const u64 d = dur[i];
+      if (dur_out) dur_out[i] = d;
+      zero |= d == 0;
+      lo += d & 0xffffffffull;
+      hi += d >> 32;
+    }
+    lo = block_sum(lo, tmp);
+    hi = block_sum(hi, tmp);
+    if (__any(zero) && lane_id() == 0) atomicOr(&st->zero_dur, 1u);
+    if (threadIdx.x == 0) {
+      atomicAdd((unsigned long long*)&st->dur_lo, (unsigned long long)lo);
+      if (hi) atomicAdd((unsigned long long*)&st->dur_hi, (unsigned long long)hi);
+    }
+  }
+  if (first < N) {
+    u32 zero = 0, ovf = 0, big = 0;
+    u64 mx = 0;
+    for (u64 i = first + threadIdx.x; i < N; i += step) {
+      const u64 x = size[i];
+      if (size_out) { size_out[i] = x; glob_out[i] = glob[i]; }
+      mx = x > mx ? x : mx;
+      zero |= x == 0;
+      ovf |= x > 0xffffffffffffffffull / 1000ull;
+      big |= (x >> 43) != 0;
+    }
+    if (__any(zero) && lane_id() == 0) atomicOr(&st->zero_size, 1u);
+    if (__any(ovf) && lane_id() == 0) atomicOr(&st->size_overflow, 1u);
+    if (__any(big) && lane_id() == 0) atomicOr(&st->big_size, 1u);
+    // (atomics on one address queue up behind each other: one per workgroup, and only where it can still raise the maximum)
+    mx = block_max(mx, tmp);
+    if (threadIdx.x == 0 && mx > *(volatile u64*)&st->max_size) atomicMax((unsigned long long*)&st->max_size, (unsigned long long)mx);
+  }
   u32 bad = 0;
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < P; i += (u64)gridDim.x * G10_BLOCK) {
+  for (u64 i = first + threadIdx.x; i < P; i += step) {
     u32 k = uk[i], t = ut[i];
     if (k >= K || t >= N) { bad = 1; k = 0; t = 0; }
     keys[i] = ((u64)t << kbits) | k;
@@ -147,6 +200,9 @@ __global__ __launch_bounds__(G10_BLOCK) void k_pack(const u32* __restrict__ uk, 
   if (__any(bad) && lane_id() == 0) atomicOr(&st->bad_index, 1u);
 }
 
+// ===========================================================================
+// use lists: radix sort, distinct
+// ===========================================================================
 // Tile layout of the sort kernels: wavefront w of a workgroup owns the
 // contiguous keys [tile + w*512, tile + (w+1)*512); in round r lane l holds key
 // tile + w*512 + r*64 + l.  Key order = (wavefront, round, lane): that is what
@@ -391,23 +447,46 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter_jobs(const SortJob*
                                 flip ? j.vals : j.valt, j.n, shift, j.hist, j.nb, cnt, gbase, tmp);
 }
 
-__global__ __launch_bounds__(G10_BLOCK) void k_flag_distinct(const u64* __restrict__ keys, u64 P, u32* __restrict__ flag) {
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < P; i += (u64)gridDim.x * G10_BLOCK)
-    flag[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1u : 0u;
+// The sorted keys without duplicates, tile by tile: how many of a tile stay (one tile: not needed), then
+// the keys and kernels that stay behind those of the tiles before.
+template <class F>
+__device__ __forceinline__ void tile_count(u64 n, u32* __restrict__ sums, F&& of) {
+  __shared__ u32 tmp[G10_WAVES + 1];
+  const u64 base = (u64)blockIdx.x * TILE + threadIdx.x;
+  u32 c = 0;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (base + (u64)i * G10_BLOCK < n) c += of(base + (u64)i * G10_BLOCK);
+  c = block_sum(c, tmp);
+  if (threadIdx.x == 0) sums[blockIdx.x] = c;
 }
-
-__global__ __launch_bounds__(G10_BLOCK) void k_compact_distinct(const u64* __restrict__ keys, u64 P,
-                                                               const u32* __restrict__ pos, u64* __restrict__ ukeys,
-                                                               u32* __restrict__ use_k, u32 kbits) {
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < P; i += (u64)gridDim.x * G10_BLOCK)
-    if (pos[i + 1] != pos[i]) {
-      ukeys[pos[i]] = keys[i];
-      use_k[pos[i]] = (u32)(keys[i] & ((1ull << kbits) - 1ull));
+__device__ __forceinline__ u32 is_distinct(const u64* __restrict__ keys, u64 i) { return i == 0 || keys[i] != keys[i - 1] ? 1u : 0u; }
+__global__ __launch_bounds__(G10_BLOCK) void k_distinct_count(const u64* __restrict__ keys, u64 P, u32* __restrict__ sums) {
+  tile_count(P, sums, [&](u64 i) { return is_distinct(keys, i); });
+}
+__global__ __launch_bounds__(G10_BLOCK) void k_distinct_write(const u64* __restrict__ keys, u64 P, const u32* __restrict__ sums, u32 nb,
+                                                             u32 scanned, u64* __restrict__ ukeys, u32* __restrict__ use_k, u32 kbits,
+                                                             VitStats* st) {
+  __shared__ u32 tmp[G10_WAVES + 1];
+  u32 all = 0, at = nb > 1 ? tile_base<u32>(sums, nb, scanned != 0, tmp, &all) : 0u;
+  const u64 first = (u64)blockIdx.x * TILE;
+  for (u32 r = 0; r < ITEMS; ++r) {            // 256 neighbouring keys at a time
+    const u64 i = first + r * G10_BLOCK + threadIdx.x;
+    const bool keep = i < P && is_distinct(keys, i);
+    u32 total;
+    const u32 pos = at + block_scan_excl(keep ? 1u : 0u, tmp, total);
+    if (keep) {
+      const u64 k = keys[i];
+      ukeys[pos] = k;
+      use_k[pos] = (u32)(k & ((1ull << kbits) - 1ull));
     }
+    at += total;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->n_uses = nb > 1 ? all : at;
 }
 
 // use_off[t] = first position whose key has tensor >= t  (t in [0, N])
-__global__ __launch_bounds__(G10_BLOCK) void k_use_off(const u64* __restrict__ ukeys, const u32* __restrict__ n_uses_p,
+__global__ __launch_bounds__(G10_BLOCK) void k_use_off(const u64* __restrict__ ukeys, const u64* __restrict__ n_uses_p,
                                                       u32 N, u32 kbits, u64* __restrict__ use_off) {
   const u64 n = *n_uses_p;
   for (u64 t = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; t <= N; t += (u64)gridDim.x * G10_BLOCK) {
@@ -450,31 +529,36 @@ __device__ __forceinline__ void period_at(const u64* ukeys, const u64* use_off, 
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_period_count(const u64* __restrict__ ukeys, const u64* __restrict__ use_off,
-                                                           const uint8_t* __restrict__ glob, const u32* __restrict__ n_uses_p,
-                                                           u32 K, u32 kbits, u32 no_wrap, u32* __restrict__ cnt) {
-  const u64 n = *n_uses_p;
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) {
+                                                           const uint8_t* __restrict__ glob, const u64* __restrict__ n_uses_p,
+                                                           u32 K, u32 kbits, u32 no_wrap, u32* __restrict__ sums) {
+  tile_count(*n_uses_p, sums, [&](u64 i) {
     bool inner, wrap;
     u32 t, k, kp, kf;
     period_at(ukeys, use_off, glob, i, K, kbits, no_wrap, inner, wrap, t, k, kp, kf);
-    cnt[i] = (u32)inner + (u32)wrap;
-  }
+    return (u32)inner + (u32)wrap;
+  });
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_period_write(const u64* __restrict__ ukeys, const u64* __restrict__ use_off,
-                                                           const uint8_t* __restrict__ glob, const u32* __restrict__ n_uses_p,
-                                                           u32 K, u32 kbits, u32 no_wrap, const u32* __restrict__ pos,
+                                                           const uint8_t* __restrict__ glob, u32 K, u32 kbits, u32 no_wrap,
+                                                           const u32* __restrict__ sums, u32 nb, u32 scanned,
                                                            u32* __restrict__ per_t, u32* __restrict__ per_L,
-                                                           u32* __restrict__ per_R) {
-  const u64 n = *n_uses_p;
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) {
-    bool inner, wrap;
-    u32 t, k, kp, kf;
-    period_at(ukeys, use_off, glob, i, K, kbits, no_wrap, inner, wrap, t, k, kp, kf);
-    u32 o = pos[i];
+                                                           u32* __restrict__ per_R, VitStats* st) {
+  __shared__ u32 tmp[G10_WAVES + 1];
+  const u64 n = st->n_uses, first = (u64)blockIdx.x * TILE;
+  u32 all = 0, at = nb > 1 ? tile_base<u32>(sums, nb, scanned != 0, tmp, &all) : 0u;
+  for (u32 r = 0; r < ITEMS; ++r) {            // 256 neighbouring uses at a time
+    const u64 i = first + r * G10_BLOCK + threadIdx.x;
+    bool inner = false, wrap = false;
+    u32 t = 0, k = 0, kp = 0, kf = 0;
+    if (i < n) period_at(ukeys, use_off, glob, i, K, kbits, no_wrap, inner, wrap, t, k, kp, kf);
+    u32 total;
+    u32 o = at + block_scan_excl((u32)inner + (u32)wrap, tmp, total);
     if (inner) { per_t[o] = t; per_L[o] = kp; per_R[o] = k; ++o; }
     if (wrap) { per_t[o] = t; per_L[o] = k; per_R[o] = kf + K; }
+    at += total;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->n_periods = nb > 1 ? all : at;
 }
 
 // the periods gathered in the order of their start (order[i]: index of the i-th) as {L, R, tensor, index}
@@ -493,11 +577,9 @@ __global__ __launch_bounds__(G10_BLOCK) void k_gather_periods(const u32* __restr
 // ===========================================================================
 // memory pressure: interval adds into a difference array, scan, max
 // ===========================================================================
-__global__ __launch_bounds__(G10_BLOCK) void k_fill_u64(u64* p, u64 n, u64 v) {
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) p[i] = v;
-}
-__global__ __launch_bounds__(G10_BLOCK) void k_fill_u32(u32* p, u64 n, u32 v) {
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) p[i] = v;
+__global__ __launch_bounds__(G10_BLOCK) void k_begin(VitStats* st, u64* __restrict__ diff, u64 n) {   // both cleared
+  if (blockIdx.x == 0 && threadIdx.x < sizeof(VitStats) / 8) ((u64*)st)[threadIdx.x] = 0;
+  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) diff[i] = 0;
 }
 
 __global__ __launch_bounds__(G10_BLOCK) void k_lifetime_adds(const u64* __restrict__ ukeys, const u64* __restrict__ use_off,
@@ -533,17 +615,30 @@ __global__ __launch_bounds__(G10_BLOCK) void k_lifetime_adds(const u64* __restri
   }
 }
 
-__global__ __launch_bounds__(G10_BLOCK) void k_max_u64(const u64* __restrict__ v, u64 n, u64* out) {
-  __shared__ u64 tmp[G10_WAVES + 1];
-  u64 m = 0;
-  for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) m = v[i] > m ? v[i] : m;
-  m = block_max(m, tmp);                        // wavefront shuffles, then 4 partials
-  if (threadIdx.x == 0) atomicMax((unsigned long long*)out, (unsigned long long)m);
+// ===========================================================================
+// the verdict and the results of g10_vitality_static
+// ===========================================================================
+__host__ __device__ inline int verdict_of(const VitStats& v) {
+  if (v.bad_index || v.zero_dur || v.zero_size) return G10_EINVAL;
+  if (v.size_overflow) return G10_EOVERFLOW;
+  const unsigned __int128 T = ((unsigned __int128)v.dur_hi << 32) + v.dur_lo, used = ((unsigned __int128)v.used_hi << 32) + v.used_lo;
+  return (T >> 62) || (used >> 64) ? G10_EOVERFLOW : G10_OK;
 }
 
-__global__ void k_store_counts(const u32* n_uses_p, const u32* n_per_p, VitStats* st) {
-  st->n_uses = *n_uses_p;
-  st->n_periods = *n_per_p;
+// The caller's buffers take the results only if the trace stands (the host learns that later).
+__global__ __launch_bounds__(G10_BLOCK) void k_results_out(const VitStats* __restrict__ st, g10_vitality_buffers out, u32 K, u32 N,
+                                                          const u64* __restrict__ use_off, const u32* __restrict__ use_k,
+                                                          const u32* __restrict__ per_t, const u32* __restrict__ per_L,
+                                                          const u32* __restrict__ per_R, const u64* __restrict__ start,
+                                                          const u64* __restrict__ pressure) {
+  const VitStats v = *st;
+  if (verdict_of(v)) return;
+  const u64 first = (u64)blockIdx.x * G10_BLOCK + threadIdx.x, step = (u64)gridDim.x * G10_BLOCK;
+  for (u64 i = first; i <= N; i += step) out.use_off[i] = use_off[i];
+  for (u64 i = first; i <= K; i += step) out.start[i] = start[i];
+  for (u64 i = first; i < K; i += step) out.pressure[i] = pressure[i];
+  for (u64 i = first; i < v.n_uses; i += step) out.use_k[i] = use_k[i];
+  for (u64 i = first; i < v.n_periods; i += step) { out.per_tensor[i] = per_t[i]; out.per_L[i] = per_L[i]; out.per_R[i] = per_R[i]; }
 }
 
 inline u32 grid_for(u64 n, u32 cap = 4096) {
@@ -620,9 +715,9 @@ static int radix_small(const KT* keys, KT* out, const u32* vals, u32* vout, u64 
 // LSD radix sort of the low `bits` bits of KT keys, 8 bits per pass, stable; PAIRS: with a 32-bit value carried
 // along with every key (iota: the values are the positions 0..n-1 and *vals need not be filled).
 // On return *keys points at the sorted keys and *alt at the other buffer, *vals / *valt likewise.
-// hist: radix_hist_elems(n) words.
+// hist: radix_hist_elems(n) words.  src: where given, the keys are read from there and *keys need not be filled.
 template <class KT, bool PAIRS>
-static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota) {
+static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota, const KT* src = nullptr) {
   if (n == 0) return G10_OK;
   auto swap = [&]() {
     KT* t = *keys; *keys = *alt; *alt = t;
@@ -630,16 +725,17 @@ static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bi
   };
   if (n <= SMALL) {
     const u32* v = PAIRS && !iota ? *vals : nullptr;
-    G10_TRY((radix_small<KT, PAIRS>(*keys, *alt, v, PAIRS ? *valt : nullptr, n, bits, s)));
+    G10_TRY((radix_small<KT, PAIRS>(src ? src : *keys, *alt, v, PAIRS ? *valt : nullptr, n, bits, s)));
     swap();
     return G10_OK;
   }
   const u32 nb = (u32)((n + TILE - 1) / TILE);
   for (u32 shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, (const KT*)*keys, n, shift, hist, nb);
+    const KT* from = src && shift == 0 ? src : *keys;
+    hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, from, n, shift, hist, nb);
     hipLaunchKernelGGL(k_radix_rows, dim3(256), dim3(G10_BLOCK), 0, s, hist, nb);
     const u32* v = PAIRS && !(iota && shift == 0) ? *vals : nullptr;
-    hipLaunchKernelGGL((k_radix_scatter<KT, PAIRS>), dim3(nb), dim3(G10_BLOCK), 0, s, (const KT*)*keys, *alt, v, PAIRS ? *valt : nullptr, n,
+    hipLaunchKernelGGL((k_radix_scatter<KT, PAIRS>), dim3(nb), dim3(G10_BLOCK), 0, s, from, *alt, v, PAIRS ? *valt : nullptr, n,
                        shift, hist, nb);
     swap();
   }
@@ -701,10 +797,11 @@ int slot_times_end(const void* check, u64* T_out) {
 // Device memory an analysis of K kernels, N tensors and P pairs takes: the temporaries of the call,
 // and what outlives it (`planning`: with own copies of the trace's arrays and the periods in the
 // order of their start, which only planning needs).
+// (a sum per tile, its total, and the scratch of a scan over them)
+static u64 tile_sums_elems(u64 n) { const u64 nb = (n + TILE - 1) / TILE; return nb + 1 + scan_scratch_elems(nb); }
 static size_t vit_tmp_bytes(u32 K, u32 N, u64 P) {
-  const u64 ss_kn = scan_scratch_elems(K > N ? K : N), rh = radix_hist_elems(P), ss_p = scan_scratch_elems(rh > P ? rh : P);
-  return Pool::need(1, sizeof(VitStats)) + Pool::need(ss_kn, 8) + 2 * Pool::need(P, 8) + 2 * Pool::need(P + 1, 4) +
-         Pool::need(rh, 4) + Pool::need(ss_p, 4);
+  const u64 ss_kn = scan_scratch_elems(K > N ? K : N), rh = radix_hist_elems(P), ss_p = tile_sums_elems(P);
+  return Pool::need(1, sizeof(VitStats)) + Pool::need(ss_kn, 8) + 2 * Pool::need(P, 8) + Pool::need(rh, 4) + 2 * Pool::need(ss_p, 4);
 }
 static size_t vit_keep_bytes(u32 K, u32 N, u64 P, bool planning) {
   // (the arrays per period are sized for P entries: there are fewer periods than uses, fewer uses than pairs)
@@ -715,103 +812,102 @@ static size_t vit_keep_bytes(u32 K, u32 N, u64 P, bool planning) {
 }
 
 // The analysis proper, in memory the caller of this function provides (two pools of at least
-// vit_tmp_bytes / vit_keep_bytes).
-static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& keep, const bool planning) {
+// vit_tmp_bytes / vit_keep_bytes).  out: where the results of an analysis without planning go.
+static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& keep, const bool planning, const g10_vitality_buffers* out) {
   hipStream_t s = h->stream;
   const u32 K = h->K, N = h->N;
   const u64 P = h->P;
 
   VitStats* st = nullptr;
   G10_TRY(tmp.take(&st, 1));
-  static_assert(sizeof(VitStats) % 8 == 0, "cleared as 64-bit words");
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(G10_BLOCK), 0, s, (u64*)st, (u64)(sizeof(VitStats) / 8), 0ull);
+  static_assert(sizeof(VitStats) % 8 == 0 && sizeof(VitStats) / 8 <= G10_BLOCK, "cleared as 64-bit words, one per thread");
+  G10_TRY(keep.take(&h->pressure_buf, (u64)K + 2));
+  hipLaunchKernelGGL(k_begin, dim3(grid_for((u64)K + 2)), dim3(G10_BLOCK), 0, s, st, h->pressure_buf, (u64)K + 2);
   G10_HIP(hipGetLastError());
 
-  if (planning) {                                 // own copies of what planning needs later
+  // ---- the trace: checks, sort keys, and own copies of what planning needs later (the checks are read by
+  // the host with the counts, at the one synchronisation below: nothing a kernel does with a zero
+  // duration, a zero or huge size or a wrapped sum leaves its arrays) --------------------------------
+  h->kbits = bits_for(K - 1);
+  const u32 tbits = bits_for(N - 1);
+  u64 *keys = nullptr, *alt = nullptr, *scratch64 = nullptr;
+  u32 *sums = nullptr, *psums = nullptr, *hist = nullptr;
+  G10_TRY(tmp.take(&keys, P));
+  G10_TRY(tmp.take(&alt, P));
+  if (planning) {
     G10_TRY(keep.take(&h->dur, K));
     G10_TRY(keep.take(&h->size, N));
     G10_TRY(keep.take(&h->glob, N));
-    G10_HIP(hipMemcpyAsync(h->dur, tr->dur_ns, (u64)K * 8, hipMemcpyDeviceToDevice, s));
-    G10_HIP(hipMemcpyAsync(h->size, tr->size_bytes, (u64)N * 8, hipMemcpyDeviceToDevice, s));
-    G10_HIP(hipMemcpyAsync(h->glob, tr->is_global, (u64)N, hipMemcpyDeviceToDevice, s));
   } else {                                        // the caller's arrays are read in place, during the call only
     h->dur = const_cast<u64*>(tr->dur_ns);
     h->size = const_cast<u64*>(tr->size_bytes);
     h->glob = const_cast<uint8_t*>(tr->is_global);
   }
-
-  // ---- validation (read by the host with the counts, at the one synchronisation below: nothing
-  // a kernel does with a zero duration, a zero or huge size or a wrapped sum leaves its arrays) ---
-  hipLaunchKernelGGL(k_check_dur, dim3(grid_for(K)), dim3(G10_BLOCK), 0, s, h->dur, K, st);
-  hipLaunchKernelGGL(k_check_size, dim3(grid_for(N, 512)), dim3(G10_BLOCK), 0, s, h->size, N, st);
-  G10_HIP(hipGetLastError());
-
-  // ---- slot start times ----------------------------------------------------
-  u64* scratch64 = nullptr;
-  G10_TRY(tmp.take(&scratch64, scan_scratch_elems(K > N ? K : N)));
-  G10_TRY(keep.take(&h->start, (u64)K + 1));
-  G10_TRY(scan_excl_u64(h->dur, h->start, K, scratch64, s));
-
-  // ---- use lists -------------------------------------------------------------
-  h->kbits = bits_for(K - 1);
-  const u32 tbits = bits_for(N - 1);
-  u64 *keys = nullptr, *alt = nullptr;
-  u32 *flag = nullptr, *scratch32 = nullptr, *hist = nullptr;
-  G10_TRY(tmp.take(&keys, P));
-  G10_TRY(tmp.take(&alt, P));
-  G10_TRY(tmp.take(&flag, P + 1));
-  G10_TRY(tmp.take(&hist, radix_hist_elems(P)));
-  G10_TRY(tmp.take(&scratch32, scan_scratch_elems(radix_hist_elems(P) > P ? radix_hist_elems(P) : P)));
-  if (P) {
-    hipLaunchKernelGGL(k_pack, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, tr->use_kernel, tr->use_tensor, P, K, N, h->kbits, keys, st);
-    G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, s));
-    hipLaunchKernelGGL(k_flag_distinct, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, keys, P, flag);
+  {
+    u64 most = P > N ? P : N;
+    if (K > most) most = K;
+    hipLaunchKernelGGL(k_load, dim3(grid_for(most)), dim3(G10_BLOCK), 0, s, tr->dur_ns, tr->size_bytes, tr->is_global, tr->use_kernel,
+                       tr->use_tensor, K, N, P, h->kbits, planning ? h->dur : (u64*)nullptr, planning ? h->size : (u64*)nullptr,
+                       planning ? h->glob : (uint8_t*)nullptr, keys, st);
     G10_HIP(hipGetLastError());
   }
-  G10_TRY(scan_excl_u32(flag, flag, P, scratch32, s));           // flag[i] = position, flag[P] = n_uses
-  const u32* n_uses_p = flag + P;
+
+  // ---- slot start times ----------------------------------------------------
+  G10_TRY(tmp.take(&scratch64, scan_scratch_elems(K > N ? K : N)));
+  G10_TRY(keep.take(&h->start, (u64)K + 1));
+  G10_TRY(scan_excl_u64(tr->dur_ns, h->start, K, scratch64, s));
+
+  // ---- use lists -------------------------------------------------------------
+  G10_TRY(tmp.take(&hist, radix_hist_elems(P)));
+  G10_TRY(tmp.take(&sums, tile_sums_elems(P)));
+  G10_TRY(tmp.take(&psums, tile_sums_elems(P)));
   G10_TRY(keep.take(&h->ukeys, P));                               // upper bounds: no host round trip here
   G10_TRY(keep.take(&h->use_k, P));
   G10_TRY(keep.take(&h->use_off, (u64)N + 1));
-  if (P) hipLaunchKernelGGL(k_compact_distinct, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, keys, P, flag, h->ukeys, h->use_k, h->kbits);
-  hipLaunchKernelGGL(k_use_off, dim3(grid_for((u64)N + 1)), dim3(G10_BLOCK), 0, s, h->ukeys, n_uses_p, N, h->kbits, h->use_off);
+  const u32 nb = (u32)((P + TILE - 1) / TILE);
+  const u32 scanned = nb > DIRECT ? 1u : 0u;                      // (many tiles: their sums are scanned in a step of its own)
+  if (P) {
+    G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, s));
+    if (nb > 1) hipLaunchKernelGGL(k_distinct_count, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)keys, P, sums);
+    if (scanned) G10_TRY(scan_excl_u32(sums, sums, nb, sums + nb + 1, s));
+    hipLaunchKernelGGL(k_distinct_write, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)keys, P, (const u32*)sums, nb, scanned, h->ukeys,
+                       h->use_k, h->kbits, st);
+    G10_HIP(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_use_off, dim3(grid_for((u64)N + 1)), dim3(G10_BLOCK), 0, s, (const u64*)h->ukeys, (const u64*)&st->n_uses, N, h->kbits, h->use_off);
   G10_HIP(hipGetLastError());
 
   // ---- inactive periods --------------------------------------------------------
-  u32* pcnt = nullptr;
-  G10_TRY(tmp.take(&pcnt, P + 1));
   const u32 no_wrap = (h->flags & G10_NO_WRAP) ? 1u : 0u;
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(P + 1)), dim3(G10_BLOCK), 0, s, pcnt, P + 1, 0u);
-  if (P) hipLaunchKernelGGL(k_period_count, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, h->ukeys, h->use_off, h->glob, n_uses_p, K, h->kbits, no_wrap, pcnt);
-  G10_TRY(scan_excl_u32(pcnt, pcnt, P, scratch32, s));           // pcnt[P] = n_periods (entries past n_uses are 0)
   G10_TRY(keep.take(&h->per_t, P));
   G10_TRY(keep.take(&h->per_L, P));
   G10_TRY(keep.take(&h->per_R, P));
-  if (P) hipLaunchKernelGGL(k_period_write, dim3(grid_for(P)), dim3(G10_BLOCK), 0, s, h->ukeys, h->use_off, h->glob, n_uses_p, K, h->kbits, no_wrap, pcnt, h->per_t, h->per_L, h->per_R);
-  G10_HIP(hipGetLastError());
+  if (P) {
+    if (nb > 1) hipLaunchKernelGGL(k_period_count, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)h->ukeys, (const u64*)h->use_off, (const uint8_t*)h->glob,
+                                   (const u64*)&st->n_uses, K, h->kbits, no_wrap, psums);
+    if (scanned) G10_TRY(scan_excl_u32(psums, psums, nb, psums + nb + 1, s));
+    hipLaunchKernelGGL(k_period_write, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)h->ukeys, (const u64*)h->use_off, (const uint8_t*)h->glob, K,
+                       h->kbits, no_wrap, (const u32*)psums, nb, scanned, h->per_t, h->per_L, h->per_R, st);
+    G10_HIP(hipGetLastError());
+  }
 
   // ---- memory pressure -----------------------------------------------------------
-  G10_TRY(keep.take(&h->pressure_buf, (u64)K + 2));
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for((u64)K + 2)), dim3(G10_BLOCK), 0, s, h->pressure_buf, (u64)K + 2, 0ull);
   hipLaunchKernelGGL(k_lifetime_adds, dim3(grid_for(N)), dim3(G10_BLOCK), 0, s, h->ukeys, h->use_off, h->size, h->glob, N, K, h->kbits, h->pressure_buf, st);
   G10_HIP(hipGetLastError());
-  // exclusive scan of diff[0..K] in place: buf[k + 1] = sum diff[0..k] = pressure[k]
-  G10_TRY(scan_excl_u64(h->pressure_buf, h->pressure_buf, (u64)K, scratch64, s));
-  hipLaunchKernelGGL(k_max_u64, dim3(grid_for(K, 1024)), dim3(G10_BLOCK), 0, s, h->pressure_buf + 1, (u64)K, &st->peak);
-  hipLaunchKernelGGL(k_store_counts, dim3(1), dim3(1), 0, s, n_uses_p, pcnt + P, st);
-  G10_HIP(hipGetLastError());
+  // exclusive scan of diff[0..K] in place: buf[k + 1] = sum diff[0..k] = pressure[k]; its largest value is the peak
+  G10_TRY(scan_excl<u64>(h->pressure_buf, h->pressure_buf, (u64)K, scratch64, s, &st->peak));
+  if (out) {
+    const u64 most = P > (u64)N + 1 ? P : (u64)N + 1;
+    hipLaunchKernelGGL(k_results_out, dim3(grid_for(most > (u64)K + 1 ? most : (u64)K + 1, 1024)), dim3(G10_BLOCK), 0, s, (const VitStats*)st, *out, K, N,
+                       (const u64*)h->use_off, (const u32*)h->use_k, (const u32*)h->per_t, (const u32*)h->per_L, (const u32*)h->per_R,
+                       (const u64*)h->start, (const u64*)(h->pressure_buf + 1));
+    G10_HIP(hipGetLastError());
+  }
   VitStats hs;
   G10_HIP(hipMemcpyAsync(&hs, st, sizeof hs, hipMemcpyDeviceToHost, s));
   G10_HIP(hipStreamSynchronize(s));
-  if (hs.bad_index || hs.zero_dur || hs.zero_size) return G10_EINVAL;
-  if (hs.size_overflow) return G10_EOVERFLOW;
-  {
-    unsigned __int128 T = ((unsigned __int128)hs.dur_hi << 32) + hs.dur_lo;
-    if (T >> 62) return G10_EOVERFLOW;
-    h->T = (u64)T;
-    unsigned __int128 used = ((unsigned __int128)hs.used_hi << 32) + hs.used_lo;
-    if (used >> 64) return G10_EOVERFLOW;
-  }
+  G10_TRY(verdict_of(hs));
+  h->T = (u64)(((unsigned __int128)hs.dur_hi << 32) + hs.dur_lo);
   h->big_size = hs.big_size != 0;
   h->max_size = hs.max_size;
   h->n_uses = hs.n_uses;
@@ -829,8 +925,7 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
   if (C) {
     // (a stable sort of the starts alone, the position carried along: equal starts keep the order of the periods)
     u32 *k32 = (u32*)keys, *k32_alt = k32 + C, *ord = (u32*)alt, *ord_alt = ord + C;      // (C <= P: two arrays of C words in one of P keys)
-    G10_HIP(hipMemcpyAsync(k32, h->per_L, C * 4, hipMemcpyDeviceToDevice, s));
-    G10_TRY(radix_sort_u32_pairs(&k32, &k32_alt, &ord, &ord_alt, C, h->kbits, hist, s, true));
+    G10_TRY((radix_sort<u32, true>(&k32, &k32_alt, &ord, &ord_alt, C, h->kbits, hist, s, true, (const u32*)h->per_L)));
     hipLaunchKernelGGL(k_gather_periods, dim3(grid_for(C)), dim3(G10_BLOCK), 0, s, (const u32*)ord, C, h->per_t, h->per_L, h->per_R,
                        h->size, h->per_by_start, h->per_size);
     G10_HIP(hipGetLastError());                     // (still running when this function returns: see vitality_run)
@@ -849,7 +944,7 @@ int vitality_run(g10_plan_s* h, const g10_trace* tr) {
   h->tmp_arena = tmp.base;
   G10_TRY(keep.reserve(vit_keep_bytes(h->K, h->N, h->P, true)));
   h->arena = keep.base;
-  return vitality_core(h, tr, tmp, keep, true);
+  return vitality_core(h, tr, tmp, keep, true, nullptr);
 }
 
 // ===========================================================================
@@ -894,19 +989,8 @@ extern "C" int g10_vitality_static(const g10_trace* tr, void* hip_stream, const 
   tmp.base = (char*)mem; tmp.cap = need_tmp;
   keep.base = (char*)mem + need_tmp; keep.cap = need_keep;
   hipStream_t s = h.stream;
-  int rc = vitality_core(&h, tr, tmp, keep, false);
+  const int rc = vitality_core(&h, tr, tmp, keep, false, out);   // (synchronises the stream where it succeeds)
   if (rc) { (void)hipStreamSynchronize(s); return rc; }
-  // the results go into the caller's buffers
-  G10_HIP(hipMemcpyAsync(out->use_off, h.use_off, ((u64)h.N + 1) * 8, hipMemcpyDeviceToDevice, s));
-  G10_HIP(hipMemcpyAsync(out->start, h.start, ((u64)h.K + 1) * 8, hipMemcpyDeviceToDevice, s));
-  G10_HIP(hipMemcpyAsync(out->pressure, h.pressure_buf + 1, (u64)h.K * 8, hipMemcpyDeviceToDevice, s));
-  if (h.n_uses) G10_HIP(hipMemcpyAsync(out->use_k, h.use_k, h.n_uses * 4, hipMemcpyDeviceToDevice, s));
-  if (h.n_periods) {
-    G10_HIP(hipMemcpyAsync(out->per_tensor, h.per_t, h.n_periods * 4, hipMemcpyDeviceToDevice, s));
-    G10_HIP(hipMemcpyAsync(out->per_L, h.per_L, h.n_periods * 4, hipMemcpyDeviceToDevice, s));
-    G10_HIP(hipMemcpyAsync(out->per_R, h.per_R, h.n_periods * 4, hipMemcpyDeviceToDevice, s));
-  }
-  G10_HIP(hipStreamSynchronize(s));
   stats->n_uses = h.n_uses; stats->n_periods = h.n_periods; stats->peak_bytes = h.peak; stats->iter_ns = h.T;
   return G10_OK;
 }
