@@ -22,6 +22,7 @@ static void handle_free(g10_plan_s* h) {
   free(h->more);
   free(h->counters);
   mem_dev_free(h->loop_args);
+  mem_host_free(h->pin);
   for (u32 k = 0; k < h->n_aux; ++k) (void)hipStreamDestroy(h->aux[k]);
   mem_dev_free(h->arena);                      // every array of the analysis
   release_tmp(h);

@@ -246,6 +246,8 @@ struct g10_plan_s {
   u32 loop_args_cap = 0;
   bool lds_opt_in = false;       // the loop kernel was allowed more than 64 KB of LDS
   void* arena = nullptr;         // the one device allocation the analysis arrays above point into
+  void* pin = nullptr;           // pinned staging of a planning call's small copies
+  size_t pin_bytes = 0;
   void* tmp_arena = nullptr;     // the analysis' temporaries, until the stream has next been waited for
   hipStream_t aux[8] = {};       // streams for the streaming kernels of the plans of a batch (made at the first batch)
   u32 n_aux = 0;

@@ -147,7 +147,11 @@ __global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, cons
                                                              u64* __restrict__ g_tot, u64* __restrict__ g_lazyP,
                                                              u64* __restrict__ g_minOver, u64* __restrict__ g_lazyH,
                                                              u64* __restrict__ g_hmax, u32* __restrict__ g_hmat,
-                                                             u32* __restrict__ g_hpend) {
+                                                             u32* __restrict__ g_hpend, u64* __restrict__ peak, u64* __restrict__ wide) {
+  if (blockIdx.x == 0) {                       // the peak after the plan; no pass left open
+    if (threadIdx.x == 0) *peak = 0;
+    if (threadIdx.x < 8) wide[threadIdx.x] = 0;
+  }
   __shared__ u64 tmp[2 * G10_WAVES];
   __shared__ u64 mins[G10_WAVES];
   const u64 cap = ctl->gpu_cap;
@@ -600,22 +604,33 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     memset(q, 0, (size_t)count * sizeof(g10_counters));
   }
   Inst* I = new (std::nothrow) Inst[count];
-  LoopArgs* hargs = (LoopArgs*)malloc((size_t)count * sizeof(LoopArgs));
-  Ctl* hctl = (Ctl*)malloc((size_t)count * sizeof(Ctl));
+  // what goes up to and comes back from the device in small pieces lies in pinned memory: copies to and
+  // from it are queued like kernels, a copy to pageable memory makes the host wait twice
+  const size_t staging = (size_t)count * (sizeof(LoopArgs) + 2 * sizeof(Ctl) + sizeof(u64) + sizeof(u32));
+  if (h->pin_bytes < staging) {
+    mem_host_free(h->pin);
+    h->pin = nullptr; h->pin_bytes = 0;
+    G10_TRY(mem_host_alloc(&h->pin, staging));
+    h->pin_bytes = staging;
+  }
+  LoopArgs* const hargs = (LoopArgs*)h->pin;
+  Ctl* const hctl = (Ctl*)(hargs + count);                                    // progress blocks of a launch
+  Ctl* const hctl0 = hctl + count;                                            // ... as they go up, and after the preparation
+  u64* const peaks = (u64*)(hctl0 + count);                                   // the plans' final peaks
+  u32* const hn = (u32*)(peaks + count);                                      // candidates kept
   u32* who = (u32*)malloc((size_t)count * sizeof(u32));                       // the plan of every entry of a launch
-  u64* peaks = (u64*)malloc((size_t)count * sizeof(u64));                     // the plans' final peaks come back here
   SortJob* hsj = (SortJob*)malloc((size_t)count * sizeof(SortJob));
   TileJob* htj = (TileJob*)malloc((size_t)count * sizeof(TileJob));
   // whatever way this function is left, nothing is in flight that reads or writes these host arrays
   struct Guard {
-    g10_plan_s* h; Inst* i; LoopArgs* a; Ctl* c; u32* w; SortJob* sj; TileJob* tj; u64* pk;
+    g10_plan_s* h; Inst* i; u32* w; SortJob* sj; TileJob* tj;
     ~Guard() {
       for (u32 k = 0; k < h->n_aux; ++k) (void)hipStreamSynchronize(h->aux[k]);
       (void)hipStreamSynchronize(h->stream);
-      delete[] i; free(a); free(c); free(w); free(sj); free(tj); free(pk);
+      delete[] i; free(w); free(sj); free(tj);
     }
-  } guard{h, I, hargs, hctl, who, hsj, htj, peaks};
-  if (!I || !hargs || !hctl || !who || !hsj || !htj || !peaks) return G10_ENOMEM;
+  } guard{h, I, who, hsj, htj};
+  if (!I || !who || !hsj || !htj) return G10_ENOMEM;
 
   for (u32 i = 0; i < count; ++i) {
     const g10_params* p = params + i;
@@ -699,14 +714,13 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     hc.rank = p->rank; hc.area = p->area;
     hc.C = C;
     hc.smax = h->max_size;
-    G10_HIP(hipMemcpyAsync(w->ctl, &hc, sizeof hc, hipMemcpyHostToDevice, q));
+    hctl0[i] = hc;
+    G10_HIP(hipMemcpyAsync(w->ctl, &hctl0[i], sizeof hc, hipMemcpyHostToDevice, q));
     Timelines& tl = x.tl;
     tl.dur = w->dur; tl.P = w->P; tl.fre = w->fre; tl.H = w->H; tl.px = w->px; tl.otc = w->otc;
     tl.K = K; tl.Kp = w->Kp; tl.nch = w->nch; tl.spt = w->spt; tl.shift_ch = w->shift_ch;
-    G10_HIP(hipMemsetAsync(w->peak_after, 0, 8, q));
-    G10_HIP(hipMemsetAsync(w->wide, 0, 64, q));           // (no pass left open)
     hipLaunchKernelGGL(k_init_timelines, dim3(w->nch), dim3(G10_BLOCK), 0, q, tl, (const u64*)(h->pressure_buf + 1),
-                       (const Ctl*)w->ctl, w->g_tot, w->g_lazyP, w->g_minOver, w->g_lazyH, w->g_hmax, w->g_hmat, w->g_hpend);
+                       (const Ctl*)w->ctl, w->g_tot, w->g_lazyP, w->g_minOver, w->g_lazyH, w->g_hmax, w->g_hmat, w->g_hpend, w->peak_after, (u64*)w->wide);
     hipLaunchKernelGGL(k_level1_init, dim3(1), dim3(LB), 0, q, (const u64*)w->g_tot, w->nch, w->base0, w->ctl);
     hipLaunchKernelGGL(k_ot_full, dim3(K / G10_BLOCK + 1), dim3(G10_BLOCK), 0, q, w->otc, (const u64*)w->base0, K, w->nch, w->shift_ch);
     G10_HIP(hipGetLastError());
@@ -721,12 +735,12 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
                          (const Ctl*)w->ctl, w->win, w->keep);
       G10_HIP(hipGetLastError());
       G10_TRY(scan_excl_u32(w->keep, w->keep, C, w->scratch32, q));
-      G10_HIP(hipMemcpyAsync(&x.n, w->keep + C, sizeof(u32), hipMemcpyDeviceToHost, q));
+      G10_HIP(hipMemcpyAsync(&hn[i], w->keep + C, sizeof(u32), hipMemcpyDeviceToHost, q));
     }
-    G10_HIP(hipMemcpyAsync(&hc, w->ctl, sizeof hc, hipMemcpyDeviceToHost, q));
+    G10_HIP(hipMemcpyAsync(&hctl[i], w->ctl, sizeof hc, hipMemcpyDeviceToHost, q));
   }
   G10_TRY(sync_all());
-  for (u32 i = 0; i < count; ++i) I[i].n = I[I[i].lead].n;
+  for (u32 i = 0; i < count; ++i) { I[i].hc = hctl[i]; I[i].n = C ? hn[I[i].lead] : 0u; }
 
   // the candidate buffers of a plan; the value cache only where the plan reads the benefit as the clipped area
   auto cands_of = [](const Inst& x, int which) {
@@ -961,9 +975,11 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     } else
     for (u32 kind = 0, first = 0; kind < 4; first += n_by_kind[kind], ++kind)
       if (n_by_kind[kind]) G10_TRY(loop_launch((const LoopArgs*)h->loop_args + first, n_by_kind[kind], lds, kind & 1u, kind >> 1, s));
-    hipLaunchKernelGGL(k_ctl_collect, dim3(na), dim3(G10_WAVE), 0, s, (const LoopArgs*)h->loop_args, ctl_side);
-    G10_HIP(hipGetLastError());
-    G10_HIP(hipMemcpyAsync(hctl, ctl_side, (size_t)na * sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    if (na > 1) {
+      hipLaunchKernelGGL(k_ctl_collect, dim3(na), dim3(G10_WAVE), 0, s, (const LoopArgs*)h->loop_args, ctl_side);
+      G10_HIP(hipGetLastError());
+    }
+    G10_HIP(hipMemcpyAsync(hctl, na > 1 ? ctl_side : I[who[0]].w->ctl, (size_t)na * sizeof(Ctl), hipMemcpyDeviceToHost, s));
     G10_HIP(hipStreamSynchronize(s));
     if (clocked) phase_end(1);
     for (u32 k = 0; k < na; ++k) I[who[k]].hc = hctl[k];
