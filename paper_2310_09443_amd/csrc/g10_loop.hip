@@ -73,12 +73,14 @@ constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the
 // ranking passes (25.8 to 31.3 ms; 26.3 ms at the median with small steps, 28.5 without).
 constexpr u32 PUB_START = 1u << 22, PUB_MIN = 1u << 12, PUB_MAX = 1u << 30;
 
+constexpr u32 LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // most threads and wavefronts of a loop workgroup
+
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
-  Winner wave_win[LW];        // best of every wavefront
+  Winner wave_win[LW_MAX];    // best of every wavefront
   Winner list[LIST_MAX];      // the candidates whose bound exceeds every bound not looked at one by one
   uint4 listA[LIST_MAX], listB[LIST_MAX];   // ... their periods and windows as in Cands; a committed one has no window left
-  u32 wave_f2[LW];            // per wavefront: largest bound among the candidates its threads scored but do not hold
+  u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
                               // host-capacity test needs the exact per-slot maximum
@@ -177,8 +179,16 @@ __device__ __forceinline__ u32 best_lane(u64 hi, u64 lo, u64 cost, u32 cand) {
   return wave_best_lane(hi, lo, cand);
 }
 
+// Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than eight
+// wavefronts take at once, so twelve (loops with eight / twelve: ResNet 5.90 / 5.57 ms, ragged stress
+// 5.76 / 5.48, stress 26.0 / 25.2, decoder 4.12 / 4.05, encoder 2.02 / 2.05; sixteen leave 128 registers
+// each and spill: 5.92, 5.66, 25.5, 4.43, 2.21).  The ratio key commits one migration a pass, four jobs:
+// eight (its passes with the scoring kernel take 5 % longer with twelve).
+constexpr u32 loop_threads(bool ratio, bool clip) { return ratio && !clip ? LB : LOOP_MAX; }
+
 template <bool RATIO, bool CLIP>
-__global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans) {
+__global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopArgs* __restrict__ plans) {
+  constexpr u32 LB = loop_threads(RATIO, CLIP), LW = LB / G10_WAVE;    // threads and wavefronts of this form
   // Several migrations per ranking pass (ranking by the benefit itself, band reading): after the
   // winner, the next best candidates of the same pass are committed with it as long as it is
   // certain that each would have won the pass after the one before it - see "more migrations
@@ -198,8 +208,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
   u64* hmax = lazyH + nch;
   u64* smark = hmax + nch;                              // [ns] tiles of a group of 64 scored in this pass
   u64* scr = smark + ns;                                // [4 * LW]
-  u64* jobs = scr + 4 * LW;                             // [8 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
-  u32* keys = (u32*)(jobs + 8 * nch + 8);               // [nt]  bound of every tile
+  u64* jobs = scr + 4 * LW_MAX;                         // [6 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
+  u32* keys = (u32*)(jobs + 6 * nch + 8);               // [nt]  bound of every tile
   u32* skeys = keys + nt;                               // [ns]  largest bound of every group of 64 tiles
   u32* hmat = skeys + ns;                               // [nch] host occupancy: migrations (by index) already added to the chunk's slots
   u32* hpend = hmat + nch;                              // [nch] ... and whether a later one that cuts the chunk is still missing
@@ -1072,8 +1082,6 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
     // (cround > 0) instead of from a new ranking.
     bool opened = false;                                 // the next pass's state is made
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
-    uint4 nextA = make_uint4(0u, 0u, 1u, 0u), nextB = make_uint4(1u, 0u, 0u, 0u);   // (last wavefront) the list entries' windows and
-    Gathered next;                                       // what a further round needs of the slot tables for them
     for (u32 cround = 0;; ++cround) {
     const bool from_list = MC && !(cround == 0u && uniform(S->fast));       // (else: the ranking has done this step)
     if (from_list && wave == LW - 1 && uniform(S->nlist) > 1u && K < (1u << 30)) {
@@ -1099,8 +1107,8 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
         mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
         if (have) {
-          const uint4 A = nextA, B = nextB;
-          const Score r = score_gathered(pv, mc, A, B, next);
+          const uint4 A = S->listA[lane], B = S->listB[lane];
+          const Score r = score_candidate(pv, mc, A, B);
           const bool ok_any = r.ok0 || r.ok1;
           const u32 d = r.ok0 ? 0u : 1u;
           const bool one = gt128(r.h1, r.l1, r.h0, r.l0);
@@ -1350,15 +1358,7 @@ __global__ __launch_bounds__(LB) void k_loop(const LoopArgs* __restrict__ plans)
         }
       }
       opened = !MC || !uniform(S->more);
-      if (wave == LW - 1) {
-        if (opened) open_pass();
-        else {                                           // the jobs are done: the slot tables are read beside the level-1 update
-          const u32 nl_ = uniform(S->nlist);
-          nextA = make_uint4(0u, 0u, 1u, 0u); nextB = make_uint4(1u, 0u, 0u, 0u);
-          if (lane < nl_) { nextA = S->listA[lane]; nextB = S->listB[lane]; }
-          next = gather_candidate(pv, nextA, nextB);
-        }
-      }
+      if (opened && wave == LW - 1) open_pass();
       __syncthreads();
     }
     if (opened) break;
@@ -1468,7 +1468,7 @@ int loop_wide_launch(const LoopArgs* plans, u32 nch, hipStream_t s) {
 size_t loop_lds_bytes(u32 nch, u32 nt) {
   const size_t ns = (nt + 63) / 64;
   size_t b = 0;
-  b += ((size_t)N_ARR * (nch + 1) + (size_t)N_ARR * nch + (size_t)4 * nch + ns + (size_t)4 * LW + (size_t)8 * nch + 8) * 8;
+  b += ((size_t)N_ARR * (nch + 1) + (size_t)N_ARR * nch + (size_t)4 * nch + ns + (size_t)4 * LW_MAX + (size_t)6 * nch + 8) * 8;      // (six jobs a chunk at most)
   b += sizeof(Shared);
   b += ((size_t)nt + ns + 2 * (size_t)nch) * 4 + (size_t)nt * 4;
   return (b + 15) & ~(size_t)15;
@@ -1493,7 +1493,7 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
 }
 
 int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, hipStream_t s) {
-  hipLaunchKernelGGL(loop_kernel(rank, area), dim3(n_plans), dim3(LB), lds, s, plans);
+  hipLaunchKernelGGL(loop_kernel(rank, area), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }

@@ -267,7 +267,7 @@ __device__ __forceinline__ Score score_gathered(const PrefixView& pv, const Mach
   r.fo_L = r.ok0 ? fo0_L : fo1_L; r.fi_R = r.ok0 ? fi0_R : fi1_R;
   return r;
 }
-// (everything is gathered before anything is used)
+// Both destinations' pairs are gathered before anything is used.
 __device__ __forceinline__ Score score_candidate(const PrefixView& pv, const Machine& mc, const uint4 A, const uint4 B) {
   return score_gathered(pv, mc, A, B, gather_candidate(pv, A, B));
 }
