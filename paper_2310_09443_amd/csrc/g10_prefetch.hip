@@ -66,37 +66,40 @@ __global__ __launch_bounds__(LB) void k_eager(const g10_migration* __restrict__ 
   // needs no barrier between them (the others wait at the barrier below; they set up and finish the timeline).
   // Most prefetches cannot move at all: the slot just before them cannot take the tensor.  That test reads one
   // slot, and the pressure changes only when a prefetch does move; so 64 records are tested at once, one per
-  // lane; those before the first that passes are done - nothing gained - and only that one takes the search.
-  // (the records of the next 64 are loaded before that search: they do not depend on it)
+  // lane; those before the first that passes are done - nothing gained - and only that one takes the search, after
+  // which the ones behind it are tested again.  (The records of the next 64 are on their way meanwhile.  Loading the 64
+  // behind every prefetch that moves anew - two dependent trips - took 7.15 ms on the stress trace, 1226 moves; 6.2 now.)
   if (wave == 0) {
     const u32 ncl = (nch + 63u) / 64u;             // chunks per lane: lane, lane + 64, ...
     u64 n_moved = 0, slots = 0;
-    u32 it = 0;
     u32 nr = 0, na = 0, nb = 0;
     u64 nsz = 0;
     if (lane < n) { nr = order[lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
-    while (it < n) {
-      const u32 idx = it + lane;
+    u32 it = 0;                                    // first record of the 64
+    u64 todo = 0;                                  // lanes whose record is not done yet
+    u32 cr = 0, ca = 0, cb = 0, cbb = 0;           // this lane's record: its number, absent window, last absent slot
+    u64 csz = 0;
+    while (true) {
+      if (!todo) {                                 // the next 64
+        if (it >= n) break;
+        const u32 cnt = n - it < 64u ? n - it : 64u;
+        todo = cnt == 64u ? ~0ull : (1ull << cnt) - 1ull;
+        cr = nr; ca = na; cb = nb; csz = nsz;
+        cbb = cb >= K ? cb - K : cb;
+        it += cnt;
+        if (it + lane < n) { nr = order[it + lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
+      }
+      const bool mine = (todo >> lane) & 1ull;
       bool pass = false;
-      if (idx < n) {
-        const u32 bb = nb >= K ? nb - K : nb;
-        pass = nsz <= cap && E[bb] + ladd[bb >> shift_ch] <= cap - nsz;
-      }
+      if (mine) pass = csz <= cap && E[cbb] + ladd[cbb >> shift_ch] <= cap - csz;
       const u64 pm = __ballot(pass);
-      const u32 left = n - it < 64u ? n - it : 64u;
-      const u32 f = pm ? (u32)__builtin_ctzll(pm) : left;      // records it .. it + f - 1 stay where they are
-      if (lane < f) { gained[nr] = 0u; last[nr] = nb >= K ? nb - K : nb; }
-      u32 r = 0, a = 0, b = 0;
-      u64 s = 0;
-      if (pm) {
-        r = (u32)__builtin_amdgcn_readlane((int)nr, (int)f);
-        a = (u32)__builtin_amdgcn_readlane((int)na, (int)f);
-        b = (u32)__builtin_amdgcn_readlane((int)nb, (int)f);
-        s = lane_value64(nsz, f);
-      }
-      it += f + (pm ? 1u : 0u);
-      if (it + lane < n) { nr = order[it + lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
-      if (!pm) continue;
+      const u32 f = pm ? (u32)__builtin_ctzll(pm) : 64u;       // the records before it stay where they are
+      if (mine && lane < f) { gained[cr] = 0u; last[cr] = cbb; }
+      if (!pm) { todo = 0; continue; }
+      todo &= f == 63u ? 0ull : ~0ull << (f + 1u);
+      const u32 r = (u32)__builtin_amdgcn_readlane((int)cr, (int)f), a = (u32)__builtin_amdgcn_readlane((int)ca, (int)f),
+                b = (u32)__builtin_amdgcn_readlane((int)cb, (int)f);
+      const u64 s = lane_value64(csz, f);
 
       // the earliest slot from which every slot up to b can hold the tensor: one past the last slot of [a, b]
       // that cannot.  The chunk maxima say which piece of a chunk may hold it, highest first; that piece is scanned.
@@ -158,15 +161,16 @@ __global__ __launch_bounds__(LB) void k_eager(const g10_migration* __restrict__ 
             const u64 lz = ladd[cc];
             u64 m = 0;
             for (u32 st = 0; st < spt; ++st) {
-              const u32 j0 = cc * CH + st * 256u + lane * 4u;
+              const u32 j0 = cc * CH + st * 256u + lane;        // (64 neighbouring slots per load and store)
+              u64 x[4];
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) x[i] = j0 + i * 64u < K ? E[j0 + i * 64u] : 0ull;
 #pragma unroll
               for (u32 i = 0; i < 4; ++i) {
-                const u32 j = j0 + i;
+                const u32 j = j0 + i * 64u;
                 if (j < K) {
-                  u64 x = E[j];
-                  if (in_doubled(j, K, p, b) != NONE32) { x += s; E[j] = x; }
-                  x += lz;
-                  m = x > m ? x : m;
+                  if (in_doubled(j, K, p, b) != NONE32) { x[i] += s; E[j] = x[i]; }
+                  m = x[i] + lz > m ? x[i] + lz : m;
                 }
               }
             }
