@@ -67,11 +67,13 @@ static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid o
 constexpr u32 MC_GUESS_SHIFT_MIN = 3;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
 constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the second and later migrations
 // How far under the round's threshold a scored candidate's bound may lie to go on the list, in key steps (2^24 are a
-// factor of two).  Entries under the bound of the tiles left out cannot be picked, so that is the lowest; within that the
-// margin follows the list towards 16 to 36 entries, in small steps near there: which entries an overflowing list takes
-// is left to chance, and a margin that doubled into an overflow every few passes gave stress plans between 400 and 1100
-// ranking passes (25.8 to 31.3 ms; 26.3 ms at the median with small steps, 28.5 without).
-constexpr u32 PUB_START = 1u << 22, PUB_MIN = 1u << 12, PUB_MAX = 1u << 30;
+// factor of two); below zero: how far above it must lie.  Entries under the bound of the tiles left out cannot be picked,
+// so that is the lowest; within that the margin follows the list towards 16 to 36 entries, in small steps near there.
+// Which entries an overflowing list takes is left to chance, and the pass is then ranked by an arg-max over all threads
+// and commits one migration: a margin that doubled into an overflow every few passes gave stress plans between 400 and
+// 1100 ranking passes, and one that could not go above the threshold left six passes in ten overflowing on the model
+// traces (many candidates of a repeated layer lie within the eighth under the last benefit).
+constexpr int PUB_START = 1 << 22, PUB_MIN = -(1 << 23), PUB_MAX = 1 << 30;
 
 constexpr u32 LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // most threads and wavefronts of a loop workgroup
 
@@ -100,7 +102,8 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   // progress (mirrors Ctl)
   u64 n_iter, n_mig, n_drop, n_evals, units, second, jobs;
   u32 thr_key, status, done, stop;
-  u32 gshift, pub;            // margins of the first threshold and of the list under it
+  u32 gshift;                 // margins of the first threshold, and of the list under it
+  int pub;
   u64 t_start;
 };
 
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->units = 0; S->second = 0; S->jobs = 0; S->evals = 0; S->refused = 0; S->more_rounds = 0; S->more = 0; S->list_rescored = 0;
     S->thr_key = ctl->thr_key; S->status = ctl->status; S->done = ctl->done;
     S->gshift = ctl->gshift ? ctl->gshift : GUESS_SHIFT;
-    S->pub = ctl->pub ? ctl->pub : PUB_START;
+    S->pub = ctl->pub ? ctl->pub : PUB_START;      // (0: not set yet; a margin of 0 starts over)
     S->nl = 0; S->restL = NONE32; S->stale_hot = 0;
     S->stop = 0; S->t_start = wall_clock64();
     S->mem[0].hi = 0; S->mem[0].lo = 0;
@@ -1000,9 +1003,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         } else {
           u32 low = thr;                           // the list's threshold
           if (MC) {
-            const u32 pub = uniform(S->pub);
-            low = thr > pub ? thr - pub : 1u;
-            low = low > rest ? low : rest + 1u;
+            const long long at = (long long)thr - (int)uniform((u32)S->pub);
+            low = at > (long long)rest ? (u32)at : rest + 1u;
           }
           score_list(low);
         }
@@ -1042,6 +1044,10 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           const bool any = (S->mem[0].hi | S->mem[0].lo) != 0;
           if (wave == 0 && any && lane < sizeof(Winner) / 4) ((u32*)&S->mem[0])[lane] = ((const u32*)&wv.win[i])[lane];
           __syncthreads();
+          // (the threads hold rankings without the rest: a further round of the pass goes on from the whole one, which
+          // beats the others)
+          mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32;
+          if (any && tid == LB - 1) mine = S->mem[0];
         }
         const u32 kb = key_dn_of<RATIO>(S->mem[0].hi, S->mem[0].lo, S->mem[0].cost);
         const u32 need = kb ? kb : 1u;
@@ -1295,12 +1301,13 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
         if (MC && cround == 0u) {
-          const u32 nl_ = S->nlist, pub = S->pub;
-          u32 x = pub;
-          if (nl_ > LIST_MAX) x = pub / 2u;
-          else if (nl_ > 36u) x = pub - pub / 8u;
-          else if (nl_ < 6u) x = pub * 2u;
-          else if (nl_ < 16u) x = pub + pub / 4u;
+          const u32 nl_ = S->nlist;
+          const int pub = S->pub, mag = pub < 0 ? -pub : pub;
+          int x = pub;
+          if (nl_ > LIST_MAX) x -= mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
+          else if (nl_ > 36u) x -= mag / 8 > (1 << 15) ? mag / 8 : 1 << 15;
+          else if (nl_ < 6u) x += mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
+          else if (nl_ < 16u) x += mag / 4 > (1 << 16) ? mag / 4 : 1 << 16;
           S->pub = x < PUB_MIN ? PUB_MIN : x > PUB_MAX ? PUB_MAX : x;
         }
         const Winner& Z = S->mem[m - 1];

@@ -42,7 +42,7 @@ struct Ctl {
   u32 thr_key;                // first threshold of the next pass (0: use the largest tile bound)
   u32 n_live;                 // candidates that could still score at the last re-scoring
   u32 gshift;                 // the guess: first threshold = last best * (1 - 2^-gshift); 0 stands for GUESS_SHIFT
-  u32 pub;                    // the list's margin under the threshold, in key steps; 0: not set yet
+  int pub;                    // the list's margin under the threshold, in key steps; 0: not set yet
   // statistics
   u64 units_scored, second_rounds, jobs_run, launches, passes;
   u64 area_evals, area_refused;   // clipped areas computed in the loop; of those, how many came out below the bound
