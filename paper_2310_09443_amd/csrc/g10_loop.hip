@@ -522,7 +522,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // jobs, from writing its plan records); jnext counts from LW - 1.
   // Slot s0 + 256 st + 64 i + lane belongs to lane `lane` (i = 0..3): every load and store of a job
   // covers 64 neighbouring slots.  A workgroup has one texture unit, about one cache line per clock,
-  // and up to eight jobs run at once: with four neighbouring slots per lane and one 64-byte record
+  // and a job for every wavefront runs at once: with four neighbouring slots per lane and one 64-byte record
   // per slot a rewrite touched 64 lines per instruction, now 8 (see the tables of px).
   auto run_jobs = [&](const u32 begin, const u32 end, const u32 keep) {
     ulonglong2* const px = reinterpret_cast<ulonglong2*>(tl.px);

@@ -17,7 +17,7 @@
 //
 // The greedy loop itself is a serial chain of small dependent steps (rank,
 // decide, range updates, prefix rebuild), bound by latency, not bandwidth.  It
-// runs in ONE persistent workgroup of 512 threads per plan (k_loop, in
+// runs in ONE persistent workgroup of 512 or 768 threads per plan (k_loop, in
 // g10_loop.hip): no grid barrier and no kernel boundary per pass, the level-1
 // state in LDS, the slot arrays in L2.  Range updates over a period are chunked: whole chunks take a lazy
 // add in LDS (pressure, host occupancy), only chunks cut by the period ends,
