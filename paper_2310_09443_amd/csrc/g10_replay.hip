@@ -276,18 +276,18 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
     G10_HIP(hipStreamSynchronize(s));
     replay_free(w);
     const u64 cap = n ? n : 1, ce = 6 * cap;
-    const u64 he = radix_hist_elems(ce), se = scan_scratch_elems(he > ce ? he : ce);
+    const u64 he = radix_hist_elems(ce);
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     const size_t o_keys = take(ce * 8), o_alt = take(ce * 8), o_res = take(ce * 8), o_late = take(cap * 8), o_pos = take(4 * cap * 4),
-                 o_hist = take(he * 4), o_scr = take(se * 4), o_st = take(sizeof(ReplayStats)), o_dur = take((u64)K * 8),
+                 o_hist = take(he * 4), o_st = take(sizeof(ReplayStats)), o_dur = take((u64)K * 8),
                  o_start = take(((u64)K + 1) * 8), o_ts = take(scan_scratch_elems(K) * 8), o_tst = take(128);
     void* q = nullptr;
     G10_TRY(mem_dev_alloc(&q, off));
     char* b = (char*)q;
     w->rp_arena = q; w->rp_cap = (u32)cap;
     w->rp_keys = (u64*)(b + o_keys); w->rp_alt = (u64*)(b + o_alt); w->rp_res = (u64*)(b + o_res); w->rp_late = (u64*)(b + o_late);
-    w->rp_pos = (u32*)(b + o_pos); w->rp_hist = (u32*)(b + o_hist); w->rp_scr = (u32*)(b + o_scr); w->rp_stats = (void*)(b + o_st);
+    w->rp_pos = (u32*)(b + o_pos); w->rp_hist = (u32*)(b + o_hist); w->rp_stats = (void*)(b + o_st);
     w->rp_dur = (u64*)(b + o_dur); w->rp_start = (u64*)(b + o_start); w->rp_tscr = (u64*)(b + o_ts); w->rp_tstats = (void*)(b + o_tst);
     w->h_rp_late = (u64*)malloc(cap * 8);
     if (!w->h_rp_late) return G10_ENOMEM;
