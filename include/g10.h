@@ -258,9 +258,10 @@ int g10_plan_counters(const g10_plan_t *handle, uint32_t plan_index, g10_counter
 
 /* Bounds of the two on-chip structures of the greedy loop for the planning calls that follow on
  * this handle; 0 = the library's default, which is also the maximum.  max_tiles: candidates are
- * ranked in tiles of 256 << k, k the smallest with at most this many tiles (8192).  max_chunks:
- * the kernel timeline is split into chunks of 256 << k slots, k the smallest with at most this
- * many chunks (512).  Both only trade speed against on-chip memory; no plan depends on them.
+ * ranked in tiles of 256 << k, k the smallest with at most this many tiles (8192; fewer beside
+ * 498 chunks or more, where on-chip memory takes no more).  max_chunks: the kernel timeline is
+ * split into chunks of 256 << k slots, k the smallest with at most this many chunks (512).  Both
+ * only trade speed against on-chip memory; no plan depends on them.
  * They exist so that tests reach the code paths of very long traces with small ones.
  * Errors: G10_EINVAL (NULL). */
 int g10_plan_limits(g10_plan_t *handle, uint32_t max_tiles, uint32_t max_chunks);

@@ -1481,6 +1481,19 @@ size_t loop_lds_bytes(u32 nch, u32 nt) {
   return (b + 15) & ~(size_t)15;
 }
 
+// The smallest tile (256 << shift) with at most max_tiles tiles that fit the LDS beside the chunks: 8192 tiles
+// and 512 chunks together are 2.4 KB more than a compute unit has (from 498 chunks on the tiles' limit is lower,
+// 7899 at 512 chunks), half as many tiles always fit.
+u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch) {
+  const u64 units = (n + UNIT - 1) / UNIT;
+  u32 sh = 0;
+  while (true) {
+    const u64 nt = (units + (1ull << sh) - 1) >> sh;
+    if (nt <= max_tiles && loop_lds_bytes(nch, (u32)nt) <= LDS_MAX) return sh;
+    ++sh;
+  }
+}
+
 typedef void (*LoopKernel)(const LoopArgs*);
 static LoopKernel loop_kernel(u32 rank, u32 area) {
   if (area == G10_AREA_CLIPPED) return rank == G10_RANK_RATIO ? k_loop<true, true> : k_loop<false, true>;
@@ -1494,7 +1507,7 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
   if (dev >= 0 && dev < 64 && done[dev]) return G10_OK;
   for (u32 rank = 0; rank < 2; ++rank)
     for (u32 area = 0; area < 2; ++area)
-      G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+      G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
   if (dev >= 0 && dev < 64) done[dev] = true;
   return G10_OK;
 }

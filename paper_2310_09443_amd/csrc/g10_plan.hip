@@ -441,12 +441,6 @@ static const u64 BATCH_LAUNCH_TICKS = 250000;    // a launch of a batch ends aft
 static const u32 WIDE_MIN_UNITS = 32;
 static const u64 WIDE_MIN_CANDS = 65536;
 
-static u32 tile_shift_for(u64 n, u32 max_tiles) { // smallest tile (256 << shift) with at most max_tiles tiles
-  u32 sh = 0;
-  while ((((n + UNIT - 1) / UNIT) + (1ull << sh) - 1) >> sh > max_tiles) ++sh;
-  return sh;
-}
-
 static u32 clamp_limit(u32 asked, u32 lib_max) { return asked == 0 || asked > lib_max ? lib_max : asked; }
 
 // One device allocation for all planning workspaces (a handle is often short-lived; every
@@ -749,13 +743,18 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     return c;
   };
 
-  // candidates of plan x into score order, in tiles
-  auto retile = [&](Inst& x, bool first, hipStream_t q) -> int {
-    PlanWork* w = x.w;
-    x.tsh = tile_shift_for(x.n, x.max_tiles);
+  // the tiles of plan x's candidates
+  auto set_tiles = [](Inst& x) {
+    x.tsh = loop_tile_shift(x.n, x.max_tiles, x.w->nch);
     const u32 tile = UNIT << x.tsh;
     x.nt = (u32)(((u64)x.n + tile - 1) / tile);
     x.n_pad = x.nt * tile;
+  };
+
+  // candidates of plan x into score order, in tiles
+  auto retile = [&](Inst& x, bool first, hipStream_t q) -> int {
+    PlanWork* w = x.w;
+    set_tiles(x);
     if (!x.n) return G10_OK;
     const u32 n = x.n;
     if (first) {
@@ -856,10 +855,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     else {
       // a batch: every plan's scoring pass on its stream, then the sorts and the tiles of all plans in the same launches
       PlanWork* w = x.w;
-      x.tsh = tile_shift_for(x.n, x.max_tiles);
-      const u32 tile = UNIT << x.tsh;
-      x.nt = (u32)(((u64)x.n + tile - 1) / tile);
-      x.n_pad = x.nt * tile;
+      set_tiles(x);
       if (x.n) {
         const u32 gn = (x.n + G10_BLOCK - 1) / G10_BLOCK;
         if (!writes_fw) G10_HIP(hipStreamWaitEvent(stream_of(i), lw->ev[2], 0));         // (recorded when an earlier plan wrote the copy)
@@ -1000,10 +996,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
         x.retile_cands += x.n;
         if (count == 1) G10_TRY(retile(x, false, s));
         else {
-          x.tsh = tile_shift_for(x.n, x.max_tiles);
-          const u32 tile = UNIT << x.tsh;
-          x.nt = (u32)(((u64)x.n + tile - 1) / tile);
-          x.n_pad = x.nt * tile;
+          set_tiles(x);
           if (x.n) {
             fill_jobs(x, nj, mx);
             ++nj;

@@ -18,6 +18,7 @@ constexpr u32 LW = LB / G10_WAVE;      // its wavefronts
 constexpr u32 UNIT = 256;              // candidates scored by four wavefronts at a time
 constexpr u32 NCH_MAX = 512;           // chunks (level-1 arrays live in LDS)
 constexpr u32 NT_MAX = 8192;           // tiles  (their bounds live in LDS)
+constexpr size_t LDS_MAX = 160 * 1024; // LDS of a compute unit (both limits together are over it: loop_tile_shift)
 constexpr u32 GUESS_SHIFT = 7;                 // first threshold of a pass: last benefit * (1 - 2^-shift), to begin with
 constexpr u32 GUESS_SHIFT_MAX = 24;            // the keys resolve no finer steps
 constexpr u64 NONE64 = ~0ull;
@@ -434,6 +435,7 @@ void replay_free(PlanWork* w);
 
 // the loop kernel (g10_loop.hip)
 size_t loop_lds_bytes(u32 nch, u32 nt);                       // dynamic LDS of one workgroup
+u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candidates on a timeline of nch chunks: 256 << this
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
 int loop_wide_launch(const g10::LoopArgs* plans, u32 nch, hipStream_t s);   // the scoring kernel for plans[0]

@@ -58,3 +58,20 @@ def test_long_kernels(g10, dur):
         a = dict(args, bw_out=bw, bw_in=bw)
         assert_plan_equal(h.plan(**a), v.plan(**a))
     h.close()
+
+
+@pytest.mark.parametrize("K,n", [(131_072, 7899 * 256), (131_072, 7899 * 256 + 1), (131_072, 8192 * 256), (127_232, 8192 * 256), (127_233, 8192 * 256)])
+def test_most_chunks_and_most_tiles(g10, K, n):
+    """497, 498 and 512 chunks of 256 slots with as many tiles of 256 candidates as fit the LDS beside them, and one more:
+    the first passes of the plan, with both ranking keys (every tensor is one candidate with a window either way)."""
+    i = np.arange(n, dtype=np.uint64)
+    first = traces.rand_int(5, 1, i, 0, K // 2 - 1).astype(np.uint32)
+    last = traces.rand_int(5, 2, i, K // 2 + 64, K - 1).astype(np.uint32)
+    tr = Trace(f"limits{n}", np.full(K, 1000, np.uint64), traces.rand_int(5, 3, i, 4096, 65536).astype(np.uint64), np.zeros(n, np.uint8),
+               np.concatenate([first, last]), np.concatenate([i, i]).astype(np.uint32))
+    h, v, args = run_both(g10, Workload(tr, cap_frac=0.5, host_cap_frac=0.1))
+    for rank in (0, 1):
+        a = dict(args, max_iters=24, rank=rank)
+        assert_plan_equal(h.plan(**a), v.plan(**a))
+        assert h._counters(0).score_full_cands == n
+    h.close()
