@@ -597,9 +597,9 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     h->counters = q;
     memset(q, 0, (size_t)count * sizeof(g10_counters));
   }
-  Inst* I = new (std::nothrow) Inst[count];
   // what goes up to and comes back from the device in small pieces lies in pinned memory: copies to and
-  // from it are queued like kernels, a copy to pageable memory makes the host wait twice
+  // from it are queued like kernels, a copy to pageable memory makes the host wait twice (grown before anything
+  // is made that a return from here would have to free)
   const size_t staging = (size_t)count * (sizeof(LoopArgs) + 2 * sizeof(Ctl) + sizeof(u64) + sizeof(u32));
   if (h->pin_bytes < staging) {
     mem_host_free(h->pin);
@@ -608,10 +608,11 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     h->pin_bytes = staging;
   }
   LoopArgs* const hargs = (LoopArgs*)h->pin;
-  Ctl* const hctl = (Ctl*)(hargs + count);                                    // progress blocks of a launch
-  Ctl* const hctl0 = hctl + count;                                            // ... as they go up, and after the preparation
+  Ctl* const hctl = (Ctl*)(hargs + count);                                    // progress blocks: after the preparation, and of a launch
+  Ctl* const hctl0 = hctl + count;                                            // ... as they go up
   u64* const peaks = (u64*)(hctl0 + count);                                   // the plans' final peaks
   u32* const hn = (u32*)(peaks + count);                                      // candidates kept
+  Inst* I = new (std::nothrow) Inst[count];
   u32* who = (u32*)malloc((size_t)count * sizeof(u32));                       // the plan of every entry of a launch
   SortJob* hsj = (SortJob*)malloc((size_t)count * sizeof(SortJob));
   TileJob* htj = (TileJob*)malloc((size_t)count * sizeof(TileJob));
