@@ -290,7 +290,7 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
     w->rp_pos = (u32*)(b + o_pos); w->rp_hist = (u32*)(b + o_hist); w->rp_stats = (void*)(b + o_st);
     w->rp_dur = (u64*)(b + o_dur); w->rp_start = (u64*)(b + o_start); w->rp_tscr = (u64*)(b + o_ts); w->rp_tstats = (void*)(b + o_tst);
     w->h_rp_late = (u64*)malloc(cap * 8);
-    if (!w->h_rp_late) return G10_ENOMEM;
+    if (!w->h_rp_late) { replay_free(w); return G10_ENOMEM; }      // both or none: the next call must find the same state as the first
   }
   // the durations to replay with: the given ones, else the ones the plan was made for
   const u64* start = w->start;
