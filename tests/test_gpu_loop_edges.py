@@ -47,7 +47,7 @@ def test_list_of_equal_candidates(g10, n):
 
 @pytest.mark.parametrize("dur", [16_777_215, 16_777_216, 16_777_217, 1 << 33, 1 << 45])
 def test_long_kernels(g10, dur):
-    """Chunk totals (256 slots) just below, at and above 2^32 ns, and far above."""
+    """Chunk totals (256 slots) a little below and above 2^32 ns, and far above."""
     w = traces.stress(K=600, N=6000, seed=9)
     tr = w.trace
     d = np.where(np.arange(tr.K) % 2 == 0, np.uint64(dur), np.uint64(max(dur - 3, 1))).astype(np.uint64)
@@ -57,6 +57,23 @@ def test_long_kernels(g10, dur):
     for bw in ((1, 3), (700, 2000), (6000, 25000)):
         a = dict(args, bw_out=bw, bw_in=bw)
         assert_plan_equal(h.plan(**a), v.plan(**a))
+    h.close()
+
+
+@pytest.mark.parametrize("total", [(1 << 32) - 1, 1 << 32, (1 << 32) + 1])
+def test_chunk_totals_at_32_bits(g10, total):
+    """Every full chunk's total exactly at the last value that its jobs sum in 32 bits, and one and two above it."""
+    w = traces.stress(K=700, N=7000, seed=10)
+    d = np.full(w.trace.K, 1 << 24, np.uint64)
+    d[100:512:256] = np.uint64(total - 255 * (1 << 24))
+    assert d[:256].sum() == total and d[256:512].sum() == total
+    w = Workload(traces.with_durations(w.trace, d), cap_frac=0.3, host_cap_frac=0.1)
+    h, v, args = run_both(g10, w)
+    for bw in ((1, 3), (700, 2000), (6000, 25000)):
+        a = dict(args, bw_out=bw, bw_in=bw)
+        p = v.plan(**a)
+        assert len(p.records)
+        assert_plan_equal(h.plan(**a), p)
     h.close()
 
 
