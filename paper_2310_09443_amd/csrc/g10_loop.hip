@@ -9,6 +9,17 @@ using namespace g10;
 
 namespace {
 
+// Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than eight
+// wavefronts take at once, so twelve (loops with eight / twelve: ResNet 5.90 / 5.57 ms, ragged stress with
+// cross-iteration periods 5.76 / 5.48, stress 26.0 / 25.2, decoder 4.12 / 4.05, encoder 2.02 / 2.05).  Twelve
+// leave 168 registers each, and the benefit key in the band reading spills ten (80 bytes a lane: the list entry
+// of the picking wavefront, the record pointers); sixteen leave 128 and spill more: 5.92, 5.66, 25.5, 4.43,
+// 2.21.  The ratio key in the band reading commits one migration a pass, four jobs: eight (its passes with the
+// scoring kernel take 5 % longer with twelve).
+constexpr u32 LOOP_MIN = 512, LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // ... least and most, and the most wavefronts
+constexpr u32 loop_threads(bool ratio, bool clip) { return ratio && !clip ? LOOP_MIN : LOOP_MAX; }
+static_assert(LOOP_MIN >= NCH_MAX && LOOP_MIN % UNIT == 0 && LOOP_MAX % UNIT == 0, "a thread per chunk; units are scored by four whole wavefronts");
+
 struct alignas(16) Winner {   // what a commit needs of the winning candidate
   u64 hi, lo;                 // benefit
   u64 cost;                   // eviction + prefetch time (ranking by benefit / cost only)
@@ -29,7 +40,7 @@ struct alignas(16) Winner {   // what a commit needs of the winning candidate
 // of tiles to score, ends in the middle of its pass, a scoring kernel takes the list (the tile
 // bounds go into the array of tile bounds in device memory, every workgroup's best candidate
 // into `win`), and the next launch of the loop kernel takes the pass up again with those.
-constexpr u32 WIDE_WG = 2 * (LB - 1);   // workgroups of the scoring kernel that take part at most: two winners per thread of the
+constexpr u32 WIDE_WG = 2 * (loop_threads(true, false) - 1);   // workgroups of the scoring kernel that take part at most: two winners per thread of the
                                         // loop kernel, whose last thread takes the best of the pass's earlier rounds
 struct WideCtx {
   u32 pending;                // the loop kernel has left a list and waits for it to be scored
@@ -74,8 +85,6 @@ constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the
 // 1100 ranking passes, and one that could not go above the threshold left six passes in ten overflowing on the model
 // traces (many candidates of a repeated layer lie within the eighth under the last benefit).
 constexpr int PUB_START = 1 << 22, PUB_MIN = -(1 << 23), PUB_MAX = 1 << 30;
-
-constexpr u32 LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // most threads and wavefronts of a loop workgroup
 
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
@@ -182,13 +191,6 @@ __device__ __forceinline__ u32 best_lane(u64 hi, u64 lo, u64 cost, u32 cand) {
   return wave_best_lane(hi, lo, cand);
 }
 
-// Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than eight
-// wavefronts take at once, so twelve (loops with eight / twelve: ResNet 5.90 / 5.57 ms, ragged stress
-// 5.76 / 5.48, stress 26.0 / 25.2, decoder 4.12 / 4.05, encoder 2.02 / 2.05; sixteen leave 128 registers
-// each and spill: 5.92, 5.66, 25.5, 4.43, 2.21).  The ratio key commits one migration a pass, four jobs:
-// eight (its passes with the scoring kernel take 5 % longer with twelve).
-constexpr u32 loop_threads(bool ratio, bool clip) { return ratio && !clip ? LB : LOOP_MAX; }
-
 template <bool RATIO, bool CLIP>
 __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopArgs* __restrict__ plans) {
   constexpr u32 LB = loop_threads(RATIO, CLIP), LW = LB / G10_WAVE;    // threads and wavefronts of this form
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   u64* lazyH = minOver + nch;
   u64* hmax = lazyH + nch;
   u64* smark = hmax + nch;                              // [ns] tiles of a group of 64 scored in this pass
-  u64* scr = smark + ns;                                // [4 * LW]
+  u64* scr = smark + ns;                                // [4 * LW_MAX]
   u64* jobs = scr + 4 * LW_MAX;                         // [6 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
   u32* keys = (u32*)(jobs + 6 * nch + 8);               // [nt]  bound of every tile
   u32* skeys = keys + nt;                               // [ns]  largest bound of every group of 64 tiles

@@ -195,15 +195,15 @@ __global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, cons
 
 // level 1 of the over-capacity time before any eviction, for the full scoring
 // pass; also the "fits already" test
-__global__ __launch_bounds__(LB) void k_level1_init(const u64* __restrict__ g_tot, u32 nch, u64* __restrict__ base0, Ctl* ctl) {
-  __shared__ u64 scr[LW];
+__global__ __launch_bounds__(WG) void k_level1_init(const u64* __restrict__ g_tot, u32 nch, u64* __restrict__ base0, Ctl* ctl) {
+  __shared__ u64 scr[WG_WAVES];
   const u32 tid = threadIdx.x;
   const u64 v = tid < nch ? g_tot[(u64)A_OT * nch + tid] : 0ull;
   const u64 inc = wave_scan_incl(v);
   if (lane_id() == G10_WAVE - 1) scr[wave_id()] = inc;
   __syncthreads();
   u64 b = 0, t = 0;
-  for (u32 w = 0; w < LW; ++w) { const u64 x = scr[w]; if (w < wave_id()) b += x; t += x; }
+  for (u32 w = 0; w < WG_WAVES; ++w) { const u64 x = scr[w]; if (w < wave_id()) b += x; t += x; }
   if (tid < nch) base0[tid] = b + inc - v;
   if (tid == 0) {
     base0[nch] = t;
@@ -716,7 +716,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     tl.K = K; tl.Kp = w->Kp; tl.nch = w->nch; tl.spt = w->spt; tl.shift_ch = w->shift_ch;
     hipLaunchKernelGGL(k_init_timelines, dim3(w->nch), dim3(G10_BLOCK), 0, q, tl, (const u64*)(h->pressure_buf + 1),
                        (const Ctl*)w->ctl, w->g_tot, w->g_lazyP, w->g_minOver, w->g_lazyH, w->g_hmax, w->g_hmat, w->g_hpend, w->peak_after, (u64*)w->wide);
-    hipLaunchKernelGGL(k_level1_init, dim3(1), dim3(LB), 0, q, (const u64*)w->g_tot, w->nch, w->base0, w->ctl);
+    hipLaunchKernelGGL(k_level1_init, dim3(1), dim3(WG), 0, q, (const u64*)w->g_tot, w->nch, w->base0, w->ctl);
     hipLaunchKernelGGL(k_ot_full, dim3(K / G10_BLOCK + 1), dim3(G10_BLOCK), 0, q, w->otc, (const u64*)w->base0, K, w->nch, w->shift_ch);
     G10_HIP(hipGetLastError());
     x.lead = i;

@@ -13,14 +13,15 @@ namespace g10 {
 enum { A_OT = 0, A_FO = 1, A_FI = 3, N_ARR = 5, PX = 8 };
 enum { J_P = 0, J_FO0 = 2, J_FO1 = 3, J_FI0 = 4, J_FI1 = 5, J_HQ = 6, J_CLIP = 7 };   // kinds of chunk jobs
 
-constexpr u32 LB = 512;                // threads of the loop workgroup (at least NCH_MAX)
-constexpr u32 LW = LB / G10_WAVE;      // its wavefronts
+constexpr u32 WG = 512;                // threads of the kernels of one workgroup around the loop (at least NCH_MAX; the loop's own: loop_threads)
+constexpr u32 WG_WAVES = WG / G10_WAVE;
 constexpr u32 UNIT = 256;              // candidates scored by four wavefronts at a time
 constexpr u32 NCH_MAX = 512;           // chunks (level-1 arrays live in LDS)
 constexpr u32 NT_MAX = 8192;           // tiles  (their bounds live in LDS)
 constexpr size_t LDS_MAX = 160 * 1024; // LDS of a compute unit (both limits together are over it: loop_tile_shift)
 constexpr u32 GUESS_SHIFT = 7;                 // first threshold of a pass: last benefit * (1 - 2^-shift), to begin with
 constexpr u32 GUESS_SHIFT_MAX = 24;            // the keys resolve no finer steps
+static_assert(WG >= NCH_MAX, "a thread per chunk");
 constexpr u64 NONE64 = ~0ull;
 constexpr u32 NONE32 = 0xffffffffu;
 

@@ -39,7 +39,7 @@ struct PfShared {
   u64 n_moved, slots;
 };
 
-__global__ __launch_bounds__(LB) void k_eager(const g10_migration* __restrict__ rec, const uint2* __restrict__ rec_ab,
+__global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ rec, const uint2* __restrict__ rec_ab,
                                              const u32* __restrict__ order, u32 n, u64* __restrict__ E, u32 K, u32 nch,
                                              u32 spt, u32 shift_ch, u64 cap, u32* __restrict__ gained,
                                              u32* __restrict__ last, u64* __restrict__ stats) {
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(LB) void k_eager(const g10_migration* __restrict__ 
   PfShared* S = (PfShared*)(ladd + nch);
   const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, CH = 1u << shift_ch;
 
-  for (u32 c = wave; c < nch; c += LW) {           // chunk maxima
+  for (u32 c = wave; c < nch; c += WG_WAVES) {           // chunk maxima
     u64 m = 0;
     for (u32 st = 0; st < spt; ++st) {
       const u32 j0 = c * CH + st * 256u + lane * 4u;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(LB) void k_eager(const g10_migration* __restrict__ 
   __syncthreads();
   // the lazy adds into the slots; the peak
   u64 m = 0;
-  for (u32 j = tid; j < K; j += LB) { const u64 x = E[j] + ladd[j >> shift_ch]; E[j] = x; m = x > m ? x : m; }
+  for (u32 j = tid; j < K; j += WG) { const u64 x = E[j] + ladd[j >> shift_ch]; E[j] = x; m = x > m ? x : m; }
   m = wave_max(m);
   if (lane == 0) atomicMax((unsigned long long*)&stats[2], (unsigned long long)m);
   if (tid == 0) { stats[0] = S->n_moved; stats[1] = S->slots; }
@@ -222,7 +222,7 @@ int prefetch_run(g10_plan_s* h, g10_prefetch_result* out) {
     G10_TRY(radix_sort_u64_pairs(&keys, &alt, &ord, &oalt, n, bits_for(2 * w->T), w->hist, s));
   }
   const size_t lds = ((size_t)2 * w->nch * 8 + sizeof(PfShared) + 15) & ~(size_t)15;
-  hipLaunchKernelGGL(k_eager, dim3(1), dim3(LB), lds, s, (const g10_migration*)w->records, (const uint2*)w->rec_ab,
+  hipLaunchKernelGGL(k_eager, dim3(1), dim3(WG), lds, s, (const g10_migration*)w->records, (const uint2*)w->rec_ab,
                      (const u32*)ord, n, w->pf_pressure, K, w->nch, w->spt, w->shift_ch, w->plan_cap, w->pf_gained, w->pf_last,
                      w->pf_stats);
   G10_HIP(hipGetLastError());
