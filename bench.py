@@ -32,9 +32,9 @@ BYTES_PER_CAND_MOVED = 20      # what k_score_full itself streams per candidate:
 # HBM traffic of the loop kernel on config 5 from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, scaled by what the
 # same counters read for a 256 MiB copy): profiles/loop_stress_hbm_counters.md has the commands and the sums.  The
 # figures hold for the kernel they were taken on: reported only while the kernel's sources hash to what they did then.
-LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "38b1dbca9eba4f72e3f5e48f8959a60a8fde6176aa4ead7a46c9ed6ded847d10",
-                           "g10_plan_defs.h": "d68baae63e053783d89434114145ea3989696c14d64dd491d90e3b0769c905e5"},
-                "workload": "config 5", "fetch_bytes_per_plan": 82.0e6, "write_bytes_per_plan": 50.0e6, "launches_per_plan": 11.6}
+LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "c61cbc7aa10f7e234310373f3c0d443c85f9a5aff4cb2ba31f48627cbc6f8e67",
+                           "g10_plan_defs.h": "7ae4493afcabab906405a18050b7f52b19b60c6cd20aa6078fbd3bdfb8aca46c"},
+                "workload": "config 5", "fetch_bytes_per_plan": 83.0e6, "write_bytes_per_plan": 49.4e6, "launches_per_plan": 11.6}
 
 
 def loop_traffic_per_launch(config):

@@ -190,7 +190,8 @@ typedef struct g10_plan_s g10_plan_t;   /* opaque: device copy of the analysis +
  * kernel slot) with its peak.  Enqueues on `hip_stream` (a hipStream_t, NULL =
  * default stream) and synchronises it before returning.
  * Errors: G10_EINVAL / G10_EOVERFLOW as listed above (array contents are
- * validated on the device before any other work), G10_ENOMEM, G10_EDEVICE. */
+ * validated on the device, beside the analysis; a trace that does not stand
+ * gives no handle), G10_ENOMEM, G10_EDEVICE. */
 int g10_vitality(const g10_trace *trace, void *hip_stream, g10_plan_t **out_handle);
 
 /* Counts and peak of a finished analysis (Section 4.2: the uses, the inactive periods that are
