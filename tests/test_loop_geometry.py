@@ -1,16 +1,19 @@
 """The sizes a plan's greedy loop is laid out for: whatever the trace and the limits of g10_plan_limits, the tiles and
 chunks together fit the LDS of a compute unit (the host functions of the library, no GPU)."""
 import ctypes
+import os
 
 import pytest
 
-from paper_2310_09443_amd import binding
+from paper_2310_09443_amd import binding, build
 
 LDS, UNIT, NT_MAX, NCH_MAX = 160 * 1024, 256, 8192, 512
 
 
 @pytest.fixture(scope="module")
 def rules():
+    if not os.path.exists(build.LIB):
+        build.build()
     lib = binding.load()
     shift, need = lib._Z15loop_tile_shiftmjj, lib._Z14loop_lds_bytesjj         # loop_tile_shift, loop_lds_bytes (C++ names)
     shift.argtypes, shift.restype = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32], ctypes.c_uint32

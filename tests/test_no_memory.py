@@ -4,6 +4,8 @@ import os
 import subprocess
 import sys
 
+from paper_2310_09443_amd import build
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 CHILD = r"""
@@ -50,6 +52,8 @@ print("ok")
 
 
 def test_every_allocation_refused_in_turn(tmp_path):
+    if not os.path.exists(build.LIB):
+        build.build()
     shim = str(tmp_path / "no_device.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", os.path.join(ROOT, "tests", "native", "no_device.cpp"), "-o", shim], check=True)
     r = subprocess.run([sys.executable, "-c", CHILD, shim], cwd=ROOT, capture_output=True, text=True, timeout=300)
