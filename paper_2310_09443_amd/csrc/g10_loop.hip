@@ -9,13 +9,11 @@ using namespace g10;
 
 namespace {
 
-// Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than eight
-// wavefronts take at once, so twelve (loops with eight / twelve: ResNet 5.90 / 5.57 ms, ragged stress with
-// cross-iteration periods 5.76 / 5.48, stress 26.0 / 25.2, decoder 4.12 / 4.05, encoder 2.02 / 2.05).  Twelve
-// leave 168 registers each, and the benefit key in the band reading spills ten (80 bytes a lane: the list entry
-// of the picking wavefront, the record pointers); sixteen leave 128 and spill more: 5.92, 5.66, 25.5, 4.43,
-// 2.21.  The ratio key in the band reading commits one migration a pass, four jobs: eight (its passes with the
-// scoring kernel take 5 % longer with twelve).
+// Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than seven wavefronts
+// take at once beside the one that picks, so twelve (loops with eight / twelve: ResNet 2.85 / 2.65 ms, ragged stress
+// 4.7 / 4.25, stress 23.6 / 21.3, decoder 3.2 / 3.1, encoder 1.20 / 1.16).  Twelve leave 168 registers each, and the
+// benefit key in the band reading spills four; sixteen leave 128.  The ratio key in the band reading commits one migration
+// a pass, four jobs: eight (its passes with the scoring kernel take 5 % longer with twelve).
 constexpr u32 LOOP_MIN = 512, LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // ... least and most, and the most wavefronts
 constexpr u32 loop_threads(bool ratio, bool clip) { return ratio && !clip ? LOOP_MIN : LOOP_MAX; }
 static_assert(LOOP_MIN >= NCH_MAX && LOOP_MIN % UNIT == 0 && LOOP_MAX % UNIT == 0, "a thread per chunk; units are scored by four whole wavefronts");
@@ -27,11 +25,8 @@ struct alignas(16) Winner {   // what a commit needs of the winning candidate
   u64 tau_o, tau_i;           // eviction and prefetch time to the destination
   u32 cand, tensor, pos, dest, L1, R, a, b;
   u32 exact;                  // clipped-area benefit only: the value was computed in this pass (else it is a bound)
-  u32 kU;                     // key of the larger of the two destinations' benefits: bounds every later benefit
-  u32 kr;                     // kU if the policy sends the candidate to flash while host could take it too (a flash
-                              // reservation in its transfer windows would move it to host, where its benefit may be
-                              // larger), else 0
   u32 slot;                   // its entry in the list of the pass (NONE32: it has none)
+  u32 pad[2];
 };
 
 // Ranking by benefit / cost keeps a bound per candidate that holds whichever destination the
@@ -75,22 +70,47 @@ static_assert(sizeof(WideCtx) % 16 == 0 && sizeof(WideKey) % 16 == 0 && sizeof(W
 constexpr u32 MAXM = 16;      // migrations committed in one ranking pass at most (a multiple of 8, at most 16: the job words hold two sets of 16)
 static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid out for 8 or 16");
 
-constexpr u32 MC_GUESS_SHIFT_MIN = 3;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
-constexpr u32 LIST_MAX = 64;  // candidates of a pass that are looked at for the second and later migrations
+constexpr u32 MC_GUESS_SHIFT_MIN = 2;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
+// The list of the pass: the candidates whose bound exceeds every bound not looked at one by one.  An entry is LIST_VECS
+// arrays of 16 bytes - period and windows as in Cands (a committed one has no window left); {index, tensor, position};
+// over-capacity times (NONE64: the destination cannot be used); free channel times at the ends of the transfer windows, out
+// and in of either destination (Score), as doubles - and the keys of its benefits at either destination.  As many entries as
+// fit the LDS beside chunks and tiles: 64 always do, 256 nearly always.  The picking wavefront holds 64, the best by bound.
+// (Ranking passes of a plan with 64 in all / with 256 and the choice: ResNet 240 / 25, decoder 186 / 70, stress 500 / 160.)
+constexpr u32 LIST_MIN = 64, LIST_MAX = 256, LIST_VECS = 8, LIST_ENTRY = LIST_VECS * 16 + 8;
+static_assert(LIST_MIN == G10_WAVE && LIST_MAX % G10_WAVE == 0, "an entry a lane; strips of whole wavefronts");
+enum { LE_A = 0, LE_B = 1, LE_I = 2, LE_OT = 3, LE_O0 = 4, LE_I0 = 5, LE_O1 = 6, LE_I1 = 7 };
 // How far under the round's threshold a scored candidate's bound may lie to go on the list, in key steps (2^24 are a
 // factor of two); below zero: how far above it must lie.  Entries under the bound of the tiles left out cannot be picked,
-// so that is the lowest; within that the margin follows the list towards 16 to 36 entries, in small steps near there.
-// Which entries an overflowing list takes is left to chance, and the pass is then ranked by an arg-max over all threads
-// and commits one migration: a margin that doubled into an overflow every few passes gave stress plans between 400 and
+// so that is the lowest; within that the margin follows the list towards a quarter to nine sixteenths of its length, in small steps near there.
+// Which entries an overflowing list takes is left to chance, and the pass is then mostly ranked by an arg-max over all
+// threads and begins with a round of one migration: with a list of 64, a margin that doubled into an overflow every few passes gave stress plans between 400 and
 // 1100 ranking passes, and one that could not go above the threshold left six passes in ten overflowing on the model
 // traces (many candidates of a repeated layer lie within the eighth under the last benefit).
 constexpr int PUB_START = 1 << 22, PUB_MIN = -(1 << 23), PUB_MAX = 1 << 30;
 
+enum { NX_RESCORE = 0, NX_PICKED = 1 };   // how a further round of a pass begins: the list scored again; its migrations picked already
+
+struct Floor {                // bound of the list's entries that the picking wavefront does not hold (see choose)
+  u64 hi, lo;
+  u32 key, cand, full, pad;
+};
+
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
   Winner wave_win[LW_MAX];    // best of every wavefront
-  Winner list[LIST_MAX];      // the candidates whose bound exceeds every bound not looked at one by one
-  uint4 listA[LIST_MAX], listB[LIST_MAX];   // ... their periods and windows as in Cands; a committed one has no window left
+  double bw[8];               // bandwidths out 0, 1, in 0, 1, and their reciprocals
+  // What the picking wavefront leaves: the migrations of the round (entry of the list, destination << 16; free times
+  // before the eviction window's start and the prefetch window's end as the picks before left them), and its state
+  u32 pick[MAXM];
+  double pick_o[MAXM], pick_i[MAXM];
+  u32 chain[2][4];            // per round (even, odd) and channel (out 0, 1, in 0, 1): some windows of the round's picks and entries meet
+  double all[4];              // free time of each channel behind the picks
+  Floor left;
+  u32 sel[G10_WAVE], nsel;    // the entries of the list it holds
+  u32 hosts;                  // the round's migrations to host
+  u32 pick_max, next;         // migrations picked in a round at most; NX_*
+  unsigned char spare[144];
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
@@ -142,6 +162,9 @@ __device__ __forceinline__ u64 read_lane64(u64 v, u32 l) {
   return ((u64)hi << 32) | lo;
 }
 
+__device__ __forceinline__ u64 umin64(u64 a, u64 b) { return a < b ? a : b; }
+__device__ __forceinline__ double read_lanef(double v, u32 l) { return __longlong_as_double((long long)read_lane64((u64)__double_as_longlong(v), l)); }
+
 // The same for benefit / cost.  The approximate keys only narrow the field: a lane stays if
 // its upper key reaches the largest lower key.  The lanes that stay are settled exactly: take
 // the first, keep the lanes that beat it (fractions compared by cross multiplication, equal
@@ -180,15 +203,63 @@ __device__ __forceinline__ void scan_strips(const u64 (&v)[4], u64 (&run)[4], u6
   carry = at;
 }
 
+// Times in doubles, which hold whole numbers up to 2^53 exactly: one instruction an addition, a minimum or a clamp
+// where 64-bit integers take two to five.  Used where PICK_EXACT bounds every time and size.
+// Channel time a migration takes between its window's start (eviction: the earliest free time is taken first) or end
+// (prefetch: the latest first) and a point `away` of free time from there.  (Negative: the point lies on the other side.)
+__device__ __forceinline__ double takenf(double away, double tau) { return fmin(fmax(away, 0.0), tau); }
+// The free time f before a point of the doubled timeline once a migration took `tau` from its window: less by what it
+// takes before that point, in the places that the window has around the doubled timeline, `all` of the channel's free
+// time apart.  ref: the free time before the window's start (out), or before its end.  (Where neither the points nor the
+// window lie in the second iteration the other places cancel.)
+__device__ __forceinline__ double after_takingf(double f, double all, double ref, double tau, bool out, bool wrap) {
+  double r = out ? f - takenf(f - ref, tau) : f + takenf(ref - f, tau) - tau;
+  if (wrap) {
+    if (out) r = r - takenf(f - all - ref, tau) - (takenf(f + all - ref, tau) - takenf(all - ref, tau));
+    else r = r + (takenf(ref - f + all, tau) - tau) + (takenf(ref - f - all, tau) - takenf(ref - all, tau));
+  }
+  return r;
+}
+constexpr u64 PICK_EXACT = 1ull << 48;   // bound of the iteration's free time and of 1000 x the largest tensor (sums of a few stay exact)
+__device__ __forceinline__ double exactf(u64 x) { return __fma_rn((double)(u32)(x >> 32), 4294967296.0, (double)(u32)x); }   // x < 2^53
+// ceil(x / bw) for whole x < 2^50: the quotient by the reciprocal is off by one at most, the remainder exact
+__device__ __forceinline__ double ceil_divf(double x, double bw, double inv) {
+  double q = floor(x * inv), r = __fma_rn(-q, bw, x);
+  if (r < 0.0) { q -= 1.0; r += bw; }
+  if (r >= bw) { q += 1.0; r -= bw; }
+  return r > 0.0 ? q + 1.0 : q;
+}
+
 // Do the doubled slot ranges [x1, y1] and [x2, y2] (each shorter than K) share a kernel slot?  (K < 2^30)
 __device__ __forceinline__ bool cyc_overlap32(u32 x1, u32 y1, u32 x2, u32 y2, u32 K) {
   return (x1 <= y2 && x2 <= y1) || (x1 + K <= y2 && x2 <= y1 + K) || (x1 <= y2 + K && x2 + K <= y1);
+}
+
+// The thread's number, anew: what is made from it here cannot be moved out of the loops around.  (The compiler keeps the
+// LDS addresses of every array and lane in registers across the whole kernel otherwise, and spills them: 30 registers.)
+__device__ __forceinline__ u32 thread_here() {
+  u32 t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
 }
 
 template <bool RATIO>
 __device__ __forceinline__ u32 best_lane(u64 hi, u64 lo, u64 cost, u32 cand) {
   if (RATIO) return wave_best_lane_ratio(hi, lo, cost, cand);
   return wave_best_lane(hi, lo, cand);
+}
+
+// LDS of the loop workgroup up to the list of the pass, and the entries of that list
+__host__ __device__ __forceinline__ size_t lds_before_list(u32 nch, u32 nt) {
+  const size_t ns = (nt + 63) / 64;
+  size_t b = sizeof(Shared);
+  b += ((size_t)N_ARR * (nch + 1) + (size_t)N_ARR * nch + (size_t)4 * nch + ns + (size_t)6 * nch + 8) * 8;      // (six jobs a chunk at most)
+  b += ((size_t)nt + ns + 2 * (size_t)nch) * 4 + (size_t)nt * 4;
+  return (b + 15) & ~(size_t)15;
+}
+__host__ __device__ __forceinline__ u32 list_cap(u32 nch, u32 nt) {
+  const size_t b = lds_before_list(nch, nt), room = b < LDS_MAX ? (LDS_MAX - b) / LIST_ENTRY : 0;
+  return room >= LIST_MAX ? LIST_MAX : room < LIST_MIN ? LIST_MIN : (u32)room / G10_WAVE * G10_WAVE;
 }
 
 template <bool RATIO, bool CLIP>
@@ -212,14 +283,22 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   u64* lazyH = minOver + nch;
   u64* hmax = lazyH + nch;
   u64* smark = hmax + nch;                              // [ns] tiles of a group of 64 scored in this pass
-  u64* scr = smark + ns;                                // [4 * LW_MAX]
-  u64* jobs = scr + 4 * LW_MAX;                         // [6 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
+  u64* scr = (u64*)S->pick_o;                           // [3 * LW] (before the passes, over pick_o, pick_i and chain)
+  static_assert(sizeof(S->pick_o) + sizeof(S->pick_i) + sizeof(S->chain) >= 3 * LW_MAX * 8, "the scan's scratch");
+  u64* jobs = smark + ns;                               // [6 * nch + 8]  chunk | kind << 16 | a set of the pass's migrations << 24 | another << 40
   u32* keys = (u32*)(jobs + 6 * nch + 8);               // [nt]  bound of every tile
   u32* skeys = keys + nt;                               // [ns]  largest bound of every group of 64 tiles
   u32* hmat = skeys + ns;                               // [nch] host occupancy: migrations (by index) already added to the chunk's slots
-  u32* hpend = hmat + nch;                              // [nch] ... and whether a later one that cuts the chunk is still missing
+  u32* hpend = hmat + nch;                              // [nch] ... and whether a later one that cuts the chunk is still missing (bit 0);
+                                                        // a slot dropped under the capacity since the list was last scored (bit 1)
   unsigned short* tlist = (unsigned short*)(hpend + nch);  // [nt]  the hot list
   unsigned short* alist = tlist + nt;                            // [nt]  tiles scored in the current round
+  const u32 lcap = MC ? list_cap(nch, nt) : 0u;         // entries of the list of the pass
+  uint4* const list = (uint4*)(smem + lds_before_list(nch, nt));         // [LIST_VECS][lcap]
+  u32* const lkey = (u32*)(list + (size_t)LIST_VECS * lcap);             // [2][lcap] keys: the larger one bounds the entry
+  auto list_at = [&](u32 field, u32 i) -> uint4& { return list[field * lcap + i]; };
+  auto list_ot = [&](u32 i, u32 d) -> u64& { return reinterpret_cast<u64*>(&list[LE_OT * lcap + i])[d]; };
+  auto list_f = [&](u32 field, u32 i) -> double2& { return reinterpret_cast<double2&>(list[field * lcap + i]); };
 
   const u32 tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
   Ctl* ctl = a.ctl;
@@ -255,7 +334,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->thr_key = ctl->thr_key; S->status = ctl->status; S->done = ctl->done;
     S->gshift = ctl->gshift ? ctl->gshift : GUESS_SHIFT;
     S->pub = ctl->pub ? ctl->pub : PUB_START;      // (0: not set yet; a margin of 0 starts over)
-    S->nl = 0; S->restL = NONE32; S->stale_hot = 0;
+    S->nl = 0; S->restL = NONE32; S->stale_hot = 0; S->pick_max = MAXM;
     S->stop = 0; S->t_start = wall_clock64();
     S->mem[0].hi = 0; S->mem[0].lo = 0;
   }
@@ -302,6 +381,17 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   }
 
 
+  // Are times and sizes small enough for doubles (PICK_EXACT)?  May the further migrations of a pass be picked (K: ranges
+  // of the doubled timeline are compared in 32 bits)?
+  bool exact = ctl->smax < PICK_EXACT / 1000 && ((bwo0 | bwo1 | bwi0 | bwi1) < PICK_EXACT);
+  for (u32 q = A_FO; q < N_ARR; ++q) exact = exact && base[(u64)q * nb1 + nch] < PICK_EXACT;
+  exact = uniform((u32)exact) != 0u;
+  const bool picks = MC && K < (1u << 30) && exact;
+  if (MC && tid < 4) {
+    const double bw = exactf(tid == 0 ? bwo0 : tid == 1 ? bwo1 : tid == 2 ? bwi0 : bwi1);
+    S->bw[tid] = bw; S->bw[4 + tid] = 1.0 / bw;
+  }
+
   // The hot list: every tile not scored in this pass whose bound reaches `thr`; restL bounds
   // the tiles left out.  Bounds only fall and only scored tiles change, so the list stays
   // complete for any later threshold above restL and is kept across passes.
@@ -341,6 +431,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // -> alist (marked, bound cleared: the scoring rebuilds it); filt bounds the others.
   // (`fresh`: the counters are cleared already)
   auto activate = [&](u32 thr, bool fresh) {
+    const u32 tid = thread_here(), lane = tid & 63u;
     if (!fresh) {
       if (tid == 0) { S->ntl = 0; S->filt = 0; }
       __syncthreads();
@@ -375,11 +466,11 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   u32 pass_units = 0;           // units of 256 candidates scored in the current pass (the same in every thread)
   // this thread's best candidate of the pass
   Winner mine;
-  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
+  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   u32 floor2 = 0;               // largest bound among the candidates this thread scored in the pass other than `mine`
 
   struct CandV { uint4 A, B; uint2 id; u32 p, t; };
-  auto load_cand = [&](u32 u) -> CandV {
+  auto load_cand = [&](u32 u, u32 tid) -> CandV {
     CandV c;
     c.t = uniform((u32)alist[u >> a.tshift]);
     c.p = (((c.t << a.tshift) + (u & ((1u << a.tshift) - 1u))) << 8) + (tid & 255u);
@@ -392,17 +483,18 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // unit, about one cache line per clock: lanes whose candidate is dead load
   // nothing, and struck destinations are written back so later passes skip them.
   auto score_list = [&](const u32 thr_pub) {
+    const u32 tid = thread_here(), lane = tid & 63u;
     const u32 nunits = uniform(S->ntl) << a.tshift;
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
     mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
     u32 u = uniform(tid >> 8);
     CandV cur;
-    if (u < nunits) cur = load_cand(u);
+    if (u < nunits) cur = load_cand(u, tid);
     while (u < nunits) {
       const u32 un = u + LB / UNIT;
       CandV nxt;
-      if (un < nunits) nxt = load_cand(un);
+      if (un < nunits) nxt = load_cand(un, tid);
       const uint4 A = cur.A, B = cur.B;
       const Score r = score_candidate(pv, mc, A, B);
       if (r.strike0) a.cd.A[cur.p] = make_uint4(A.x, A.y, 1u, 0u);
@@ -450,13 +542,14 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           off = (u32)__builtin_amdgcn_readlane((int)off, (int)leader);
           slot = off + (u32)__popcll(pm & ((1ull << lane) - 1ull));
         }
-        if (pub && slot < LIST_MAX) {
+        if (pub && slot < lcap) {
           listed = slot;
-          S->listA[slot] = A; S->listB[slot] = B;
-          Winner& e = S->list[slot];
-          e.hi = hi; e.lo = lo; e.cost = cost; e.cand = cur.id.x; e.tensor = cur.id.y; e.pos = cur.p; e.dest = d;
-          e.L1 = A.x; e.R = A.y; e.a = d ? B.x : A.z; e.b = d ? B.y : A.w; e.s = ((u64)B.w << 32) | B.z;
-          e.fo_base = rr.fo_L; e.fi_end = rr.fi_R; e.exact = 0; e.kU = kc; e.kr = (rr.ok0 && rr.ok1) ? kc : 0u; e.slot = slot;
+          list_at(LE_A, slot) = A; list_at(LE_B, slot) = B;
+          list_at(LE_I, slot) = make_uint4(cur.id.x, cur.id.y, cur.p, 0u);
+          list_ot(slot, 0) = rr.ok0 ? rr.ot0 : NONE64; list_ot(slot, 1) = rr.ok1 ? rr.ot1 : NONE64;
+          list_f(LE_O0, slot) = make_double2(exactf(rr.fL0), exactf(rr.fa0)); list_f(LE_I0, slot) = make_double2(exactf(rr.fb0), exactf(rr.fR0));
+          list_f(LE_O1, slot) = make_double2(exactf(rr.fL1), exactf(rr.fa1)); list_f(LE_I1, slot) = make_double2(exactf(rr.fb1), exactf(rr.fR1));
+          lkey[slot] = upkey(rr.h0, rr.l0); lkey[lcap + slot] = upkey(rr.h1, rr.l1);
         } else if (kc > floor2) floor2 = kc;
       }
       if ((hi | lo) != 0 && (RATIO ? better_ratio(hi, lo, cost, cur.id.x, mine.hi, mine.lo, mine.cost, mine.cand)
@@ -476,6 +569,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // them): tile by tile where they are few, else the groups with any mark (a round of 840 tiles in 70 groups
   // spent 17 us here tile by tile).
   auto group_bounds = [&](const u32 w) {
+    const u32 lane = thread_here() & 63u;
     const u32 ntl = uniform(S->ntl);
     const bool few = ntl <= 2 * (LW - 1);
     for (u32 i = w; i < (few ? ntl : ns); i += LW - 1) {
@@ -521,12 +615,13 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // cuts the chunk, B = those that cover it whole.  (Host occupancy has no such job: see J_HQ.) --
   // Jobs begin .. end - 1 of the list, about the migrations in `keep`: a job for each wavefront but
   // the last, then whoever is done takes the next one (the last wavefront comes late to a round's
-  // jobs, from writing its plan records); jnext counts from LW - 1.
+  // jobs, from the plan records and the next round's picks); jnext counts from LW - 1.
   // Slot s0 + 256 st + 64 i + lane belongs to lane `lane` (i = 0..3): every load and store of a job
   // covers 64 neighbouring slots.  A workgroup has one texture unit, about one cache line per clock,
   // and a job for every wavefront runs at once: with four neighbouring slots per lane and one 64-byte record
   // per slot a rewrite touched 64 lines per instruction, now 8 (see the tables of px).
-  auto run_jobs = [&](const u32 begin, const u32 end, const u32 keep) {
+  auto run_jobs = [&](const u32 begin, const u32 end, const u32 keep, const u32 odd) {
+    const u32 tid = thread_here(), lane = tid & 63u;
     ulonglong2* const px = reinterpret_cast<ulonglong2*>(tl.px);
     auto take = [&]() -> u32 {
       u32 x = 0;
@@ -538,7 +633,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       const u64 jw = uniform(jobs[jb]);
       const u32 after = take();                            // (known by the time this job is done)
       const u32 type = (u32)(jw >> 16) & 0xffu, c = (u32)jw & 0xffffu, ma_ = (u32)(jw >> 24) & keep, mb_ = (u32)(jw >> 40) & keep;
-      const u32 s0 = c * CH, s1 = (s0 + CH - 1 < K - 1) ? s0 + CH - 1 : K - 1;
+      const u32 s0 = c * CH;
       if (type >= J_FO0 && type <= J_FI1) {
         if (ma_) {
         // channel time of the transfer windows of this destination that meet the chunk is taken
@@ -553,50 +648,105 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         const u32 mask = ma_;                            // the migrations of this destination whose window meets the chunk
         // (sums of free time inside the chunk stay under its old total: usually 32 bits hold them)
         const bool narrow = uniform((u32)(tot[(u64)arr * nch + c] >> 32)) == 0u;
-        u32 first = NONE32;
-        u64 carry = 0;
+        // Where windows of the round meet (chain), a migration's free time before its window (fo_base, fi_end) is the one
+        // that the earlier ones of the channel left, and so is the free time before a slot here - before the chunk (cb),
+        // inside it (loc) and all of the channel's (call).  Migrations behind the last one that meets the chunk change
+        // nothing here.
+        const bool linked = MC && uniform(S->chain[odd][type - J_FO0]) != 0u;
+        const u32 hosts = MC ? uniform(S->hosts) : 0u;
+        const u32 all_of = linked ? (d ? hosts : ~hosts) & ((2u << (31u - (u32)__builtin_clz(mask))) - 1u) : mask;
+        u64* const frc = fr + s0;
+        ulonglong2* const tabc = tab + s0;
+        u64 carry = 0;                                   // the chunk's new total
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane;
-          u64 f[4], old[4];
-          bool took[4];
+          const u32 o = st * 256u + lane, jn = K - s0;   // (slots of the timeline from the chunk's first on)
+          u64 fu[4], old[4], now[4], run[4];
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i * 64u;
-            f[i] = j < K ? fr[j] : 0ull;
-            old[i] = j < K ? tab[j].x : 0ull;            // free time of the chunk before the slot
-            took[i] = false;
+            const u32 j = o + i * 64u;
+            fu[i] = j < jn ? frc[j] : 0ull;
+            old[i] = j < jn ? tabc[j].x : 0ull;          // free time of the chunk before the slot
           }
-          for (u32 pb = mask; pb; pb &= pb - 1) {
-            const Winner& W = S->mem[__builtin_ctz(pb)];
-            const u32 x = uniform(out ? W.L1 : W.b + 1), y = uniform(out ? W.a - 1 : W.R - 1);
-            const u64 tau = out ? W.tau_o : W.tau_i, ref = out ? W.fo_base : W.fi_end;
-            if (st == 0) {
-              const u32 fc = first_covered(s0, s1, K, x, y);
-              first = fc < first ? fc : first;
-            }
+          if (exact) {
+            // A migration takes what lies between its window's end point `ref` and tau of free time from there - ahead
+            // of it for an eviction (the earliest free time first), behind it for a prefetch (the latest): so from
+            // a slot the difference of the two clamped distances of its ends, 0 outside the window, and from the
+            // free time before a slot what it takes between the chunk's start and the slot.  (So no sum over the
+            // slots is made anew.)
+            double f[4], loc[4], res[4], cb = exactf(bc), call = exactf(ball);
+            const double sg = out ? 1.0 : -1.0;
+            double end = exactf(tot[(u64)arr * nch + c]), end_res;     // the same for the chunk's end
+            if (narrow) {
 #pragma unroll
-            for (u32 i = 0; i < 4; ++i) {
-              const u32 j = j0 + i * 64u;
-              const u32 jj = j < K ? in_doubled(j, K, x, y) : NONE32;
-              if (jj != NONE32) {
-                const u64 before_slot = (jj >= K ? ball : 0ull) + bc + old[i];  // free time before slot jj
-                // eviction: earliest free time of the window first; prefetch: latest free time first
-                const u64 gone = out ? before_slot - ref : ref - (before_slot + f[i]);
-                const u64 used = gone < tau ? gone : tau;
-                const u64 take = f[i] < tau - used ? f[i] : tau - used;
-                f[i] -= take;
-                took[i] = take != 0;
+              for (u32 i = 0; i < 4; ++i) { f[i] = (double)(u32)fu[i]; loc[i] = (double)(u32)old[i]; res[i] = loc[i]; }
+            } else {
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) { f[i] = exactf(fu[i]); loc[i] = exactf(old[i]); res[i] = loc[i]; }
+            }
+            end_res = end;
+            for (u32 pb = all_of; pb; pb &= pb - 1) {
+              const u32 mi = (u32)__builtin_ctz(pb);
+              const Winner& W = S->mem[mi];
+              const double ref = (double)(long long)(out ? W.fo_base : W.fi_end), tau = exactf(out ? W.tau_o : W.tau_i);
+              const u32 x = uniform(out ? W.L1 : W.b + 1), y = uniform(out ? W.a - 1 : W.R - 1);
+              if ((mask >> mi) & 1u) {
+                auto place = [&](const double r) {       // the window's first or second place on the doubled timeline, seen from the chunk's start
+                  const double p = -sg * r, gc = takenf(p, tau);
+#pragma unroll
+                  for (u32 i = 0; i < 4; ++i) {
+                    const double p0 = __fma_rn(loc[i], sg, p), g0 = takenf(p0, tau), g1 = takenf(__fma_rn(f[i], sg, p0), tau);
+                    f[i] = __fma_rn(-sg, g1 - g0, f[i]);
+                    res[i] = __fma_rn(-sg, g0 - gc, res[i]);
+                  }
+                  end_res = __fma_rn(-sg, takenf(__fma_rn(end, sg, p), tau) - gc, end_res);
+                };
+                if (y < K) place(ref - cb);
+                else if (x >= K) place(ref - call - cb);
+                else { place(ref - cb); place(ref - call - cb); }     // (no slot lies in both places)
+                if (linked) {
+#pragma unroll
+                  for (u32 i = 0; i < 4; ++i) loc[i] = res[i];
+                  end = end_res;
+                }
+              }
+              if (linked) { cb = after_takingf(cb, call, ref, tau, out, y >= K); call -= tau; }
+            }
+            if (narrow) {
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) { now[i] = (u32)f[i]; run[i] = (u32)res[i]; }
+            } else {
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) { now[i] = (u64)f[i]; run[i] = (u64)res[i]; }
+            }
+            carry = (u64)end_res;
+          } else {
+            // the same in whole numbers, for times over PICK_EXACT: one migration a pass
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) now[i] = fu[i];
+            for (u32 pb = mask; pb; pb &= pb - 1) {
+              const Winner& W = S->mem[__builtin_ctz(pb)];
+              const u32 x = uniform(out ? W.L1 : W.b + 1), y = uniform(out ? W.a - 1 : W.R - 1);
+              const u64 tau = out ? W.tau_o : W.tau_i, ref = out ? W.fo_base : W.fi_end;
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) {
+                const u32 j = s0 + o + i * 64u;
+                const u32 jj = j < K ? in_doubled(j, K, x, y) : NONE32;
+                if (jj != NONE32) {
+                  const u64 before_slot = (jj >= K ? ball : 0ull) + bc + old[i];  // free time before slot jj
+                  // eviction: earliest free time of the window first; prefetch: latest free time first
+                  const u64 gone = out ? before_slot - ref : ref - (before_slot + now[i]);
+                  const u64 used = gone < tau ? gone : tau;
+                  now[i] -= now[i] < tau - used ? now[i] : tau - used;
+                }
               }
             }
+            scan_strips<u64>(now, run, carry);
           }
-          u64 run[4];
-          if (narrow) scan_strips<u32>(f, run, carry);
-          else scan_strips<u64>(f, run, carry);
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i * 64u;
-            if (took[i]) fr[j] = f[i];
-            if (j < K && j > first) tab[j].x = run[i];
+            const u32 j = o + i * 64u;
+            if (now[i] != fu[i]) frc[j] = now[i];        // (slots beyond the timeline hold 0)
+            if (j < jn && run[i] != old[i]) tabc[j].x = run[i];
           }
         }
         if (lane == 0) tot[(u64)arr * nch + c] = carry;
@@ -612,14 +762,16 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         u64 mn = NONE64, carry = 0;
         u32 first = NONE32;                              // first slot that dropped under the capacity
         const bool narrow = uniform((u32)(tot[(u64)A_OT * nch + c] >> 32)) == 0u;   // (the over-capacity time only falls)
+        u64* const Pc = tl.P + s0;
+        const u64* const durc = tl.dur + s0;
         for (u32 st = 0; st < tl.spt; ++st) {
-          const u32 j0 = s0 + st * 256u + lane;
+          const u32 j0 = s0 + st * 256u + lane, o = st * 256u + lane, jn = K - s0;
           u64 p[4], v[4], sub[4];
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i * 64u;
-            p[i] = j < K ? tl.P[j] : 0ull;
-            v[i] = j < K ? tl.dur[j] : 0ull;
+            const u32 j = o + i * 64u;
+            p[i] = j < jn ? Pc[j] : 0ull;
+            v[i] = j < jn ? durc[j] : 0ull;
             sub[i] = 0;
           }
           if (st == 0) for (u32 pb = mb_; pb; pb &= pb - 1) lz_full += S->mem[__builtin_ctz(pb)].s;
@@ -628,11 +780,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             const Winner& W = S->mem[__builtin_ctz(pb)];
             const u32 x = uniform(W.a), y = uniform(W.b);
             const u64 s = W.s;
+            // its slots: [x, y], both less K where it lies in the second iteration, or all but the (y - K, x) between
+            const bool both = x < K && y >= K;
+            const u32 lo = both ? y - K + 1 : x >= K ? x - K : x, n = both ? x - lo : y - x + 1;
 #pragma unroll
-            for (u32 i = 0; i < 4; ++i) {
-              const u32 j = j0 + i * 64u;
-              if (j < K && in_doubled(j, K, x, y) != NONE32) sub[i] += s;
-            }
+            for (u32 i = 0; i < 4; ++i)
+              if ((j0 + i * 64u - lo < n) != both) sub[i] += s;        // (beyond the timeline: not stored)
           }
           u32 myfirst = NONE32;
 #pragma unroll
@@ -641,7 +794,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             bool over = false;
             if (j < K) {
               const u64 before = p[i] - lz0, act = p[i] - sub[i] - lz;     // pressure before and after this pass
-              if (sub[i]) tl.P[j] = p[i] - sub[i];
+              if (sub[i]) Pc[o + i * 64u] = p[i] - sub[i];
               over = act > cap;
               if (over) mn = act < mn ? act : mn;
               else if (before > cap && myfirst == NONE32) myfirst = j;
@@ -672,7 +825,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         }
         if (lane == 0) {
           minOver[c] = mn; lazyP[c] = lz0 + lz_full;
-          if (first != NONE32) { tot[(u64)A_OT * nch + c] = carry; S->ot_changed = 1; }
+          if (first != NONE32) { tot[(u64)A_OT * nch + c] = carry; S->ot_changed = 1; if (MC) atomicOr(&hpend[c], 2u); }
         }
       } else if (type == J_CLIP) {
         // clipped area of the winner's absent window inside this chunk: per slot over the
@@ -712,7 +865,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         // that cut the chunk are added to its slots, after which the bound is exact again.
         const u32 L1 = S->mem[0].L1, R = S->mem[0].R;
         const u64 lz = lazyH[c];
-        const bool bring = hpend[c] != 0u;
+        const bool bring = (hpend[c] & 1u) != 0u;
         const u32 from = hmat[c], to = (u32)S->n_mig;
         u64 m_cov = 0, m_all = 0;
         for (u32 st = 0; st < tl.spt; ++st) {
@@ -754,7 +907,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         m_cov = wave_max(m_cov);
         if (bring) {
           m_all = wave_max(m_all);
-          if (lane == 0) { hmax[c] = m_all; hmat[c] = to; hpend[c] = 0u; }
+          if (lane == 0) { hmax[c] = m_all; hmat[c] = to; hpend[c] &= ~1u; }
         }
         if (lane == 0) atomicMax((unsigned long long*)&S->hq, (unsigned long long)m_cov);
       }
@@ -763,49 +916,229 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     if (tid == 0) S->jobs += end - begin;
   };
 
-  // The next best entries of the list of the pass, a list entry per lane of one wavefront: entry by
-  // entry in the order of their benefit, as far as it is certain that each wins Algorithm 1's next
-  // pass (see "more migrations of the same pass" below).  F bounds every candidate that is not on
-  // the list; `m` migrations of the round stand already (0, or 1: the one in mem[0], `picked` by
-  // its lane if it is on the list); at most `allowed` are made.  Picked entries go to mem[]; the
-  // number of migrations is returned.
-  auto pick = [&](const Winner& e, const bool have, bool picked, const u32 F, u32 m, const u32 allowed, u32& by_floor) -> u32 {
-    u32 kB = (have && !picked) ? upkey(e.hi, e.lo) : 0u;           // (0: cannot be picked)
-    const u32 eE0 = e.L1, eE1 = e.a - 1, eW0 = e.b + 1, eW1 = e.R - 1, ed = e.dest;
-    const u32 kr = ed == 0u ? e.kr : 0u;
-    u32 at = NONE32;                               // which migration this lane's entry becomes
-    bool ov = false;                               // a transfer window meets one of a picked migration on the same channel
-    auto meet = [&](u32 wd, u32 wL1, u32 wa, u32 wb, u32 wR) {
-      const bool hit = cyc_overlap32(eE0, eE1, wL1, wa - 1, K) || cyc_overlap32(eW0, eW1, wb + 1, wR - 1, K);
-      ov = ov || (hit && ed == wd && !picked);
-    };
-    if (m) { const Winner& W1 = S->mem[0]; meet(W1.dest, W1.L1, W1.a, W1.b, W1.R); }
-    by_floor = 0;
-    while (m < allowed) {
-      const u32 kmax = wave_max(kB);
-      if (kmax <= F) { by_floor = 1; break; }      // (also when nothing is left)
-      u64 mk = __ballot(kB == kmax);
-      if (mk & (mk - 1)) {                         // equal keys: high word, low word, lowest index
-        const bool in1 = kB == kmax;
-        const u64 hmx = wave_max(in1 ? e.hi : 0ull);
-        const bool in2 = in1 && e.hi == hmx;
-        const u64 lmx = wave_max(in2 ? e.lo : 0ull);
-        const bool in3 = in2 && e.lo == lmx;
-        const u32 cmin = wave_min(in3 ? e.cand : NONE32);
-        mk = __ballot(in3 && e.cand == cmin);
-      }
-      const u32 bl = (u32)__builtin_ctzll(mk);
-      const u64 ovm = __ballot(ov);
-      if ((ovm >> bl) & 1ull) break;               // its own windows are not what they were
-      if (ovm && wave_max(ov ? kr : 0u) >= kmax) break;   // a candidate at risk might rise above it
-      if (lane == bl) { kB = 0u; picked = true; ov = false; at = m; }
-      ++m;
-      if (m == allowed) break;
-      meet((u32)__builtin_amdgcn_readlane((int)ed, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.L1, (int)bl),
-           (u32)__builtin_amdgcn_readlane((int)e.a, (int)bl), (u32)__builtin_amdgcn_readlane((int)e.b, (int)bl),
-           (u32)__builtin_amdgcn_readlane((int)e.R, (int)bl));
+  // The next best entries of the list of the pass, a list entry per lane of one wavefront (entry: {period and windows},
+  // identity, over-capacity times, free channel times): entry by entry in the order of their benefit, as far as it is
+  // certain that each wins Algorithm 1's next pass (see "more migrations of the same pass" below).  F bounds every
+  // candidate that is not on the list; at most `allowed` migrations are made.  Picked entries go to mem[]; the number of
+  // migrations is returned.
+  struct Entry { uint4 A, B, I; u64 ot0, ot1; double2 O0, I0, O1, I1; u32 k0, k1; };
+  auto load_entry = [&](const u32 i) -> Entry {          // (NONE32: none)
+    Entry e;
+    const double2 z = make_double2(0.0, 0.0);
+    e.A = make_uint4(1u, 1u, 1u, 0u); e.B = make_uint4(1u, 0u, 0u, 0u); e.I = make_uint4(NONE32, 0u, 0u, 0u);
+    e.ot0 = NONE64; e.ot1 = NONE64; e.O0 = z; e.I0 = z; e.O1 = z; e.I1 = z; e.k0 = 0u; e.k1 = 0u;
+    if (i != NONE32) {
+      e.A = list_at(LE_A, i); e.B = list_at(LE_B, i); e.I = list_at(LE_I, i); e.ot0 = list_ot(i, 0); e.ot1 = list_ot(i, 1);
+      e.O0 = list_f(LE_O0, i); e.I0 = list_f(LE_I0, i); e.O1 = list_f(LE_O1, i); e.I1 = list_f(LE_I1, i);
+      e.k0 = lkey[i]; e.k1 = lkey[lcap + i];
     }
-    if (at != NONE32) S->mem[at] = e;
+    return e;
+  };
+  // The entries of the list scored again, against the timelines as the rounds so far left them: a thread per entry and
+  // destination, whole wavefronts per destination.
+  static_assert(2 * LIST_MAX <= LOOP_MAX, "a thread per entry and destination");
+  auto rescore_list = [&](const u32 n) {
+    const u32 tid = thread_here();
+    const u32 n64 = (n + 63u) & ~63u, d = uniform((u32)(tid >= n64 ? 1u : 0u)), i = tid - (d ? n64 : 0u);
+    if (tid < 2 * n64 && i < n) {
+      const uint4 A = list_at(LE_A, i), B = list_at(LE_B, i);
+      const u32 wa = d ? B.x : A.z, wb = d ? B.y : A.w;
+      u64 ot = NONE64;
+      u32 key = 0;
+      if (wa <= wb) {
+        const bool sL = A.x >= K, sR = A.y >= K, sa = wa >= K, sb = wb + 1 >= K;
+        const u32 jL = sL ? A.x - K : A.x, jR = sR ? A.y - K : A.y, ja = sa ? wa - K : wa, jb = sb ? wb + 1 - K : wb + 1;
+        const ulonglong2* const to = reinterpret_cast<const ulonglong2*>(tl.px) + (u64)(T_FO + d) * tl.Kp;
+        const ulonglong2* const ti = reinterpret_cast<const ulonglong2*>(tl.px) + (u64)(T_FI + d) * tl.Kp;
+        const ulonglong2 gL = to[jL], ga = to[ja], gb = ti[jb], gR = ti[jR];
+        const u64 *bO = base + (u64)(A_FO + d) * nb1, *bI = base + (u64)(A_FI + d) * nb1, *bT = base + (u64)A_OT * nb1;
+        const u64 allO = bO[nch], allI = bI[nch], allT = bT[nch], s = ((u64)B.w << 32) | B.z, x1000 = s * 1000ull;
+        const u32 cL = jL >> tl.shift_ch, cR = jR >> tl.shift_ch, ca = ja >> tl.shift_ch, cb = jb >> tl.shift_ch;
+        const u64 fL = (sL ? allO : 0ull) + bO[cL] + gL.x, fa = (sa ? allO : 0ull) + bO[ca] + ga.x;
+        const u64 fb = (sb ? allI : 0ull) + bI[cb] + gb.x, fR = (sR ? allI : 0ull) + bI[cR] + gR.x;
+        list_f(d ? LE_O1 : LE_O0, i) = make_double2(exactf(fL), exactf(fa));
+        list_f(d ? LE_I1 : LE_I0, i) = make_double2(exactf(fb), exactf(fR));
+        if (carries(fa - fL, d ? bwo1 : bwo0, x1000) && carries(fR - fb, d ? bwi1 : bwi0, x1000)) {
+          ot = ((sb ? allT : 0ull) + bT[cb] + gb.y) - ((sa ? allT : 0ull) + bT[ca] + ga.y);
+          key = upkey(__umul64hi(s, ot), s * ot);
+        }
+      }
+      list_ot(i, d) = ot;
+      lkey[d * lcap + i] = key;
+    }
+    for (u32 c = tid; c < nch; c += LB) hpend[c] &= 1u;
+    if (tid == 0) S->list_rescored += n;
+  };
+  // The entry this lane of the picking wavefront looks at (NONE32: none): all n entries, or the 64 with the best bounds,
+  // equal keys by the lowest index.  What is left out counts with `fl`: its largest key and, where an entry looked at has
+  // that key too, the best bound in full (value and index) among those left out with it.
+  auto choose = [&](const u32 n, const u32 F, Floor& fl) -> u32 {
+    fl.key = F; fl.full = 0u; fl.hi = 0; fl.lo = 0; fl.cand = 0; fl.pad = 0;
+    if (n <= G10_WAVE) {
+      if (lane == 0) S->nsel = n;
+      S->sel[lane] = lane;
+      return lane < n ? lane : NONE32;
+    }
+    constexpr u32 Q = LIST_MAX / G10_WAVE;
+    u32 k[Q], top = 0;
+#pragma unroll
+    for (u32 q = 0; q < Q; ++q) {
+      const u32 i = q * G10_WAVE + lane;
+      const u32 k0 = i < n ? lkey[i] : 0u, k1 = i < n ? lkey[lcap + i] : 0u;
+      k[q] = k0 > k1 ? k0 : k1;
+      top = k[q] > top ? k[q] : top;
+    }
+    top = wave_max(top);
+    if (top <= F) { if (lane == 0) S->nsel = 0; return NONE32; }
+    auto above = [&](u32 t) -> u32 { u32 c = 0;
+#pragma unroll
+      for (u32 q = 0; q < Q; ++q) c += (u32)__popcll(__ballot(k[q] > t));
+      return c; };
+    u32 t = F, x = 0u;                             // chosen: keys above t; of those at t the ones with an index below x
+    if (above(F) > G10_WAVE) {
+      u32 lo = F, hi = top;                        // above(lo) > 64 >= above(hi)
+      while (hi - lo > 1u) {
+        const u32 mid = lo + (hi - lo) / 2u;
+        const u32 c = above(mid);
+        if (c > G10_WAVE) lo = mid;
+        else { hi = mid; if (c >= G10_WAVE / 2) break; }             // (near enough)
+      }
+      t = hi;
+      fl.key = t;
+      const u32 room = hi - lo > 1u ? 0u : G10_WAVE - above(t);
+      if (room) {                                  // (more than that have key t: above(t - 1) > 64)
+        u32 id[Q];
+#pragma unroll
+        for (u32 q = 0; q < Q; ++q) id[q] = k[q] == t ? list_at(LE_I, q * G10_WAVE + lane).x : NONE32;
+        auto under = [&](u32 y) -> u32 { u32 c = 0;
+#pragma unroll
+          for (u32 q = 0; q < Q; ++q) c += (u32)__popcll(__ballot(k[q] == t && id[q] < y));
+          return c; };
+        u32 ylo = 0, yhi = NONE32;                 // under(ylo) <= room < under(yhi): indices are distinct
+        while (yhi - ylo > 1u) {
+          const u32 mid = ylo + (yhi - ylo) / 2u;
+          if (under(mid) > room) yhi = mid; else ylo = mid;
+        }
+        x = ylo;
+        // the best of those left out with key t
+        u64 bh = 0, bl = 0;
+        u32 bc = NONE32;
+#pragma unroll
+        for (u32 q = 0; q < Q; ++q) {
+          const bool out = k[q] == t && id[q] >= x;
+          if (!__any(out)) continue;
+          if (out) {
+            const u32 i = q * G10_WAVE + lane;
+            const uint4 B = list_at(LE_B, i);
+            const u64 sz = ((u64)B.w << 32) | B.z;
+            const u64 t0 = list_ot(i, 0), t1 = list_ot(i, 1), o0 = t0 == NONE64 ? 0ull : t0, o1 = t1 == NONE64 ? 0ull : t1;
+            const u64 o = o0 > o1 ? o0 : o1, h = __umul64hi(sz, o), l = sz * o;
+            if (better(h, l, id[q], bh, bl, bc)) { bh = h; bl = l; bc = id[q]; }
+          }
+        }
+        fl.full = 1u;
+        fl.hi = wave_max(bh);
+        fl.lo = wave_max(bh == fl.hi ? bl : 0ull);
+        fl.cand = wave_min(bh == fl.hi && bl == fl.lo ? bc : NONE32);
+      }
+    }
+    u32 cnt = 0;
+#pragma unroll
+    for (u32 q = 0; q < Q; ++q) {
+      const u32 i = q * G10_WAVE + lane;
+      bool in = k[q] > t;
+      if (x && k[q] == t) in = list_at(LE_I, i).x < x;
+      const u64 mk = __ballot(in);
+      if (in) S->sel[cnt + (u32)__popcll(mk & ((1ull << lane) - 1ull))] = i;
+      cnt += (u32)__popcll(mk);
+    }
+    if (lane == 0) S->nsel = cnt;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return lane < cnt ? S->sel[lane] : NONE32;
+  };
+  auto pick = [&](const Entry& e, const u32 slot, const Floor& fl, const u32 F, const u32 allowed, const bool fresh, const u32 odd) -> u32 {
+    const u32 lane = thread_here() & 63u;
+    const u64 s = ((u64)e.B.w << 32) | e.B.z;
+    const u32 L1 = e.A.x, R = e.A.y;
+    bool ok0 = e.ot0 != NONE64, ok1 = e.ot1 != NONE64, open = true;
+    // free times before the ends of the windows, transfer times
+    double f0L = e.O0.x, f0a = e.O0.y, f0b = e.I0.x, f0R = e.I0.y, f1L = e.O1.x, f1a = e.O1.y, f1b = e.I1.x, f1R = e.I1.y;
+    const double x1000 = exactf(s) * 1000.0;
+    const double to0 = ceil_divf(x1000, S->bw[0], S->bw[4]), to1 = ceil_divf(x1000, S->bw[1], S->bw[5]),
+                 ti0 = ceil_divf(x1000, S->bw[2], S->bw[6]), ti1 = ceil_divf(x1000, S->bw[3], S->bw[7]);
+    double all_o0 = fresh ? exactf(base[(u64)(A_FO + 0) * nb1 + nch]) : S->all[0], all_o1 = fresh ? exactf(base[(u64)(A_FO + 1) * nb1 + nch]) : S->all[1],
+           all_i0 = fresh ? exactf(base[(u64)(A_FI + 0) * nb1 + nch]) : S->all[2], all_i1 = fresh ? exactf(base[(u64)(A_FI + 1) * nb1 + nch]) : S->all[3];
+    u32 ch_o0 = 0, ch_o1 = 0, ch_i0 = 0, ch_i1 = 0;    // a window of a pick met one of an entry
+    const bool wrap = __any(R > K);                    // (something lies in the second iteration)
+    u32 m = 0, by_floor = 0;
+    while (true) {
+      // flash first; host only if flash cannot take it.  (0: cannot be picked)
+      const u32 kB = open ? (ok0 ? e.k0 : ok1 ? e.k1 : 0u) : 0u;
+      const u32 kmax = wave_max(kB);
+      if (kmax <= F) { by_floor = fl.key <= F ? 1u : 0u; break; }     // (also when nothing is left)
+      if (kmax < fl.key || (kmax == fl.key && !fl.full)) break;
+      const bool in1 = kB == kmax;
+      const u64 m1 = __ballot(in1);
+      u32 bl = (u32)__builtin_ctzll(m1);
+      const u64 ot = ok0 ? e.ot0 : e.ot1;
+      if (m1 & (m1 - 1)) {                             // equal keys
+        const u64 s_ = read_lane64(s, bl), ot_ = read_lane64(ot, bl);
+        bool in3 = in1;
+        if (__any(in1 && (s != s_ || ot != ot_))) {    // high word, low word (mostly the sizes and times are equal: a layer repeats)
+          const u64 hi = __umul64hi(s, ot), lo = s * ot;
+          const u64 hmx = wave_max(in1 ? hi : 0ull);
+          const bool in2 = in1 && hi == hmx;
+          const u64 lmx = wave_max(in2 ? lo : 0ull);
+          in3 = in2 && lo == lmx;
+        }
+        const u32 cmin = wave_min(in3 ? e.I.x : NONE32);               // lowest index
+        bl = (u32)__builtin_ctzll(__ballot(in3 && e.I.x == cmin));
+      }
+      if (kmax == fl.key) {                            // (as large a bound was left out: the whole values decide)
+        const u64 s_ = read_lane64(s, bl), ot_ = read_lane64(ot, bl);
+        if (!better(__umul64hi(s_, ot_), s_ * ot_, (u32)__builtin_amdgcn_readlane((int)e.I.x, (int)bl), fl.hi, fl.lo, fl.cand)) break;
+      }
+      const u64 flash = __ballot(ok0);
+      const u32 d = (flash >> bl) & 1ull ? 0u : 1u;
+      if (lane == bl) {
+        S->pick[m] = slot | d << 16;
+        S->pick_o[m] = d ? f1L : f0L; S->pick_i[m] = d ? f1R : f0R;
+        open = false;
+      }
+      ++m;
+      // The free times of the entries become those that the picked migration leaves, and an entry that its destination
+      // cannot carry any more gets the other destination, or none.
+      auto commit = [&](bool& ok, const u32 ea, const u32 eb, double& fL, double& fa, double& fb, double& fR, const double to, const double ti,
+                        double& all_o, double& all_i, u32& ch_o, u32& ch_i) {
+        const u32 wL1 = (u32)__builtin_amdgcn_readlane((int)L1, (int)bl), wR = (u32)__builtin_amdgcn_readlane((int)R, (int)bl);
+        const u32 wa = (u32)__builtin_amdgcn_readlane((int)ea, (int)bl), wb = (u32)__builtin_amdgcn_readlane((int)eb, (int)bl);
+        bool hit_o = L1 <= wa - 1 && wL1 <= ea - 1, hit_i = eb + 1 <= wR - 1 && wb + 1 <= R - 1;
+        if (wrap) { hit_o = cyc_overlap32(L1, ea - 1, wL1, wa - 1, K); hit_i = cyc_overlap32(eb + 1, R - 1, wb + 1, wR - 1, K); }
+        const bool may = open && ok;
+        const u64 any_o = __ballot(may && hit_o), any_i = __ballot(may && hit_i);
+        const double ro = read_lanef(fL, bl), po = read_lanef(to, bl), ri = read_lanef(fR, bl), pi = read_lanef(ti, bl);
+        const double nL = after_takingf(fL, all_o, ro, po, true, wrap), nR = after_takingf(fR, all_i, ri, pi, false, wrap);
+        fa = after_takingf(fa, all_o, ro, po, true, wrap); fb = after_takingf(fb, all_i, ri, pi, false, wrap);
+        if (open) { fL = nL; fR = nR; }                // (a picked one keeps its own)
+        all_o -= po; all_i -= pi;
+        ch_o |= any_o ? 1u : 0u; ch_i |= any_i ? 1u : 0u;
+        ok = ok && fa - fL >= to && fR - fb >= ti;
+      };
+      if (d == 0u) commit(ok0, e.A.z, e.A.w, f0L, f0a, f0b, f0R, to0, ti0, all_o0, all_i0, ch_o0, ch_i0);
+      else commit(ok1, e.B.x, e.B.y, f1L, f1a, f1b, f1R, to1, ti1, all_o1, all_i1, ch_o1, ch_i1);
+      if (m == allowed) break;
+    }
+    if (open && slot != NONE32) {                      // what a next round of picks goes on from
+      list_f(LE_O0, slot) = make_double2(f0L, f0a); list_f(LE_I0, slot) = make_double2(f0b, f0R);
+      list_f(LE_O1, slot) = make_double2(f1L, f1a); list_f(LE_I1, slot) = make_double2(f1b, f1R);
+      if (!ok0) list_ot(slot, 0) = NONE64;
+      if (!ok1) list_ot(slot, 1) = NONE64;
+    }
+    if (lane == 0) {
+      S->chain[odd][0] = ch_o0; S->chain[odd][1] = ch_o1; S->chain[odd][2] = ch_i0; S->chain[odd][3] = ch_i1;
+      S->all[0] = all_o0; S->all[1] = all_o1; S->all[2] = all_i0; S->all[3] = all_i1;
+      S->m0 = m; S->by_floor = by_floor;
+    }
     return m;
   };
 
@@ -842,7 +1175,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       }
     }
     __syncthreads();
-    run_jobs(0u, uniform(S->njobs), 0xffffu);
+    run_jobs(0u, uniform(S->njobs), 0xffffu, 0u);
     __syncthreads();
     const u64 a0 = S->acc[0], a1 = S->acc[1], a2 = S->acc[2];
     const u64 vlo = a0 + (a1 << 32), vhi = a2 + (a1 >> 32) + (vlo < a0 ? 1ull : 0ull);
@@ -877,6 +1210,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // What the next ranking pass finds: made by the last wavefront at the end of the pass before,
   // beside the level-1 update, so that a pass begins without a barrier of its own.
   auto open_pass = [&]() {
+    const u32 lane = thread_here() & 63u;
     for (u32 i = lane; i < ns; i += 64u) smark[i] = 0;   // no tile scored yet
     if (lane == 0) {
       S->hq = 0; S->njobs = 0; S->ntl = 0; S->filt = 0;
@@ -906,7 +1240,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (WIDE && S->no_wide) break;               // (the last launch of a round only ends the pass left open)
       ++passes; ++used;
     }
-    mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0;
+    mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0;
     floor2 = 0;
     pass_units = 0;
     if (!thr) thr = NONE32;
@@ -923,6 +1257,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (!(WIDE && resume)) { S->n_iter += 1; S->n_evals += C - S->n_mig - S->n_drop; }
       S->touched = 0; S->ot_changed = 0;
     }
+    if (MC) for (u32 c = tid; c < nch; c += LB) hpend[c] &= 1u;
 
     // rank: score the hot tiles whose bound reaches a threshold (first a guess a little under
     // the last benefit), lower the threshold to the best benefit found, repeat until no tile
@@ -1015,7 +1350,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           if (tid == 0) wv.ctx->pending = 0;
         }
         ++rounds;
-        if (MC && K < (1u << 30)) {
+        if (MC && picks) {
           // The winner is the best entry of the list if that clears every bound of what is not on the
           // list: then one wavefront takes it from there, and the next ones with it, while the others
           // bring the group bounds up to date, and no arg-max over the threads is needed (2.5 us a
@@ -1024,16 +1359,15 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           if (lane == 0 && f2) atomicMax(&S->F2, f2);
           __syncthreads();
           if (wave == LW - 1) {
-            const u32 nl_ = uniform(S->nlist), n = nl_ < LIST_MAX ? nl_ : LIST_MAX, f2_ = uniform(S->F2);
+            const u32 nl_ = uniform(S->nlist), n = nl_ < lcap ? nl_ : lcap, f2_ = uniform(S->F2);
             const u32 F = rest > f2_ ? rest : f2_;
-            const bool have = lane < n;
-            Winner e;
-            if (have) e = S->list[lane];
-            else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
-            u32 allowed = MAXM, by_floor;                // passes of Algorithm 1 this round may stand for
+            Floor fl;
+            const u32 slot = choose(n, F, fl);
+            const Entry e = load_entry(slot);
+            u32 allowed = uniform(S->pick_max);             // passes of Algorithm 1 this round may stand for
             if (max_iter && max_iter - uniform(S->n_iter) + 1 < allowed) allowed = (u32)(max_iter - uniform(S->n_iter) + 1);   // (n_iter counts this pass already)
-            const u32 m = pick(e, have, false, F, 0u, allowed, by_floor);
-            if (lane == 0) { S->m0 = m ? m : 1u; S->by_floor = by_floor; S->Fkeep = F; S->fast = m ? 1u : 0u; }
+            const u32 m = pick(e, slot, fl, F, allowed, true, 0u);
+            if (lane == 0) { S->Fkeep = F; S->fast = m ? 1u : 0u; S->left = fl; }
           } else {
             group_bounds(wave);
           }
@@ -1068,84 +1402,91 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     }
     if (WIDE && wide_exit) break;
 
-    const bool none = (S->mem[0].hi | S->mem[0].lo) == 0;
+    const bool none = !(MC && uniform(S->fast)) && (S->mem[0].hi | S->mem[0].lo) == 0;
     if (none) { __syncthreads(); if (tid == 0) { S->done = 1; S->status = G10_RESIDUAL; } break; }
 
     // ---- decide and commit -------------------------------------------------------------------
     // More migrations of the same pass (MC): the ranking also tells which candidate comes second,
-    // third, ...  Candidate w_j wins the pass after w_1 .. w_(j-1) were committed if (1) nothing
-    // those commits change enters its own score - no slot of its absent window can drop under the
-    // capacity, and its transfer windows meet none of theirs on the same channel - and (2) no
-    // other candidate can have risen above it.  Pressure only falls and reservations only grow,
-    // so a benefit rises in one case only: a candidate the policy sends to flash, with a host
-    // window as well, loses its flash window to a reservation and moves to host.  Such a
-    // candidate is at risk once a committed flash migration's transfer windows meet its own; it
-    // then counts with the bound of its host benefit.  Every candidate not on the list of the
-    // pass (tiles left out, candidates under the round's threshold, the overflow of the list)
-    // counts with its bound: the floor F.
+    // third, ...  Candidate w_j wins the pass after w_1 .. w_(j-1) were committed if its score is the
+    // best of the list as those leave it, and clears the bound F of every candidate not on the list
+    // (tiles left out, candidates under the list's threshold, its overflow: bounds only fall).  What a
+    // commit changes in a score: the free time of transfer windows that meet its own on the same channel,
+    // and with it whether the destination can carry the candidate - the picking wavefront follows that
+    // exactly, in registers (pick); and the over-capacity time of absent windows in which a slot drops under
+    // the capacity - a pick whose absent window touches a chunk where the picks before it may let one
+    // drop waits for the list to be scored again (step 2).
     //
-    // Step 1 (the last wavefront, a list entry per lane): the candidates in the order of their
-    // benefit, as far as (2) and the transfer windows allow.  Where a round of commits ends with
-    // entries still on the list that might clear the floor, the steps are taken again from here
-    // (cround > 0) instead of from a new ranking.
+    // Step 1 (the last wavefront, a list entry per lane): the entries in the order of their benefit.  Where a
+    // round of commits ends with entries that might clear the floor, the steps are taken again from here
+    // (cround > 0) instead of from a new ranking: with picks made beside the round's jobs (NX_PICKED), or
+    // from the list scored again.  (A further round's picking took 4 to 5 us for two or three migrations while it
+    // stopped at the first window that met another; now 5 to 10 for eight to fifteen, half of them beside the jobs.)
     bool opened = false;                                 // the next pass's state is made
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     for (u32 cround = 0;; ++cround) {
-    const bool from_list = MC && !(cround == 0u && uniform(S->fast));       // (else: the ranking has done this step)
-    if (from_list && wave == LW - 1 && uniform(S->nlist) > 1u && K < (1u << 30)) {
-      const u32 nl_ = uniform(S->nlist), n = nl_ < LIST_MAX ? nl_ : LIST_MAX;
-      const bool have = lane < n;
-      Winner e;
-      if (have) e = S->list[lane];
-      else { e.hi = 0; e.lo = 0; e.cand = NONE32; e.dest = 1; e.kr = 0; e.L1 = 0; e.R = 0; e.a = 1; e.b = 0; e.s = 0; e.pos = 0; e.slot = NONE32; }
-      u32 allowed = MAXM, m, by_floor;                 // passes of Algorithm 1 this round may stand for
-      if (cround == 0u) {
-        const u32 f2_ = uniform(S->F2), F = rest_final > f2_ ? rest_final : f2_;
-        if (max_iter && max_iter - uniform(S->n_iter) + 1 < allowed) allowed = (u32)(max_iter - uniform(S->n_iter) + 1);   // (n_iter counts this pass already)
-        if (lane == 0) S->Fkeep = F;
-        m = pick(e, have, have && e.cand == S->mem[0].cand, F, 1u, allowed, by_floor);
-      } else {
-        // Another round from the same list: its entries are scored again against the timelines as
-        // the earlier rounds left them (a committed candidate has no window any more and scores
-        // nothing), and the best of them wins the next pass of Algorithm 1 if its key clears the
-        // floor - every candidate not on the list is still bounded by it, since bounds only fall.
+    const u32 tid = thread_here(), lane = tid & 63u;
+    if (MC && cround && uniform(S->next) == NX_RESCORE) {
+      // Another round from the same list: its entries are scored again against the timelines as
+      // the earlier rounds left them (a committed candidate has no window any more and scores
+      // nothing), and the best of them wins the next pass of Algorithm 1 if its key clears the
+      // floor - every candidate not on the list is still bounded by it, since bounds only fall.
+      const u32 nl_ = uniform(S->nlist), n = nl_ < lcap ? nl_ : lcap;
+      rescore_list(n);
+      __syncthreads();
+      if (wave == LW - 1) {
+        u32 allowed = uniform(S->pick_max);              // passes of Algorithm 1 this round may stand for
         const u32 F = uniform(S->Fkeep);
-        if (max_iter && max_iter - uniform(S->n_iter) < allowed) allowed = (u32)(max_iter - uniform(S->n_iter));
-        if (lane == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->touched = 0; S->ot_changed = 0; S->hq = 0; S->list_rescored += n; }
-        Machine mc; mc.bwo0 = bwo0; mc.bwo1 = bwo1; mc.bwi0 = bwi0; mc.bwi1 = bwi1;
-        mc.ivo0 = ivo0; mc.ivo1 = ivo1; mc.ivi0 = ivi0; mc.ivi1 = ivi1;
-        if (have) {
-          const uint4 A = S->listA[lane], B = S->listB[lane];
-          const Score r = score_candidate(pv, mc, A, B);
-          const bool ok_any = r.ok0 || r.ok1;
-          const u32 d = r.ok0 ? 0u : 1u;
-          const bool one = gt128(r.h1, r.l1, r.h0, r.l0);
-          const u32 kc = upkey(one ? r.h1 : r.h0, one ? r.l1 : r.l0);
-          e.hi = ok_any ? (d ? r.h1 : r.h0) : 0ull; e.lo = ok_any ? (d ? r.l1 : r.l0) : 0ull;
-          e.dest = d; e.a = d ? B.x : A.z; e.b = d ? B.y : A.w;
-          e.fo_base = r.fo_L; e.fi_end = r.fi_R; e.kU = kc; e.kr = (r.ok0 && r.ok1) ? kc : 0u;
-        }
-        // (nothing on the list clears the floor: the pass is over)
-        m = pick(e, have, false, F, 0u, allowed, by_floor);
-        if (m == 0u) open_pass();
+        if (max_iter) { const u32 left = (u32)umin64(max_iter - uniform(S->n_iter), NONE32); allowed = left < allowed ? left : allowed; }
+        Floor fl;
+        const u32 slot = choose(n, F, fl);
+        const Entry e = load_entry(slot);
+        const u32 m = pick(e, slot, fl, F, allowed, true, cround & 1u);
+        if (lane == 0) S->left = fl;
+        if (m == 0u) open_pass();                        // (nothing on the list clears the floor, or the bounds left out: the pass is over)
       }
-      if (lane == 0) { S->m0 = m; S->by_floor = by_floor; }
-    } else if (from_list && wave == LW - 1 && lane == 0) { S->m0 = 1; S->by_floor = 1; }     // (nothing else on the list)
-    if (from_list) __syncthreads();
+      __syncthreads();
+    } else if (MC && !cround && !uniform(S->fast)) {     // the winner of the arg-max alone; the list goes on in the next round
+      if (tid == 0) {
+        const u32 f2_ = S->F2;
+        S->m0 = 1; S->by_floor = 0; S->Fkeep = rest_final > f2_ ? rest_final : f2_;
+        S->chain[0][0] = 0; S->chain[0][1] = 0; S->chain[0][2] = 0; S->chain[0][3] = 0;
+      }
+      __syncthreads();
+    }
 
     // Step 2, chunk by chunk: what every picked migration does to the chunk (sets of migrations, a
     // bit each), the jobs that follow - for a chunk that is cut, that holds a transfer window, or
     // in which a slot drops under the capacity - and how many migrations can go together: the first
-    // that might let a slot drop under the capacity, or that host memory might not hold on top of
-    // the earlier ones, ends the set (it is ranked again in the next pass, and the jobs leave it
-    // out).  For the winner itself the two tests only decide how it is committed: alone, and with
+    // whose absent window touches a chunk where the earlier ones may have let a slot drop, or that host
+    // memory might not hold on top of the earlier ones, ends the set (the jobs leave it out).  (No branches in
+    // the loop but the ones on the destination and the iteration: skipping what touches none of a wavefront's
+    // chunks, or ending at the first that waits, cost up to 5 % of the loop.)  For the winner itself the two tests only decide how it is committed: alone, and with
     // the exact host-capacity test.
     const u32 m0 = uniform(S->m0);
     if (MC && m0 == 0u) { opened = true; break; }        // (a later round found nothing above the floor)
     u32 cutP = 0, allP = 0, cutH = 0, allH = 0, eF = 0, eH = 0, wF = 0, wH = 0;   // absent window / period cuts, covers the chunk whole;
                                                          // eviction and prefetch windows meet it, to flash and to host
-    u64 lzP = 0, lzH = 0, cutHs = 0;                     // sizes of allP, allH, cutH
+    u64 runP = 0, runH = 0, lzH = 0;                     // sizes of allP and cutP, of allH and cutH, of allH
     bool jobP = false;
+    const bool picked = MC && (cround || uniform(S->fast));     // the round's migrations are entries of the list
+    if (MC && picked && wave == LW - 1) {                // ... and in full in mem[] for what follows
+      u32 d = 0;
+      if (lane < m0) {
+        const u32 pk = S->pick[lane], slot = pk & 0xffffu;
+        d = pk >> 16;
+        const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot), I = list_at(LE_I, slot);
+        const u64 s = ((u64)B.w << 32) | B.z, ot = list_ot(slot, d);
+        // (free times behind the earlier picks only where the jobs follow those: run_jobs)
+        const double fo = S->chain[cround & 1u][d] ? S->pick_o[lane] : list_f(d ? LE_O1 : LE_O0, slot).x;
+        const double fi = S->chain[cround & 1u][2u + d] ? S->pick_i[lane] : list_f(d ? LE_I1 : LE_I0, slot).y;
+        Winner& M = S->mem[lane];
+        M.hi = __umul64hi(s, ot); M.lo = s * ot; M.s = s; M.fo_base = (u64)(long long)fo; M.fi_end = (u64)(long long)fi;
+        M.cand = I.x; M.tensor = I.y; M.pos = I.z; M.dest = d; M.L1 = A.x; M.R = A.y; M.a = d ? B.x : A.z; M.b = d ? B.y : A.w; M.slot = slot;
+      }
+      const u64 hosts = __ballot(lane < m0 && d != 0u);
+      if (lane == 0) S->hosts = (u32)hosts;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
     if (wave == LW - 1 && (lane & 31u) < m0) {           // transfer times (needed by the jobs and the records): out in lane i, in in lane 32 + i
       Winner& M = S->mem[lane & 31u];
       const bool out = lane < 32u;
@@ -1153,52 +1494,76 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (out) M.tau_o = tau;
       else M.tau_i = tau;
     }
-    if (tid == 0) S->jnext = LW - 1;
+    if (tid == 0) { S->jnext = LW - 1; S->touched = 0; S->ot_changed = 0; }
     if (tid < ((nch + 63u) & ~63u)) {
       // migration i lies in lane i of every wavefront and is read from there into scalars: with a trip to
       // LDS for every migration this loop took 2.1 us a round on the stress trace
       u32 gL = 0, gR = 0, ga = 1, gb = 0, gd = 0;
       u64 gs = 0;
-      if (lane < m0) { const Winner& M = S->mem[lane]; gL = M.L1; gR = M.R; ga = M.a; gb = M.b; gd = M.dest; gs = M.s; }
+      if (MC && picked) {
+        if (lane < m0) {
+          const u32 pk = S->pick[lane], slot = pk & 0xffffu;
+          const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot);
+          gd = pk >> 16;
+          gL = A.x; gR = A.y; ga = gd ? B.x : A.z; gb = gd ? B.y : A.w; gs = ((u64)B.w << 32) | B.z;
+        }
+      } else if (lane < m0) { const Winner& M = S->mem[lane]; gL = M.L1; gR = M.R; ga = M.a; gb = M.b; gd = M.dest; gs = M.s; }
+      const bool stale = MC && tid < nch && (hpend[tid] & 2u) != 0u;   // (picked by an over-capacity time that has fallen since)
       const bool in = tid < nch;
       const u64 mo = in ? minOver[tid] : NONE64, hm = in ? hmax[tid] : 0ull;
       const u32 c0 = in ? tid * CH : 0u, c1 = in ? (c0 + CH < K ? c0 + CH : K) : 0u, len = c1 - c0;
-      u32 cut = MAXM;
-      bool ex0 = false;
-      u64 runP = 0, runH = 0;
+      // what the pressure over the capacity can still lose in this chunk (0: nothing may touch a stale one)
+      const u64 spare = stale ? 0ull : mo == NONE64 ? NONE64 : mo - cap;
+      const u64 hroom = hm < host_cap ? host_cap - hm : 0ull;
+      u32 cut = MAXM;                                    // (of this wavefront's chunks: the migrations from there on wait)
       for (u32 i = 0; i < m0; ++i) {
         const u32 mL1 = (u32)__builtin_amdgcn_readlane((int)gL, (int)i), mR = (u32)__builtin_amdgcn_readlane((int)gR, (int)i);
         const u32 ma = (u32)__builtin_amdgcn_readlane((int)ga, (int)i), mb = (u32)__builtin_amdgcn_readlane((int)gb, (int)i);
         const u32 md = (u32)__builtin_amdgcn_readlane((int)gd, (int)i), bit = 1u << i;
         const u64 ms = read_lane64(gs, i);
-        const u32 nP = covered(c0, c1, K, mL1, mR);      // the period: eviction window, absent window, prefetch window
-        if (!nP) continue;                               // (most migrations do not touch most chunks)
-        const u32 nE = covered(c0, c1, K, mL1, ma), nA = covered(c0, c1, K, ma, mb + 1);
-        if (nA) {
-          runP += ms;
-          if (mo != NONE64 && mo - cap <= runP) { const u32 lim = i ? i : 1u; cut = lim < cut ? lim : cut; }
-          if (nA == len) { allP |= bit; lzP += ms; }
-          else cutP |= bit;
+        // slots that the chunk shares with the eviction window [L1, a), the absent window [a, b], the prefetch window
+        // (b, R) (not above zero: none); does the whole period cover it?
+        int nE, nA, nW;
+        bool fP;
+        if (mR <= K) {
+          nE = (int)((c1 < ma ? c1 : ma) - (c0 > mL1 ? c0 : mL1));
+          nA = (int)((c1 < mb + 1 ? c1 : mb + 1) - (c0 > ma ? c0 : ma));
+          nW = (int)((c1 < mR ? c1 : mR) - (c0 > mb + 1 ? c0 : mb + 1));
+          fP = mL1 <= c0 && c1 <= mR;
+        } else {                                         // (ends in the second iteration)
+          const u32 nP = covered(c0, c1, K, mL1, mR);
+          nE = (int)covered(c0, c1, K, mL1, ma); nA = (int)covered(c0, c1, K, ma, mb + 1); nW = (int)nP - nE - nA;
+          fP = nP != 0 && nP == len;
         }
+        // the earlier ones may have let a slot of its absent window drop (its own pressure falls behind its win)
+        bool wait = nA > 0 && spare <= runP;
+        const u64 sA = nA > 0 ? ms : 0ull;
         if (md == G10_HOST) {
-          if (nE) eH |= bit;
-          if (nE + nA != nP) wH |= bit;
-          if (ms > host_cap || hm + runH > host_cap - ms) { if (i == 0) ex0 = true; else cut = i < cut ? i : cut; }
-          runH += ms;
-          if (nP == len) { allH |= bit; lzH += ms; }
-          else { cutH |= bit; cutHs += ms; }
+          // host memory may not hold it on top of the earlier ones
+          const bool tH = nE > 0 || nA > 0 || nW > 0;
+          const bool full = tH && runH + ms > hroom;
+          if (i == 0) { if (__any(full)) S->need_exact = 1; }
+          else wait = wait || full;
+          if (__any(wait) && cut == MAXM) cut = i;
+          eH |= nE > 0 ? bit : 0u;
+          wH |= nW > 0 ? bit : 0u;
+          runH += tH ? ms : 0ull;
+          lzH += tH && fP ? ms : 0ull;
+          allH |= tH && fP ? bit : 0u;
+          cutH |= tH && !fP ? bit : 0u;
         } else {
-          if (nE) eF |= bit;
-          if (nE + nA != nP) wF |= bit;
+          if (__any(wait) && cut == MAXM) cut = i;
+          eF |= nE > 0 ? bit : 0u;
+          wF |= nW > 0 ? bit : 0u;
         }
+        runP += sA;
+        cutP |= nA > 0 ? bit : 0u;
+        allP |= nA == (int)len ? bit : 0u;               // (len > 0)
       }
-      if (__any(cut < MAXM)) {
-        cut = wave_min(cut);
-        if (lane == 0) atomicMin(&S->cut, cut);
-      }
-      if (ex0) S->need_exact = 1;
+      cutP &= ~allP;
+      if (cut < MAXM && lane == 0) atomicMin(&S->cut, cut);
       // (a job adds the sizes of the migrations that cover its chunk whole itself)
-      jobP = cutP != 0 || (lzP != 0 && mo != NONE64 && mo - cap <= lzP);
+      jobP = cutP != 0 || (runP != 0 && spare <= runP);
       const u64 b0 = __ballot(jobP), b1 = __ballot(eF != 0), b2 = __ballot(eH != 0), b3 = __ballot(wF != 0), b4 = __ballot(wH != 0);
       const u32 n0 = (u32)__popcll(b0), n1 = n0 + (u32)__popcll(b1), n2 = n1 + (u32)__popcll(b2), n3 = n2 + (u32)__popcll(b3), n4 = n3 + (u32)__popcll(b4);
       if (n4) {
@@ -1217,16 +1582,22 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     const u32 nj = uniform(S->njobs), cut_ = uniform(S->cut), need_exact = uniform(S->need_exact);   // (nj: the jobs of the round)
     u32 m = m0 < cut_ ? m0 : cut_;
     bool room = true;
+    if (MC && m == 0u) {                                 // (not even the first stands: the list is scored again)
+      __syncthreads();
+      if (tid == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->next = NX_RESCORE; }
+      __syncthreads();
+      continue;
+    }
     if (MC && cround && need_exact) break;               // (the exact host-memory test is left to the next ranking pass)
     if (need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
       if (tid == 0) S->hq = 0;
       __syncthreads();
-      if ((cutH & 1u) || ((allH & 1u) && hpend[tid])) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_HQ << 16) | tid;   // (behind the round's jobs)
+      if ((cutH & 1u) || ((allH & 1u) && (hpend[tid] & 1u))) jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_HQ << 16) | tid;   // (behind the round's jobs)
       else if (allH & 1u) atomicMax((unsigned long long*)&S->hq, (unsigned long long)hmax[tid]);   // (exact: nothing is missing there)
       __syncthreads();
-      run_jobs(nj, uniform(S->njobs), 0xffffu);
+      run_jobs(nj, uniform(S->njobs), 0xffffu, cround & 1u);
       __syncthreads();
       room = s <= host_cap && S->hq <= host_cap - s;
       if (tid == 0) S->jnext = LW - 1;
@@ -1241,22 +1612,22 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (m != m0) {                                     // the migrations left out
         const u32 keep = (1u << m) - 1u;
         allP &= keep; allH &= keep; cutH &= keep;
-        lzP = 0; lzH = 0; cutHs = 0;
+        runP = 0; lzH = 0; runH = 0;
         for (u32 i = 0; i < m; ++i) {
           const u64 ms = S->mem[i].s;
-          if ((allP >> i) & 1u) lzP += ms;
-          if ((allH >> i) & 1u) lzH += ms;
-          if ((cutH >> i) & 1u) cutHs += ms;
+          if ((allP >> i) & 1u) runP += ms;
+          if ((allH >> i) & 1u) { lzH += ms; runH += ms; }
+          if ((cutH >> i) & 1u) runH += ms;
         }
       }
-      if (!jobP && lzP) {
-        lazyP[c] += lzP;
+      if (!jobP && runP) {                               // (no job: nothing cuts the chunk)
+        lazyP[c] += runP;
         const u64 mo = minOver[c];
-        if (mo != NONE64) minOver[c] = mo - lzP;
+        if (mo != NONE64) minOver[c] = mo - runP;
       }
       // host occupancy: whole covers into the lazy add; cuts only into the chunk's bound, the slots follow on demand (J_HQ)
-      if (lzH | cutHs) { lazyH[c] += lzH; hmax[c] += lzH + cutHs; }
-      if (cutH) hpend[c] = 1u;
+      if (runH) { lazyH[c] += lzH; hmax[c] += runH; }
+      if (cutH) atomicOr(&hpend[c], 1u);
     }
     if (wave == LW - 1) {
       const u64 nm = S->n_mig, nd = S->n_drop;
@@ -1267,8 +1638,9 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         a.cd.A[M.pos] = make_uint4(mL1, mR, 1u, 0u);       // the candidate leaves the live set
         a.cd.B[M.pos] = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
         if (MC && M.slot != NONE32) {                      // (and has nothing left to win on the list of the pass)
-          S->listA[M.slot] = make_uint4(mL1, mR, 1u, 0u);
-          S->listB[M.slot] = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
+          list_at(LE_A, M.slot) = make_uint4(mL1, mR, 1u, 0u);
+          list_at(LE_B, M.slot) = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
+          lkey[M.slot] = 0u; list_ot(M.slot, 0) = NONE64; list_ot(M.slot, 1) = NONE64;
         }
         if (!room) {
           g10_dropped dr; dr.iteration = S->n_iter - 1; dr.cand = M.cand; dr.reserved = 0;
@@ -1298,18 +1670,18 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           // the margin doubles whenever a pass needed one, and narrows only now and then
           if (rounds > 1u) { if (gs > 2u) --gs; }
           else if ((S->n_iter & 31u) == 0u && gs < GUESS_SHIFT) ++gs;
-        } else if (pass_units > 8u && gs < GUESS_SHIFT_MAX) ++gs;
-        else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 6u && gs > MC_GUESS_SHIFT_MIN) --gs; }
+        } else if (pass_units > 24u && gs < GUESS_SHIFT_MAX) ++gs;
+        else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 18u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
         if (MC && cround == 0u) {
           const u32 nl_ = S->nlist;
           const int pub = S->pub, mag = pub < 0 ? -pub : pub;
           int x = pub;
-          if (nl_ > LIST_MAX) x -= mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
-          else if (nl_ > 36u) x -= mag / 8 > (1 << 15) ? mag / 8 : 1 << 15;
-          else if (nl_ < 6u) x += mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
-          else if (nl_ < 16u) x += mag / 4 > (1 << 16) ? mag / 4 : 1 << 16;
+          if (nl_ > lcap) x -= mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
+          else if (nl_ > lcap / 16u * 9u) x -= mag / 8 > (1 << 15) ? mag / 8 : 1 << 15;
+          else if (nl_ < lcap / 32u * 3u) x += mag / 2 > (1 << 18) ? mag / 2 : 1 << 18;
+          else if (nl_ < lcap / 4u) x += mag / 4 > (1 << 16) ? mag / 4 : 1 << 16;
           S->pub = x < PUB_MIN ? PUB_MIN : x > PUB_MAX ? PUB_MAX : x;
         }
         const Winner& Z = S->mem[m - 1];
@@ -1327,14 +1699,36 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           S->n_evals += cround ? x * live - x * (x - 1) / 2 : x * live - x * (x + 1) / 2;
           // another round of commits from the same list: unless the picking ran out of entries above
           // the floor and every one it picked was committed
-          const bool more = MC && S->nlist > 1u && K < (1u << 30) && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
+          const bool more = MC && S->nlist > 1u && picks && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
           S->more = more ? 1u : 0u;
+          // (where the chunks cut a round short the next one picks little more than went through)
+          if (MC) { const u32 pm = S->pick_max; S->pick_max = m < m0 ? (m + 2u < MAXM ? m + 2u : MAXM) : m0 == pm ? (2u * pm < MAXM ? 2u * pm : MAXM) : pm; }
           if (cround) S->more_rounds += 1;
         }
       }
     }
     if (!room) { __syncthreads(); break; }
-    run_jobs(0u, nj, (1u << m) - 1u);
+    if (MC && wave == LW - 1) {
+      // Beside the jobs the last wavefront picks the next round's migrations: it knows the channels as this round leaves
+      // them, and over-capacity times that fall in this round are marked by the jobs (stale), which the next chunk test
+      // heeds.  Not where the chunks cut this round short: the channels are then not as the picking left them.
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_s_setprio(3);                     // (the longest chain of the round; two job wavefronts share its SIMD)
+      u32 next = NX_RESCORE;
+      if (uniform(S->more) && picked && m == m0) {
+        u32 allowed = uniform(S->pick_max);
+        if (max_iter) { const u32 left = (u32)umin64(max_iter - uniform(S->n_iter), NONE32); allowed = left < allowed ? left : allowed; }
+        const Floor fl = S->left;
+        const u32 slot = lane < uniform(S->nsel) ? S->sel[lane] : NONE32;
+        const Entry e = load_entry(slot);
+        const u32 mn = pick(e, slot, fl, uniform(S->Fkeep), allowed, false, (cround + 1u) & 1u);
+        if (mn) next = NX_PICKED;
+        else if (uniform(S->by_floor)) { if (lane == 0) S->more = 0; }   // (what is left has only fallen: the pass is over)
+      }
+      if (lane == 0) S->next = next;
+      __builtin_amdgcn_s_setprio(0);
+    }
+    run_jobs(0u, nj, (1u << m) - 1u, cround & 1u);
     __syncthreads();
     // level 1: the bases of the timelines whose chunk totals changed, one wavefront per timeline
     {
@@ -1367,7 +1761,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         }
       }
       opened = !MC || !uniform(S->more);
-      if (opened && wave == LW - 1) open_pass();
+      if (opened) { if (wave == LW - 1) open_pass(); }
+      else if (tid == LB - 1) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->hq = 0; }
       __syncthreads();
     }
     if (opened) break;
@@ -1383,7 +1778,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
 
   // ---- state out ---------------------------------------------------------------------
   for (u32 i = tid; i < N_ARR * nch; i += LB) a.g_tot[i] = tot[i];
-  for (u32 i = tid; i < nch; i += LB) { a.g_lazyP[i] = lazyP[i]; a.g_minOver[i] = minOver[i]; a.g_lazyH[i] = lazyH[i]; a.g_hmax[i] = hmax[i]; a.g_hmat[i] = hmat[i]; a.g_hpend[i] = hpend[i]; }
+  for (u32 i = tid; i < nch; i += LB) { a.g_lazyP[i] = lazyP[i]; a.g_minOver[i] = minOver[i]; a.g_lazyH[i] = lazyH[i]; a.g_hmax[i] = hmax[i]; a.g_hmat[i] = hmat[i]; a.g_hpend[i] = hpend[i] & 1u; }
   for (u32 i = tid; i < nt; i += LB) a.g_keys[i] = keys[i];
   for (u32 i = tid; i < N_ARR * nb1; i += LB) a.g_base[i] = base[i];
   if (tid == 0) {
@@ -1418,7 +1813,7 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
   Machine mc; mc.bwo0 = ctl->bw_out[0]; mc.bwo1 = ctl->bw_out[1]; mc.bwi0 = ctl->bw_in[0]; mc.bwi1 = ctl->bw_in[1];
   mc.ivo0 = ctl->inv_out[0]; mc.ivo1 = ctl->inv_out[1]; mc.ivi0 = ctl->inv_in[0]; mc.ivi1 = ctl->inv_in[1];
   Winner mine;
-  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.kU = 0; mine.kr = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
+  mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   mine.s = 0; mine.fo_base = 0; mine.fi_end = 0; mine.tensor = 0; mine.pos = 0; mine.dest = 0; mine.L1 = 0; mine.R = 0; mine.a = 1; mine.b = 0;
   const u32 nunits = wv.ctx->ntl << a.tshift;
   for (u32 u = blockIdx.x; u < nunits; u += nwg) {
@@ -1474,14 +1869,9 @@ int loop_wide_launch(const LoopArgs* plans, u32 nch, hipStream_t s) {
   return G10_OK;
 }
 
-size_t loop_lds_bytes(u32 nch, u32 nt) {
-  const size_t ns = (nt + 63) / 64;
-  size_t b = 0;
-  b += ((size_t)N_ARR * (nch + 1) + (size_t)N_ARR * nch + (size_t)4 * nch + ns + (size_t)4 * LW_MAX + (size_t)6 * nch + 8) * 8;      // (six jobs a chunk at most)
-  b += sizeof(Shared);
-  b += ((size_t)nt + ns + 2 * (size_t)nch) * 4 + (size_t)nt * 4;
-  return (b + 15) & ~(size_t)15;
-}
+// (the least a plan needs: with the shortest list)
+size_t loop_lds_bytes(u32 nch, u32 nt) { return lds_before_list(nch, nt) + (size_t)LIST_MIN * LIST_ENTRY; }
+size_t loop_lds_taken(u32 nch, u32 nt) { return lds_before_list(nch, nt) + (size_t)list_cap(nch, nt) * LIST_ENTRY; }
 
 // The smallest tile (256 << shift) with at most max_tiles tiles that fit the LDS beside the chunks: 8192 tiles
 // and 512 chunks together are 2.4 KB more than a compute unit has (from 498 chunks on the tiles' limit is lower,

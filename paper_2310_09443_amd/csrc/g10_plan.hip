@@ -431,9 +431,9 @@ void plan_work_free(PlanWork* w) {
 static const u32 SCORE_SORT_BITS = 23;           // significant bits of a score sort key
 static const u32 SCORE_SORT_PASSES = (SCORE_SORT_BITS + 7) / 8;
 static const u32 PASS_BUDGET = 4096;             // ranking passes per launch of the loop kernel
-static const u32 RETILE_PASSES = 128;   // ... between two re-tilings of a long candidate list
+static const u32 RETILE_PASSES = 64;    // ... between two re-tilings of a long candidate list
 static const u32 RETILE_MIN_CANDS = 8192;        // shorter lists are never re-tiled
-static const u64 BATCH_LAUNCH_TICKS = 250000;    // a launch of a batch ends after 2.5 ms (100 MHz clock)
+static const u64 BATCH_LAUNCH_TICKS = 200000;    // a launch of a batch ends after 2 ms (100 MHz clock)
 // Ranking by benefit / cost on a long list (one plan, band reading): a scoring round of WIDE_MIN_UNITS
 // x 256 candidates or more is left to a kernel on all compute units.  The loop kernel then ends in
 // the middle of its pass and takes it up in its next launch, so such launches are queued in pairs,
@@ -868,7 +868,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
         x.cur ^= 1;
       }
     }
-    const size_t lds = loop_lds_bytes(x.w->nch, x.nt);
+    const size_t lds = loop_lds_taken(x.w->nch, x.nt);
     if (lds > lds_max) lds_max = lds;
   }
   if (count > 1) {
@@ -884,9 +884,8 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // Long lists are put back into score order every RETILE_PASSES passes or more: the tiles the
   // loop looks at are dense with live candidates again, and the list is cut to those that can
   // still score.  A batch ends its launches by the clock instead, so that no plan waits long for
-  // the slowest one.
-  // (a batch re-tiles half as often: its loops run side by side, its re-tilings one after the other)
-  const u32 retile_every = count == 1 ? RETILE_PASSES : 2 * RETILE_PASSES;
+  // the slowest one.  (Loops re-tiled every 64 / 128 / 192 rounds: stress 21.6 / 22.1 / 23.8 ms, ragged stress 4.44 / 4.62 /
+  // 5.19; a 20-plan capacity sweep of the stress trace 35 ms at 64, 39 at 256.)
   const bool timed_loop = n_active != 0;
   // The results of a finished plan: the pressure with the lazy adds applied and its peak, then the
   // copies to one block of pinned host memory (so that they run as plain DMA), grown when a plan
@@ -956,7 +955,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
         x.loop_seq += x.wide ? la.pass_budget + 1 : 1;
         x.seen_passes_w = x.hc.passes; x.seen_units = x.hc.units_scored;
       }
-      const size_t l = loop_lds_bytes(w->nch, x.nt);
+      const size_t l = loop_lds_taken(w->nch, x.nt);
       if (l > lds) lds = l;
     }
     G10_HIP(hipMemcpyAsync(h->loop_args, hargs, (size_t)na * sizeof(LoopArgs), hipMemcpyHostToDevice, s));
@@ -991,7 +990,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       }
       ++n_active;
       // (the cadence counts the rounds of commits: ranking passes and the further rounds made from their lists)
-      if (x.n > RETILE_MIN_CANDS && x.hc.passes + x.hc.more_rounds - x.seen_passes >= retile_every) {
+      if (x.n > RETILE_MIN_CANDS && x.hc.passes + x.hc.more_rounds - x.seen_passes >= RETILE_PASSES) {
         x.seen_passes = x.hc.passes + x.hc.more_rounds;
         if (x.counted && x.hc.n_live < x.n) x.n = x.hc.n_live;   // live candidates come first in the list
         x.retile_cands += x.n;

@@ -191,6 +191,9 @@ struct PrefixView {           // slot tables in HBM / L2, level 1 in LDS
 struct Score {
   u64 h0, l0, h1, l1;         // benefit per destination (0 if it cannot be used now)
   u64 fo_L, fi_R;             // of the policy's destination: free out-channel time before L1, in-channel before R
+  u64 ot0, ot1;               // over-capacity time in the absent window (0 if the destination cannot be used now)
+  u64 fL0, fa0, fb0, fR0;     // free channel time before both ends of the eviction window, [L1, a), and of the prefetch
+  u64 fL1, fa1, fb1, fR1;     // window, [b + 1, R), on the doubled timeline (0 without a window)
   bool ok0, ok1;              // the destination's channels can carry the transfer now
   bool strike0, strike1;      // the destination can never count again
 };
@@ -226,7 +229,8 @@ __device__ __forceinline__ Gathered gather_candidate(const PrefixView& pv, const
 // host could still score, a feasible flash window keeps the policy on flash.
 __device__ __forceinline__ Score score_gathered(const PrefixView& pv, const Machine& mc, const uint4 A, const uint4 B, const Gathered& g) {
   Score r;
-  r.h0 = r.l0 = r.h1 = r.l1 = r.fo_L = r.fi_R = 0;
+  r.h0 = r.l0 = r.h1 = r.l1 = r.fo_L = r.fi_R = r.ot0 = r.ot1 = 0;
+  r.fL0 = r.fa0 = r.fb0 = r.fR0 = r.fL1 = r.fa1 = r.fb1 = r.fR1 = 0;
   r.ok0 = r.ok1 = r.strike0 = r.strike1 = false;
   const bool v0 = A.z <= A.w, v1 = B.x <= B.y;
   if (!(v0 || v1)) return r;
@@ -235,18 +239,17 @@ __device__ __forceinline__ Score score_gathered(const PrefixView& pv, const Mach
   const bool sL = A.x >= K, sR = A.y >= K;
   const u32 cL = (sL ? A.x - K : A.x) >> pv.shift_ch, cR = (sR ? A.y - K : A.y) >> pv.shift_ch;
   const u64* bOT = pv.base + (u64)A_OT * nb1;
-  u64 fo0_L = 0, fi0_R = 0, fo1_L = 0, fi1_R = 0;
   if (v0) {
     const bool sa = A.z >= K, sb = A.w + 1 >= K;
     const u32 ca = (sa ? A.z - K : A.z) >> pv.shift_ch, cb = (sb ? A.w + 1 - K : A.w + 1) >> pv.shift_ch;
     const u64 *bFO = pv.base + (u64)(A_FO + 0) * nb1, *bFI = pv.base + (u64)(A_FI + 0) * nb1;
     const u64 allFO = bFO[pv.nch], allFI = bFI[pv.nch], allOT = bOT[pv.nch];
-    fo0_L = (sL ? allFO : 0ull) + bFO[cL] + g.L0.x; fi0_R = (sR ? allFI : 0ull) + bFI[cR] + g.R0.x;
-    const u64 fo_a = (sa ? allFO : 0ull) + bFO[ca] + g.a0.x, fi_b = (sb ? allFI : 0ull) + bFI[cb] + g.b0.x;
-    r.ok0 = carries(fo_a - fo0_L, mc.bwo0, x1000) && carries(fi0_R - fi_b, mc.bwi0, x1000);
+    r.fL0 = (sL ? allFO : 0ull) + bFO[cL] + g.L0.x; r.fR0 = (sR ? allFI : 0ull) + bFI[cR] + g.R0.x;
+    r.fa0 = (sa ? allFO : 0ull) + bFO[ca] + g.a0.x; r.fb0 = (sb ? allFI : 0ull) + bFI[cb] + g.b0.x;
+    r.ok0 = carries(r.fa0 - r.fL0, mc.bwo0, x1000) && carries(r.fR0 - r.fb0, mc.bwi0, x1000);
     if (r.ok0) {
-      const u64 ot = ((sb ? allOT : 0ull) + bOT[cb] + g.b0.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a0.y);
-      r.h0 = __umul64hi(s, ot); r.l0 = s * ot;
+      r.ot0 = ((sb ? allOT : 0ull) + bOT[cb] + g.b0.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a0.y);
+      r.h0 = __umul64hi(s, r.ot0); r.l0 = s * r.ot0;
     }
   }
   if (v1) {
@@ -254,19 +257,19 @@ __device__ __forceinline__ Score score_gathered(const PrefixView& pv, const Mach
     const u32 ca = (sa ? B.x - K : B.x) >> pv.shift_ch, cb = (sb ? B.y + 1 - K : B.y + 1) >> pv.shift_ch;
     const u64 *bFO = pv.base + (u64)(A_FO + 1) * nb1, *bFI = pv.base + (u64)(A_FI + 1) * nb1;
     const u64 allFO = bFO[pv.nch], allFI = bFI[pv.nch], allOT = bOT[pv.nch];
-    fo1_L = (sL ? allFO : 0ull) + bFO[cL] + g.L1.x; fi1_R = (sR ? allFI : 0ull) + bFI[cR] + g.R1.x;
-    const u64 fo_a = (sa ? allFO : 0ull) + bFO[ca] + g.a1.x, fi_b = (sb ? allFI : 0ull) + bFI[cb] + g.b1.x;
-    r.ok1 = carries(fo_a - fo1_L, mc.bwo1, x1000) && carries(fi1_R - fi_b, mc.bwi1, x1000);
+    r.fL1 = (sL ? allFO : 0ull) + bFO[cL] + g.L1.x; r.fR1 = (sR ? allFI : 0ull) + bFI[cR] + g.R1.x;
+    r.fa1 = (sa ? allFO : 0ull) + bFO[ca] + g.a1.x; r.fb1 = (sb ? allFI : 0ull) + bFI[cb] + g.b1.x;
+    r.ok1 = carries(r.fa1 - r.fL1, mc.bwo1, x1000) && carries(r.fR1 - r.fb1, mc.bwi1, x1000);
     if (r.ok1) {
-      const u64 ot = ((sb ? allOT : 0ull) + bOT[cb] + g.b1.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a1.y);
-      r.h1 = __umul64hi(s, ot); r.l1 = s * ot;
+      r.ot1 = ((sb ? allOT : 0ull) + bOT[cb] + g.b1.y) - ((sa ? allOT : 0ull) + bOT[ca] + g.a1.y);
+      r.h1 = __umul64hi(s, r.ot1); r.l1 = s * r.ot1;
     }
   }
   const bool keep1 = r.ok1 && (r.h1 | r.l1) != 0;
   const bool keep0 = r.ok0 && (keep1 || (r.h0 | r.l0) != 0);
   r.strike0 = v0 && !keep0;
   r.strike1 = v1 && !keep1;
-  r.fo_L = r.ok0 ? fo0_L : fo1_L; r.fi_R = r.ok0 ? fi0_R : fi1_R;
+  r.fo_L = r.ok0 ? r.fL0 : r.fL1; r.fi_R = r.ok0 ? r.fR0 : r.fR1;
   return r;
 }
 // Both destinations' pairs are gathered before anything is used.
@@ -435,7 +438,8 @@ struct PlanWork {
 void replay_free(PlanWork* w);
 
 // the loop kernel (g10_loop.hip)
-size_t loop_lds_bytes(u32 nch, u32 nt);                       // dynamic LDS of one workgroup
+size_t loop_lds_bytes(u32 nch, u32 nt);                       // dynamic LDS of one workgroup, the least
+size_t loop_lds_taken(u32 nch, u32 nt);                       // ... with as long a list of the pass as fits
 u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candidates on a timeline of nch chunks: 256 << this
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
