@@ -64,13 +64,16 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
 
   // The chain itself runs in the first wavefront alone: every step waits for the one before, and one wavefront
   // needs no barrier between them (the others wait at the barrier below; they set up and finish the timeline).
-  // Most prefetches cannot move at all: the slot just before them cannot take the tensor.  That test reads one
-  // slot, and the pressure changes only when a prefetch does move; so 64 records are tested at once, one per
-  // lane; those before the first that passes are done - nothing gained - and only that one takes the search, after
-  // which the ones behind it are tested again.  (The records of the next 64 are on their way meanwhile.  Loading the 64
-  // behind every prefetch that moves anew - two dependent trips - took 7.15 ms on the stress trace, 1226 moves; 6.2 now.)
+  // Most prefetches cannot move at all: the slot just before them cannot take the tensor.  That test needs the pressure
+  // of one slot; so 64 records are tested at once, one per lane, those before the first that passes are done - nothing
+  // gained -, only that one takes the search, and the ones behind it are tested again with what its move adds to their
+  // slots (kept in the lanes, not loaded anew).  (The records of the next 64 are on their way meanwhile.)
+  // A move is bound by its dependent trips to L2 (0.6 us each).  It takes one where the highest chunk that may refuse does:
+  // that chunk and the one at the end of the window are loaded together, whole, and the chunks cut are written back from
+  // those registers, without a wait - the accesses of one wavefront are served in order.  (Stress trace, 1226 moves: 3.4 ms;
+  // 6.2 with a trip for the test, one or more for the search, one per cut chunk and one for the stores to arrive, and with a
+  // look at every chunk of the timeline, seven a lane, in the search and in the update.)
   if (wave == 0) {
-    const u32 ncl = (nch + 63u) / 64u;             // chunks per lane: lane, lane + 64, ...
     u64 n_moved = 0, slots = 0;
     u32 nr = 0, na = 0, nb = 0;
     u64 nsz = 0;
@@ -78,7 +81,14 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
     u32 it = 0;                                    // first record of the 64
     u64 todo = 0;                                  // lanes whose record is not done yet
     u32 cr = 0, ca = 0, cb = 0, cbb = 0;           // this lane's record: its number, absent window, last absent slot
-    u64 csz = 0;
+    u64 csz = 0, val = 0;                          // ... size; pressure of that slot
+    struct Strip { u64 x[4]; };                    // a strip of 256 slots of a chunk, 64 apart in a lane
+    auto load_strip = [&](u32 c, u32 st) -> Strip {
+      Strip v;
+#pragma unroll
+      for (u32 i = 0; i < 4; ++i) { const u32 j = c * CH + st * 256u + i * 64u + lane; v.x[i] = E[j < K ? j : K - 1]; }
+      return v;
+    };
     while (true) {
       if (!todo) {                                 // the next 64
         if (it >= n) break;
@@ -87,59 +97,54 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
         cr = nr; ca = na; cb = nb; csz = nsz;
         cbb = cb >= K ? cb - K : cb;
         it += cnt;
+        if ((todo >> lane) & 1ull) val = E[cbb] + ladd[cbb >> shift_ch];
         if (it + lane < n) { nr = order[it + lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
       }
       const bool mine = (todo >> lane) & 1ull;
-      bool pass = false;
-      if (mine) pass = csz <= cap && E[cbb] + ladd[cbb >> shift_ch] <= cap - csz;
-      const u64 pm = __ballot(pass);
+      const u64 pm = __ballot(mine && csz <= cap && val <= cap - csz);
       const u32 f = pm ? (u32)__builtin_ctzll(pm) : 64u;       // the records before it stay where they are
       if (mine && lane < f) { gained[cr] = 0u; last[cr] = cbb; }
       if (!pm) { todo = 0; continue; }
       todo &= f == 63u ? 0ull : ~0ull << (f + 1u);
       const u32 r = (u32)__builtin_amdgcn_readlane((int)cr, (int)f), a = (u32)__builtin_amdgcn_readlane((int)ca, (int)f),
-                b = (u32)__builtin_amdgcn_readlane((int)cb, (int)f);
+                b = (u32)__builtin_amdgcn_readlane((int)cb, (int)f), bb = b >= K ? b - K : b;
       const u64 s = lane_value64(csz, f);
 
       // the earliest slot from which every slot up to b can hold the tensor: one past the last slot of [a, b]
-      // that cannot.  The chunk maxima say which piece of a chunk may hold it, highest first; that piece is scanned.
+      // that cannot.  The window in pieces of chunks, from its end back - the part in the second iteration, then the one in
+      // the first -, a piece per lane: the chunk maxima say which piece may hold that slot, and that piece is scanned.
       const u64 lim = cap - s;                     // a slot holds the tensor iff its pressure <= lim
-      u32 upper = b;                               // the search is still open over [a, upper]
+      const u32 c_end = bb >> shift_ch;            // the chunk at the end of the window
+      const u32 n2 = b >= K ? c_end + 1u - ((a > K ? a - K : 0u) >> shift_ch) : 0u;     // pieces of the second iteration
+      const u32 t1 = (b < K ? b : K - 1u) >> shift_ch, n1 = a < K ? t1 + 1u - (a >> shift_ch) : 0u;      // last chunk, pieces of the first
+      auto chunk_of = [&](u32 t) -> u32 { return t < n2 ? c_end - t : t1 - (t - n2); };
       u32 p = a;
-      while (true) {
-        unsigned long long cd = 0ull;              // (upper end + 1) << 32 | lower end of the highest such piece
-        for (u32 q = 0; q < ncl; ++q) {
-          const u32 c = q * 64u + lane;
-          if (c < nch && cmax[c] > lim) {          // the two places of the chunk on the doubled timeline
-            const u64 s0 = (u64)c * CH, s1 = (s0 + CH - 1 < (u64)K - 1) ? s0 + CH - 1 : (u64)K - 1;
-#pragma unroll
-            for (u32 rep = 0; rep < 2; ++rep) {
-              const u64 o = rep ? K : 0u;
-              const u64 plo = s0 + o > a ? s0 + o : a, phi = s1 + o < upper ? s1 + o : upper;
-              if (plo <= phi) { const unsigned long long v = ((phi + 1) << 32) | plo; cd = v > cd ? v : cd; }
-            }
-          }
-        }
-        cd = wave_max((u64)cd);
-        if (cd == 0ull) break;                     // no chunk holds a refusing slot inside [a, upper]
-        const u32 hi = (u32)(cd >> 32) - 1u, lo = (u32)cd;
+      u32 c_seen = NONE32;                         // the chunk scanned last; its first strip and the end chunk's
+      Strip v_end = {}, v_seen = {};
+      bool end_loaded = false;
+      u32 t0 = 0, pieces = n1 + n2;                // (pieces from the end down to the one of p)
+      while (t0 < n1 + n2) {
+        const u32 t = t0 + lane;
+        const u64 hits = __ballot(t < n1 + n2 && cmax[t < n1 + n2 ? chunk_of(t) : 0u] > lim);
+        if (!hits) { t0 += 64u; continue; }
+        const u32 th = uniform(t0 + (u32)__builtin_ctzll(hits)), c = chunk_of(th), second = th < n2 ? K : 0u;
+        const u32 lo = c * CH + second > a ? c * CH + second : a, end_ = c * CH + CH < K ? c * CH + CH : K;
+        const u32 hi = end_ - 1u + second < b ? end_ - 1u + second : b;
         u32 best = 0;                              // doubled coordinate + 1 of the last refusing slot of the piece
-        for (u64 j0 = lo; j0 <= hi; j0 += 256) {   // four loads in flight per lane (64-bit counter: hi may be near 2^32)
-          u64 x[4];
+        const u64 lz = ladd[c];
+        for (u32 st = 0; st < spt; ++st) {
+          const Strip v = load_strip(c, st);
+          if (!end_loaded) { v_end = c == c_end ? v : load_strip(c_end, 0); end_loaded = true; }
+          if (spt == 1u) { c_seen = c; v_seen = v; }
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u64 j = j0 + i * 64u + lane;
-            const u32 jj = j >= K ? (u32)(j - K) : (u32)j;
-            x[i] = j <= hi ? E[jj] + ladd[jj >> shift_ch] : 0ull;
+            const u32 j = c * CH + st * 256u + i * 64u + lane + second;
+            if (j >= lo && j <= hi && v.x[i] + lz > lim) best = j + 1;    // ascending: the last one stays
           }
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i)
-            if (x[i] > lim) best = (u32)j0 + i * 64u + lane + 1;         // ascending: the last one stays
         }
         best = wave_max(best);
-        if (best) { p = best; break; }
-        if (lo == a) break;                        // nothing refuses in [a, upper]
-        upper = lo - 1;
+        if (best) { p = best; pieces = best > hi ? th : th + 1u; break; }      // (one past the piece's end: the piece is not gained)
+        t0 = th + 1u;
       }
       const u32 g = b + 1 - p;
       if (lane == 0) {
@@ -149,36 +154,51 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
       }
       if (g) {                                     // the slots gained take the tensor
         n_moved += 1; slots += g;
-        for (u32 q = 0; q < ncl; ++q) {
-          const u32 c = q * 64u + lane;
-          u32 len = 0, cv = 0;
-          if (c < nch) cv = cover(c, CH, K, p, b, len);
-          if (cv && cv == len) { ladd[c] += s; cmax[c] += s; }
-          u64 part = __ballot(cv && cv != len);    // chunks the range cuts: slot by slot, the whole wavefront on each
-          while (part) {
-            const u32 cc = q * 64u + (u32)__builtin_ctzll(part);
-            part &= part - 1;
-            const u64 lz = ladd[cc];
-            u64 m = 0;
-            for (u32 st = 0; st < spt; ++st) {
-              const u32 j0 = cc * CH + st * 256u + lane;        // (64 neighbouring slots per load and store)
-              u64 x[4];
-#pragma unroll
-              for (u32 i = 0; i < 4; ++i) x[i] = j0 + i * 64u < K ? E[j0 + i * 64u] : 0ull;
-#pragma unroll
-              for (u32 i = 0; i < 4; ++i) {
-                const u32 j = j0 + i * 64u;
-                if (j < K) {
-                  if (in_doubled(j, K, p, b) != NONE32) { x[i] += s; E[j] = x[i]; }
-                  m = x[i] + lz > m ? x[i] + lz : m;
-                }
-              }
-            }
-            m = wave_max(m);
-            if (lane == 0) cmax[cc] = m;
+        if (mine && in_doubled(cbb, K, p, b) != NONE32) val += s;
+        // whole chunks lazily; the window cuts the first and the last piece at most (of one chunk, where it goes around)
+        u32 cut0 = NONE32, cut1 = NONE32;
+        for (u32 q = 0; q < pieces; q += 64u) {
+          const u32 t = q + lane;
+          bool cut = false;
+          u32 c = 0;
+          if (t < pieces) {
+            c = chunk_of(t);
+            const u32 second = t < n2 ? K : 0u, lo = c * CH + second, end_ = (c * CH + CH < K ? c * CH + CH : K) + second;
+            cut = lo < p || end_ > b + 1u;
+            if (!cut) { ladd[c] += s; cmax[c] += s; }
           }
+          u64 cm = __ballot(cut);
+          if (cm && cut0 == NONE32) { cut0 = (u32)__builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(cm)); cm &= cm - 1; }
+          if (cm) cut1 = (u32)__builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(cm));
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // the next tests read the slots just written
+        if (cut1 == cut0) cut1 = NONE32;
+        // (slots in [p, b]: both less K where it lies in the second iteration, or all but the (b - K, p) between)
+        const bool both = p < K && b >= K;
+        const u32 rlo = both ? b - K + 1u : p >= K ? p - K : p, rn = both ? p - rlo : b - p + 1u;
+#pragma unroll 1
+        for (u32 w = 0; w < 2; ++w) {
+          const u32 cc = w ? cut1 : cut0;
+          if (cc == NONE32) continue;
+          const u64 lz = ladd[cc];
+          u64 m = 0;
+          for (u32 st = 0; st < spt; ++st) {
+            const u32 j0 = cc * CH + st * 256u + lane;          // (64 neighbouring slots per load and store)
+            Strip v;
+            if (cc == c_seen) v = v_seen;                       // (strips of a chunk of one strip only)
+            else if (spt == 1u && end_loaded && cc == c_end) v = v_end;
+            else v = load_strip(cc, st);
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u32 j = j0 + i * 64u;
+              if ((j - rlo < rn) != both && j < K) { v.x[i] += s; E[j] = v.x[i]; }
+              const u64 x = j < K ? v.x[i] + lz : 0ull;
+              m = x > m ? x : m;
+            }
+          }
+          m = wave_max(m);
+          if (lane == 0) cmax[cc] = m;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next loads find what was just written (in order)
       }
     }
     if (lane == 0) { S->n_moved = n_moved; S->slots = slots; }
