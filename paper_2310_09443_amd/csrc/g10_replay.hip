@@ -18,11 +18,13 @@
 // channel and on the stalls before it - and runs in one wavefront, 64 events at a time, one per
 // lane.  What couples the channels is the delay of the kernels alone, and that changes only
 // where a kernel waits: up to the next such event every channel is a queue of known requests,
-// whose completion times come from one scan of the steps x -> max(x + a, b) per channel.  So the
-// walk takes a step per 64 events and one per wait instead of one per event.  Bound by the
-// latency of those steps (four scans of six dependent cross-lane moves, then a vote): stress
-// trace, 55 476 events with about 1400 waits, 14.4 ms with one event after the other (240 ns
-// each, scalar state, operands read lane by lane), 4.3 ms with the scans.
+// whose completion times come from running maxima.  So the walk takes a step per 64 events and one
+// per wait instead of one per event (1240 of the waits of the stress trace follow from one another,
+// whatever is walked at a time).  Bound by the latency of those steps.  Stress trace, 55 476 events with about
+// 1400 waits: 14.4 ms with one event after the other; 4.2 with a scan of the steps x -> max(x + a, b) per channel
+// in 64-bit integers and three dependent trips to memory before every 64 events; 2.6 with the lanes in the order of
+// their channels, running maxima in doubles - one for both channels of a direction - and every trip a
+// stage ahead.
 // A result needed by a later event of the same 64, or of the next, is passed on through a
 // register; older ones come from the result array.
 
@@ -35,7 +37,9 @@ using namespace g10;
 
 namespace {
 
-enum { EV_EVICT = 0, EV_FETCH = 1, EV_USE = 2 };
+// Kinds of events in the order of one point; eviction and prefetch per destination (their channels are independent, so
+// the order between the two does not matter).
+enum { EV_OUT = 0, EV_IN = 2, EV_USE = 4, EV_NONE = 5, EV_BITS = 3 };
 
 struct ReplayStats {
   u64 iter_ns, stall_ns, n_stalled, pad;
@@ -52,11 +56,11 @@ __global__ __launch_bounds__(G10_BLOCK) void k_rp_events(const g10_migration* __
   if (i < n) {
     const g10_migration m = rec[i];
     const u32 b2 = rec_ab[i].y, R2 = m.next_use + (m.wraps ? K : 0u);
-    const u32 issue = b2 + 1 - (gained ? gained[i] : 0u);
+    const u32 kind[3] = {EV_OUT + m.dest, EV_IN + m.dest, EV_USE}, issue = b2 + 1 - (gained ? gained[i] : 0u);
     for (u32 c = 0; c < 2; ++c) {
       const u32 pt[3] = {m.evict_after + 1 + c * K, issue + c * K, R2 + c * K};
       for (u32 t = 0; t < 3; ++t)
-        keys[(u64)6 * i + 3 * c + t] = pt[t] < 2 * K ? ((((u64)pt[t] * 4 + t) << (rbits + 1)) | ((u64)i << 1) | c) : NONE64;
+        keys[(u64)6 * i + 3 * c + t] = pt[t] < 2 * K ? (((((u64)pt[t] << EV_BITS) | kind[t]) << (rbits + 1)) | ((u64)i << 1) | c) : NONE64;
     }
     by[m.dest] = m.size_bytes; bo[m.dest] = m.t_out_ns; bi[m.dest] = m.t_in_ns;
   }
@@ -77,8 +81,8 @@ __global__ __launch_bounds__(G10_BLOCK) void k_rp_index(const u64* __restrict__ 
   if (p >= ne) return;
   const u64 k = sorted[p];
   if (k == NONE64) return;
-  const u32 c = (u32)(k & 1ull), i = (u32)((k >> 1) & ((1ull << rbits) - 1ull)), t = (u32)((k >> (rbits + 1)) & 3ull);
-  if (t != EV_USE) pos_of[(u64)(t * 2 + c) * n + i] = p;
+  const u32 c = (u32)(k & 1ull), i = (u32)((k >> 1) & ((1ull << rbits) - 1ull)), t = (u32)((k >> (rbits + 1)) & ((1u << EV_BITS) - 1u));
+  if (t != EV_USE) pos_of[(u64)((t >= EV_IN ? 2u : 0u) + c) * n + i] = p;
 }
 
 __device__ __forceinline__ u64 lane_get(u64 v, u32 l) {
@@ -115,7 +119,9 @@ __device__ __forceinline__ Queue queue_scan(Queue f) {
   return f;
 }
 
-__global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sorted, u32 ne, const g10_migration* __restrict__ rec,
+// The walk in whole numbers, for times over REPLAY_EXACT: an event per lane in the order of the events, a scan of the
+// steps x -> max(x + a, b) per channel.
+__global__ __launch_bounds__(G10_WAVE) void k_replay_long(const u64* __restrict__ sorted, u32 ne, const g10_migration* __restrict__ rec,
                                                     u32 n, u32 rbits, const u32* __restrict__ pos_of,
                                                     const u64* __restrict__ start, u32 K, u64 T, u64* __restrict__ res,
                                                     u64* __restrict__ late, ReplayStats* __restrict__ st) {
@@ -143,12 +149,13 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
       const u32 c = (u32)(k & 1ull);
       v.i = (u32)((k >> 1) & ((1ull << rbits) - 1ull));
       const u64 q = k >> (rbits + 1);
-      v.type = (u32)(q & 3ull); v.pt = (u32)(q >> 2);
+      const u32 kind = (u32)(q & ((1u << EV_BITS) - 1u));
+      v.type = kind >= EV_USE ? 2u : kind >= EV_IN ? 1u : 0u; v.pt = (u32)(q >> EV_BITS);
       const g10_migration m = rec[v.i];
       v.dest = m.dest;
-      v.tau = v.type == EV_EVICT ? m.t_out_ns : m.t_in_ns;
+      v.tau = v.type == 0u ? m.t_out_ns : m.t_in_ns;
       v.sp = v.pt < K ? start[v.pt] : start[v.pt - K] + T;     // end of kernel pt - 1 without any stall
-      if (v.type != EV_EVICT) {                                 // its eviction / its prefetch
+      if (v.type != 0u) {                                 // its eviction / its prefetch
         const u32 pp = pos_of[(u64)((v.type - 1) * 2 + c) * n + v.i];
         if (pp >= base) { v.psrc = 1; v.pin = pp - base; }
         else if (pp >= done) { v.psrc = 2; v.pin = pp - done; }
@@ -176,9 +183,9 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
     const u64 from_prev = lane_any(resv_prev, cur.pin);                     // (every lane takes part: a lane read must be active)
     const u64 pv = cur.psrc == 2 ? from_prev : cur.pval;                    // what the event waits for, if it is older than these 64
     const bool here = valid && cur.psrc == 1;                               // (else it is lane pin's result)
-    const u64 use_m = __ballot(valid && type == EV_USE), second_m = __ballot(valid && pt >= K);
-    const u64 out_m[2] = {__ballot(valid && type == EV_EVICT && dest == 0), __ballot(valid && type == EV_EVICT && dest == 1)};
-    const u64 in_m[2] = {__ballot(valid && type == EV_FETCH && dest == 0), __ballot(valid && type == EV_FETCH && dest == 1)};
+    const u64 use_m = __ballot(valid && type == 2u), second_m = __ballot(valid && pt >= K);
+    const u64 out_m[2] = {__ballot(valid && type == 0u && dest == 0), __ballot(valid && type == 0u && dest == 1)};
+    const u64 in_m[2] = {__ballot(valid && type == 1u && dest == 0), __ballot(valid && type == 1u && dest == 1)};
     u32 from = 0;
     while (from < cnt) {
       const bool open = valid && lane >= from;
@@ -188,26 +195,26 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
 #pragma unroll
       for (u32 d = 0; d < 2; ++d) {                                         // evictions
         if (!(out_m[d] & open_m)) continue;
-        const bool mine = open && type == EV_EVICT && dest == d;
+        const bool mine = open && type == 0u && dest == d;
         const Queue q = queue_scan(Queue{mine ? tau : 0ull, mine ? free_at + tau : 0ull});
         const u64 x = ch_out[d] + q.a, y = x > q.b ? x : q.b;
         if (mine) t = y;
       }
       u64 w = pv;
       const u64 from_out = lane_any(t, cur.pin);
-      if (here && type == EV_FETCH) w = from_out;
+      if (here && type == 1u) w = from_out;
 #pragma unroll
       for (u32 d = 0; d < 2; ++d) {                                         // prefetches, not before their evictions
         if (!(in_m[d] & open_m)) continue;
-        const bool mine = open && type == EV_FETCH && dest == d;
+        const bool mine = open && type == 1u && dest == d;
         const u64 ready = free_at > w ? free_at : w;
         const Queue q = queue_scan(Queue{mine ? tau : 0ull, mine ? ready + tau : 0ull});
         const u64 x = ch_in[d] + q.a, y = x > q.b ? x : q.b;
         if (mine) t = y;
       }
       const u64 from_in = lane_any(t, cur.pin);
-      if (here && type == EV_USE) w = from_in;
-      const bool is_use = open && type == EV_USE;
+      if (here && type == 2u) w = from_in;
+      const bool is_use = open && type == 2u;
       const u64 waits = __ballot(is_use && w > free_at);
       const u32 f = waits ? (u32)__builtin_ctzll(waits) : cnt - 1;          // the step ends with event f
       const u64 step_m = open_m & (f >= 63u ? ~0ull : (1ull << (f + 1)) - 1ull);
@@ -240,8 +247,8 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
       from = f + 1;
     }
     // ---- results out ---------------------------------------------------------------------
-    if (valid && type != EV_USE) res[p] = resv;
-    if (valid && type == EV_USE && pt >= K) late[i] = latev;
+    if (valid && type != 2u) res[p] = resv;
+    if (valid && type == 2u && pt >= K) late[i] = latev;
     resv_prev = resv;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);                              // the next gather may read what was just written
@@ -251,6 +258,198 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
   if (lane == 0) {
     st->iter_ns = T + delta - delta_first;
     st->stall_ns = stall;
+    st->n_stalled = n_stalled;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The walk.  Times in doubles, exact below 2^53: no time of the walk exceeds two iterations and every transfer one after
+// the other, 2 T + 8 T of the plan (a channel's transfers fit the iteration they were planned for).
+// ---------------------------------------------------------------------------
+constexpr u64 REPLAY_EXACT = 1ull << 48;          // bound of 2 T + 8 T (with SEGMENT between the channels of a scan)
+constexpr double SEGMENT = 0x1p50;
+
+struct OpAddF {
+  static __device__ __forceinline__ u64 f(u64 a, u64 b) {
+    return (u64)__double_as_longlong(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+  }
+};
+// Running maximum of values that are not negative: lanes without a source give 0, and a maximum may meet a value twice,
+// so the steps across rows need no mask and no identity of their own.
+template <int CTRL>
+__device__ __forceinline__ double max_from(double v) {
+  const u64 x = (u64)__double_as_longlong(v);
+  const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)x, CTRL, 0xf, 0xf, true);
+  const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(x >> 32), CTRL, 0xf, 0xf, true);
+  return fmax(v, __longlong_as_double((long long)(((u64)hi << 32) | lo)));
+}
+__device__ __forceinline__ double scan_max(double v) {
+  v = max_from<0x111>(v);                                        // row_shr:1, 2, 4, 8
+  v = max_from<0x112>(v);
+  v = max_from<0x114>(v);
+  v = max_from<0x118>(v);
+  v = max_from<0x142>(v);                                        // lane 15 of a row into the next row
+  return max_from<0x143>(v);                                     // lane 31 into rows 2 and 3
+}
+__device__ __forceinline__ double scan_sum(double v) { return __longlong_as_double((long long)wave_scan_dpp<OpAddF>((u64)__double_as_longlong(v), (u64)0)); }
+__device__ __forceinline__ double lane_getf(double v, u32 l) { return __longlong_as_double((long long)lane_get((u64)__double_as_longlong(v), l)); }
+__device__ __forceinline__ double lane_anyf(double v, u32 l) { return __longlong_as_double((long long)lane_any((u64)__double_as_longlong(v), l)); }
+__device__ __forceinline__ u32 to_lane(u32 v, u32 l) { return (u32)__builtin_amdgcn_ds_permute((int)(l << 2), (int)v); }   // (l: another one for every lane)
+__device__ __forceinline__ double whole(u64 x) { return __fma_rn((double)(u32)(x >> 32), 4294967296.0, (double)(u32)x); }
+
+__global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sorted, u32 ne, const g10_migration* __restrict__ rec,
+                                                    u32 n, u32 rbits, const u32* __restrict__ pos_of,
+                                                    const u64* __restrict__ start, u32 K, u64 T, u64* __restrict__ res,
+                                                    u64* __restrict__ late, ReplayStats* __restrict__ st) {
+  const u32 lane = threadIdx.x;
+  const u64 below = (1ull << lane) - 1ull;
+  // the state of the walk; the same in every lane
+  double delta = 0;                     // end of the previous kernel minus its end without any stall
+  double delta_first = 0;               // the same when the second iteration begins
+  bool second = false;
+  double free0 = 0, free1 = 0, free2 = 0, free3 = 0;       // when each channel is free again (out 0, 1, in 0, 1)
+  double stall = 0;
+  u64 n_stalled = 0;
+  u32 use_pt = NONE32, stalled_pt = NONE32;
+  double delta_pt = 0;                  // delta when the uses of the current point began
+
+  // 64 events at a time, one per lane, the lanes in the order of their kinds: each channel's requests lie side by side, in
+  // order.  They are fetched in stages, a stage a step of 64 ahead of the next, so that no trip to memory is waited for:
+  // the keys; record, time of the point and where the event's predecessor stands; the predecessor's result.
+  struct Keys { u64 k; u32 place, pos; };                  // place: the lane that the event of this position goes to; pos: the position of this lane's event
+  // (loaded words stay as they come until a later stage uses them: a conversion beside the load would wait for it)
+  struct Loads { u64 tau, sp; u32 kind, i, pt, pos, place, pred; };
+  struct Ev { Loads l; u64 pval; u32 src, psrc; };         // psrc 0: pval; 1: lane src of these 64; 2: of the 64 before
+  auto load_key = [&](u64 at) -> u64 { return at + lane < ne ? sorted[at + lane] : NONE64; };
+  auto spread = [&](u64 k) -> Keys {
+    const u32 kind = k == NONE64 ? (u32)EV_NONE : (u32)(k >> (rbits + 1)) & ((1u << EV_BITS) - 1u);
+    Keys r;
+    u32 at = 0;
+    r.place = 0;
+#pragma unroll
+    for (u32 c = 0; c <= EV_NONE; ++c) {
+      const u64 m = __ballot(kind == c);
+      if (kind == c) r.place = at + (u32)__popcll(m & below);
+      at += (u32)__popcll(m);
+    }
+    r.k = ((u64)to_lane((u32)(k >> 32), r.place) << 32) | to_lane((u32)k, r.place);
+    r.pos = to_lane(lane, r.place);
+    return r;
+  };
+  auto load_ops = [&](const Keys& q) -> Loads {
+    Loads v;
+    const bool valid = q.k != NONE64;
+    const u64 x = q.k >> (rbits + 1);
+    v.i = valid ? (u32)((q.k >> 1) & ((1ull << rbits) - 1ull)) : 0u;
+    v.kind = valid ? (u32)(x & ((1u << EV_BITS) - 1u)) : (u32)EV_NONE;
+    v.pt = valid ? (u32)(x >> EV_BITS) : 0u;
+    v.pos = q.pos; v.place = q.place;
+    v.tau = *(v.kind < EV_IN ? &rec[v.i].t_out_ns : &rec[v.i].t_in_ns);
+    v.sp = start[v.pt < K ? v.pt : v.pt - K];
+    v.pred = pos_of[(u64)((v.kind == EV_USE ? 2u : 0u) + (u32)(q.k & 1ull)) * n + v.i];   // its eviction / its prefetch (an eviction: not used)
+    return v;
+  };
+  // (the events from `base` on; those before `done` have their results in memory, the ones between lie where place_prev says)
+  auto load_pred = [&](const Loads& l, u32 base, u32 done, u32 place_prev) -> Ev {
+    Ev v;
+    v.l = l;
+    const bool has = l.kind >= EV_IN && l.kind <= EV_USE;
+    const u32 here = (u32)__shfl((int)l.place, (int)((l.pred - base) & 63u)), there = (u32)__shfl((int)place_prev, (int)((l.pred - done) & 63u));
+    v.psrc = !has ? 0u : l.pred >= base ? 1u : l.pred >= done ? 2u : 0u;
+    v.src = v.psrc == 1u ? here : there;
+    v.pval = res[has && v.psrc == 0u ? l.pred : 0u];       // (the others: not used)
+    return v;
+  };
+  Keys kq = spread(load_key(0));
+  Loads lq = load_ops(kq);
+  kq = spread(load_key(G10_WAVE));
+  u64 kraw = load_key(2 * G10_WAVE);
+  Ev nxt = load_pred(lq, 0, 0, 0);
+  lq = load_ops(kq);
+  double t_prev = 0;                    // results of the 64 before, one per lane
+  for (u32 base = 0; base < ne; base += G10_WAVE) {
+    const Ev cur = nxt;
+    const u32 kind = cur.l.kind, pt = cur.l.pt, pos = cur.l.pos;
+    const double tau = kind >= EV_USE ? 0.0 : whole(cur.l.tau), sp = whole(cur.l.sp + (pt < K ? 0ull : T));     // (sp: end of kernel pt - 1 without any stall)
+    nxt = load_pred(lq, base + G10_WAVE, base, cur.l.place);
+    lq = load_ops(spread(kraw));
+    kraw = load_key((u64)base + 3 * G10_WAVE);
+    const bool is_out = kind < EV_IN, is_in = kind >= EV_IN && kind < EV_USE, is_use = kind == EV_USE;
+    const u64 use_m = __ballot(is_use), valid_m = __ballot(kind != EV_NONE);
+    const u32 cnt = (u32)__popcll(valid_m);                     // the valid events come first
+    const u64 out1_m = __ballot(kind == EV_OUT + 1), in0_m = __ballot(kind == EV_IN), in1_m = __ballot(kind == EV_IN + 1), out0_m = __ballot(kind == EV_OUT);
+    // A channel that is free at x serves requests that are ready at r_1, r_2, .. and take tau_1, tau_2, ..: the k-th is done
+    // at A_k + max(x, r_j - A_(j-1) for j <= k), A the sums of tau.  Those do not change while the delay does, so a step
+    // of the walk is a running maximum for the evictions and one for the prefetches, both destinations in one
+    // (SEGMENT apart).  Settled requests keep their maximum.
+    const double sum = scan_sum(tau);
+    const double before1 = out0_m ? lane_getf(sum, 63u - (u32)__builtin_clzll(out0_m)) : 0.0;
+    const u64 o01 = out0_m | out1_m, in01 = in0_m | in1_m, o012 = o01 | in0_m;
+    const double before2 = o01 ? lane_getf(sum, 63u - (u32)__builtin_clzll(o01)) : 0.0, before3 = o012 ? lane_getf(sum, 63u - (u32)__builtin_clzll(o012)) : 0.0;
+    const double A = sum - (kind == EV_OUT ? 0.0 : kind == EV_OUT + 1 ? before1 : kind == EV_IN ? before2 : before3);
+    const double free_c = kind == EV_OUT ? free0 : kind == EV_OUT + 1 ? free1 : kind == EV_IN ? free2 : free3;
+    const double seg = (kind & 1u) ? 2.0 * SEGMENT : SEGMENT;    // (a request's ready time less the sums before it is above -SEGMENT)
+    const double from_prev = lane_anyf(t_prev, cur.src);
+    const bool here = cur.psrc == 1;
+    const double pv = cur.psrc == 2 ? from_prev : whole(cur.pval);      // what the event waits for, if it is older than these 64
+    const bool any_here_in = __any(here && is_in), any_here_use = __any(here && is_use);
+    double M = 0, t = 0, latev = 0;                              // the request's maximum (`seg` up) and completion time
+    u32 from = 0;                                                // events before this position are settled
+    while (from < cnt) {
+      const bool open = pos >= from;
+      const double free_at = sp + delta;                         // end of the previous kernel
+      const u64 open_m = __ballot(open);
+      if (o01 & open_m) {                                        // evictions
+        const double m = scan_max(is_out ? (open ? free_at + (seg - (A - tau)) : M) : 0.0);
+        if (is_out) { M = m; const double y = m - seg; t = A + (y > free_c ? y : free_c); }
+      }
+      double w = pv;
+      if (any_here_in) { const double x = lane_anyf(t, cur.src); if (here && is_in) w = x; }
+      if (in01 & open_m) {                                       // prefetches, not before their evictions
+        const double ready = free_at > w ? free_at : w;
+        const double m = scan_max(is_in ? (open ? ready + (seg - (A - tau)) : M) : 0.0);
+        if (is_in) { M = m; const double y = m - seg; t = A + (y > free_c ? y : free_c); }
+      }
+      if (any_here_use) { const double x = lane_anyf(t, cur.src); if (here && is_use) w = x; }
+      const u64 waits = __ballot(is_use && open && w > free_at);
+      const u32 fl = waits ? (u32)__builtin_ctzll(waits) : 0u;   // (the uses lie in their order)
+      const u32 f = waits ? (u32)__builtin_amdgcn_readlane((int)pos, (int)fl) : cnt - 1;       // the step ends with event f
+      const bool in_step = open && pos <= f && kind != EV_NONE;
+      if (!second && __any(in_step && pt >= K)) { second = true; delta_first = delta; }
+      if (is_use && in_step && pt >= K) {                        // lateness: beyond the previous kernel's end, before any wait of this one
+        const double prev_end = sp + (pt == use_pt ? delta_pt : delta);
+        latev = w > prev_end ? w - prev_end : 0.0;
+      }
+      const u64 um = use_m & __ballot(in_step);
+      if (um) {
+        const u32 upt = (u32)__builtin_amdgcn_readlane((int)pt, (int)(63u - (u32)__builtin_clzll(um)));
+        if (upt != use_pt) { use_pt = upt; delta_pt = delta; }
+      }
+      if (waits) {                                               // the kernel waits for this prefetch
+        const double pf = lane_getf(w, fl), spf = lane_getf(sp, fl);
+        if (use_pt >= K) {
+          stall += pf - (spf + delta);
+          if (stalled_pt != use_pt) { stalled_pt = use_pt; n_stalled += 1; }
+        }
+        delta = pf - spf;
+      }
+      from = f + 1;
+    }
+    // ---- results out ---------------------------------------------------------------------
+    if (out0_m) free0 = lane_getf(t, 63u - (u32)__builtin_clzll(out0_m));
+    if (out1_m) free1 = lane_getf(t, 63u - (u32)__builtin_clzll(out1_m));
+    if (in0_m) free2 = lane_getf(t, 63u - (u32)__builtin_clzll(in0_m));
+    if (in1_m) free3 = lane_getf(t, 63u - (u32)__builtin_clzll(in1_m));
+    if (is_out || is_in) res[base + pos] = (u64)t;
+    if (is_use && pt >= K) late[cur.l.i] = (u64)latev;
+    t_prev = t;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the next loads find what was just written (in order)
+    if (cnt < G10_WAVE) break;
+  }
+  if (!second) delta_first = delta;
+  if (lane == 0) {
+    st->iter_ns = T + (u64)(delta - delta_first);
+    st->stall_ns = (u64)stall;
     st->n_stalled = n_stalled;
   }
 }
@@ -312,12 +511,14 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
     hipLaunchKernelGGL(k_rp_events, dim3((n + G10_BLOCK - 1) / G10_BLOCK), dim3(G10_BLOCK), 0, s, (const g10_migration*)w->records,
                        (const uint2*)w->rec_ab, eager ? (const u32*)w->pf_gained : (const u32*)nullptr, n, K, rbits, keys, st);
     G10_HIP(hipGetLastError());
-    G10_TRY(radix_sort_u64(&keys, &alt, ne, bits_for(2ull * K) + 2 + rbits + 1, w->rp_hist, s));
+    G10_TRY(radix_sort_u64(&keys, &alt, ne, bits_for(2ull * K) + EV_BITS + rbits + 1, w->rp_hist, s));
     hipLaunchKernelGGL(k_rp_index, dim3((u32)((ne + G10_BLOCK - 1) / G10_BLOCK)), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)ne, n, rbits,
                        w->rp_pos);
     G10_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_replay, dim3(1), dim3(G10_WAVE), 0, s, (const u64*)keys, (u32)ne, (const g10_migration*)w->records, n, rbits,
+  // (a channel's transfers fit the iteration that they were planned for, w->T; each is made twice)
+  const bool exact = T < REPLAY_EXACT / 10 && w->T < REPLAY_EXACT / 10;
+  hipLaunchKernelGGL((exact ? k_replay : k_replay_long), dim3(1), dim3(G10_WAVE), 0, s, (const u64*)keys, (u32)ne, (const g10_migration*)w->records, n, rbits,
                      (const u32*)w->rp_pos, start, K, T, w->rp_res, w->rp_late, st);
   G10_HIP(hipGetLastError());
   ReplayStats hs;
