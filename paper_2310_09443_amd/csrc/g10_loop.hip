@@ -766,12 +766,11 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         const u64* const durc = tl.dur + s0;
         for (u32 st = 0; st < tl.spt; ++st) {
           const u32 j0 = s0 + st * 256u + lane, o = st * 256u + lane, jn = K - s0;
-          u64 p[4], v[4], sub[4];
+          u64 p[4], sub[4];
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
             const u32 j = o + i * 64u;
             p[i] = j < jn ? Pc[j] : 0ull;
-            v[i] = j < jn ? durc[j] : 0ull;
             sub[i] = 0;
           }
           if (st == 0) for (u32 pb = mb_; pb; pb &= pb - 1) lz_full += S->mem[__builtin_ctz(pb)].s;
@@ -787,26 +786,25 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             for (u32 i = 0; i < 4; ++i)
               if ((j0 + i * 64u - lo < n) != both) sub[i] += s;        // (beyond the timeline: not stored)
           }
-          u32 myfirst = NONE32;
+          u32 myfirst = NONE32, overs = 0;               // (overs: a bit per slot over the capacity)
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
-            const u32 j = j0 + i * 64u;
-            bool over = false;
-            if (j < K) {
-              const u64 before = p[i] - lz0, act = p[i] - sub[i] - lz;     // pressure before and after this pass
-              if (sub[i]) Pc[o + i * 64u] = p[i] - sub[i];
-              over = act > cap;
-              if (over) mn = act < mn ? act : mn;
-              else if (before > cap && myfirst == NONE32) myfirst = j;
-            }
-            if (!over) v[i] = 0;
+            const u64 before = p[i] - lz0, act = p[i] - sub[i] - lz;       // pressure before and after this pass
+            const bool in = o + i * 64u < jn;
+            if (in && sub[i]) Pc[o + i * 64u] = p[i] - sub[i];
+            const bool over = in && act > cap;
+            mn = over && act < mn ? act : mn;
+            overs |= over ? 1u << i : 0u;
+            if (in && !over && before > cap && myfirst == NONE32) myfirst = j0 + i * 64u;
           }
           if (first == NONE32) {
             first = wave_min(myfirst);
             if (first != NONE32 && st) carry = px[s0 + st * 256u].y;   // (nothing before this slot changes)
           }
-          if (first != NONE32) {                         // rewrite the prefix of the slots after it
-            u64 run[4];
+          if (first != NONE32) {                         // rewrite the prefix of the slots after it (most jobs let no slot drop)
+            u64 v[4], run[4];
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) v[i] = (overs >> i) & 1u ? durc[o + i * 64u] : 0ull;
             if (narrow) scan_strips<u32>(v, run, carry);
             else scan_strips<u64>(v, run, carry);
 #pragma unroll
@@ -1059,7 +1057,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   auto pick = [&](const Entry& e, const u32 slot, const Floor& fl, const u32 F, const u32 allowed, const bool fresh, const u32 odd) -> u32 {
     const u32 lane = thread_here() & 63u;
     const u64 s = ((u64)e.B.w << 32) | e.B.z;
-    const u32 L1 = e.A.x, R = e.A.y;
+    const u32 R = e.A.y;
     bool ok0 = e.ot0 != NONE64, ok1 = e.ot1 != NONE64, open = true;
     // free times before the ends of the windows, transfer times
     double f0L = e.O0.x, f0a = e.O0.y, f0b = e.I0.x, f0R = e.I0.y, f1L = e.O1.x, f1a = e.O1.y, f1b = e.I1.x, f1R = e.I1.y;
@@ -1108,24 +1106,21 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       ++m;
       // The free times of the entries become those that the picked migration leaves, and an entry that its destination
       // cannot carry any more gets the other destination, or none.
-      auto commit = [&](bool& ok, const u32 ea, const u32 eb, double& fL, double& fa, double& fb, double& fR, const double to, const double ti,
+      // (Where no entry's window has less left, none of them meets what the pick took: `chain` stays.)
+      auto commit = [&](bool& ok, double& fL, double& fa, double& fb, double& fR, const double to, const double ti,
                         double& all_o, double& all_i, u32& ch_o, u32& ch_i) {
-        const u32 wL1 = (u32)__builtin_amdgcn_readlane((int)L1, (int)bl), wR = (u32)__builtin_amdgcn_readlane((int)R, (int)bl);
-        const u32 wa = (u32)__builtin_amdgcn_readlane((int)ea, (int)bl), wb = (u32)__builtin_amdgcn_readlane((int)eb, (int)bl);
-        bool hit_o = L1 <= wa - 1 && wL1 <= ea - 1, hit_i = eb + 1 <= wR - 1 && wb + 1 <= R - 1;
-        if (wrap) { hit_o = cyc_overlap32(L1, ea - 1, wL1, wa - 1, K); hit_i = cyc_overlap32(eb + 1, R - 1, wb + 1, wR - 1, K); }
-        const bool may = open && ok;
-        const u64 any_o = __ballot(may && hit_o), any_i = __ballot(may && hit_i);
         const double ro = read_lanef(fL, bl), po = read_lanef(to, bl), ri = read_lanef(fR, bl), pi = read_lanef(ti, bl);
         const double nL = after_takingf(fL, all_o, ro, po, true, wrap), nR = after_takingf(fR, all_i, ri, pi, false, wrap);
-        fa = after_takingf(fa, all_o, ro, po, true, wrap); fb = after_takingf(fb, all_i, ri, pi, false, wrap);
-        if (open) { fL = nL; fR = nR; }                // (a picked one keeps its own)
+        const double na = after_takingf(fa, all_o, ro, po, true, wrap), nb = after_takingf(fb, all_i, ri, pi, false, wrap);
+        const double wo = na - nL, wi = nR - nb;
+        const bool may = open && ok;
+        ch_o |= __any(may && wo != fa - fL) ? 1u : 0u; ch_i |= __any(may && wi != fR - fb) ? 1u : 0u;
+        if (open) { fL = nL; fa = na; fb = nb; fR = nR; }      // (a picked one keeps its own)
         all_o -= po; all_i -= pi;
-        ch_o |= any_o ? 1u : 0u; ch_i |= any_i ? 1u : 0u;
-        ok = ok && fa - fL >= to && fR - fb >= ti;
+        ok = ok && wo >= to && wi >= ti;
       };
-      if (d == 0u) commit(ok0, e.A.z, e.A.w, f0L, f0a, f0b, f0R, to0, ti0, all_o0, all_i0, ch_o0, ch_i0);
-      else commit(ok1, e.B.x, e.B.y, f1L, f1a, f1b, f1R, to1, ti1, all_o1, all_i1, ch_o1, ch_i1);
+      if (d == 0u) commit(ok0, f0L, f0a, f0b, f0R, to0, ti0, all_o0, all_i0, ch_o0, ch_i0);
+      else commit(ok1, f1L, f1a, f1b, f1R, to1, ti1, all_o1, all_i1, ch_o1, ch_i1);
       if (m == allowed) break;
     }
     if (open && slot != NONE32) {                      // what a next round of picks goes on from
