@@ -217,7 +217,7 @@ __device__ __forceinline__ u64 tile_index(u32 r) {
 // The two kernels of a sort pass; blockIdx.x is the tile (the batched forms below put the job in blockIdx.y).
 template <class KT>
 __device__ __forceinline__ void radix_hist_tile(const KT* __restrict__ keys, u64 P, u32 shift, u32* __restrict__ hist, u32 nblocks,
-                                                u32* cnt) {
+                                                u32* cnt, bool by_tile = false) {
   cnt[threadIdx.x] = 0;
   __syncthreads();
 #pragma unroll
@@ -226,14 +226,14 @@ __device__ __forceinline__ void radix_hist_tile(const KT* __restrict__ keys, u64
     if (i < P) atomicAdd(&cnt[(keys[i] >> shift) & 255u], 1u);
   }
   __syncthreads();
-  hist[(u64)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];     // digit-major
+  hist[by_tile ? blockIdx.x * 256u + threadIdx.x : (u64)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];     // else by digit
 }
 
 template <class KT>
 __global__ __launch_bounds__(G10_BLOCK) void k_radix_hist(const KT* __restrict__ keys, u64 P, u32 shift,
-                                                         u32* __restrict__ hist, u32 nblocks) {
+                                                         u32* __restrict__ hist, u32 nblocks, u32 by_tile) {
   __shared__ u32 cnt[256];
-  radix_hist_tile<KT>(keys, P, shift, hist, nblocks, cnt);
+  radix_hist_tile<KT>(keys, P, shift, hist, nblocks, cnt, by_tile != 0);
 }
 
 // Exclusive scan of one digit's counts over the tiles, in place, by one workgroup; the digit's total goes
@@ -268,8 +268,18 @@ template <class KT, bool PAIRS>
 __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, KT* __restrict__ out,
                                                    const u32* __restrict__ vals, u32* __restrict__ vout,
                                                    u64 P, u32 shift, const u32* __restrict__ offs,
-                                                   u32 nblocks, u32 (*cnt)[256], u32* gbase, u32* tmp) {
+                                                   u32 nblocks, u32 (*cnt)[256], u32* gbase, u32* tmp, bool by_tile = false) {
   for (u32 i = threadIdx.x; i < G10_WAVES * 256; i += G10_BLOCK) (&cnt[0][0])[i] = 0;
+  // counts by tile, not scanned yet (few tiles): a thread per digit adds them up
+  u32 earlier = 0, every = 0;
+  if (by_tile) {
+#pragma unroll 8
+    for (u32 b = 0; b < nblocks; ++b) {
+      const u32 x = offs[b * 256u + threadIdx.x];
+      earlier += b < blockIdx.x ? x : 0u;
+      every += x;
+    }
+  }
   __syncthreads();
   const u32 w = wave_id(), l = lane_id();
   const u64 lt = (1ull << l) - 1ull;
@@ -298,7 +308,7 @@ __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, 
   {                                           // one thread per digit: offsets of the wavefronts, and where the tile's keys of the digit go
     const u32 d = threadIdx.x;
     u32 all;
-    const u32 before = block_scan_excl(offs[(u64)256 * nblocks + d], tmp, all);      // keys of lower digits
+    const u32 before = block_scan_excl(by_tile ? every : offs[(u64)256 * nblocks + d], tmp, all);      // keys of lower digits
     u32 run = 0;
 #pragma unroll
     for (u32 ww = 0; ww < G10_WAVES; ++ww) {
@@ -306,7 +316,7 @@ __device__ __forceinline__ void radix_scatter_tile(const KT* __restrict__ keys, 
       cnt[ww][d] = run;
       run += c;
     }
-    gbase[d] = before + offs[(u64)d * nblocks + blockIdx.x];
+    gbase[d] = before + (by_tile ? earlier : offs[(u64)d * nblocks + blockIdx.x]);
   }
   __syncthreads();
 #pragma unroll
@@ -325,11 +335,11 @@ template <class KT, bool PAIRS>
 __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter(const KT* __restrict__ keys, KT* __restrict__ out,
                                                             const u32* __restrict__ vals, u32* __restrict__ vout,
                                                             u64 P, u32 shift, const u32* __restrict__ offs,
-                                                            u32 nblocks) {
+                                                            u32 nblocks, u32 by_tile) {
   __shared__ u32 cnt[G10_WAVES][256];        // per wavefront: running count per digit
   __shared__ u32 gbase[256];
   __shared__ u32 tmp[G10_WAVES + 1];
-  radix_scatter_tile<KT, PAIRS>(keys, out, vals, vout, P, shift, offs, nblocks, cnt, gbase, tmp);
+  radix_scatter_tile<KT, PAIRS>(keys, out, vals, vout, P, shift, offs, nblocks, cnt, gbase, tmp, by_tile != 0);
 }
 
 // ---- a sort of at most SMALL keys in one launch ---------------------------------------------------------
@@ -337,6 +347,7 @@ __global__ __launch_bounds__(G10_BLOCK) void k_radix_scatter(const KT* __restric
 // turn: the passes of a small sort are bound by their launches (three each, 3 to 4 us apiece), not by
 // their keys.  The limit is what LDS takes with 64-bit keys and values beside them.
 constexpr u32 SMALL_WAVES = 16, SMALL = SMALL_WAVES * G10_WAVE * ITEMS;      // 8192
+constexpr u32 RADIX_DIRECT = 64;
 template <class KT, bool PAIRS>
 struct SmallSort {
   KT key[SMALL];
@@ -587,10 +598,8 @@ __global__ __launch_bounds__(G10_BLOCK) void k_begin(VitStats* st, u64* __restri
   for (u64 i = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; i < n; i += (u64)gridDim.x * G10_BLOCK) diff[i] = 0;
 }
 
-__global__ __launch_bounds__(G10_BLOCK) void k_lifetime_adds(const u64* __restrict__ ukeys, const u64* __restrict__ use_off,
-                                                            const u64* __restrict__ size, const uint8_t* __restrict__ glob,
-                                                            u32 N, u32 K, u32 kbits, u64* diff, VitStats* st) {
-  __shared__ u64 tmp[G10_WAVES + 1];
+__device__ __forceinline__ void lifetime_adds(const u64* ukeys, const u64* use_off, const u64* __restrict__ size, const uint8_t* __restrict__ glob,
+                                              u32 N, u32 K, u32 kbits, u64* diff, VitStats* st, u64* tmp) {
   const u64 kmask = (1ull << kbits) - 1ull;
   u64 gsum = 0, lo32 = 0, hi32 = 0;
   for (u64 t = (u64)blockIdx.x * G10_BLOCK + threadIdx.x; t < N; t += (u64)gridDim.x * G10_BLOCK) {
@@ -618,6 +627,80 @@ __global__ __launch_bounds__(G10_BLOCK) void k_lifetime_adds(const u64* __restri
     atomicAdd((unsigned long long*)&st->used_lo, (unsigned long long)lo32);
     atomicAdd((unsigned long long*)&st->used_hi, (unsigned long long)hi32);
   }
+}
+__global__ __launch_bounds__(G10_BLOCK) void k_lifetime_adds(const u64* __restrict__ ukeys, const u64* __restrict__ use_off,
+                                                            const u64* __restrict__ size, const uint8_t* __restrict__ glob,
+                                                            u32 N, u32 K, u32 kbits, u64* diff, VitStats* st) {
+  __shared__ u64 tmp[G10_WAVES + 1];
+  lifetime_adds(ukeys, use_off, size, glob, N, K, kbits, diff, st, tmp);
+}
+
+// ===========================================================================
+// distinct uses, use lists, periods and pressure of a trace of one tile of pairs, by one workgroup in one launch (six
+// otherwise, 4 us each where they have nothing to do).  The limits: one tile of pairs; a few rounds of the workgroup
+// over tensors and kernels.  Analysis of 189 pairs 96 -> 67 us, step of the 80-pair trace 399 -> 339.
+// ===========================================================================
+constexpr u32 TINY = 4096;
+__global__ __launch_bounds__(G10_BLOCK) void k_tiny(const u64* __restrict__ keys, u32 P, u32 K, u32 N, u32 kbits, u32 no_wrap,
+                                                   const u64* __restrict__ size, const uint8_t* __restrict__ glob, u64* ukeys, u32* use_k,
+                                                   u64* use_off, u32* per_t, u32* per_L, u32* per_R, u64* diff, VitStats* st) {
+  __shared__ u32 tmp[G10_WAVES + 1];
+  __shared__ u64 tmp64[G10_WAVES + 1];
+  const u64 kmask = (1ull << kbits) - 1ull;
+  u32 n = 0;
+  for (u32 r = 0; r < ITEMS; ++r) {               // distinct uses
+    const u32 i = r * G10_BLOCK + threadIdx.x;
+    const u64 k = i < P ? keys[i] : 0ull;
+    const bool is_new = i < P && (i == 0 || keys[i - 1] != k);
+    u32 total;
+    const u32 o = n + block_scan_excl((u32)is_new, tmp, total);
+    if (is_new) { ukeys[o] = k; use_k[o] = (u32)(k & kmask); }
+    n += total;
+  }
+  __syncthreads();
+  for (u32 t = threadIdx.x; t <= N; t += G10_BLOCK) {      // use lists
+    const u64 key = (u64)t << kbits;
+    u32 lo = 0, hi = n;
+    while (lo < hi) { const u32 mid = (lo + hi) / 2; if (ukeys[mid] < key) lo = mid + 1; else hi = mid; }
+    use_off[t] = lo;
+  }
+  __syncthreads();
+  u32 at = 0;
+  for (u32 r = 0; r < ITEMS; ++r) {               // periods
+    const u32 i = r * G10_BLOCK + threadIdx.x;
+    bool inner = false, wrap = false;
+    u32 t = 0, k = 0, kp = 0, kf = 0;
+    if (i < n) period_at(ukeys, use_off, glob, i, K, kbits, no_wrap, inner, wrap, t, k, kp, kf);
+    u32 total;
+    u32 o = at + block_scan_excl((u32)inner + (u32)wrap, tmp, total);
+    if (inner) { per_t[o] = t; per_L[o] = kp; per_R[o] = k; ++o; }
+    if (wrap) { per_t[o] = t; per_L[o] = k; per_R[o] = kf + K; }
+    at += total;
+  }
+  if (threadIdx.x == 0) { st->n_uses = n; st->n_periods = at; }
+  lifetime_adds(ukeys, use_off, size, glob, N, K, kbits, diff, st, tmp64);
+  __syncthreads();
+  u64 carry = 0, top = 0;                         // diff[0..K] into its exclusive sums, in place; their largest is the peak
+  for (u32 b0 = 0; b0 <= K; b0 += TILE) {
+    u64 v[ITEMS], acc = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const u32 j = b0 + threadIdx.x * ITEMS + i;
+      v[i] = j < K ? __hip_atomic_load(&diff[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+      acc += v[i];
+    }
+    u64 total, run = block_scan_excl(acc, tmp64, total);
+    run += carry;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const u32 j = b0 + threadIdx.x * ITEMS + i;
+      if (j <= K) { diff[j] = run; top = run > top ? run : top; }
+      run += v[i];
+    }
+    carry += total;
+  }
+  top = block_max(top, tmp64);
+  if (threadIdx.x == 0) st->peak = top;
 }
 
 // ===========================================================================
@@ -736,13 +819,17 @@ static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bi
     return G10_OK;
   }
   const u32 nb = (u32)((n + TILE - 1) / TILE);
+  // Few tiles: every scatter workgroup adds the counts of the tiles up itself (nb rows of 1 KB from L2, all in flight at
+  // once) and the launch in between falls away.  Analysis of 22 642 pairs 181 -> 160 us, 118 055 pairs (58 tiles) 214 -> 202;
+  // of 243 340 (119 tiles) 234 -> 240, so from 64 tiles on the counts are scanned in a launch of their own.
+  const u32 by_tile = nb <= RADIX_DIRECT ? 1u : 0u;
   for (u32 shift = 0; shift < bits; shift += 8) {
     const KT* from = src && shift == 0 ? src : *keys;
-    hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, from, n, shift, hist, nb);
-    hipLaunchKernelGGL(k_radix_rows, dim3(256), dim3(G10_BLOCK), 0, s, hist, nb);
+    hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, from, n, shift, hist, nb, by_tile);
+    if (!by_tile) hipLaunchKernelGGL(k_radix_rows, dim3(256), dim3(G10_BLOCK), 0, s, hist, nb);
     const u32* v = PAIRS && !(iota && shift == 0) ? *vals : nullptr;
     hipLaunchKernelGGL((k_radix_scatter<KT, PAIRS>), dim3(nb), dim3(G10_BLOCK), 0, s, from, *alt, v, PAIRS ? *valt : nullptr, n,
-                       shift, hist, nb);
+                       shift, hist, nb, by_tile);
     swap();
   }
   G10_HIP(hipGetLastError());
@@ -870,10 +957,19 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
   G10_TRY(keep.take(&h->ukeys, P));                               // upper bounds: no host round trip here
   G10_TRY(keep.take(&h->use_k, P));
   G10_TRY(keep.take(&h->use_off, (u64)N + 1));
+  G10_TRY(keep.take(&h->per_t, P));
+  G10_TRY(keep.take(&h->per_L, P));
+  G10_TRY(keep.take(&h->per_R, P));
   const u32 nb = (u32)((P + TILE - 1) / TILE);
   const u32 scanned = nb > DIRECT ? 1u : 0u;                      // (many tiles: their sums are scanned in a step of its own)
+  const u32 no_wrap = (h->flags & G10_NO_WRAP) ? 1u : 0u;
+  if (P) G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, s));
+  if (nb == 1 && N <= TINY && K <= TINY) {                        // (uses, periods and pressure in one launch)
+    hipLaunchKernelGGL(k_tiny, dim3(1), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)P, K, N, h->kbits, no_wrap, (const u64*)h->size,
+                       (const uint8_t*)h->glob, h->ukeys, h->use_k, h->use_off, h->per_t, h->per_L, h->per_R, h->pressure_buf, st);
+    G10_HIP(hipGetLastError());
+  } else {
   if (P) {
-    G10_TRY(radix_sort_u64(&keys, &alt, P, h->kbits + tbits, hist, s));
     if (nb > 1) hipLaunchKernelGGL(k_distinct_count, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)keys, P, sums);
     if (scanned) G10_TRY(scan_excl_u32(sums, sums, nb, sums + nb + 1, s));
     hipLaunchKernelGGL(k_distinct_write, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)keys, P, (const u32*)sums, nb, scanned, h->ukeys,
@@ -884,10 +980,6 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
   G10_HIP(hipGetLastError());
 
   // ---- inactive periods --------------------------------------------------------
-  const u32 no_wrap = (h->flags & G10_NO_WRAP) ? 1u : 0u;
-  G10_TRY(keep.take(&h->per_t, P));
-  G10_TRY(keep.take(&h->per_L, P));
-  G10_TRY(keep.take(&h->per_R, P));
   if (P) {
     if (nb > 1) hipLaunchKernelGGL(k_period_count, dim3(nb), dim3(G10_BLOCK), 0, s, (const u64*)h->ukeys, (const u64*)h->use_off, (const uint8_t*)h->glob,
                                    (const u64*)&st->n_uses, K, h->kbits, no_wrap, psums);
@@ -902,6 +994,7 @@ static int vitality_core(g10_plan_s* h, const g10_trace* tr, Pool& tmp, Pool& ke
   G10_HIP(hipGetLastError());
   // exclusive scan of diff[0..K] in place: buf[k + 1] = sum diff[0..k] = pressure[k]; its largest value is the peak
   G10_TRY(scan_excl<u64>(h->pressure_buf, h->pressure_buf, (u64)K, scratch64, s, &st->peak));
+  }
   if (out) {
     const u64 most = P > (u64)N + 1 ? P : (u64)N + 1;
     hipLaunchKernelGGL(k_results_out, dim3(grid_for(most > (u64)K + 1 ? most : (u64)K + 1, 1024)), dim3(G10_BLOCK), 0, s, (const VitStats*)st, *out, K, N,
