@@ -32,9 +32,9 @@ BYTES_PER_CAND_MOVED = 20      # what k_score_full itself streams per candidate:
 # HBM traffic of the loop kernel on config 5 from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, scaled by what the
 # same counters read for a 256 MiB copy): profiles/loop_stress_hbm_counters.md has the commands and the sums.  The
 # figures hold for the kernel they were taken on: reported only while the kernel's sources hash to what they did then.
-LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "c61cbc7aa10f7e234310373f3c0d443c85f9a5aff4cb2ba31f48627cbc6f8e67",
-                           "g10_plan_defs.h": "7ae4493afcabab906405a18050b7f52b19b60c6cd20aa6078fbd3bdfb8aca46c"},
-                "workload": "config 5", "fetch_bytes_per_plan": 83.0e6, "write_bytes_per_plan": 49.4e6, "launches_per_plan": 11.6}
+LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "6251218e9e4f851c2b7c85eb02c245c76694a41d89a01e8e89889cb3bb244d03",
+                           "g10_plan_defs.h": "9ae1db43f99ad1911291c7c8eb69d4da1c61da73da74be6eb19d0a40a929da81"},
+                "workload": "config 5", "fetch_bytes_per_plan": 63.8e6, "write_bytes_per_plan": 44.9e6, "launches_per_plan": 13.0}
 
 
 def loop_traffic_per_launch(config):

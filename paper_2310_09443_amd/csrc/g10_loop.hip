@@ -67,7 +67,7 @@ __host__ __device__ __forceinline__ WideView wide_view(void* blob) {
 }
 static_assert(sizeof(WideCtx) % 16 == 0 && sizeof(WideKey) % 16 == 0 && sizeof(Winner) % 16 == 0, "the arrays of the scoring kernel's block stay aligned");
 
-constexpr u32 MAXM = 16;      // migrations committed in one ranking pass at most (a multiple of 8, at most 16: the job words hold two sets of 16)
+constexpr u32 MAXM = 16;      // migrations committed in one round at most (a multiple of 8, at most 16: the job words hold two sets of 16)
 static_assert(MAXM % 8 == 0 && MAXM <= 16, "job words and chunk flags are laid out for 8 or 16");
 
 constexpr u32 MC_GUESS_SHIFT_MIN = 2;   // the widest margin of a pass's first threshold under the last benefit: 2^-this
@@ -110,7 +110,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 sel[G10_WAVE], nsel;    // the entries of the list it holds
   u32 hosts;                  // the round's migrations to host
   u32 pick_max, next;         // migrations picked in a round at most; NX_*
-  unsigned char spare[144];
+  unsigned char spare[144];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
@@ -1415,7 +1415,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     // round of commits ends with entries that might clear the floor, the steps are taken again from here
     // (cround > 0) instead of from a new ranking: with picks made beside the round's jobs (NX_PICKED), or
     // from the list scored again.  (A further round's picking took 4 to 5 us for two or three migrations while it
-    // stopped at the first window that met another; now 5 to 10 for eight to fifteen, half of them beside the jobs.)
+    // stopped at the first window that met another; now 5 to 9 for eight to twelve, half of them beside the jobs.)
     bool opened = false;                                 // the next pass's state is made
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     for (u32 cround = 0;; ++cround) {

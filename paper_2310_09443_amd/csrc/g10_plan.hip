@@ -886,6 +886,11 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // still score.  A batch ends its launches by the clock instead, so that no plan waits long for
   // the slowest one.  (Loops re-tiled every 64 / 128 / 192 rounds: stress 21.6 / 22.1 / 23.8 ms, ragged stress 4.44 / 4.62 /
   // 5.19; a 20-plan capacity sweep of the stress trace 35 ms at 64, 39 at 256.)
+  // (The other readings make one migration a round: every 128, in a batch every 256.)
+  auto retile_after = [&](const Inst& x) -> u32 {
+    const bool several = x.p->rank == G10_RANK_BENEFIT && x.p->area == G10_AREA_BAND;
+    return several ? RETILE_PASSES : count == 1 ? 2 * RETILE_PASSES : 4 * RETILE_PASSES;
+  };
   const bool timed_loop = n_active != 0;
   // The results of a finished plan: the pressure with the lazy adds applied and its peak, then the
   // copies to one block of pinned host memory (so that they run as plain DMA), grown when a plan
@@ -937,7 +942,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       la.g_keys = w->tkeys; la.ctl = w->ctl; la.records = w->records; la.rec_ab = w->rec_ab; la.dropped = w->dropped;
       la.rec_h = w->rec_h; la.g_hmat = w->g_hmat; la.g_hpend = w->g_hpend;
       la.cd = cands_of(x, x.cur); la.n_pad = x.n_pad; la.nt = x.nt; la.tshift = x.tsh;
-      la.pass_budget = x.n > RETILE_MIN_CANDS && count == 1 ? RETILE_PASSES : PASS_BUDGET;
+      la.pass_budget = x.n > RETILE_MIN_CANDS && count == 1 ? retile_after(x) : PASS_BUDGET;
       la.tick_budget = count > 1 ? BATCH_LAUNCH_TICKS : 0;
       // one plan ranked by benefit / cost: with the scoring kernel where the list is long and the
       // last round of launches scored much of it per pass (or none has run yet)
@@ -990,7 +995,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       }
       ++n_active;
       // (the cadence counts the rounds of commits: ranking passes and the further rounds made from their lists)
-      if (x.n > RETILE_MIN_CANDS && x.hc.passes + x.hc.more_rounds - x.seen_passes >= RETILE_PASSES) {
+      if (x.n > RETILE_MIN_CANDS && x.hc.passes + x.hc.more_rounds - x.seen_passes >= retile_after(x)) {
         x.seen_passes = x.hc.passes + x.hc.more_rounds;
         if (x.counted && x.hc.n_live < x.n) x.n = x.hc.n_live;   // live candidates come first in the list
         x.retile_cands += x.n;
