@@ -307,16 +307,28 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // progress; one that finds nothing to do ends at once.
   WideView wv = {};
   u32 resume = 0;
+  WideCtx wc = {};                                     // all that the launch reads of a pass left open, in one trip to memory:
+  WideKey wk[2];                                       // the scoring kernel's winners, two per thread: their rankings only (the
+                                                       // whole winners, 112 bytes each at 112-byte steps, kept this workgroup's
+                                                       // texture unit busy for 18 us a pass); the last thread: the best of the rounds before
+  u64 units0 = 0, second0 = 0, jobs0 = 0, launches0 = 0, wide0 = 0;   // the plan's counters
+  constexpr u32 MPT = (NT_MAX / 64 + LB - 1) / LB;
+  u64 wmark[MPT];
   if (tid == 0) S->no_wide = 0;
   if (WIDE && a.wide) {
     wv = wide_view(a.wide);
-    if (wv.ctx->pending) resume = wv.ctx->scored ? 1u : 2u;   // (the launches of a stream follow one another: it ran to its end)
+    wc = *wv.ctx;
+    wk[0] = wv.key[tid < LB - 1 ? tid : WIDE_WG];
+    wk[1] = wv.key[tid < LB - 1 ? tid + LB - 1 : WIDE_WG];
+#pragma unroll
+    for (u32 j = 0; j < MPT; ++j) wmark[j] = wv.smark[tid + j * LB < NT_MAX / 64 ? tid + j * LB : 0u];
+    units0 = ctl->units_scored; second0 = ctl->second_rounds; jobs0 = ctl->jobs_run; wide0 = ctl->wide_rounds;
+    if (wc.pending) resume = wc.scored ? 1u : 2u;   // (the launches of a stream follow one another: it ran to its end)
     if (tid == 0) {                                  // (read by everyone after the barrier that ends "state in")
-      const u32 seq = wv.ctx->seq + 1;
+      const u32 seq = wc.seq + 1;
       wv.ctx->seq = seq;
       S->no_wide = seq == a.wide_last_seq ? 1u : 0u;
     }
-    if (!resume && (ctl->done || (a.pass_stop && ctl->passes >= a.pass_stop))) return;
   }
   const u64 passes_before = ctl->passes;
   const u64 cap = ctl->gpu_cap, host_cap = ctl->host_cap, max_iter = ctl->max_iter, C = ctl->C;
@@ -324,9 +336,37 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   const u64 ivo0 = ctl->inv_out[0], ivo1 = ctl->inv_out[1], ivi0 = ctl->inv_in[0], ivi1 = ctl->inv_in[1];
 
   // ---- state in ----------------------------------------------------------------------
-  for (u32 i = tid; i < N_ARR * nch; i += LB) tot[i] = a.g_tot[i];
-  for (u32 i = tid; i < nch; i += LB) { lazyP[i] = a.g_lazyP[i]; minOver[i] = a.g_minOver[i]; lazyH[i] = a.g_lazyH[i]; hmax[i] = a.g_hmax[i]; hmat[i] = a.g_hmat[i]; hpend[i] = a.g_hpend[i]; }
-  for (u32 i = tid; i < nt; i += LB) keys[i] = a.g_keys[i];
+  // Every load is on its way before the first value is stored (a loop that copies word by word takes a trip to memory a
+  // turn, and a trip right behind a launch is long): 22.5 -> 21.0 us a launch where every pass takes one, the loops of 500
+  // passes by benefit / cost on the stress trace 18.3 -> 17.6 ms.
+  {
+    constexpr u32 TPT = (N_ARR * NCH_MAX + LB - 1) / LB, BPT = (N_ARR * (NCH_MAX + 1) + LB - 1) / LB, CPT = (NCH_MAX + LB - 1) / LB, KPT = 8;
+    static_assert(CPT == 1, "a thread per chunk");
+    const u32 nc0 = tid < nch ? tid : 0u;
+    u64 vt[TPT], vb[BPT];
+    u32 vk[KPT];
+#pragma unroll
+    for (u32 j = 0; j < TPT; ++j) { const u32 i = tid + j * LB; vt[j] = a.g_tot[i < N_ARR * nch ? i : 0u]; }
+#pragma unroll
+    for (u32 j = 0; j < BPT; ++j) { const u32 i = tid + j * LB; vb[j] = a.g_base[i < N_ARR * nb1 ? i : 0u]; }   // (level 1 as the plan's last launch left it, if there was one)
+#pragma unroll
+    for (u32 j = 0; j < KPT; ++j) { const u32 i = tid + j * LB; vk[j] = a.g_keys[i < nt ? i : 0u]; }
+    const u64 c_lp = a.g_lazyP[nc0], c_mo = a.g_minOver[nc0], c_lh = a.g_lazyH[nc0], c_hm = a.g_hmax[nc0];
+    const u32 c_ht = a.g_hmat[nc0], c_hp = a.g_hpend[nc0];
+    launches0 = ctl->launches;
+    const u32 ended = ctl->done;
+    if (WIDE && a.wide && !resume && (ended || (a.pass_stop && passes_before >= a.pass_stop))) return;
+#pragma unroll
+    for (u32 j = 0; j < TPT; ++j) { const u32 i = tid + j * LB; if (i < N_ARR * nch) tot[i] = vt[j]; }
+    if (launches0) {
+#pragma unroll
+      for (u32 j = 0; j < BPT; ++j) { const u32 i = tid + j * LB; if (i < N_ARR * nb1) base[i] = vb[j]; }
+    }
+#pragma unroll
+    for (u32 j = 0; j < KPT; ++j) { const u32 i = tid + j * LB; if (i < nt) keys[i] = vk[j]; }
+    for (u32 i = tid + KPT * LB; i < nt; i += LB) keys[i] = a.g_keys[i];
+    if (tid < nch) { lazyP[tid] = c_lp; minOver[tid] = c_mo; lazyH[tid] = c_lh; hmax[tid] = c_hm; hmat[tid] = c_ht; hpend[tid] = c_hp; }
+  }
   for (u32 i = tid; i < ns; i += LB) smark[i] = 0;
   if (tid == 0) {
     S->n_iter = ctl->n_iter; S->n_mig = ctl->n_mig; S->n_drop = ctl->n_drop; S->n_evals = ctl->n_evals;
@@ -372,13 +412,10 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       for (u32 q = 0; q < na; ++q) base[(u64)arrs[q] * nb1 + tid] = scr[q * LW + wave] + inc[q] - v[q];
     __syncthreads();
   };
-  if (ctl->launches) {                                  // level 1 as the plan's last launch left it
-    for (u32 i = tid; i < N_ARR * nb1; i += LB) base[i] = a.g_base[i];
-    __syncthreads();
-  } else {
+  if (!launches0) {                                     // the plan's first launch: level 1 from the chunk totals
     scan_bases(0, 1, 2, 3);
     scan_bases(3, 4, 0, 2);
-  }
+  } else __syncthreads();
 
 
   // Are times and sizes small enough for doubles (PICK_EXACT)?  May the further migrations of a pass be picked (K: ranges
@@ -1241,10 +1278,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     if (!thr) thr = NONE32;
     bool fresh = true;
     if (WIDE && resume) {                          // the tiles the open pass has scored, and the list of its open round
-      thr = wv.ctx->thr;
-      for (u32 i = tid; i < ns; i += LB) smark[i] = wv.smark[i];
-      for (u32 i = tid; i < wv.ctx->ntl; i += LB) alist[i] = wv.alist[i];
-      if (tid == 0) { S->ntl = wv.ctx->ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; }
+      thr = wc.thr;
+#pragma unroll
+      for (u32 j = 0; j < MPT; ++j) if (tid + j * LB < ns) smark[tid + j * LB] = wmark[j];
+#pragma unroll 4
+      for (u32 i = tid; i < wc.ntl; i += LB) alist[i] = wv.alist[i];
+      if (tid == 0) { S->ntl = wc.ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; }
       fresh = false;
       __syncthreads();
     }
@@ -1263,11 +1302,11 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       u32 rest;
       bool decided = false;                      // the best by bound is known
       if (WIDE && resume) {
-        rest = wv.ctx->rest;
-        rounds = wv.ctx->rounds;
-        pass_units = wv.ctx->pass_units;
+        rest = wc.rest;
+        rounds = wc.rounds;
+        pass_units = wc.pass_units;
         if (tid == LB - 1 && rounds) {                         // the best of the rounds before
-          if (resume == 1) { const WideKey k = wv.key[WIDE_WG]; mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = WIDE_WG; }
+          if (resume == 1) { const WideKey k = wk[0]; mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = WIDE_WG; }
           else mine = wv.win[WIDE_WG];
         }
       } else if (!again) {
@@ -1308,22 +1347,20 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             wv.ctx->ntl = ntl; wv.ctx->thr = thr; wv.ctx->rest = rest;
             wv.ctx->nwg = nu < WIDE_WG ? nu : WIDE_WG; wv.ctx->scored = 0;
             wv.ctx->pending = 1;
-            ctl->wide_rounds += 1;
+            ctl->wide_rounds = wide0 + 1;          // (one a launch at most)
           }
           wide_exit = true;
           break;
         }
         bool from_wide = false;
         if (WIDE && resume == 1) {
-          // the scoring kernel's winners, two per thread: their rankings only (the whole winners, 112 bytes
-          // each at 112-byte steps, kept this workgroup's texture unit busy for 18 us a pass)
           from_wide = true;
-          const u32 nw = wv.ctx->nwg;
+          const u32 nw = wc.nwg;
 #pragma unroll
           for (u32 q = 0; q < 2; ++q) {
             const u32 i = tid + q * (LB - 1);
             if (tid < LB - 1 && i < nw) {
-              const WideKey k = wv.key[i];
+              const WideKey k = wk[q];
               if ((k.hi | k.lo) != 0 && better_ratio(k.hi, k.lo, k.cost, (u32)k.cand, mine.hi, mine.lo, mine.cost, mine.cand)) {
                 mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = i;
               }
@@ -1781,6 +1818,11 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     ctl->thr_key = S->thr_key; ctl->status = S->status; ctl->done = S->done;
     ctl->gshift = S->gshift; ctl->pub = S->pub;
     ctl->overtime_after = base[(u64)A_OT * nb1 + nch];
+    if (WIDE && a.wide) {
+      ctl->units_scored = units0 + S->units; ctl->second_rounds = second0 + S->second; ctl->jobs_run = jobs0 + S->jobs;
+      ctl->launches = launches0 + 1; ctl->passes = passes_before + passes;
+      return;                                            // (the other counters do not move in this form)
+    }
     ctl->units_scored += S->units; ctl->second_rounds += S->second; ctl->jobs_run += S->jobs; ctl->launches += 1;
     ctl->passes += passes;
     ctl->area_evals += S->evals; ctl->area_refused += S->refused;
