@@ -45,8 +45,10 @@ struct WideCtx {
   u32 seq, pad[3];            // launches of the loop kernel on this plan so far
 };
 struct WideKey {              // the ranking of a winner on its own, for the arg-max over them
-  u64 hi, lo, cost, cand;
+  u64 hi, lo, cost;
+  u32 cand, skipped;          // (the largest key its workgroup took from the memo instead of scoring)
 };
+constexpr u32 MEMO_SPAN = 2;   // migrations a memo of the scoring kernel may be older than the list (one per pass)
 struct WideView {
   WideCtx* ctx;
   WideKey* key;               // [WIDE_WG + 1] of win[]
@@ -1283,7 +1285,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       for (u32 j = 0; j < MPT; ++j) if (tid + j * LB < ns) smark[tid + j * LB] = wmark[j];
 #pragma unroll 4
       for (u32 i = tid; i < wc.ntl; i += LB) alist[i] = wv.alist[i];
-      if (tid == 0) { S->ntl = wc.ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; }
+      if (tid == 0) { S->ntl = wc.ntl; S->filt = 0; S->nl = 0; S->restL = NONE32; S->stale_hot = 0; S->F2 = 0; }
       fresh = false;
       __syncthreads();
     }
@@ -1306,7 +1308,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         rounds = wc.rounds;
         pass_units = wc.pass_units;
         if (tid == LB - 1 && rounds) {                         // the best of the rounds before
-          if (resume == 1) { const WideKey k = wk[0]; mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = WIDE_WG; }
+          if (resume == 1) { const WideKey k = wk[0]; mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = k.cand; mine.slot = WIDE_WG; }
           else mine = wv.win[WIDE_WG];
         }
       } else if (!again) {
@@ -1342,7 +1344,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           for (u32 i = tid; i < ntl; i += LB) wv.alist[i] = alist[i];
           if (tid == 0) {
             wv.win[WIDE_WG] = S->mem[0];         // (hi = lo = 0: none yet)
-            wv.key[WIDE_WG] = WideKey{S->mem[0].hi, S->mem[0].lo, S->mem[0].cost, S->mem[0].cand};
+            wv.key[WIDE_WG] = WideKey{S->mem[0].hi, S->mem[0].lo, S->mem[0].cost, S->mem[0].cand, 0u};
             wv.ctx->rounds = rounds; wv.ctx->pass_units = pass_units;
             wv.ctx->ntl = ntl; wv.ctx->thr = thr; wv.ctx->rest = rest;
             wv.ctx->nwg = nu < WIDE_WG ? nu : WIDE_WG; wv.ctx->scored = 0;
@@ -1361,11 +1363,14 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             const u32 i = tid + q * (LB - 1);
             if (tid < LB - 1 && i < nw) {
               const WideKey k = wk[q];
-              if ((k.hi | k.lo) != 0 && better_ratio(k.hi, k.lo, k.cost, (u32)k.cand, mine.hi, mine.lo, mine.cost, mine.cand)) {
-                mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = (u32)k.cand; mine.slot = i;
+              floor2 = k.skipped > floor2 ? k.skipped : floor2;
+              if ((k.hi | k.lo) != 0 && better_ratio(k.hi, k.lo, k.cost, k.cand, mine.hi, mine.lo, mine.cost, mine.cand)) {
+                mine.hi = k.hi; mine.lo = k.lo; mine.cost = k.cost; mine.cand = k.cand; mine.slot = i;
               }
             }
           }
+          const u32 f2 = wave_max(floor2);
+          if (lane == 0 && f2) atomicMax(&S->F2, f2);
           const u32 nu = S->ntl << a.tshift;
           if (tid == 0) S->units += nu;
           pass_units += nu;
@@ -1419,10 +1424,18 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         }
         const u32 kb = key_dn_of<RATIO>(S->mem[0].hi, S->mem[0].lo, S->mem[0].cost);
         const u32 need = kb ? kb : 1u;
-        if (rest < need) decided = true;                 // every tile left out is below the best found
+        u32 out = rest;
+        if (WIDE && from_wide) {
+          // what the scoring kernel took from the memo lies under the threshold; where the best found does too, the
+          // round's tiles are taken again with a lower one
+          const u32 sk = uniform(S->F2);
+          if (sk > out) out = sk;
+          if (sk >= need) for (u32 i = tid; i < ns; i += LB) smark[i] = 0;
+        }
+        if (out < need) decided = true;                  // every tile left out is below the best found
         else {
           // a tile left out may hold an equal or better one; with nothing found yet, step down a few percent
-          thr = kb ? kb : (rest > (1u << 19) ? rest - (1u << 19) : 1u);
+          thr = kb ? kb : (out > (1u << 19) ? out - (1u << 19) : 1u);
           if (tid == 0) S->second += 1;
           __syncthreads();
           continue;
@@ -1833,6 +1846,16 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
 // The scoring kernel of WideCtx: workgroup b scores the units b, b + nwg, ... of the list the
 // loop kernel left (256 candidates each, scored as the loop kernel's own rounds score them),
 // raises the bounds of their tiles in device memory and leaves its best candidate in win[b].
+// A list is 160 000 to 215 000 candidates on the stress trace, because their bounds hold for either destination while the
+// policy keeps nearly all of them on flash; what bounded the kernel were the eight 16-byte gathers of each, from tables
+// larger than an L2.  So every candidate's bound and the key of its policy's destination are kept (LoopArgs::memo, with the
+// number of migrations there were, per wavefront of candidates).  A key kept can only have fallen since, unless a
+// migration to flash took channel time from a flash window of the candidate and it moves to host: where the few migrations
+// since meet none of its windows, and the key lies under the round's threshold, the candidate is not scored again: 12.6 -> 9.2 us a
+// launch, what is left are the launch, three dependent trips and the records.
+__device__ __forceinline__ bool may_meet(u64 K, u64 x, u64 y, u64 u, u64 v) {   // [x, y) and [u, v) of the doubled timeline, modulo K
+  return (x < v && u < y) || (x + K < v && u < y + K) || (x < v + K && u + K < y);
+}
 __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict__ plans) {
   extern __shared__ __align__(16) unsigned char smem[];
   const LoopArgs a = in_global(plans[0]);
@@ -1852,19 +1875,49 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
   Winner mine;
   mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   mine.s = 0; mine.fo_base = 0; mine.fi_end = 0; mine.tensor = 0; mine.pos = 0; mine.dest = 0; mine.L1 = 0; mine.R = 0; mine.a = 1; mine.b = 0;
-  const u32 nunits = wv.ctx->ntl << a.tshift;
+  const u32 nunits = wv.ctx->ntl << a.tshift, made = (u32)ctl->n_mig, top = wv.ctx->thr;
+  // Keys from a sixteenth of the threshold on are made again: where the best lies under the threshold, the round is not
+  // taken anew for a key that was kept.  (Kept from 0.7, 1/2, 1/4, 1/16 of it on: 52, 44, 28, 5 rounds more on 500
+  // passes, loops 17.9, 17.7, 17.3, 16.3 ms; nothing kept 18.3.)
+  const u32 thr = top > (1u << 25) ? top - (1u << 25) : 1u;
+  u32* const stamp = (u32*)(a.memo + a.n_pad);          // 1 + the migrations made when the 64 candidates' memo held (0: it holds nothing)
+  uint4 mh[MEMO_SPAN];                                  // the latest migrations: {L, R, size if to host} and {a, b}
+  uint2 mw[MEMO_SPAN];
+#pragma unroll
+  for (u32 j = 0; j < MEMO_SPAN; ++j) {
+    const u32 m = made > j ? made - 1u - j : 0u;
+    mh[j] = made > j ? a.rec_h[m] : make_uint4(0, 0, 0, 0);
+    mw[j] = made > j ? a.rec_ab[m] : make_uint2(0, 0);
+  }
+  u32 skipped = 0;
   for (u32 u = blockIdx.x; u < nunits; u += nwg) {
     const u32 t = wv.alist[u >> a.tshift];
     const u32 p = (((t << a.tshift) + (u & ((1u << a.tshift) - 1u))) << 8) + tid;
     const uint4 A = a.cd.A[p], B = a.cd.B[p];
-    const uint2 id = a.cd.id[p];
-    const Score r = score_candidate(pv, mc, A, B);
-    if (r.strike0) a.cd.A[p] = make_uint4(A.x, A.y, 1u, 0u);
-    if (r.strike1) a.cd.B[p] = make_uint4(1u, 0u, B.z, B.w);
+    const uint2 id = a.cd.id[p], was = a.memo[p];
+    const u32 st = uniform(stamp[p >> 6]), since = made + 1u - st;
+    bool anew = st == 0u || since > MEMO_SPAN || was.y >= thr;
+    if (st != 0u && since <= MEMO_SPAN) {
+#pragma unroll
+      for (u32 j = 0; j < MEMO_SPAN; ++j)
+        if (j < since && (mh[j].z | mh[j].w) == 0u && A.z <= A.w)      // (to flash)
+          anew |= may_meet(K, A.x, A.z, mh[j].x, mw[j].x) || may_meet(K, (u64)A.w + 1, A.y, (u64)mw[j].y + 1, mh[j].y);
+    }
+    if (lane == 0 && st != made + 1u) stamp[p >> 6] = made + 1u;
+    u32 kb = was.x;                                     // the candidate's bound
+    Score r;
+    r.ok0 = r.ok1 = false;
     u64 c0 = 1, c1 = 1;
-    if (r.ok0 || r.ok1) costs_of(mc, ((u64)B.w << 32) | B.z, c0, c1);
-    const u32 k0 = key_up_of<true>(r.h0, r.l0, c0), k1 = key_up_of<true>(r.h1, r.l1, c1);
-    const u32 k = wave_max(k0 > k1 ? k0 : k1);         // the tile's bound holds for either destination
+    if (anew) {
+      r = score_candidate(pv, mc, A, B);
+      if (r.strike0) a.cd.A[p] = make_uint4(A.x, A.y, 1u, 0u);
+      if (r.strike1) a.cd.B[p] = make_uint4(1u, 0u, B.z, B.w);
+      if (r.ok0 || r.ok1) costs_of(mc, ((u64)B.w << 32) | B.z, c0, c1);
+      const u32 k0 = key_up_of<true>(r.h0, r.l0, c0), k1 = key_up_of<true>(r.h1, r.l1, c1);
+      kb = k0 > k1 ? k0 : k1;                           // it holds for either destination
+      a.memo[p] = make_uint2(kb, r.ok0 ? k0 : k1);
+    } else if (was.y > skipped) skipped = was.y;
+    const u32 k = wave_max(kb);
     if (lane == 0 && k) atomicMax(&a.g_keys[t], k);
     const bool ok_any = r.ok0 || r.ok1;                // flash first; host only if flash cannot take it
     const u32 d = r.ok0 ? 0u : 1u;
@@ -1875,6 +1928,9 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
       mine.fo_base = r.fo_L; mine.fi_end = r.fi_R;
     }
   }
+  skipped = wave_max(skipped);
+  u32* const wskip = (u32*)(wwin + UNIT / 64);          // [UNIT / 64]
+  if (lane == 0) wskip[wave] = skipped;
   const u32 bl = wave_best_lane_ratio(mine.hi, mine.lo, mine.cost, mine.cand);
   if (bl == NONE32) { if (lane == 0) { mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; wwin[wave] = mine; } }
   else if (lane == bl) wwin[wave] = mine;
@@ -1884,10 +1940,11 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
     u32 c = NONE32;
     if (lane < UNIT / 64) { h = wwin[lane].hi; l = wwin[lane].lo; cs = wwin[lane].cost; c = wwin[lane].cand; }
     const u32 w = wave_best_lane_ratio(h, l, cs, c);
+    const u32 sk = wave_max(lane < UNIT / 64 ? wskip[lane] : 0u);
     if (lane == 0) {
       const Winner& b = wwin[w == NONE32 ? 0u : w];     // (none: any of the four, all empty)
       wv.win[blockIdx.x] = b;
-      wv.key[blockIdx.x] = WideKey{b.hi, b.lo, b.cost, b.cand};
+      wv.key[blockIdx.x] = WideKey{b.hi, b.lo, b.cost, b.cand, sk};
       // (No fence and no count of the workgroups that are done: the next launch on the stream sees what this one wrote.  A
       // device-wide fence in each of 840 workgroups writes an L2 back 840 times: 21.3 us a launch with it, 12.6 without.)
       if (blockIdx.x == 0) wv.ctx->scored = 1;
@@ -1901,7 +1958,7 @@ size_t loop_wide_bytes() { return WIDE_BYTES; }
 
 int loop_wide_launch(const LoopArgs* plans, u32 nch, hipStream_t s) {
   (void)nch;
-  const size_t lds = (UNIT / 64) * sizeof(Winner);
+  const size_t lds = (UNIT / 64) * (sizeof(Winner) + sizeof(u32));
   hipLaunchKernelGGL(k_wide_score, dim3(WIDE_WG), dim3(UNIT), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;

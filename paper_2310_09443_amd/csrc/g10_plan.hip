@@ -541,6 +541,7 @@ struct Inst {
   u64 times_check[16] = {};     // the checks of the plan's own durations come back here
   u64 seen_passes = 0;         // passes of the loop kernel done at the last re-tiling
   u64 seen_units = 0, seen_passes_w = 0;   // units scored and passes done when the last round of launches began
+  u32 memo_of = 0;             // 1 + the re-tilings the scoring kernel's memo was cleared after
   bool wide = false;           // long scoring rounds are left to the scoring kernel in the current round of launches
   u32 loop_seq = 0;            // launches of the loop kernel queued so far (with a block for the scoring kernel)
   u32 lead = 0;                // the plan of the batch whose candidate windows this one reads (itself, or an
@@ -946,13 +947,19 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       la.tick_budget = count > 1 ? BATCH_LAUNCH_TICKS : 0;
       // one plan ranked by benefit / cost: with the scoring kernel where the list is long and the
       // last round of launches scored much of it per pass (or none has run yet)
-      la.wide = nullptr; la.wide_min = 0; la.pass_stop = 0; la.wide_last_seq = 0;
+      la.wide = nullptr; la.memo = nullptr; la.wide_min = 0; la.pass_stop = 0; la.wide_last_seq = 0;
       x.wide = false;
       if (count == 1 && x.p->rank == G10_RANK_RATIO && x.p->area == G10_AREA_BAND && x.n >= WIDE_MIN_CANDS) {
         const u64 dp = x.hc.passes - x.seen_passes_w, du = x.hc.units_scored - x.seen_units;
         la.wide = w->wide;                       // (always there for this kind of plan: a pass may have been left open)
         if (x.launches == 1 || du >= (u64)WIDE_MIN_UNITS * dp) {
           x.wide = true;
+          // the memo lies in the other buffer of candidates, which nobody reads before the next re-tiling writes it
+          la.memo = (uint2*)w->cd[x.cur ^ 1].A;
+          if (x.memo_of != x.retiles + 1) {
+            G10_HIP(hipMemsetAsync(la.memo + x.n_pad, 0, (size_t)(x.n_pad / G10_WAVE) * sizeof(u32), s));
+            x.memo_of = x.retiles + 1;
+          }
           la.wide_min = WIDE_MIN_UNITS;
           la.pass_stop = x.hc.passes + la.pass_budget;
           la.wide_last_seq = x.loop_seq + la.pass_budget + 1;

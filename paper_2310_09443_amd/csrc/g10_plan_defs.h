@@ -299,6 +299,7 @@ struct LoopArgs {
   // the block of loop_wide_bytes() bytes the loop kernel and the scoring kernel talk through, and
   // the length of a round's list, in units of 256 candidates, from which it is left to that kernel
   void* wide;
+  uint2* memo;                // [n_pad] {bound, key of the policy's destination} of the candidates it scored, then a stamp per 64
   u32 wide_min;
   u32 wide_last_seq;          // the launch of the loop kernel (counted from 1 over the plan) behind which no scoring kernel is queued
 };
@@ -315,7 +316,7 @@ __device__ __forceinline__ LoopArgs in_global(LoopArgs a) {
   a.g_hmat = ::in_global(a.g_hmat); a.g_hpend = ::in_global(a.g_hpend); a.g_keys = ::in_global(a.g_keys);
   a.ctl = ::in_global(a.ctl); a.records = ::in_global(a.records); a.rec_ab = ::in_global(a.rec_ab); a.rec_h = ::in_global(a.rec_h);
   a.dropped = ::in_global(a.dropped);
-  a.wide = (void*)::in_global((char*)a.wide);
+  a.wide = (void*)::in_global((char*)a.wide); a.memo = ::in_global(a.memo);
   return a;
 }
 
