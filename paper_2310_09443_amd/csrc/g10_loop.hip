@@ -1897,10 +1897,13 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
     const uint2 id = a.cd.id[p], was = a.memo[p];
     const u32 st = uniform(stamp[p >> 6]), since = made + 1u - st;
     bool anew = st == 0u || since > MEMO_SPAN || was.y >= thr;
-    if (st != 0u && since <= MEMO_SPAN) {
+    // (A key that is the bound itself cannot be passed, wherever the candidate goes.  Flash struck since: a round of the
+    // loop kernel's own found it full.)
+    if (!anew && was.x > was.y) {
+      anew = A.z > A.w;
 #pragma unroll
       for (u32 j = 0; j < MEMO_SPAN; ++j)
-        if (j < since && (mh[j].z | mh[j].w) == 0u && A.z <= A.w)      // (to flash)
+        if (j < since && (mh[j].z | mh[j].w) == 0u)                    // (to flash)
           anew |= may_meet(K, A.x, A.z, mh[j].x, mw[j].x) || may_meet(K, (u64)A.w + 1, A.y, (u64)mw[j].y + 1, mh[j].y);
     }
     if (lane == 0 && st != made + 1u) stamp[p >> 6] = made + 1u;
