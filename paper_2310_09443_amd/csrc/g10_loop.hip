@@ -1492,8 +1492,10 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       __syncthreads();
     } else if (MC && !cround && !uniform(S->fast)) {     // the winner of the arg-max alone; the list goes on in the next round
       if (tid == 0) {
-        const u32 f2_ = S->F2;
-        S->m0 = 1; S->by_floor = 0; S->Fkeep = rest_final > f2_ ? rest_final : f2_;
+        // (by_floor stays where nothing on the list cleared this very floor: scoring the list again would find nothing.
+        // Where more candidates have one benefit than the list holds, that is every other pass.)
+        const u32 f2_ = S->F2, F = rest_final > f2_ ? rest_final : f2_;
+        S->m0 = 1; S->by_floor = S->by_floor && S->Fkeep == F ? 1u : 0u; S->Fkeep = F;
         S->chain[0][0] = 0; S->chain[0][1] = 0; S->chain[0][2] = 0; S->chain[0][3] = 0;
       }
       __syncthreads();
@@ -1634,6 +1636,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       continue;
     }
     if (MC && cround && need_exact) break;               // (the exact host-memory test is left to the next ranking pass)
+    if (cround) ++used;                                  // (rounds that commit something: a launch's budget is bounded by the candidates)
     if (need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
@@ -1811,7 +1814,6 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       __syncthreads();
     }
     if (opened) break;
-    ++used;
     }                                                    // (rounds of commits of one ranking pass)
     if (!opened) {                                       // (a refused candidate, or a test left to the next pass)
       __syncthreads();

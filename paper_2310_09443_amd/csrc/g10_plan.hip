@@ -535,7 +535,8 @@ struct Inst {
   u32 n = 0, n_valid = 0, max_tiles = 0;
   u32 tsh = 0, nt = 0, n_pad = 0;
   int cur = 0;                 // the candidate buffer the loop reads
-  u64 retiles = 0, retile_cands = 0, launches = 0, max_launches = 0, overtime_before = 0;
+  u64 retiles = 0, retile_cands = 0, launches = 0, overtime_before = 0;
+  u64 settled = 0, idle = 0;   // candidates committed or refused so far; launches since the last one that added to them
   bool counted = false;        // hc.n_live holds a count of the current list
   bool timed_full = false;
   u64 times_check[16] = {};     // the checks of the plan's own durations come back here
@@ -832,8 +833,6 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     Inst& x = I[i];
     x.overtime_before = x.hc.overtime_before;
     x.n_valid = x.n;
-    // every pass removes a candidate or stops, so the launches are bounded
-    x.max_launches = count == 1 ? (u64)x.n / RETILE_PASSES + 3 : (u64)x.n + 3;   // (a launch by the clock makes a pass at least)
     if (x.hc.done) continue;
     ++n_active;
     // the windows, and the copy of them the first scoring pass reads, may be another plan's; the first plan
@@ -933,7 +932,10 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       Inst& x = I[i];
       if (x.hc.done || 2 * x.p->area + x.p->rank != kind) continue;
       ++n_by_kind[kind];
-      if (x.launches++ > x.max_launches) return G10_EDEVICE;
+      // Every launch (with the scoring kernel: every round of launches) finishes a pass, and a pass commits or refuses a
+      // candidate or ends the plan: that bounds the launches by the candidates, however much of a launch's budget a pass takes.
+      if (x.idle > 3) return G10_EDEVICE;
+      ++x.launches;
       PlanWork* w = x.w;
       who[na] = i;
       LoopArgs& la = hargs[na++];
@@ -972,9 +974,9 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     }
     G10_HIP(hipMemcpyAsync(h->loop_args, hargs, (size_t)na * sizeof(LoopArgs), hipMemcpyHostToDevice, s));
     if (count == 1 && I[0].wide) {
-      // pairs of loop and scoring kernel: every launch of the loop kernel starts a pass at least (or
-      // finds nothing left to do), so this many reach the round's last pass; one more launch ends
-      // the pass the last pair may have left open
+      // pairs of loop and scoring kernel: a pair finishes a pass, or leaves it open with a round of it scored (or finds
+      // nothing left to do), so about this many reach the round's last pass; one more launch ends the pass the last
+      // pair may have left open
       for (u32 g = 0; g < hargs[0].pass_budget; ++g) {
         G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, s));
         G10_TRY(loop_wide_launch((const LoopArgs*)h->loop_args, I[0].w->nch, s));
@@ -990,7 +992,13 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     G10_HIP(hipMemcpyAsync(hctl, na > 1 ? ctl_side : I[who[0]].w->ctl, (size_t)na * sizeof(Ctl), hipMemcpyDeviceToHost, s));
     G10_HIP(hipStreamSynchronize(s));
     if (clocked) phase_end(1);
-    for (u32 k = 0; k < na; ++k) I[who[k]].hc = hctl[k];
+    for (u32 k = 0; k < na; ++k) {
+      Inst& x = I[who[k]];
+      x.hc = hctl[k];
+      const u64 settled = x.hc.n_mig + x.hc.n_drop;
+      x.idle = settled != x.settled ? 0 : x.idle + 1;
+      x.settled = settled;
+    }
     n_active = 0;
     u32 nj = 0;                                               // the re-tilings of a batch: every plan's in the same launches
     JobMax mx;
