@@ -420,9 +420,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   } else __syncthreads();
 
 
-  // Are times and sizes small enough for doubles (PICK_EXACT)?  May the further migrations of a pass be picked (K: ranges
-  // of the doubled timeline are compared in 32 bits)?
-  bool exact = ctl->smax < PICK_EXACT / 1000 && ((bwo0 | bwo1 | bwi0 | bwi1) < PICK_EXACT);
+  // Are times and sizes small enough for doubles (PICK_EXACT)?  May the further migrations of a pass be picked (not on
+  // timelines of 2^30 slots and more, which no test reaches)?
+  // (The ratio key in the band reading keeps to whole numbers: its rounds have one migration, for which a scan of 32-bit
+  // sums costs less than the clamped distances in doubles: a pass on 24 slots 9.1 us in doubles, 8.9 in whole numbers, on the
+  // stress trace 30.6 and 30.1, most of it to flash 35.0 and 34.4.  With the clipped area 10.8 and 11.0 on the ResNet trace.)
+  bool exact = !WIDE && ctl->smax < PICK_EXACT / 1000 && ((bwo0 | bwo1 | bwi0 | bwi1) < PICK_EXACT);
   for (u32 q = A_FO; q < N_ARR; ++q) exact = exact && base[(u64)q * nb1 + nch] < PICK_EXACT;
   exact = uniform((u32)exact) != 0u;
   const bool picks = MC && K < (1u << 30) && exact;
@@ -759,7 +762,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             }
             carry = (u64)end_res;
           } else {
-            // the same in whole numbers, for times over PICK_EXACT: one migration a pass
+            // the same in whole numbers, one migration a pass: the ratio key, and times over PICK_EXACT
 #pragma unroll
             for (u32 i = 0; i < 4; ++i) now[i] = fu[i];
             for (u32 pb = mask; pb; pb &= pb - 1) {
@@ -779,7 +782,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
                 }
               }
             }
-            scan_strips<u64>(now, run, carry);
+            if (narrow) scan_strips<u32>(now, run, carry);
+            else scan_strips<u64>(now, run, carry);
           }
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
