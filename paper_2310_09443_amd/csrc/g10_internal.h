@@ -194,9 +194,9 @@ size_t scan_scratch_elems(u64 n);
 int scan_excl_u32(const u32* in, u32* out, u64 n, u32* scratch, hipStream_t s);
 int scan_excl_u64(const u64* in, u64* out, u64 n, u64* scratch, hipStream_t s);
 
-// stable LSD radix sort of the low `bits` bits of 64-bit keys (see g10_vitality.hip)
+// stable LSD radix sort of 64-bit keys by their bits first_bit .. bits - 1 (see g10_vitality.hip)
 size_t radix_hist_elems(u64 n);
-int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, hipStream_t s);
+int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, hipStream_t s, u32 first_bit = 0);
 int radix_sort_u32_pairs(u32** keys, u32** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist,
                          hipStream_t s, bool iota = false);
 // Many such sorts in the same launches.  One job: n > 0 pairs in (keys, vals), buffers (alt, valt) of the same

@@ -437,6 +437,7 @@ struct PlanWork {
 
 // plan replay (g10_replay.hip)
 void replay_free(PlanWork* w);
+bool replay_key_fits(u32 K, u32 n);                           // the replay's events of n migrations on K slots sort by 64-bit keys
 
 // the loop kernel (g10_loop.hip)
 size_t loop_lds_bytes(u32 nch, u32 nt);                       // dynamic LDS of one workgroup, the least

@@ -46,7 +46,10 @@ struct ReplayStats {
   u64 bytes[2], busy_out[2], busy_in[2];
 };
 
-// keys of the events of migration i in both iterations; ~0 for events beyond the second iteration
+// Keys of the events of migration i in both iterations: {point, kind | migration, iteration}; ~0 for events beyond the
+// second iteration.  The events are written in the order of migration and iteration, and the sort is stable: so it goes by
+// point and kind alone (for the migrations of the encoder trace two digits; with the low bits four, and three of them for
+// the kind in three bits where two had done).
 __global__ __launch_bounds__(G10_BLOCK) void k_rp_events(const g10_migration* __restrict__ rec, const uint2* __restrict__ rec_ab,
                                                         const u32* __restrict__ gained, u32 n, u32 K, u32 rbits,
                                                         u64* __restrict__ keys, ReplayStats* __restrict__ st) {
@@ -462,6 +465,10 @@ void replay_free(PlanWork* w) {
   free(w->h_rp_late); w->h_rp_late = nullptr;
 }
 
+// Do the keys of n migrations on K slots fit 64 bits?  (They do not from 2^28 migrations and 2^29 slots on: with its
+// timelines and candidates such a plan takes more memory than a GPU has.)
+bool replay_key_fits(u32 K, u32 n) { return bits_for(2ull * K) + EV_BITS + bits_for(n ? n - 1 : 0) + 1 <= 64; }
+
 int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* out) {
   PlanWork* w = h->work;
   if (!w || !w->planned) return G10_EINVAL;
@@ -469,7 +476,7 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
   hipStream_t s = h->stream;
   const u32 K = h->K, n = (u32)w->plan_n_mig;
   const u64 ne = (u64)6 * n;
-  if (ne >= (1ull << 32)) return G10_EINVAL;
+  if (ne >= (1ull << 32) || !replay_key_fits(K, n)) return G10_EINVAL;
   // workspace of its own, sized for this plan's migrations
   if (!w->rp_arena || w->rp_cap < n) {
     G10_HIP(hipStreamSynchronize(s));
@@ -505,13 +512,13 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
   ReplayStats* st = (ReplayStats*)w->rp_stats;
   G10_HIP(hipMemsetAsync(st, 0, sizeof(ReplayStats), s));
   if (n) G10_HIP(hipMemsetAsync(w->rp_late, 0, (u64)n * 8, s));
-  u32 rbits = bits_for(n ? n - 1 : 0);
+  const u32 rbits = bits_for(n ? n - 1 : 0);
   u64 *keys = w->rp_keys, *alt = w->rp_alt;
   if (n) {
     hipLaunchKernelGGL(k_rp_events, dim3((n + G10_BLOCK - 1) / G10_BLOCK), dim3(G10_BLOCK), 0, s, (const g10_migration*)w->records,
                        (const uint2*)w->rec_ab, eager ? (const u32*)w->pf_gained : (const u32*)nullptr, n, K, rbits, keys, st);
     G10_HIP(hipGetLastError());
-    G10_TRY(radix_sort_u64(&keys, &alt, ne, bits_for(2ull * K) + EV_BITS + rbits + 1, w->rp_hist, s));
+    G10_TRY(radix_sort_u64(&keys, &alt, ne, rbits + 1 + EV_BITS + bits_for(2ull * K), w->rp_hist, s, rbits + 1));
     hipLaunchKernelGGL(k_rp_index, dim3((u32)((ne + G10_BLOCK - 1) / G10_BLOCK)), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)ne, n, rbits,
                        w->rp_pos);
     G10_HIP(hipGetLastError());

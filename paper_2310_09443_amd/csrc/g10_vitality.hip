@@ -358,7 +358,7 @@ struct SmallSort {
 template <class KT, bool PAIRS>
 __global__ __launch_bounds__(SMALL_WAVES * G10_WAVE) void k_radix_small(const KT* __restrict__ keys, KT* __restrict__ out,
                                                                        const u32* __restrict__ vals, u32* __restrict__ vout, u32 n,
-                                                                       u32 bits) {
+                                                                       u32 first_bit, u32 bits) {
   extern __shared__ __align__(16) unsigned char smem[];
   SmallSort<KT, PAIRS>& S = *(SmallSort<KT, PAIRS>*)smem;
   const u32 tid = threadIdx.x, w = tid >> 6, l = tid & 63u;
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(SMALL_WAVES * G10_WAVE) void k_radix_small(const KT
     key[r] = ok ? keys[i] : (KT)0;
     val[r] = PAIRS && ok ? (vals ? vals[i] : i) : 0u;          // no values given: the positions themselves
   }
-  for (u32 shift = 0; shift < bits; shift += 8) {
+  for (u32 shift = first_bit; shift < bits; shift += 8) {
     for (u32 i = tid; i < SMALL_WAVES * 256; i += SMALL_WAVES * G10_WAVE) (&S.cnt[0][0])[i] = 0;
     __syncthreads();
 #pragma unroll
@@ -786,7 +786,7 @@ int g10_hip_fail(hipError_t e, const char* file, int line) {
 size_t radix_hist_elems(u64 n) { return (size_t)256 * ((n + TILE - 1) / TILE ? (n + TILE - 1) / TILE : 1) + 256; }
 
 template <class KT, bool PAIRS>
-static int radix_small(const KT* keys, KT* out, const u32* vals, u32* vout, u64 n, u32 bits, hipStream_t s) {
+static int radix_small(const KT* keys, KT* out, const u32* vals, u32* vout, u64 n, u32 first_bit, u32 bits, hipStream_t s) {
   constexpr size_t lds = sizeof(SmallSort<KT, PAIRS>);
   static_assert(lds <= 160 * 1024, "the LDS of one workgroup");
   static std::atomic<bool> allowed[64];           // (per device: the attribute belongs to the kernel)
@@ -796,17 +796,18 @@ static int radix_small(const KT* keys, KT* out, const u32* vals, u32* vout, u64 
     G10_HIP(hipFuncSetAttribute((const void*)k_radix_small<KT, PAIRS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (dev >= 0 && dev < 64) allowed[dev].store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((k_radix_small<KT, PAIRS>), dim3(1), dim3(SMALL_WAVES * G10_WAVE), lds, s, keys, out, vals, vout, (u32)n, bits);
+  hipLaunchKernelGGL((k_radix_small<KT, PAIRS>), dim3(1), dim3(SMALL_WAVES * G10_WAVE), lds, s, keys, out, vals, vout, (u32)n, first_bit, bits);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }
 
-// LSD radix sort of the low `bits` bits of KT keys, 8 bits per pass, stable; PAIRS: with a 32-bit value carried
+// LSD radix sort of KT keys by their bits first_bit .. bits - 1, 8 bits per pass, stable; PAIRS: with a 32-bit value carried
 // along with every key (iota: the values are the positions 0..n-1 and *vals need not be filled).
 // On return *keys points at the sorted keys and *alt at the other buffer, *vals / *valt likewise.
 // hist: radix_hist_elems(n) words.  src: where given, the keys are read from there and *keys need not be filled.
 template <class KT, bool PAIRS>
-static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota, const KT* src = nullptr) {
+static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota, const KT* src = nullptr,
+                      u32 first_bit = 0) {
   if (n == 0) return G10_OK;
   auto swap = [&]() {
     KT* t = *keys; *keys = *alt; *alt = t;
@@ -814,7 +815,7 @@ static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bi
   };
   if (n <= SMALL) {
     const u32* v = PAIRS && !iota ? *vals : nullptr;
-    G10_TRY((radix_small<KT, PAIRS>(src ? src : *keys, *alt, v, PAIRS ? *valt : nullptr, n, bits, s)));
+    G10_TRY((radix_small<KT, PAIRS>(src ? src : *keys, *alt, v, PAIRS ? *valt : nullptr, n, first_bit, bits, s)));
     swap();
     return G10_OK;
   }
@@ -823,11 +824,11 @@ static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bi
   // once) and the launch in between falls away.  Analysis of 22 642 pairs 181 -> 160 us, 118 055 pairs (58 tiles) 214 -> 202;
   // of 243 340 (119 tiles) 234 -> 240, so from 64 tiles on the counts are scanned in a launch of their own.
   const u32 by_tile = nb <= RADIX_DIRECT ? 1u : 0u;
-  for (u32 shift = 0; shift < bits; shift += 8) {
-    const KT* from = src && shift == 0 ? src : *keys;
+  for (u32 shift = first_bit; shift < bits; shift += 8) {
+    const KT* from = src && shift == first_bit ? src : *keys;
     hipLaunchKernelGGL(k_radix_hist<KT>, dim3(nb), dim3(G10_BLOCK), 0, s, from, n, shift, hist, nb, by_tile);
     if (!by_tile) hipLaunchKernelGGL(k_radix_rows, dim3(256), dim3(G10_BLOCK), 0, s, hist, nb);
-    const u32* v = PAIRS && !(iota && shift == 0) ? *vals : nullptr;
+    const u32* v = PAIRS && !(iota && shift == first_bit) ? *vals : nullptr;
     hipLaunchKernelGGL((k_radix_scatter<KT, PAIRS>), dim3(nb), dim3(G10_BLOCK), 0, s, from, *alt, v, PAIRS ? *valt : nullptr, n,
                        shift, hist, nb, by_tile);
     swap();
@@ -835,8 +836,8 @@ static int radix_sort(KT** keys, KT** alt, u32** vals, u32** valt, u64 n, u32 bi
   G10_HIP(hipGetLastError());
   return G10_OK;
 }
-int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, hipStream_t s) {
-  return radix_sort<u64, false>(keys, alt, nullptr, nullptr, n, bits, hist, s, false);
+int radix_sort_u64(u64** keys, u64** alt, u64 n, u32 bits, u32* hist, hipStream_t s, u32 first_bit) {
+  return radix_sort<u64, false>(keys, alt, nullptr, nullptr, n, bits, hist, s, false, nullptr, first_bit);
 }
 int radix_sort_u64_pairs(u64** keys, u64** alt, u32** vals, u32** valt, u64 n, u32 bits, u32* hist, hipStream_t s, bool iota) {
   return radix_sort<u64, true>(keys, alt, vals, valt, n, bits, hist, s, iota);
