@@ -433,7 +433,13 @@ static const u32 SCORE_SORT_PASSES = (SCORE_SORT_BITS + 7) / 8;
 static const u32 PASS_BUDGET = 4096;             // ranking passes per launch of the loop kernel
 static const u32 RETILE_PASSES = 64;    // ... between two re-tilings of a long candidate list
 static const u32 RETILE_MIN_CANDS = 8192;        // shorter lists are never re-tiled
-static const u64 BATCH_LAUNCH_TICKS = 200000;    // a launch of a batch ends after 2 ms (100 MHz clock)
+// A launch of a batch ends after 2 ms (100 MHz clock), of a batch with long lists after 4: every launch is followed by
+// re-tilings, which take the whole chip one after the other and grow with the lists.  (Capacity sweeps with launches of 2 / 4 ms:
+// 0.2 million candidates, 20 plans 7.3 / 7.8 ms, 256 plans 36.1 / 36.0; 0.46 million, 20 plans 13.1 / 14.0, 128 plans 34.8 /
+// 33.8; 0.7 million, 19.4 / 19.5, 52.4 / 48.5; the stress trace, 1.15 million, 6, 20, 64, 128, 256 plans: 25.3, 31.7, 51.2,
+// 80.6, 139.7 / 25.7, 30.9, 50.3, 76.0, 124.9, and bandwidths, 20 and 256 plans 47.8, 181.7 / 45.5, 160.9.)
+static const u64 BATCH_LAUNCH_TICKS = 200000;
+static const u32 BATCH_LONG_LIST = 1u << 19;
 // Ranking by benefit / cost on a long list (one plan, band reading): a scoring round of WIDE_MIN_UNITS
 // x 256 candidates or more is left to a kernel on all compute units.  The loop kernel then ends in
 // the middle of its pass and takes it up in its next launch, so such launches are queued in pairs,
@@ -883,7 +889,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // ---- the greedy loops: one workgroup per plan, side by side ------------------------------
   // Long lists are put back into score order every RETILE_PASSES passes or more: the tiles the
   // loop looks at are dense with live candidates again, and the list is cut to those that can
-  // still score.  A batch ends its launches by the clock instead, so that no plan waits long for
+  // still score.  A batch ends its launches by the clock as well, so that no plan waits long for
   // the slowest one.  (Loops re-tiled every 64 / 128 / 192 rounds: stress 21.6 / 22.1 / 23.8 ms, ragged stress 4.44 / 4.62 /
   // 5.19; a 20-plan capacity sweep of the stress trace 35 ms at 64, 39 at 256.)
   // (The other readings make one migration a round: every 128, in a batch every 256.)
@@ -891,6 +897,9 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     const bool several = x.p->rank == G10_RANK_BENEFIT && x.p->area == G10_AREA_BAND;
     return several ? RETILE_PASSES : count == 1 ? 2 * RETILE_PASSES : 4 * RETILE_PASSES;
   };
+  u32 longest = 0;
+  for (u32 i = 0; i < count; ++i) longest = I[i].n_valid > longest ? I[i].n_valid : longest;
+  const u64 batch_ticks = longest > BATCH_LONG_LIST ? 2 * BATCH_LAUNCH_TICKS : BATCH_LAUNCH_TICKS;
   const bool timed_loop = n_active != 0;
   // The results of a finished plan: the pressure with the lazy adds applied and its peak, then the
   // copies to one block of pinned host memory (so that they run as plain DMA), grown when a plan
@@ -946,7 +955,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       la.rec_h = w->rec_h; la.g_hmat = w->g_hmat; la.g_hpend = w->g_hpend;
       la.cd = cands_of(x, x.cur); la.n_pad = x.n_pad; la.nt = x.nt; la.tshift = x.tsh;
       la.pass_budget = x.n > RETILE_MIN_CANDS && count == 1 ? retile_after(x) : PASS_BUDGET;
-      la.tick_budget = count > 1 ? BATCH_LAUNCH_TICKS : 0;
+      la.tick_budget = count > 1 ? batch_ticks : 0;
       // one plan ranked by benefit / cost: with the scoring kernel where the list is long and the
       // last round of launches scored much of it per pass (or none has run yet)
       la.wide = nullptr; la.memo = nullptr; la.wide_min = 0; la.pass_stop = 0; la.wide_last_seq = 0;
