@@ -370,6 +370,7 @@ def main():
         base_args = dict(gpu_cap=cap, host_cap=hcap, bw_out=w.bw_out_Bpus, bw_in=w.bw_in_Bpus)
         b0 = hv.plan(**base_args)
         out["readings"] = {}
+        # (cands_rescored_per_pass: candidates looked at; the scoring kernel of the ratio key keeps the keys of most and scores the others)
         for name, va in (("clipped_area", dict(area=1)), ("ratio_key_first_1000_passes", dict(rank=1, max_iters=1000))):
             hv.plan(**base_args, **va)
             rv = hv.plan(**base_args, **va)

@@ -166,8 +166,10 @@ typedef struct {
                                   (its entries scored again) instead of a new ranking pass        */
   uint64_t loop_retiles;       /* times the candidate list was put back into score order */
   uint64_t retile_cands;       /* candidates scored again by those re-orderings        */
-  uint64_t loop_cands_scored;  /* candidates re-scored inside the loop (tiles * 256, and the list
-                                  entries scored again for loop_more_rounds)              */
+  uint64_t loop_cands_scored;  /* candidates looked at inside the loop (tiles * 256, and the list
+                                  entries scored again for loop_more_rounds); all are scored, but for
+                                  those of a round left to the scoring kernel whose kept key cannot
+                                  have risen                                              */
   uint64_t loop_second_rounds; /* passes that needed a second scoring round            */
   uint64_t loop_chunk_jobs;    /* timeline chunks rewritten slot by slot               */
   uint64_t loop_area_evals;    /* G10_AREA_CLIPPED: clipped areas summed exactly       */

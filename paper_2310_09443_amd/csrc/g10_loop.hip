@@ -49,6 +49,7 @@ struct WideKey {              // the ranking of a winner on its own, for the arg
   u32 cand, skipped;          // (the largest key its workgroup took from the memo instead of scoring)
 };
 constexpr u32 MEMO_SPAN = 2;   // migrations a memo of the scoring kernel may be older than the list (one per pass)
+constexpr u32 MEMO_MARGIN = 2u << 24;   // kept keys lie this far under the round's threshold, in key steps (2^24 are a factor of two): a quarter of it
 struct WideView {
   WideCtx* ctx;
   WideKey* key;               // [WIDE_WG + 1] of win[]
@@ -230,11 +231,6 @@ __device__ __forceinline__ double ceil_divf(double x, double bw, double inv) {
   if (r < 0.0) { q -= 1.0; r += bw; }
   if (r >= bw) { q += 1.0; r -= bw; }
   return r > 0.0 ? q + 1.0 : q;
-}
-
-// Do the doubled slot ranges [x1, y1] and [x2, y2] (each shorter than K) share a kernel slot?  (K < 2^30)
-__device__ __forceinline__ bool cyc_overlap32(u32 x1, u32 y1, u32 x2, u32 y2, u32 K) {
-  return (x1 <= y2 && x2 <= y1) || (x1 + K <= y2 && x2 <= y1 + K) || (x1 <= y2 + K && x2 + K <= y1);
 }
 
 // The thread's number, anew: what is made from it here cannot be moved out of the loops around.  (The compiler keeps the
@@ -679,8 +675,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (type >= J_FO0 && type <= J_FI1) {
         if (ma_) {
         // channel time of the transfer windows of this destination that meet the chunk is taken
-        // from its slots (the windows of one pass are disjoint); the free-time prefix of the
-        // slots after the first window slot is rewritten from a scan of the new values
+        // from its slots, one migration after the other (windows of one round may meet, see chain);
+        // the slots, and the free-time prefixes before them, are stored where they changed
         const bool out = type < J_FI0;
         const u32 d = (type - J_FO0) & 1u;
         const u32 arr = (out ? A_FO : A_FI) + d;
@@ -1849,16 +1845,20 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   }
 }
 
-// The scoring kernel of WideCtx: workgroup b scores the units b, b + nwg, ... of the list the
-// loop kernel left (256 candidates each, scored as the loop kernel's own rounds score them),
-// raises the bounds of their tiles in device memory and leaves its best candidate in win[b].
+// The scoring kernel of WideCtx: workgroup b goes through the units b, b + nwg, ... of the list the loop kernel left (256
+// candidates each), scores the candidates whose key may have risen as the loop kernel's own rounds score theirs, raises the
+// bounds of the tiles in device memory and leaves its best candidate in win[b], its ranking and the largest key that it did
+// not make anew (skipped) in key[b].
 // A list is 160 000 to 215 000 candidates on the stress trace, because their bounds hold for either destination while the
 // policy keeps nearly all of them on flash; what bounded the kernel were the eight 16-byte gathers of each, from tables
 // larger than an L2.  So every candidate's bound and the key of its policy's destination are kept (LoopArgs::memo, with the
 // number of migrations there were, per wavefront of candidates).  A key kept can only have fallen since, unless a
 // migration to flash took channel time from a flash window of the candidate and it moves to host: where the few migrations
-// since meet none of its windows, and the key lies under the round's threshold, the candidate is not scored again: 12.6 -> 9.2 us a
-// launch, what is left are the launch, three dependent trips and the records.
+// since meet none of its windows, and the key lies under the round's threshold, the candidate is not scored again and counts
+// with the key kept: where the best that was scored does not clear the largest of those, the loop kernel has the round's
+// tiles taken again with its key as the threshold, which scores every candidate whose kept key could reach it; each time
+// the threshold falls, so the pass comes to its end.  12.6 -> 9.2 us a launch; what is left are the launch, three
+// dependent trips and the records.
 __device__ __forceinline__ bool may_meet(u64 K, u64 x, u64 y, u64 u, u64 v) {   // [x, y) and [u, v) of the doubled timeline, modulo K
   return (x < v && u < y) || (x + K < v && u < y + K) || (x < v + K && u + K < y);
 }
@@ -1882,10 +1882,13 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
   mine.hi = 0; mine.lo = 0; mine.cost = 1; mine.cand = NONE32; mine.exact = 0; mine.tau_o = 0; mine.tau_i = 0; mine.slot = NONE32;
   mine.s = 0; mine.fo_base = 0; mine.fi_end = 0; mine.tensor = 0; mine.pos = 0; mine.dest = 0; mine.L1 = 0; mine.R = 0; mine.a = 1; mine.b = 0;
   const u32 nunits = wv.ctx->ntl << a.tshift, made = (u32)ctl->n_mig, top = wv.ctx->thr;
-  // Keys from a sixteenth of the threshold on are made again: where the best lies under the threshold, the round is not
-  // taken anew for a key that was kept.  (Kept from 0.7, 1/2, 1/4, 1/16 of it on: 52, 44, 28, 5 rounds more on 500
-  // passes, loops 17.9, 17.7, 17.3, 16.3 ms; nothing kept 18.3.)
-  const u32 thr = top > (1u << 25) ? top - (1u << 25) : 1u;
+  // Keys from a quarter of the threshold on are made again: where the best lies under the threshold, the round is not
+  // taken anew for a key that was kept.  (Loops of 500 passes, every key made anew / kept under a quarter of the threshold:
+  // the stress trace on its own machine, where 498 migrations go to host and the keys on flash are a quarter of those to
+  // host, 17.5 / 15.1 ms, the same with margins of 0.84, 0.7 and a half, and 18.0 with a sixteenth, where nothing is
+  // kept; on machines whose migrations go to flash, to either, or cost the same on both the look at the
+  // migrations costs more than is kept: 16.9 / 17.2, 14.9 / 15.4, 13.8 / 14.3.)
+  const u32 thr = top > MEMO_MARGIN ? top - MEMO_MARGIN : 1u;
   u32* const stamp = (u32*)(a.memo + a.n_pad);          // 1 + the migrations made when the 64 candidates' memo held (0: it holds nothing)
   uint4 mh[MEMO_SPAN];                                  // the latest migrations: {L, R, size if to host} and {a, b}
   uint2 mw[MEMO_SPAN];

@@ -350,20 +350,6 @@ __device__ __forceinline__ u32 covered(u32 c0, u32 c1, u32 K, u32 x, u32 y) {
   return __builtin_elementwise_sub_sat(h0, l0) + __builtin_elementwise_sub_sat(h1, l1);
 }
 
-// first plain slot of [s0, s1] inside the doubled range [x, y] (y - x < K), or NONE32
-__device__ __forceinline__ u32 first_covered(u32 s0, u32 s1, u32 K, u32 x, u32 y) {
-  u32 first = NONE32;
-  if (y >= K) {                                   // the part in the second iteration: plain [max(x, K) - K, y - K]
-    const u32 x2 = x >= K ? x - K : 0u, lo = s0 > x2 ? s0 : x2, hi = s1 < y - K ? s1 : y - K;
-    if (lo <= hi) first = lo;
-  }
-  if (x < K) {                                    // the part in the first iteration: plain [x, min(y, K - 1)]
-    const u32 y1 = y < K - 1 ? y : K - 1, lo = s0 > x ? s0 : x, hi = s1 < y1 ? s1 : y1;
-    if (lo <= hi && lo < first) first = lo;
-  }
-  return first;
-}
-
 // position of plain slot j inside the doubled range [x, y] (y - x < K), or NONE32
 __device__ __forceinline__ u32 in_doubled(u32 j, u32 K, u32 x, u32 y) {
   if (j >= x && j <= y) return j;
