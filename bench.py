@@ -32,9 +32,9 @@ BYTES_PER_CAND_MOVED = 20      # what k_score_full itself streams per candidate:
 # HBM traffic of the loop kernel on config 5 from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, scaled by what the
 # same counters read for a 256 MiB copy): profiles/loop_stress_hbm_counters.md has the commands and the sums.  The
 # figures hold for the kernel they were taken on: reported only while the kernel's sources hash to what they did then.
-LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "f0789c31ee1ffba87bb29dfc4f4409ecfa4a9a1badb2aee671c61dfa3e65e101",
-                           "g10_plan_defs.h": "101ae99dbb1a7f4beed3a252717f26dba0e85397267f8beedfde274dc2536d50"},
-                "workload": "config 5", "fetch_bytes_per_plan": 63.8e6, "write_bytes_per_plan": 44.9e6, "launches_per_plan": 13.0}
+LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "31c397f79039f97e7d2f4db72c5be8ef0173e432777bf391ba422b3bcd89add6",
+                           "g10_plan_defs.h": "380aa5e449dd99921867e217dcdabccf67e1912c6710626bee9ae52c53ac8c99"},
+                "workload": "config 5", "fetch_bytes_per_plan": 61.8e6, "write_bytes_per_plan": 44.6e6, "launches_per_plan": 12.0}
 
 
 def loop_traffic_per_launch(config):
