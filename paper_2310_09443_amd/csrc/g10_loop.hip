@@ -1864,6 +1864,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
 __device__ __forceinline__ bool may_meet(u64 K, u64 x, u64 y, u64 u, u64 v) {   // [x, y) and [u, v) of the doubled timeline, modulo K
   return (x < v && u < y) || (x + K < v && u < y + K) || (x < v + K && u + K < y);
 }
+// KEPT: keys are kept (the memo is there).
+template <bool KEPT>
 __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict__ plans) {
   extern __shared__ __align__(16) unsigned char smem[];
   const LoopArgs a = in_global(plans[0]);
@@ -1888,8 +1890,7 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
   // taken anew for a key that was kept.  (Loops of 500 passes, every key made anew / kept under a quarter of the threshold:
   // the stress trace on its own machine, where 498 migrations go to host and the keys on flash are a quarter of those to
   // host, 17.5 / 15.1 ms, the same with margins of 0.84, 0.7 and a half, and 18.0 with a sixteenth, where nothing is
-  // kept; on machines whose migrations go to flash, to either, or cost the same on both the look at the
-  // migrations costs more than is kept: 16.9 / 17.2, 14.9 / 15.4, 13.8 / 14.3.)
+  // kept.  Where it does not pay nothing is kept: see MEMO_MIN_CANDS.)
   const u32 thr = top > MEMO_MARGIN ? top - MEMO_MARGIN : 1u;
   u32* const stamp = (u32*)(a.memo + a.n_pad);          // 1 + the migrations made when the 64 candidates' memo held (0: it holds nothing)
   uint4 mh[MEMO_SPAN];                                  // the latest migrations: {L, R, size if to host} and {a, b}
@@ -1905,8 +1906,8 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
     const u32 t = wv.alist[u >> a.tshift];
     const u32 p = (((t << a.tshift) + (u & ((1u << a.tshift) - 1u))) << 8) + tid;
     const uint4 A = a.cd.A[p], B = a.cd.B[p];
-    const uint2 id = a.cd.id[p], was = a.memo[p];
-    const u32 st = uniform(stamp[p >> 6]), since = made + 1u - st;
+    const uint2 id = a.cd.id[p], was = KEPT ? a.memo[p] : make_uint2(0u, 0u);
+    const u32 st = KEPT ? uniform(stamp[p >> 6]) : 0u, since = made + 1u - st;
     bool anew = st == 0u || since > MEMO_SPAN || was.y >= thr;
     // (A key that is the bound itself cannot be passed, wherever the candidate goes.  Flash struck since: a round of the
     // loop kernel's own found it full.)
@@ -1917,7 +1918,7 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
         if (j < since && (mh[j].z | mh[j].w) == 0u)                    // (to flash)
           anew |= may_meet(K, A.x, A.z, mh[j].x, mw[j].x) || may_meet(K, (u64)A.w + 1, A.y, (u64)mw[j].y + 1, mh[j].y);
     }
-    if (lane == 0 && st != made + 1u) stamp[p >> 6] = made + 1u;
+    if (KEPT && lane == 0 && st != made + 1u) stamp[p >> 6] = made + 1u;
     u32 kb = was.x;                                     // the candidate's bound
     Score r;
     r.ok0 = r.ok1 = false;
@@ -1929,7 +1930,7 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
       if (r.ok0 || r.ok1) costs_of(mc, ((u64)B.w << 32) | B.z, c0, c1);
       const u32 k0 = key_up_of<true>(r.h0, r.l0, c0), k1 = key_up_of<true>(r.h1, r.l1, c1);
       kb = k0 > k1 ? k0 : k1;                           // it holds for either destination
-      a.memo[p] = make_uint2(kb, r.ok0 ? k0 : k1);
+      if (KEPT) a.memo[p] = make_uint2(kb, r.ok0 ? k0 : k1);
     } else if (was.y > skipped) skipped = was.y;
     const u32 k = wave_max(kb);
     if (lane == 0 && k) atomicMax(&a.g_keys[t], k);
@@ -1970,10 +1971,9 @@ __global__ __launch_bounds__(UNIT) void k_wide_score(const LoopArgs* __restrict_
 
 size_t loop_wide_bytes() { return WIDE_BYTES; }
 
-int loop_wide_launch(const LoopArgs* plans, u32 nch, hipStream_t s) {
-  (void)nch;
+int loop_wide_launch(const LoopArgs* plans, bool kept, hipStream_t s) {
   const size_t lds = (UNIT / 64) * (sizeof(Winner) + sizeof(u32));
-  hipLaunchKernelGGL(k_wide_score, dim3(WIDE_WG), dim3(UNIT), lds, s, plans);
+  hipLaunchKernelGGL((kept ? k_wide_score<true> : k_wide_score<false>), dim3(WIDE_WG), dim3(UNIT), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }

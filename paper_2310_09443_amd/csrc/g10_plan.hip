@@ -446,6 +446,13 @@ static const u32 BATCH_LONG_LIST = 1u << 19;
 // a round of them ahead of what the host knows.
 static const u32 WIDE_MIN_UNITS = 32;
 static const u64 WIDE_MIN_CANDS = 65536;
+// The scoring kernel keeps keys (LoopArgs::memo) where its rounds are long and a kept key seldom turns out to be the best, which
+// costs the pair of launches again: on lists of this length, while no more than a quarter of the passes took a second round.
+// (Loops with every key made anew / kept, by flash, host in MB/s.  1.15 million candidates, 500 passes: 6000, 25000 16.9 / 14.6 ms;
+// 12000, 96000 19.3 / 17.8; 30000, 12000 16.2 / 16.6; 300, 2400, where most passes are taken again, 22.2 / 29.5, by this rule 22.8.
+// 0.35 million, 500 passes: 15.2 / 15.9; 14.8 / 14.8; 13.2 / 14.0; 16.5 / 18.1.  0.13 million, 600 passes: 16.7 / 17.7; 17.2 / 28.7;
+// 12.8 / 13.0; 14.2 / 15.2; 2000, 64000 18.2 / 24.3.)
+static const u32 MEMO_MIN_CANDS = 1u << 19;
 
 static u32 clamp_limit(u32 asked, u32 lib_max) { return asked == 0 || asked > lib_max ? lib_max : asked; }
 
@@ -547,7 +554,7 @@ struct Inst {
   bool timed_full = false;
   u64 times_check[16] = {};     // the checks of the plan's own durations come back here
   u64 seen_passes = 0;         // passes of the loop kernel done at the last re-tiling
-  u64 seen_units = 0, seen_passes_w = 0;   // units scored and passes done when the last round of launches began
+  u64 seen_units = 0, seen_passes_w = 0, seen_second = 0;   // units scored, passes and second rounds done when the last round of launches began
   u32 memo_of = 0;             // 1 + the re-tilings the scoring kernel's memo was cleared after
   bool wide = false;           // long scoring rounds are left to the scoring kernel in the current round of launches
   u32 loop_seq = 0;            // launches of the loop kernel queued so far (with a block for the scoring kernel)
@@ -966,17 +973,19 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
         if (x.launches == 1 || du >= (u64)WIDE_MIN_UNITS * dp) {
           x.wide = true;
           // the memo lies in the other buffer of candidates, which nobody reads before the next re-tiling writes it
-          la.memo = (uint2*)w->cd[x.cur ^ 1].A;
-          if (x.memo_of != x.retiles + 1) {
-            G10_HIP(hipMemsetAsync(la.memo + x.n_pad, 0, (size_t)(x.n_pad / G10_WAVE) * sizeof(u32), s));
-            x.memo_of = x.retiles + 1;
+          if (x.n >= MEMO_MIN_CANDS && 4 * (x.hc.second_rounds - x.seen_second) <= dp) {
+            la.memo = (uint2*)w->cd[x.cur ^ 1].A;
+            if (x.memo_of != x.retiles + 1) {
+              G10_HIP(hipMemsetAsync(la.memo + x.n_pad, 0, (size_t)(x.n_pad / G10_WAVE) * sizeof(u32), s));
+              x.memo_of = x.retiles + 1;
+            }
           }
           la.wide_min = WIDE_MIN_UNITS;
           la.pass_stop = x.hc.passes + la.pass_budget;
           la.wide_last_seq = x.loop_seq + la.pass_budget + 1;
         }
         x.loop_seq += x.wide ? la.pass_budget + 1 : 1;
-        x.seen_passes_w = x.hc.passes; x.seen_units = x.hc.units_scored;
+        x.seen_passes_w = x.hc.passes; x.seen_units = x.hc.units_scored; x.seen_second = x.hc.second_rounds;
       }
       const size_t l = loop_lds_taken(w->nch, x.nt);
       if (l > lds) lds = l;
@@ -988,7 +997,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       // pair may have left open
       for (u32 g = 0; g < hargs[0].pass_budget; ++g) {
         G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, s));
-        G10_TRY(loop_wide_launch((const LoopArgs*)h->loop_args, I[0].w->nch, s));
+        G10_TRY(loop_wide_launch((const LoopArgs*)h->loop_args, hargs[0].memo != nullptr, s));
       }
       G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, s));
     } else

@@ -299,7 +299,7 @@ struct LoopArgs {
   // the block of loop_wide_bytes() bytes the loop kernel and the scoring kernel talk through, and
   // the length of a round's list, in units of 256 candidates, from which it is left to that kernel
   void* wide;
-  uint2* memo;                // [n_pad] {bound, key of the policy's destination} of the candidates it scored, then a stamp per 64
+  uint2* memo;                // [n_pad] {bound, key of the policy's destination} of the candidates it scored, then a stamp per 64; NULL: keeps none
   u32 wide_min;
   u32 wide_last_seq;          // the launch of the loop kernel (counted from 1 over the plan) behind which no scoring kernel is queued
 };
@@ -431,5 +431,5 @@ size_t loop_lds_taken(u32 nch, u32 nt);                       // ... with as lon
 u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candidates on a timeline of nch chunks: 256 << this
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
-int loop_wide_launch(const g10::LoopArgs* plans, u32 nch, hipStream_t s);   // the scoring kernel for plans[0]
+int loop_wide_launch(const g10::LoopArgs* plans, bool kept, hipStream_t s);   // the scoring kernel for plans[0]; kept: with its memo
 int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, hipStream_t s);   // all of one ranking key and benefit reading

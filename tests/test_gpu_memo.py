@@ -1,5 +1,6 @@
-"""The scoring kernel of the ratio key keeps every candidate's key and scores again only what a migration to flash may have
-moved to host: plans with many migrations to flash, against the oracle, record by record."""
+"""The scoring kernel of the ratio key, and the keys it keeps between passes on lists of 2^19 candidates and more, of which it
+scores again only those that a migration to flash may have moved to host: plans with many migrations to flash, against the
+oracle, record by record."""
 import numpy as np
 import pytest
 
@@ -23,6 +24,25 @@ def test_keys_kept_between_passes(g10, flash, host, host_share):
         r = h.plan(rank=1, max_iters=limit, **a)
         assert r.loop_wide_rounds > 0            # (the scoring kernel took part; where bound and key are one, lists are soon short)
         assert_plan_equal(r, v.plan(rank=1, max_iters=limit, **a))
+    h.close()
+
+
+@pytest.mark.parametrize("flash, host, taken_again", [
+    (6000, 25000, False),     # keys on flash a little under a quarter of those to host
+    (12000, 96000, True),     # ... an eighth: migrations to flash and to host by turns, rounds whose best lies under a kept key
+    (300, 2400, True),        # the same with long windows, most of which meet: too many such rounds, nothing is kept any more
+    (30000, 12000, False),    # bound and key are one
+])
+def test_keys_kept_on_long_lists(g10, flash, host, taken_again):
+    w = traces.stress(K=20000, N=640000, seed=0x67100017)
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * 0.2), host_cap=v.peak, bw_out=(flash, host), bw_in=(flash, host), rank=1, max_iters=300)
+    r = h.plan(**a)
+    assert h._counters(0).score_full_cands >= 1 << 19
+    assert r.loop_wide_rounds > 128
+    if taken_again:
+        assert r.loop_second_rounds > 0
+    assert_plan_equal(r, v.plan(**a))
     h.close()
 
 
@@ -51,7 +71,7 @@ def _struck_between_long_rounds():
     add(9000, 98, 245)                    # A: absent 100 .. 243
     add(1, 1101, 1226)                    # x: absent 1103 .. 1224
     add(212, 120, 222)                    # fills x's tile: absent 122 .. 220, dead behind z
-    add(58_000, 400, 478)                 # B: absent 402 .. 476
+    add(520_000, 400, 478)                # B: absent 402 .. 476 (so many that keys are kept)
     N, K = len(size), 1300
     i = np.arange(N)
     at = np.array(uses)
@@ -59,7 +79,7 @@ def _struck_between_long_rounds():
     ballast = [(N, 0, 99), (N + 1, 245, K - 1), (N + 2, 100, 119), (N + 3, 223, 244)]
     ut = np.concatenate([i, i] + [np.full(b - a + 1, t) for t, a, b in ballast])
     uk = np.concatenate([at[:, 0], at[:, 1]] + [np.arange(a, b + 1) for _, a, b in ballast])
-    size = np.array(size + [60_000 * s] * 2 + [212 * s] * 2, np.uint64)
+    size = np.array(size + [600_000 * s] * 2 + [212 * s] * 2, np.uint64)
     tr = Trace("struck_between", np.full(K, slot, np.uint64), size, np.zeros(N + 4, np.uint8), uk.astype(np.uint32), ut.astype(np.uint32))
     return tr, s
 
@@ -72,6 +92,6 @@ def test_flash_struck_between_two_long_rounds(g10):
     assert p.records["tensor"][:4].tolist() == [2, 0, 9003, 1]             # z, w, x, c
     assert p.records["dest"][:4].tolist() == [1, 0, 1, 1]
     r = h.plan(**a)
-    assert r.loop_wide_rounds >= 2
+    assert r.loop_wide_rounds >= 2 and h._counters(0).score_full_cands >= 1 << 19
     assert_plan_equal(r, p)
     h.close()
