@@ -32,8 +32,8 @@ BYTES_PER_CAND_MOVED = 20      # what k_score_full itself streams per candidate:
 # HBM traffic of the loop kernel on config 5 from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, scaled by what the
 # same counters read for a 256 MiB copy): profiles/loop_stress_hbm_counters.md has the commands and the sums.  The
 # figures hold for the kernel they were taken on: reported only while the kernel's sources hash to what they did then.
-LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "31c397f79039f97e7d2f4db72c5be8ef0173e432777bf391ba422b3bcd89add6",
-                           "g10_plan_defs.h": "380aa5e449dd99921867e217dcdabccf67e1912c6710626bee9ae52c53ac8c99"},
+LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "8acc4cfb5eea55077a87eb112f852ea57f948defd4cc390d2522984930c29f79",
+                           "g10_plan_defs.h": "0c25d5b7de273e7ae90d70be831d9a27fb6c2cb9af69f3557e356914ea7a13c3"},
                 "workload": "config 5", "fetch_bytes_per_plan": 61.8e6, "write_bytes_per_plan": 44.6e6, "launches_per_plan": 12.0}
 
 
