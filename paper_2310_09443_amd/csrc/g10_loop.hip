@@ -82,6 +82,10 @@ constexpr u32 MC_GUESS_SHIFT_MIN = 2;   // the widest margin of a pass's first t
 // (Ranking passes of a plan with 64 in all / with 256 and the choice: ResNet 240 / 25, decoder 186 / 70, stress 500 / 160.)
 constexpr u32 LIST_MIN = 64, LIST_MAX = 256, LIST_VECS = 8, LIST_ENTRY = LIST_VECS * 16 + 8;
 static_assert(LIST_MIN == G10_WAVE && LIST_MAX % G10_WAVE == 0, "an entry a lane; strips of whole wavefronts");
+// LE_I's last word: host memory was found to have no room for the entry, at any later time neither, or to have room (as long
+// as nothing else goes there: Shared::probed).
+enum : u32 { E_NOROOM = 4, E_ROOM = 8 };
+constexpr u32 PK_DROP = 1u << 17, PK_ROOM = 1u << 18;   // a pick that host memory has no room for: the candidate is refused; one it has room for
 enum { LE_A = 0, LE_B = 1, LE_I = 2, LE_OT = 3, LE_O0 = 4, LE_I0 = 5, LE_O1 = 6, LE_I1 = 7 };
 // How far under the round's threshold a scored candidate's bound may lie to go on the list, in key steps (2^24 are a
 // factor of two); below zero: how far above it must lie.  Entries under the bound of the tiles left out cannot be picked,
@@ -105,15 +109,16 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   double bw[8];               // bandwidths out 0, 1, in 0, 1, and their reciprocals
   // What the picking wavefront leaves: the migrations of the round (entry of the list, destination << 16; free times
   // before the eviction window's start and the prefetch window's end as the picks before left them), and its state
-  u32 pick[MAXM];
+  u32 pick[MAXM];             // entry | destination << 16 | PK_DROP, PK_ROOM (to host only)
   double pick_o[MAXM], pick_i[MAXM];
   u32 chain[2][4];            // per round (even, odd) and channel (out 0, 1, in 0, 1): some windows of the round's picks and entries meet
   double all[4];              // free time of each channel behind the picks
   Floor left;
   u32 sel[G10_WAVE], nsel;    // the entries of the list it holds
-  u32 hosts;                  // the round's migrations to host
+  u32 dests[2];               // the round's migrations to flash, to host
+  u32 probed;                 // nothing has gone to host since the entries with E_ROOM were looked at
   u32 pick_max, next;         // migrations picked in a round at most; NX_*
-  unsigned char spare[144];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
+  unsigned char spare[136];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
@@ -260,7 +265,9 @@ __host__ __device__ __forceinline__ u32 list_cap(u32 nch, u32 nt) {
   return room >= LIST_MAX ? LIST_MAX : room < LIST_MIN ? LIST_MIN : (u32)room / G10_WAVE * G10_WAVE;
 }
 
-template <bool RATIO, bool CLIP>
+// TIGHT: the form for plans whose host memory refuses candidates, several of which go in one round (probe_host).  A form of its
+// own because what it adds to the chunk test, the picks and the commit costs the others 3 to 4 % (18 us a round, 0.6 more).
+template <bool RATIO, bool CLIP, bool TIGHT>
 __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopArgs* __restrict__ plans) {
   constexpr u32 LB = loop_threads(RATIO, CLIP), LW = LB / G10_WAVE;    // threads and wavefronts of this form
   // Several migrations per ranking pass (ranking by the benefit itself, band reading): after the
@@ -268,6 +275,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // certain that each would have won the pass after the one before it - see "more migrations
   // of the same pass" below.
   constexpr bool MC = !RATIO && !CLIP;
+  static_assert(MC || !TIGHT, "several migrations a pass");
   constexpr bool WIDE = RATIO && !CLIP;        // long scoring rounds may be left to the scoring kernel (see WideCtx)
   extern __shared__ __align__(16) unsigned char smem[];
   const LoopArgs a = in_global(plans[blockIdx.x]);   // one workgroup per plan
@@ -646,6 +654,34 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     __syncthreads();
   };
 
+  // Host bytes of four slots of chunk c (strip st) a lane, brought up to date with the migrations `from` .. `to` - 1 of the plan
+  // that cut the chunk (J_HQ says why they are not kept up to date).
+  auto host_slots = [&](const u32 c, const u32 st, const bool bring, const u32 from, const u32 to, u64 (&h)[4]) {
+    const u32 lane = thread_here() & 63u, j0 = c * CH + st * 256u + lane;
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) h[i] = j0 + i * 64u < K ? tl.H[j0 + i * 64u] : 0ull;
+    if (!bring) return;
+    for (u32 r0 = from; r0 < to; r0 += 64u) {
+      const u32 r = r0 + lane;
+      const uint4 q = r < to ? a.rec_h[r] : make_uint4(0u, 1u, 0u, 0u);
+      const u64 qs = ((u64)q.w << 32) | q.z;
+      u32 len = 0;
+      const u32 cv = qs ? cover(c, CH, K, q.x, q.y - 1, len) : 0u;
+      u64 rel = __ballot(qs != 0ull && cv != 0u && cv != len);
+      while (rel) {
+        const u32 l = (u32)__builtin_ctzll(rel);
+        rel &= rel - 1;
+        const u32 x = (u32)__builtin_amdgcn_readlane((int)q.x, (int)l), y = (u32)__builtin_amdgcn_readlane((int)q.y, (int)l);
+        const u64 sz = read_lane64(qs, l);
+#pragma unroll
+        for (u32 i = 0; i < 4; ++i)
+          if (j0 + i * 64u < K && in_doubled(j0 + i * 64u, K, x, y - 1) != NONE32) h[i] += sz;
+      }
+    }
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) if (j0 + i * 64u < K) tl.H[j0 + i * 64u] = h[i];
+  };
+
   // ---- chunk jobs: one wavefront rewrites one chunk of one timeline, for all migrations of the
   // pass at once.  A job word: chunk | kind << 16 | set A << 24 | set B << 40, the sets being
   // bits over the pass's migrations: for a transfer-window job, A = the migrations of that
@@ -691,8 +727,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         // inside it (loc) and all of the channel's (call).  Migrations behind the last one that meets the chunk change
         // nothing here.
         const bool linked = MC && uniform(S->chain[odd][type - J_FO0]) != 0u;
-        const u32 hosts = MC ? uniform(S->hosts) : 0u;
-        const u32 all_of = linked ? (d ? hosts : ~hosts) & ((2u << (31u - (u32)__builtin_clz(mask))) - 1u) : mask;
+        const u32 dests = MC ? uniform(S->dests[d]) : 0u;
+        const u32 all_of = linked ? dests & ((2u << (31u - (u32)__builtin_clz(mask))) - 1u) : mask;
         u64* const frc = fr + s0;
         ulonglong2* const tabc = tab + s0;
         u64 carry = 0;                                   // the chunk's new total
@@ -908,29 +944,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         for (u32 st = 0; st < tl.spt; ++st) {
           const u32 j0 = s0 + st * 256u + lane;
           u64 h[4];
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i) h[i] = j0 + i * 64u < K ? tl.H[j0 + i * 64u] : 0ull;
-          if (bring) {
-            for (u32 r0 = from; r0 < to; r0 += 64u) {
-              const u32 r = r0 + lane;
-              const uint4 q = r < to ? a.rec_h[r] : make_uint4(0u, 1u, 0u, 0u);
-              const u64 qs = ((u64)q.w << 32) | q.z;
-              u32 len = 0;
-              const u32 cv = qs ? cover(c, CH, K, q.x, q.y - 1, len) : 0u;
-              u64 rel = __ballot(qs != 0ull && cv != 0u && cv != len);
-              while (rel) {
-                const u32 l = (u32)__builtin_ctzll(rel);
-                rel &= rel - 1;
-                const u32 x = (u32)__builtin_amdgcn_readlane((int)q.x, (int)l), y = (u32)__builtin_amdgcn_readlane((int)q.y, (int)l);
-                const u64 sz = read_lane64(qs, l);
-#pragma unroll
-                for (u32 i = 0; i < 4; ++i)
-                  if (j0 + i * 64u < K && in_doubled(j0 + i * 64u, K, x, y - 1) != NONE32) h[i] += sz;
-              }
-            }
-#pragma unroll
-            for (u32 i = 0; i < 4; ++i) if (j0 + i * 64u < K) tl.H[j0 + i * 64u] = h[i];
-          }
+          host_slots(c, st, bring, from, to, h);
 #pragma unroll
           for (u32 i = 0; i < 4; ++i) {
             const u32 j = j0 + i * 64u;
@@ -951,6 +965,75 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       jb = begin + uniform(after);
     }
     if (tid == 0) S->jobs += end - begin;
+  };
+
+  // Host memory's room for the entries the picking wavefront holds that can go there only, in the state as it is: a chunk a
+  // wavefront; an entry whose period covers the chunk whole takes the chunk's maximum, one that cuts it the maximum over its
+  // slots.  An entry without room is refused when its turn comes (PK_DROP), in a round with others: it changes nothing that the
+  // entries behind it depend on.  (Loops, one candidate tested and refused per ranking pass / this: the encoder with 1031 refused
+  // ones 15.8 / 3.15 ms, the decoder with 6275 89.8 / 24.7, ResNet with 1118 19.5 / 5.5, 105 000 tensors on 29 000 slots with 102 894
+  // 2490 / 190.)
+  auto probe_host = [&]() {
+    const u32 tid = thread_here(), lane = tid & 63u;
+    u64* const room = (u64*)S->wave_win;                 // [64] the largest occupancy over the entry's period
+    static_assert(sizeof(S->wave_win) >= G10_WAVE * 8, "a word an entry");
+    if (tid < G10_WAVE) room[tid] = 0;
+    const u32 nl_ = uniform(S->nlist), n = nl_ < lcap ? nl_ : lcap;
+    if (tid < n) list_at(LE_I, tid).w &= ~E_ROOM;        // (of an earlier state)
+    __syncthreads();
+    u32 x = 1, y = 0, slot = NONE32;                     // its period [x, y] (y < x: none)
+    u64 s = 0;
+    if (lane < uniform(S->nsel)) {
+      const u32 i = S->sel[lane];
+      if (list_ot(i, 0) == NONE64 && list_ot(i, 1) != NONE64) {
+        const uint4 A = list_at(LE_A, i), B = list_at(LE_B, i);
+        slot = i; x = A.x; y = A.y - 1; s = ((u64)B.w << 32) | B.z;
+      }
+    }
+    const u32 to = (u32)uniform(S->n_mig);
+    for (u32 c = wave; c < nch; c += LW) {
+      u32 len = 0;
+      const u32 cv = slot != NONE32 ? cover(c, CH, K, x, y, len) : 0u;
+      const bool whole = cv != 0u && cv == len;
+      const u64 cuts = __ballot(cv != 0u && !whole);
+      if (!cuts && !__any(whole)) continue;
+      const bool bring = (uniform(hpend[c]) & 1u) != 0u;
+      u64 most = hmax[c];                                // (exact where nothing is missing)
+      if (cuts || bring) {
+        const u64 lz = lazyH[c];
+        const u32 from = uniform(hmat[c]);
+        u64 all = 0;
+        for (u32 st = 0; st < tl.spt; ++st) {
+          u64 h[4];
+          host_slots(c, st, bring, from, to, h);
+          const u32 j0 = c * CH + st * 256u + lane;
+          for (u64 cb = cuts; cb; cb &= cb - 1) {
+            const u32 l = (u32)__builtin_ctzll(cb);
+            const u32 px_ = (u32)__builtin_amdgcn_readlane((int)x, (int)l), py_ = (u32)__builtin_amdgcn_readlane((int)y, (int)l);
+            u64 mx = 0;
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u32 j = j0 + i * 64u;
+              if (j < K && in_doubled(j, K, px_, py_) != NONE32) mx = h[i] + lz > mx ? h[i] + lz : mx;
+            }
+            mx = wave_max(mx);
+            if (lane == 0) atomicMax((unsigned long long*)&room[l], (unsigned long long)mx);
+          }
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i) if (j0 + i * 64u < K) all = h[i] + lz > all ? h[i] + lz : all;
+        }
+        if (bring) {
+          most = wave_max(all);
+          if (lane == 0) { hmax[c] = most; hmat[c] = to; hpend[c] &= ~1u; }
+        }
+      }
+      if (whole) atomicMax((unsigned long long*)&room[lane], (unsigned long long)most);
+    }
+    __syncthreads();
+    if (wave == LW - 1) {
+      if (slot != NONE32) list_at(LE_I, slot).w |= s <= host_cap && room[lane] <= host_cap - s ? E_ROOM : E_NOROOM;
+      if (lane == 0) S->probed = 1;
+    }
   };
 
   // The next best entries of the list of the pass, a list entry per lane of one wavefront (entry: {period and windows},
@@ -1107,6 +1190,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
            all_i0 = fresh ? exactf(base[(u64)(A_FI + 0) * nb1 + nch]) : S->all[2], all_i1 = fresh ? exactf(base[(u64)(A_FI + 1) * nb1 + nch]) : S->all[3];
     u32 ch_o0 = 0, ch_o1 = 0, ch_i0 = 0, ch_i1 = 0;    // a window of a pick met one of an entry
     const bool wrap = __any(R > K);                    // (something lies in the second iteration)
+    const u64 noroom = TIGHT ? __ballot((e.I.w & E_NOROOM) != 0u) : 0ull;
+    const u32 word = TIGHT ? slot | (e.I.w & E_NOROOM ? PK_DROP : 0u) | (e.I.w & E_ROOM ? PK_ROOM : 0u) : slot;
     u32 m = 0, by_floor = 0;
     while (true) {
       // flash first; host only if flash cannot take it.  (0: cannot be picked)
@@ -1138,7 +1223,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       const u64 flash = __ballot(ok0);
       const u32 d = (flash >> bl) & 1ull ? 0u : 1u;
       if (lane == bl) {
-        S->pick[m] = slot | d << 16;
+        S->pick[m] = word | d << 16;
         S->pick_o[m] = d ? f1L : f0L; S->pick_i[m] = d ? f1R : f0R;
         open = false;
       }
@@ -1159,7 +1244,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         ok = ok && wo >= to && wi >= ti;
       };
       if (d == 0u) commit(ok0, f0L, f0a, f0b, f0R, to0, ti0, all_o0, all_i0, ch_o0, ch_i0);
-      else commit(ok1, f1L, f1a, f1b, f1R, to1, ti1, all_o1, all_i1, ch_o1, ch_i1);
+      else if (!TIGHT || !noroom || !((noroom >> bl) & 1ull)) commit(ok1, f1L, f1a, f1b, f1R, to1, ti1, all_o1, all_i1, ch_o1, ch_i1);   // (refused: nothing changes)
       if (m == allowed) break;
     }
     if (open && slot != NONE32) {                      // what a next round of picks goes on from
@@ -1243,10 +1328,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
 
   // What the next ranking pass finds: made by the last wavefront at the end of the pass before,
   // beside the level-1 update, so that a pass begins without a barrier of its own.
-  auto open_pass = [&]() {
+  // (undo: the pass before settled no candidate: it is none of Algorithm 1's)
+  auto open_pass = [&](const bool undo) {
     const u32 lane = thread_here() & 63u;
     for (u32 i = lane; i < ns; i += 64u) smark[i] = 0;   // no tile scored yet
     if (lane == 0) {
+      if (TIGHT && undo) { S->n_iter -= 1; S->n_evals -= C - S->n_mig - S->n_drop; }
       S->hq = 0; S->njobs = 0; S->ntl = 0; S->filt = 0;
       S->mem[0].hi = 0; S->mem[0].lo = 0;
       S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->by_floor = 0;
@@ -1256,8 +1343,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     }
   };
   __syncthreads();
-  if (wave == LW - 1) open_pass();
-  if (tid == 0) S->m0 = 1;
+  if (wave == LW - 1) open_pass(false);
+  if (tid == 0) { S->m0 = 1; S->probed = 0; }
   __syncthreads();
   // ---- passes ------------------------------------------------------------------------
   u32 passes = 0, used = 0;                          // ranking passes of this launch; with the further rounds of commits: what the budget counts
@@ -1467,6 +1554,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     // from the list scored again.  (A further round's picking took 4 to 5 us for two or three migrations while it
     // stopped at the first window that met another; now 5 to 9 for eight to twelve, half of them beside the jobs.)
     bool opened = false;                                 // the next pass's state is made
+    bool owed = true;                                    // no migration or refused candidate stands for the pass yet
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     for (u32 cround = 0;; ++cround) {
     const u32 tid = thread_here(), lane = tid & 63u;
@@ -1481,13 +1569,13 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (wave == LW - 1) {
         u32 allowed = uniform(S->pick_max);              // passes of Algorithm 1 this round may stand for
         const u32 F = uniform(S->Fkeep);
-        if (max_iter) { const u32 left = (u32)umin64(max_iter - uniform(S->n_iter), NONE32); allowed = left < allowed ? left : allowed; }
+        if (max_iter) { const u32 left = (u32)umin64(max_iter - uniform(S->n_iter) + (TIGHT && owed ? 1u : 0u), NONE32); allowed = left < allowed ? left : allowed; }
         Floor fl;
         const u32 slot = choose(n, F, fl);
         const Entry e = load_entry(slot);
         const u32 m = pick(e, slot, fl, F, allowed, true, cround & 1u);
         if (lane == 0) S->left = fl;
-        if (m == 0u) open_pass();                        // (nothing on the list clears the floor, or the bounds left out: the pass is over)
+        if (m == 0u) open_pass(owed);                    // (nothing on the list clears the floor, or the bounds left out: the pass is over)
       }
       __syncthreads();
     } else if (MC && !cround && !uniform(S->fast)) {     // the winner of the arg-max alone; the list goes on in the next round
@@ -1517,10 +1605,10 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     bool jobP = false;
     const bool picked = MC && (cround || uniform(S->fast));     // the round's migrations are entries of the list
     if (MC && picked && wave == LW - 1) {                // ... and in full in mem[] for what follows
-      u32 d = 0;
+      u32 d = 0, to = NONE32;                            // where it goes: 0, 1, or 3, refused
       if (lane < m0) {
         const u32 pk = S->pick[lane], slot = pk & 0xffffu;
-        d = pk >> 16;
+        d = (pk >> 16) & 1u; to = TIGHT && d ? (pk >> 16) & 3u : d;
         const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot), I = list_at(LE_I, slot);
         const u64 s = ((u64)B.w << 32) | B.z, ot = list_ot(slot, d);
         // (free times behind the earlier picks only where the jobs follow those: run_jobs)
@@ -1528,10 +1616,10 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         const double fi = S->chain[cround & 1u][2u + d] ? S->pick_i[lane] : list_f(d ? LE_I1 : LE_I0, slot).y;
         Winner& M = S->mem[lane];
         M.hi = __umul64hi(s, ot); M.lo = s * ot; M.s = s; M.fo_base = (u64)(long long)fo; M.fi_end = (u64)(long long)fi;
-        M.cand = I.x; M.tensor = I.y; M.pos = I.z; M.dest = d; M.L1 = A.x; M.R = A.y; M.a = d ? B.x : A.z; M.b = d ? B.y : A.w; M.slot = slot;
+        M.cand = I.x; M.tensor = I.y; M.pos = I.z; M.dest = to; M.L1 = A.x; M.R = A.y; M.a = d ? B.x : A.z; M.b = d ? B.y : A.w; M.slot = slot;
       }
-      const u64 hosts = __ballot(lane < m0 && d != 0u);
-      if (lane == 0) S->hosts = (u32)hosts;
+      const u64 hosts = __ballot(to == G10_HOST), flash = __ballot(to == G10_FLASH);
+      if (lane == 0) { S->dests[G10_FLASH] = (u32)flash; S->dests[G10_HOST] = (u32)hosts; }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     if (wave == LW - 1 && (lane & 31u) < m0) {           // transfer times (needed by the jobs and the records): out in lane i, in in lane 32 + i
@@ -1551,8 +1639,9 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         if (lane < m0) {
           const u32 pk = S->pick[lane], slot = pk & 0xffffu;
           const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot);
-          gd = pk >> 16;
-          gL = A.x; gR = A.y; ga = gd ? B.x : A.z; gb = gd ? B.y : A.w; gs = ((u64)B.w << 32) | B.z;
+          const u32 d = (pk >> 16) & 1u;
+          gd = TIGHT && d ? (pk >> 16) & 3u : d;
+          gL = A.x; gR = A.y; ga = d ? B.x : A.z; gb = d ? B.y : A.w; gs = ((u64)B.w << 32) | B.z;
         }
       } else if (lane < m0) { const Winner& M = S->mem[lane]; gL = M.L1; gR = M.R; ga = M.a; gb = M.b; gd = M.dest; gs = M.s; }
       const bool stale = MC && tid < nch && (hpend[tid] & 2u) != 0u;   // (picked by an over-capacity time that has fallen since)
@@ -1600,6 +1689,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           cutH |= tH && !fP ? bit : 0u;
         } else {
           if (__any(wait) && cut == MAXM) cut = i;
+          if (TIGHT && md != G10_FLASH) continue;                   // (refused: it changes nothing)
           eF |= nE > 0 ? bit : 0u;
           wF |= nW > 0 ? bit : 0u;
         }
@@ -1629,15 +1719,22 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     const u32 nj = uniform(S->njobs), cut_ = uniform(S->cut), need_exact = uniform(S->need_exact);   // (nj: the jobs of the round)
     u32 m = m0 < cut_ ? m0 : cut_;
     bool room = true;
+    // (the first one host memory might not hold: looked up for all entries, which are then picked again)
+    bool looked_up = false;
+    if (TIGHT && picked && need_exact) {
+      looked_up = (S->pick[0] & PK_ROOM) && S->probed;
+      __syncthreads();                                   // (both may change from here on)
+      if (!looked_up) { probe_host(); m = 0; }
+    }
     if (MC && m == 0u) {                                 // (not even the first stands: the list is scored again)
       __syncthreads();
       if (tid == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->next = NX_RESCORE; }
       __syncthreads();
       continue;
     }
-    if (MC && cround && need_exact) break;               // (the exact host-memory test is left to the next ranking pass)
-    if (cround) ++used;                                  // (rounds that commit something: a launch's budget is bounded by the candidates)
-    if (need_exact) {                                 // the winner alone; host memory slot by slot where its period cuts a chunk
+    if (MC && !TIGHT && cround && need_exact) break;     // (the exact host-memory test is left to the next ranking pass)
+    if (!owed) ++used;                                   // (rounds that commit something: a launch's budget is bounded by the candidates)
+    if (need_exact && !looked_up) {                   // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
       if (tid == 0) S->hq = 0;
@@ -1679,8 +1776,17 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     }
     if (wave == LW - 1) {
       const u64 nm = S->n_mig, nd = S->n_drop;
+      u32 drops = 0, hosts = 0;                            // of the round: candidates refused, migrations to host
       if (lane < m) {
         const Winner& M = S->mem[lane];
+        const u32 to = M.dest;
+        if (TIGHT) { drops = (u32)__ballot(to > G10_HOST); hosts = (u32)__ballot(to == G10_HOST); }
+        u64 at = nm + lane, at_d = nd;
+        bool refused = !room;
+        if (TIGHT && drops) {
+          const u32 before = (u32)__popc(drops & ((1u << lane) - 1u));
+          refused = to > G10_HOST; at -= before; at_d += before;
+        }
         const u32 mL1 = M.L1, mR = M.R, ma = M.a, mb = M.b;
         const u64 ms = M.s;
         a.cd.A[M.pos] = make_uint4(mL1, mR, 1u, 0u);       // the candidate leaves the live set
@@ -1690,20 +1796,20 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           list_at(LE_B, M.slot) = make_uint4(1u, 0u, (u32)ms, (u32)(ms >> 32));
           lkey[M.slot] = 0u; list_ot(M.slot, 0) = NONE64; list_ot(M.slot, 1) = NONE64;
         }
-        if (!room) {
-          g10_dropped dr; dr.iteration = S->n_iter - 1; dr.cand = M.cand; dr.reserved = 0;
-          a.dropped[nd] = dr;
+        if (refused) {
+          g10_dropped dr; dr.iteration = S->n_iter - (owed ? 1u : 0u) + lane; dr.cand = M.cand; dr.reserved = 0;
+          a.dropped[at_d] = dr;
         } else {
           g10_migration mg;
           mg.cand = M.cand; mg.tensor = M.tensor;
           mg.evict_after = mL1 - 1; mg.absent_first = ma >= K ? ma - K : ma; mg.absent_last = mb >= K ? mb - K : mb;
           mg.next_use = mR >= K ? mR - K : mR;
-          mg.dest = M.dest; mg.wraps = mR >= K ? 1u : 0u;
+          mg.dest = to; mg.wraps = mR >= K ? 1u : 0u;
           mg.size_bytes = ms; mg.t_out_ns = M.tau_o; mg.t_in_ns = M.tau_i; mg.benefit_lo = M.lo; mg.benefit_hi = M.hi;
-          a.records[nm + lane] = mg;
-          a.rec_ab[nm + lane] = make_uint2(ma, mb);
-          a.rec_h[nm + lane] = M.dest == G10_HOST ? make_uint4(mL1, mR, (u32)ms, (u32)(ms >> 32)) : make_uint4(mL1, mR, 0u, 0u);
-          atomicOr(&S->touched, (1u << (A_FO + M.dest)) | (1u << (A_FI + M.dest)));
+          a.records[at] = mg;
+          a.rec_ab[at] = make_uint2(ma, mb);
+          a.rec_h[at] = to == G10_HOST ? make_uint4(mL1, mR, (u32)ms, (u32)(ms >> 32)) : make_uint4(mL1, mR, 0u, 0u);
+          atomicOr(&S->touched, (1u << (A_FO + to)) | (1u << (A_FI + to)));
         }
       }
       if (lane == 0) {
@@ -1711,7 +1817,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         // where many candidates are nearly equal (a pass scored thousands) the margin halves; it
         // doubles when a pass ran out of candidates above the floor with little scored
         u32 gs = S->gshift;
-        if (cround) {
+        if (!owed) {
           // (the margin adapts once per ranking pass)
         } else if (WIDE && a.wide_min) {
           // with the scoring kernel a longer list costs little and a second round a pair of launches:
@@ -1724,7 +1830,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 18u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
-        if (MC && cround == 0u) {
+        if (MC && owed) {
           const u32 nl_ = S->nlist;
           const int pub = S->pub, mag = pub < 0 ? -pub : pub;
           int x = pub;
@@ -1740,23 +1846,28 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         const u64 nlo = glo - dlo;
         ghi = ghi - dhi - (glo < dlo ? 1ull : 0ull);
         S->thr_key = RATIO ? rkey_dn(ratio_approx(Z.hi, Z.lo, Z.cost) * (1.0 - 1.0 / (double)(1u << gs))) : upkey(ghi, nlo);
-        if (!room) { S->n_drop = nd + 1; S->more = 0; }
+        if (!room) {
+          S->n_drop = nd + 1; S->more = 0;
+          if (MC && !TIGHT && nd + 1 >= TIGHT_FROM) S->stop = 1;           // (the form for it goes on)
+        }
         else {
           // the passes of Algorithm 1 this round stands for beyond the one the ranking pass counted
           // at its top (a later round: all of its own), each with one live candidate fewer to rank
-          const u64 x = cround ? m : m - 1, live = C - nm - nd;
-          S->n_mig = nm + m; S->n_iter += x;
-          S->n_evals += cround ? x * live - x * (x - 1) / 2 : x * live - x * (x + 1) / 2;
+          const u64 x = owed ? m - 1 : m, live = C - nm - nd;
+          S->n_mig = nm + m - (u32)__popc(drops); S->n_drop = nd + (u32)__popc(drops); S->n_iter += x;
+          S->n_evals += owed ? x * live - x * (x + 1) / 2 : x * live - x * (x - 1) / 2;
+          if (TIGHT && hosts) S->probed = 0;
           // another round of commits from the same list: unless the picking ran out of entries above
           // the floor and every one it picked was committed
           const bool more = MC && S->nlist > 1u && picks && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
           S->more = more ? 1u : 0u;
           // (where the chunks cut a round short the next one picks little more than went through)
           if (MC) { const u32 pm = S->pick_max; S->pick_max = m < m0 ? (m + 2u < MAXM ? m + 2u : MAXM) : m0 == pm ? (2u * pm < MAXM ? 2u * pm : MAXM) : pm; }
-          if (cround) S->more_rounds += 1;
+          if (!owed) S->more_rounds += 1;
         }
       }
     }
+    owed = false;
     if (!room) { __syncthreads(); break; }
     if (MC && wave == LW - 1) {
       // Beside the jobs the last wavefront picks the next round's migrations: it knows the channels as this round leaves
@@ -1811,7 +1922,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         }
       }
       opened = !MC || !uniform(S->more);
-      if (opened) { if (wave == LW - 1) open_pass(); }
+      if (opened) { if (wave == LW - 1) open_pass(false); }
       else if (tid == LB - 1) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->hq = 0; }
       __syncthreads();
     }
@@ -1819,7 +1930,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     }                                                    // (rounds of commits of one ranking pass)
     if (!opened) {                                       // (a refused candidate, or a test left to the next pass)
       __syncthreads();
-      if (wave == LW - 1) open_pass();
+      if (wave == LW - 1) open_pass(owed);
       __syncthreads();
     }
   }
@@ -1996,9 +2107,10 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch) {
 }
 
 typedef void (*LoopKernel)(const LoopArgs*);
-static LoopKernel loop_kernel(u32 rank, u32 area) {
-  if (area == G10_AREA_CLIPPED) return rank == G10_RANK_RATIO ? k_loop<true, true> : k_loop<false, true>;
-  return rank == G10_RANK_RATIO ? k_loop<true, false> : k_loop<false, false>;
+static LoopKernel loop_kernel(u32 rank, u32 area, bool tight) {
+  if (area == G10_AREA_CLIPPED) return rank == G10_RANK_RATIO ? k_loop<true, true, false> : k_loop<false, true, false>;
+  if (rank == G10_RANK_RATIO) return k_loop<true, false, false>;
+  return tight ? k_loop<false, false, true> : k_loop<false, false, false>;
 }
 
 int loop_allow_large_lds() {                     // (once per device: the attribute belongs to the kernel, not to a handle)
@@ -2008,13 +2120,14 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
   if (dev >= 0 && dev < 64 && done[dev]) return G10_OK;
   for (u32 rank = 0; rank < 2; ++rank)
     for (u32 area = 0; area < 2; ++area)
-      G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
+      for (u32 tight = 0; tight < 2; ++tight)
+        G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area, tight != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
   if (dev >= 0 && dev < 64) done[dev] = true;
   return G10_OK;
 }
 
-int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, hipStream_t s) {
-  hipLaunchKernelGGL(loop_kernel(rank, area), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
+int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool tight, hipStream_t s) {
+  hipLaunchKernelGGL(loop_kernel(rank, area, tight), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }

@@ -19,6 +19,9 @@ constexpr u32 UNIT = 256;              // candidates scored by four wavefronts a
 constexpr u32 NCH_MAX = 512;           // chunks (level-1 arrays live in LDS)
 constexpr u32 NT_MAX = 8192;           // tiles  (their bounds live in LDS)
 constexpr size_t LDS_MAX = 160 * 1024; // LDS of a compute unit (both limits together are over it: loop_tile_shift)
+// A plan goes on in the loop kernel's form for little host memory from this many refused candidates on: the launch that ends for it
+// costs 25 us, a refused candidate 12 to 15 us in the general form and 1 to 6 in the other.
+constexpr u32 TIGHT_FROM = 8;
 constexpr u32 GUESS_SHIFT = 7;                 // first threshold of a pass: last benefit * (1 - 2^-shift), to begin with
 constexpr u32 GUESS_SHIFT_MAX = 24;            // the keys resolve no finer steps
 static_assert(WG >= NCH_MAX, "a thread per chunk");
@@ -432,4 +435,4 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candi
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
 int loop_wide_launch(const g10::LoopArgs* plans, bool kept, hipStream_t s);   // the scoring kernel for plans[0]; kept: with its memo
-int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, hipStream_t s);   // all of one ranking key and benefit reading
+int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool tight, hipStream_t s);   // all of one ranking key and benefit reading; tight: in the form for plans that refuse candidates
