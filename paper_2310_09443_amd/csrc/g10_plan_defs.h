@@ -416,7 +416,9 @@ struct PlanWork {
   u32 rp_cap = 0;
   u64 *rp_keys = nullptr, *rp_alt = nullptr, *rp_res = nullptr, *rp_late = nullptr, *rp_dur = nullptr, *rp_start = nullptr,
       *rp_tscr = nullptr;
-  u32 *rp_pos = nullptr, *rp_hist = nullptr;
+  double *rp_sp = nullptr, *rp_A = nullptr, *rp_off = nullptr;
+  uint2* rp_ev = nullptr;
+  u32 *rp_pos = nullptr, *rp_hist = nullptr, *rp_pred = nullptr;
   void *rp_stats = nullptr, *rp_tstats = nullptr;
   u64* h_rp_late = nullptr;
   void* arena = nullptr;        // the one device allocation all pointers above point into

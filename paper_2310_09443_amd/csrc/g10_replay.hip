@@ -20,13 +20,14 @@
 // where a kernel waits: up to the next such event every channel is a queue of known requests,
 // whose completion times come from running maxima.  So the walk takes a step per 64 events and one
 // per wait instead of one per event (1240 of the waits of the stress trace follow from one another,
-// whatever is walked at a time).  Bound by the latency of those steps.  Stress trace, 55 476 events with about
-// 1400 waits: 14.4 ms with one event after the other; 4.2 with a scan of the steps x -> max(x + a, b) per channel
-// in 64-bit integers and three dependent trips to memory before every 64 events; 2.6 with the lanes in the order of
-// their channels, running maxima in doubles - one for both channels of a direction - and every trip a
-// stage ahead.
-// A result needed by a later event of the same 64, or of the next, is passed on through a
-// register; older ones come from the result array.
+// whatever is walked at a time).  Bound by the latency of those steps, which one wavefront issues an instruction after the
+// other.  Stress trace, 55 476 events with about 3000 waits in both iterations: 14.4 ms with one event after the other; 4.2
+// with a scan of the steps x -> max(x + a, b) per channel in 64-bit integers and three dependent trips to memory before
+// every 64 events; 2.4 with the lanes in the order of their channels, running maxima in doubles and every trip a stage ahead;
+// 1.6 with all that an event needs worked out beforehand, in parallel (k_rp_expand), and loaded four steps ahead; 1.35 with
+// one running maximum for all four channels and a third of the instructions per wait (540 cycles, and 1080 per 64 events).
+// A result needed by a later event of the same 64 is passed on through a register, of the next 192 through LDS; older ones
+// come from the result array.
 
 #include "g10_plan_defs.h"
 
@@ -77,15 +78,30 @@ __global__ __launch_bounds__(G10_BLOCK) void k_rp_events(const g10_migration* __
   }
 }
 
-// where the eviction and the prefetch of every (iteration, migration) stand in the sorted order
-__global__ __launch_bounds__(G10_BLOCK) void k_rp_index(const u64* __restrict__ sorted, u32 ne, u32 n, u32 rbits,
+// The lanes of 64 neighbouring events in the order of their kinds: the lane that this lane's event goes to.  Each channel's
+// requests lie side by side then, in order, and the uses behind them.
+__device__ __forceinline__ u32 place_of(u32 kind) {
+  const u64 below = (1ull << lane_id()) - 1ull;
+  u32 at = 0, place = 0;
+#pragma unroll
+  for (u32 c = 0; c <= EV_NONE; ++c) {
+    const u64 m = __ballot(kind == c);
+    if (kind == c) place = at + (u32)__popcll(m & below);
+    at += (u32)__popcll(m);
+  }
+  return place;
+}
+__device__ __forceinline__ u32 kind_of(u64 k, u32 rbits) { return k == NONE64 ? (u32)EV_NONE : (u32)(k >> (rbits + 1)) & ((1u << EV_BITS) - 1u); }
+
+// where the eviction and the prefetch of every (iteration, migration) stand in the sorted order (by_lane: the place in their 64)
+__global__ __launch_bounds__(G10_BLOCK) void k_rp_index(const u64* __restrict__ sorted, u32 ne, u32 n, u32 rbits, u32 by_lane,
                                                        u32* __restrict__ pos_of) {
   const u32 p = blockIdx.x * G10_BLOCK + threadIdx.x;
-  if (p >= ne) return;
-  const u64 k = sorted[p];
-  if (k == NONE64) return;
-  const u32 c = (u32)(k & 1ull), i = (u32)((k >> 1) & ((1ull << rbits) - 1ull)), t = (u32)((k >> (rbits + 1)) & ((1u << EV_BITS) - 1u));
-  if (t != EV_USE) pos_of[(u64)((t >= EV_IN ? 2u : 0u) + c) * n + i] = p;
+  const u64 k = p < ne ? sorted[p] : NONE64;
+  const u32 t = kind_of(k, rbits), place = place_of(t);
+  if (t >= EV_USE) return;
+  const u32 c = (u32)(k & 1ull), i = (u32)((k >> 1) & ((1ull << rbits) - 1ull));
+  pos_of[(u64)((t >= EV_IN ? 2u : 0u) + c) * n + i] = by_lane ? (p & ~63u) + place : p;
 }
 
 __device__ __forceinline__ u64 lane_get(u64 v, u32 l) {
@@ -279,12 +295,19 @@ struct OpAddF {
 };
 // Running maximum of values that are not negative: lanes without a source give 0, and a maximum may meet a value twice,
 // so the steps across rows need no mask and no identity of their own.
+// (no NaN is compared: fmax() would cost an instruction more per operand, in case it were a signalling one)
+__device__ __forceinline__ double larger(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 template <int CTRL>
 __device__ __forceinline__ double max_from(double v) {
   const u64 x = (u64)__double_as_longlong(v);
   const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)x, CTRL, 0xf, 0xf, true);
   const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(x >> 32), CTRL, 0xf, 0xf, true);
-  return fmax(v, __longlong_as_double((long long)(((u64)hi << 32) | lo)));
+  const double o = __longlong_as_double((long long)(((u64)hi << 32) | lo));
+  return larger(v, o);
 }
 __device__ __forceinline__ double scan_max(double v) {
   v = max_from<0x111>(v);                                        // row_shr:1, 2, 4, 8
@@ -297,13 +320,83 @@ __device__ __forceinline__ double scan_max(double v) {
 __device__ __forceinline__ double scan_sum(double v) { return __longlong_as_double((long long)wave_scan_dpp<OpAddF>((u64)__double_as_longlong(v), (u64)0)); }
 __device__ __forceinline__ double lane_getf(double v, u32 l) { return __longlong_as_double((long long)lane_get((u64)__double_as_longlong(v), l)); }
 __device__ __forceinline__ double lane_anyf(double v, u32 l) { return __longlong_as_double((long long)lane_any((u64)__double_as_longlong(v), l)); }
+__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+// (at: four times the lane)
+__device__ __forceinline__ double lane_at(double v, u32 at) {
+  const u64 x = (u64)__double_as_longlong(v);
+  const u32 lo = (u32)__builtin_amdgcn_ds_bpermute((int)at, (int)(u32)x), hi = (u32)__builtin_amdgcn_ds_bpermute((int)at, (int)(u32)(x >> 32));
+  return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
 __device__ __forceinline__ u32 to_lane(u32 v, u32 l) { return (u32)__builtin_amdgcn_ds_permute((int)(l << 2), (int)v); }   // (l: another one for every lane)
 __device__ __forceinline__ double whole(u64 x) { return __fma_rn((double)(u32)(x >> 32), 4294967296.0, (double)(u32)x); }
 
-__global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sorted, u32 ne, const g10_migration* __restrict__ rec,
-                                                    u32 n, u32 rbits, const u32* __restrict__ pos_of,
-                                                    const u64* __restrict__ start, u32 K, u64 T, u64* __restrict__ res,
-                                                    u64* __restrict__ late, ReplayStats* __restrict__ st) {
+// What the walk needs of an event, worked out for all events at once, a wavefront per 64 events and in the order of their
+// lanes: a walk that gathered keys, records, times and predecessors itself waited for them at every 64.
+struct Walk {
+  double* sp;        // end of the kernel before the event's point without any stall
+  double* A;         // transfer times of its channel's requests among the 64, up to and with this one
+  double* off;       // what is added to the time it is ready to find the running maximum: its segment less the requests before it
+  uint2* ev;         // W_* below; migration
+  u32* pred;         // place of its eviction / its prefetch, NONE32 if it waits for none
+};
+enum : u32 {         // ev.x: kind in the lowest bits, then
+  W_POS = 3,         // where the event stands among the 64 (6 bits)
+  W_FIRST = 9,       // a use: the lane of the first use at its point among the 64 (6 bits)
+  W_CONT = 1u << 15, // ... and that point has uses among the 64 before
+  W_SECOND = 1u << 16              // in the second iteration
+};
+constexpr u32 WALK_STAGES = 4;                    // steps of 64 between an event's loads and its use
+constexpr u32 WALK_PAD = 2 * WALK_STAGES * 64;    // events (of no kind) behind the last: what is loaded ahead of the walk
+u64 walk_events(u64 ne) { return (ne + 64 * WALK_STAGES - 1) / (64 * WALK_STAGES) * (64 * WALK_STAGES) + WALK_PAD; }
+
+__global__ __launch_bounds__(G10_BLOCK) void k_rp_expand(const u64* __restrict__ sorted, u32 ne, u32 np, const g10_migration* __restrict__ rec, u32 n,
+                                                        u32 rbits, const u32* __restrict__ pos_of, const u64* __restrict__ start, u32 K, u64 T, Walk w) {
+  const u32 p = blockIdx.x * G10_BLOCK + threadIdx.x, lane = lane_id(), base = p & ~63u;
+  if (base >= np) return;
+  const u64 k0 = p < ne ? sorted[p] : NONE64;
+  const u32 place = place_of(kind_of(k0, rbits));
+  const u64 k = ((u64)to_lane((u32)(k0 >> 32), place) << 32) | to_lane((u32)k0, place);
+  const u32 pos = to_lane(lane, place), kind = kind_of(k, rbits);
+  const bool valid = kind != EV_NONE;
+  const u32 i = valid ? (u32)((k >> 1) & ((1ull << rbits) - 1ull)) : 0u, pt = valid ? (u32)(k >> (rbits + 1 + EV_BITS)) : 0u;
+  double tau = 0, sp = 0;
+  u32 pred = NONE32;
+  if (valid) {
+    if (kind < EV_USE) tau = whole(kind < EV_IN ? rec[i].t_out_ns : rec[i].t_in_ns);
+    sp = whole(pt < K ? start[pt] : start[pt - K] + T);
+    if (kind >= EV_IN) pred = pos_of[(u64)((kind == EV_USE ? 2u : 0u) + (u32)(k & 1ull)) * n + i];
+  }
+  // sums of the transfer times per channel
+  const double sum = scan_sum(tau);
+  double before = 0;
+#pragma unroll
+  for (u32 c = EV_OUT; c < EV_USE; ++c) {
+    const u64 m = __ballot(kind == c);
+    const double x = m ? lane_getf(sum - tau, (u32)__builtin_ctzll(m)) : 0.0;
+    if (kind == c) before = x;
+  }
+  const double A = sum - before;
+  // the uses by point: they lie in the order of their points
+  const u64 use_m = __ballot(kind == EV_USE);
+  const u32 pt_left = (u32)__shfl_up((int)pt, 1);
+  const u64 heads = __ballot(kind == EV_USE && (!((use_m << 1) >> lane & 1ull) || pt_left != pt));
+  const u64 mine = heads & (((1ull << lane) - 1ull) | (1ull << lane));
+  const u32 first = kind == EV_USE ? 63u - (u32)__builtin_clzll(mine) : 0u;
+  // (uses at one point are neighbours in the sorted order: the point goes on if the event before these 64 is one of its uses)
+  bool cont = false;
+  if (base && use_m) {
+    const u64 kp = sorted[base - 1];
+    cont = kind == EV_USE && first == (u32)__builtin_ctzll(use_m) && kind_of(kp, rbits) == EV_USE && (u32)(kp >> (rbits + 1 + EV_BITS)) == pt;
+  }
+  w.sp[p] = sp; w.A[p] = A; w.off[p] = (double)(kind + 1u) * SEGMENT - (A - tau);
+  w.ev[p] = make_uint2(kind | (pos << W_POS) | (first << W_FIRST) | (cont ? W_CONT : 0u) | (pt >= K ? W_SECOND : 0u), i);
+  w.pred[p] = pred;
+}
+
+__global__ __launch_bounds__(G10_WAVE) void k_replay(Walk w, u32 steps, u64 T, double* __restrict__ res, u64* __restrict__ late,
+                                                    ReplayStats* __restrict__ st) {
+  // results of the last steps (those before have come back from memory when they are needed)
+  __shared__ double recent[WALK_STAGES * 64];
   const u32 lane = threadIdx.x;
   const u64 below = (1ull << lane) - 1ull;
   // the state of the walk; the same in every lane
@@ -311,145 +404,103 @@ __global__ __launch_bounds__(G10_WAVE) void k_replay(const u64* __restrict__ sor
   double delta_first = 0;               // the same when the second iteration begins
   bool second = false;
   double free0 = 0, free1 = 0, free2 = 0, free3 = 0;       // when each channel is free again (out 0, 1, in 0, 1)
-  double stall = 0;
-  u64 n_stalled = 0;
-  u32 use_pt = NONE32, stalled_pt = NONE32;
-  double delta_pt = 0;                  // delta when the uses of the current point began
+  double delta_pt = 0;                  // delta when the uses of the last point began
+  bool stalled_pt = false;              // ... and whether its kernel has waited
+  double stall = 0;                     // of this lane's events
+  u32 n_stalled = 0;
 
-  // 64 events at a time, one per lane, the lanes in the order of their kinds: each channel's requests lie side by side, in
-  // order.  They are fetched in stages, a stage a step of 64 ahead of the next, so that no trip to memory is waited for:
-  // the keys; record, time of the point and where the event's predecessor stands; the predecessor's result.
-  struct Keys { u64 k; u32 place, pos; };                  // place: the lane that the event of this position goes to; pos: the position of this lane's event
-  // (loaded words stay as they come until a later stage uses them: a conversion beside the load would wait for it)
-  struct Loads { u64 tau, sp; u32 kind, i, pt, pos, place, pred; };
-  struct Ev { Loads l; u64 pval; u32 src, psrc; };         // psrc 0: pval; 1: lane src of these 64; 2: of the 64 before
-  auto load_key = [&](u64 at) -> u64 { return at + lane < ne ? sorted[at + lane] : NONE64; };
-  auto spread = [&](u64 k) -> Keys {
-    const u32 kind = k == NONE64 ? (u32)EV_NONE : (u32)(k >> (rbits + 1)) & ((1u << EV_BITS) - 1u);
-    Keys r;
-    u32 at = 0;
-    r.place = 0;
+  // An event's own values are loaded WALK_STAGES steps ahead, its predecessor's place as many steps before that, so
+  // that the predecessor's result - if it was stored by then - comes with the values.
+  double r_sp[WALK_STAGES], r_A[WALK_STAGES], r_off[WALK_STAGES], r_val[WALK_STAGES];
+  uint2 r_ev[WALK_STAGES];
+  u32 r_pred[WALK_STAGES], ahead[WALK_STAGES];
 #pragma unroll
-    for (u32 c = 0; c <= EV_NONE; ++c) {
-      const u64 m = __ballot(kind == c);
-      if (kind == c) r.place = at + (u32)__popcll(m & below);
-      at += (u32)__popcll(m);
-    }
-    r.k = ((u64)to_lane((u32)(k >> 32), r.place) << 32) | to_lane((u32)k, r.place);
-    r.pos = to_lane(lane, r.place);
-    return r;
-  };
-  auto load_ops = [&](const Keys& q) -> Loads {
-    Loads v;
-    const bool valid = q.k != NONE64;
-    const u64 x = q.k >> (rbits + 1);
-    v.i = valid ? (u32)((q.k >> 1) & ((1ull << rbits) - 1ull)) : 0u;
-    v.kind = valid ? (u32)(x & ((1u << EV_BITS) - 1u)) : (u32)EV_NONE;
-    v.pt = valid ? (u32)(x >> EV_BITS) : 0u;
-    v.pos = q.pos; v.place = q.place;
-    v.tau = *(v.kind < EV_IN ? &rec[v.i].t_out_ns : &rec[v.i].t_in_ns);
-    v.sp = start[v.pt < K ? v.pt : v.pt - K];
-    v.pred = pos_of[(u64)((v.kind == EV_USE ? 2u : 0u) + (u32)(q.k & 1ull)) * n + v.i];   // its eviction / its prefetch (an eviction: not used)
-    return v;
-  };
-  // (the events from `base` on; those before `done` have their results in memory, the ones between lie where place_prev says)
-  auto load_pred = [&](const Loads& l, u32 base, u32 done, u32 place_prev) -> Ev {
-    Ev v;
-    v.l = l;
-    const bool has = l.kind >= EV_IN && l.kind <= EV_USE;
-    const u32 here = (u32)__shfl((int)l.place, (int)((l.pred - base) & 63u)), there = (u32)__shfl((int)place_prev, (int)((l.pred - done) & 63u));
-    v.psrc = !has ? 0u : l.pred >= base ? 1u : l.pred >= done ? 2u : 0u;
-    v.src = v.psrc == 1u ? here : there;
-    v.pval = res[has && v.psrc == 0u ? l.pred : 0u];       // (the others: not used)
-    return v;
-  };
-  Keys kq = spread(load_key(0));
-  Loads lq = load_ops(kq);
-  kq = spread(load_key(G10_WAVE));
-  u64 kraw = load_key(2 * G10_WAVE);
-  Ev nxt = load_pred(lq, 0, 0, 0);
-  lq = load_ops(kq);
-  double t_prev = 0;                    // results of the 64 before, one per lane
-  for (u32 base = 0; base < ne; base += G10_WAVE) {
-    const Ev cur = nxt;
-    const u32 kind = cur.l.kind, pt = cur.l.pt, pos = cur.l.pos;
-    const double tau = kind >= EV_USE ? 0.0 : whole(cur.l.tau), sp = whole(cur.l.sp + (pt < K ? 0ull : T));     // (sp: end of kernel pt - 1 without any stall)
-    nxt = load_pred(lq, base + G10_WAVE, base, cur.l.place);
-    lq = load_ops(spread(kraw));
-    kraw = load_key((u64)base + 3 * G10_WAVE);
-    const bool is_out = kind < EV_IN, is_in = kind >= EV_IN && kind < EV_USE, is_use = kind == EV_USE;
-    const u64 use_m = __ballot(is_use), valid_m = __ballot(kind != EV_NONE);
-    const u32 cnt = (u32)__popcll(valid_m);                     // the valid events come first
-    const u64 out1_m = __ballot(kind == EV_OUT + 1), in0_m = __ballot(kind == EV_IN), in1_m = __ballot(kind == EV_IN + 1), out0_m = __ballot(kind == EV_OUT);
-    // A channel that is free at x serves requests that are ready at r_1, r_2, .. and take tau_1, tau_2, ..: the k-th is done
-    // at A_k + max(x, r_j - A_(j-1) for j <= k), A the sums of tau.  Those do not change while the delay does, so a step
-    // of the walk is a running maximum for the evictions and one for the prefetches, both destinations in one
-    // (SEGMENT apart).  Settled requests keep their maximum.
-    const double sum = scan_sum(tau);
-    const double before1 = out0_m ? lane_getf(sum, 63u - (u32)__builtin_clzll(out0_m)) : 0.0;
-    const u64 o01 = out0_m | out1_m, in01 = in0_m | in1_m, o012 = o01 | in0_m;
-    const double before2 = o01 ? lane_getf(sum, 63u - (u32)__builtin_clzll(o01)) : 0.0, before3 = o012 ? lane_getf(sum, 63u - (u32)__builtin_clzll(o012)) : 0.0;
-    const double A = sum - (kind == EV_OUT ? 0.0 : kind == EV_OUT + 1 ? before1 : kind == EV_IN ? before2 : before3);
-    const double free_c = kind == EV_OUT ? free0 : kind == EV_OUT + 1 ? free1 : kind == EV_IN ? free2 : free3;
-    const double seg = (kind & 1u) ? 2.0 * SEGMENT : SEGMENT;    // (a request's ready time less the sums before it is above -SEGMENT)
-    const double from_prev = lane_anyf(t_prev, cur.src);
-    const bool here = cur.psrc == 1;
-    const double pv = cur.psrc == 2 ? from_prev : whole(cur.pval);      // what the event waits for, if it is older than these 64
-    const bool any_here_in = __any(here && is_in), any_here_use = __any(here && is_use);
-    double M = 0, t = 0, latev = 0;                              // the request's maximum (`seg` up) and completion time
-    u32 from = 0;                                                // events before this position are settled
-    while (from < cnt) {
-      const bool open = pos >= from;
-      const double free_at = sp + delta;                         // end of the previous kernel
-      const u64 open_m = __ballot(open);
-      if (o01 & open_m) {                                        // evictions
-        const double m = scan_max(is_out ? (open ? free_at + (seg - (A - tau)) : M) : 0.0);
-        if (is_out) { M = m; const double y = m - seg; t = A + (y > free_c ? y : free_c); }
-      }
-      double w = pv;
-      if (any_here_in) { const double x = lane_anyf(t, cur.src); if (here && is_in) w = x; }
-      if (in01 & open_m) {                                       // prefetches, not before their evictions
-        const double ready = free_at > w ? free_at : w;
-        const double m = scan_max(is_in ? (open ? ready + (seg - (A - tau)) : M) : 0.0);
-        if (is_in) { M = m; const double y = m - seg; t = A + (y > free_c ? y : free_c); }
-      }
-      if (any_here_use) { const double x = lane_anyf(t, cur.src); if (here && is_use) w = x; }
-      const u64 waits = __ballot(is_use && open && w > free_at);
-      const u32 fl = waits ? (u32)__builtin_ctzll(waits) : 0u;   // (the uses lie in their order)
-      const u32 f = waits ? (u32)__builtin_amdgcn_readlane((int)pos, (int)fl) : cnt - 1;       // the step ends with event f
-      const bool in_step = open && pos <= f && kind != EV_NONE;
-      if (!second && __any(in_step && pt >= K)) { second = true; delta_first = delta; }
-      if (is_use && in_step && pt >= K) {                        // lateness: beyond the previous kernel's end, before any wait of this one
-        const double prev_end = sp + (pt == use_pt ? delta_pt : delta);
-        latev = w > prev_end ? w - prev_end : 0.0;
-      }
-      const u64 um = use_m & __ballot(in_step);
-      if (um) {
-        const u32 upt = (u32)__builtin_amdgcn_readlane((int)pt, (int)(63u - (u32)__builtin_clzll(um)));
-        if (upt != use_pt) { use_pt = upt; delta_pt = delta; }
-      }
-      if (waits) {                                               // the kernel waits for this prefetch
-        const double pf = lane_getf(w, fl), spf = lane_getf(sp, fl);
-        if (use_pt >= K) {
-          stall += pf - (spf + delta);
-          if (stalled_pt != use_pt) { stalled_pt = use_pt; n_stalled += 1; }
+  for (u32 q = 0; q < WALK_STAGES; ++q) {
+    const u32 p = q * 64u + lane;
+    r_sp[q] = w.sp[p]; r_A[q] = w.A[p]; r_off[q] = w.off[p]; r_ev[q] = w.ev[p]; r_pred[q] = w.pred[p];
+    r_val[q] = 0;                       // (no result is in memory yet)
+    ahead[q] = w.pred[p + WALK_STAGES * 64u];
+  }
+  for (u32 step0 = 0; step0 < steps; step0 += WALK_STAGES) {
+#pragma unroll
+    for (u32 q = 0; q < WALK_STAGES; ++q) {
+      const u32 base = (step0 + q) * 64u;
+      const double sp = r_sp[q], A = r_A[q], off = r_off[q];
+      const u32 ev = r_ev[q].x, mig = r_ev[q].y, kind = ev & 7u, pos = (ev >> W_POS) & 63u, pred = r_pred[q];
+      const bool has = pred != NONE32, here = has && pred >= base;
+      // what it waits for: in memory when its values were loaded, one of the steps since, or of these 64
+      double pv = !has ? 0.0 : pred + WALK_STAGES * 64u < base + 64u ? r_val[q] : recent[pred % (WALK_STAGES * 64u)];
+      if (here) pv = 0;
+      const bool is_in = kind >= EV_IN && kind < EV_USE, is_use = kind == EV_USE;
+      const u64 m0 = ballot(kind == EV_OUT), m1 = ballot(kind == EV_OUT + 1), m2 = ballot(kind == EV_IN), m3 = ballot(kind == EV_IN + 1),
+                use_m = ballot(is_use), second_m = ballot((ev & W_SECOND) != 0);
+      const u64 in_here = ballot(here && is_in), use_here = ballot(here && is_use);
+      const u32 src = (pred & 63u) << 2;
+      // A channel that is free at x serves requests that are ready at r_1, r_2, .. and take tau_1, tau_2, ..: the k-th is done
+      // at A_k + max(x, r_j - A_(j-1) for j <= k), A the sums of tau.  Those do not change while the delay does, so a step
+      // of the walk is one running maximum for all four channels, SEGMENT apart (two, where a prefetch's eviction is among
+      // the 64).  A settled event keeps the end of the kernel before it, and so its maximum.
+      const double As = A - (double)(kind + 1u) * SEGMENT;
+      const double served = A + (kind == EV_OUT ? free0 : kind == EV_OUT + 1 ? free1 : kind == EV_IN ? free2 : free3);
+      double win = is_in ? pv : 0.0, wuse = is_use ? pv : 0.0;     // what a prefetch, a use waits for
+      double free_at = sp + delta, t;                              // end of the previous kernel
+      u64 waited = 0;
+      while (true) {
+        if (in_here) {
+          const double out = lane_at(larger(scan_max(free_at + off) + As, served), src);
+          if (here && is_in) win = out;
         }
-        delta = pf - spf;
+        t = larger(scan_max(larger(win, free_at) + off) + As, served);
+        if (use_here) { const double x = lane_at(t, src); if (here && is_use) wuse = x; }
+        const u64 waits = ballot(wuse > free_at) & ~waited;
+        if (!waits) break;
+        const u32 fl = (u32)__builtin_ctzll(waits);                // the kernel waits for this prefetch (the uses lie in their order)
+        waited |= 1ull << fl;
+        delta = lane_getf(wuse - sp, fl);
+        const double next = sp + delta;
+        if (pos > (u32)__builtin_amdgcn_readlane((int)pos, (int)fl)) free_at = next;     // (the events behind it)
       }
-      from = f + 1;
+      const double dl = free_at - sp;                              // the delay when the event was settled
+      if (!second && second_m) {
+        // (the first event of the second iteration: all behind it are of it too)
+        second = true;
+        const u32 cnt = (u32)__popcll(m0 | m1 | m2 | m3 | use_m);
+        delta_first = lane_getf(dl, (u32)__builtin_ctzll(ballot(pos == cnt - (u32)__popcll(second_m))));
+      }
+      if (use_m) {
+        const u32 first = (ev >> W_FIRST) & 63u;
+        double began = lane_at(dl, first << 2);                    // the delay when the uses of its point began
+        if (ev & W_CONT) began = delta_pt;
+        if (is_use && (ev & W_SECOND)) { const double e = sp + began; late[mig] = wuse > e ? (u64)(wuse - e) : 0ull; }
+        const u32 last = 63u - (u32)__builtin_clzll(use_m);
+        delta_pt = lane_getf(began, last);
+        const u32 ev_last = (u32)__builtin_amdgcn_readlane((int)ev, (int)last);
+        const u64 of_last = ~0ull << ((ev_last >> W_FIRST) & 63u);
+        // points whose kernels waited, counted at the first use that did
+        const u64 w2 = waited & second_m;
+        if (w2) {
+          const bool is = (w2 >> lane) & 1ull;
+          if (is) stall += wuse - free_at;
+          n_stalled += (u32)__popcll(ballot(is && !(w2 & below & (~0ull << first)) && !((ev & W_CONT) && stalled_pt)));
+        }
+        stalled_pt = (w2 & of_last) != 0 || ((ev_last & W_CONT) && stalled_pt);
+      }
+      if (m0) free0 = lane_getf(t, 63u - (u32)__builtin_clzll(m0));
+      if (m1) free1 = lane_getf(t, 63u - (u32)__builtin_clzll(m1));
+      if (m2) free2 = lane_getf(t, 63u - (u32)__builtin_clzll(m2));
+      if (m3) free3 = lane_getf(t, 63u - (u32)__builtin_clzll(m3));
+      res[base + lane] = t;
+      recent[(base + lane) % (WALK_STAGES * 64u)] = t;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // the next loads find what was just written (in order)
+      // the step that takes these registers next
+      const u32 p = base + WALK_STAGES * 64u + lane, pn = ahead[q];
+      r_sp[q] = w.sp[p]; r_A[q] = w.A[p]; r_off[q] = w.off[p]; r_ev[q] = w.ev[p]; r_pred[q] = pn;
+      r_val[q] = res[pn < base + 64u ? pn : 0u];                   // (the others: not used)
+      ahead[q] = w.pred[p + WALK_STAGES * 64u];
     }
-    // ---- results out ---------------------------------------------------------------------
-    if (out0_m) free0 = lane_getf(t, 63u - (u32)__builtin_clzll(out0_m));
-    if (out1_m) free1 = lane_getf(t, 63u - (u32)__builtin_clzll(out1_m));
-    if (in0_m) free2 = lane_getf(t, 63u - (u32)__builtin_clzll(in0_m));
-    if (in1_m) free3 = lane_getf(t, 63u - (u32)__builtin_clzll(in1_m));
-    if (is_out || is_in) res[base + pos] = (u64)t;
-    if (is_use && pt >= K) late[cur.l.i] = (u64)latev;
-    t_prev = t;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the next loads find what was just written (in order)
-    if (cnt < G10_WAVE) break;
   }
   if (!second) delta_first = delta;
+  stall = lane_getf(scan_sum(stall), 63u);
   if (lane == 0) {
     st->iter_ns = T + (u64)(delta - delta_first);
     st->stall_ns = (u64)stall;
@@ -481,13 +532,14 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
   if (!w->rp_arena || w->rp_cap < n) {
     G10_HIP(hipStreamSynchronize(s));
     replay_free(w);
-    const u64 cap = n ? n : 1, ce = 6 * cap;
+    const u64 cap = n ? n : 1, ce = 6 * cap, cp = walk_events(ce);
     const u64 he = radix_hist_elems(ce);
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-    const size_t o_keys = take(ce * 8), o_alt = take(ce * 8), o_res = take(ce * 8), o_late = take(cap * 8), o_pos = take(4 * cap * 4),
+    const size_t o_keys = take(ce * 8), o_alt = take(ce * 8), o_res = take(cp * 8), o_late = take(cap * 8), o_pos = take(4 * cap * 4),
                  o_hist = take(he * 4), o_st = take(sizeof(ReplayStats)), o_dur = take((u64)K * 8),
-                 o_start = take(((u64)K + 1) * 8), o_ts = take(scan_scratch_elems(K) * 8), o_tst = take(128);
+                 o_start = take(((u64)K + 1) * 8), o_ts = take(scan_scratch_elems(K) * 8), o_tst = take(128),
+                 o_sp = take(cp * 8), o_A = take(cp * 8), o_off = take(cp * 8), o_ev = take(cp * 8), o_pred = take(cp * 4);
     void* q = nullptr;
     G10_TRY(mem_dev_alloc(&q, off));
     char* b = (char*)q;
@@ -495,6 +547,8 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
     w->rp_keys = (u64*)(b + o_keys); w->rp_alt = (u64*)(b + o_alt); w->rp_res = (u64*)(b + o_res); w->rp_late = (u64*)(b + o_late);
     w->rp_pos = (u32*)(b + o_pos); w->rp_hist = (u32*)(b + o_hist); w->rp_stats = (void*)(b + o_st);
     w->rp_dur = (u64*)(b + o_dur); w->rp_start = (u64*)(b + o_start); w->rp_tscr = (u64*)(b + o_ts); w->rp_tstats = (void*)(b + o_tst);
+    w->rp_sp = (double*)(b + o_sp); w->rp_A = (double*)(b + o_A); w->rp_off = (double*)(b + o_off); w->rp_ev = (uint2*)(b + o_ev);
+    w->rp_pred = (u32*)(b + o_pred);
     w->h_rp_late = (u64*)malloc(cap * 8);
     if (!w->h_rp_late) { replay_free(w); return G10_ENOMEM; }      // both or none: the next call must find the same state as the first
   }
@@ -514,19 +568,27 @@ int replay_run(g10_plan_s* h, const u64* dur_ns, u32 eager, g10_replay_result* o
   if (n) G10_HIP(hipMemsetAsync(w->rp_late, 0, (u64)n * 8, s));
   const u32 rbits = bits_for(n ? n - 1 : 0);
   u64 *keys = w->rp_keys, *alt = w->rp_alt;
+  // (a channel's transfers fit the iteration that they were planned for, w->T; each is made twice)
+  const bool exact = T < REPLAY_EXACT / 10 && w->T < REPLAY_EXACT / 10 && walk_events(ne) < (1ull << 32);
   if (n) {
     hipLaunchKernelGGL(k_rp_events, dim3((n + G10_BLOCK - 1) / G10_BLOCK), dim3(G10_BLOCK), 0, s, (const g10_migration*)w->records,
                        (const uint2*)w->rec_ab, eager ? (const u32*)w->pf_gained : (const u32*)nullptr, n, K, rbits, keys, st);
     G10_HIP(hipGetLastError());
     G10_TRY(radix_sort_u64(&keys, &alt, ne, rbits + 1 + EV_BITS + bits_for(2ull * K), w->rp_hist, s, rbits + 1));
     hipLaunchKernelGGL(k_rp_index, dim3((u32)((ne + G10_BLOCK - 1) / G10_BLOCK)), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)ne, n, rbits,
-                       w->rp_pos);
+                       exact ? 1u : 0u, w->rp_pos);
     G10_HIP(hipGetLastError());
   }
-  // (a channel's transfers fit the iteration that they were planned for, w->T; each is made twice)
-  const bool exact = T < REPLAY_EXACT / 10 && w->T < REPLAY_EXACT / 10;
-  hipLaunchKernelGGL((exact ? k_replay : k_replay_long), dim3(1), dim3(G10_WAVE), 0, s, (const u64*)keys, (u32)ne, (const g10_migration*)w->records, n, rbits,
-                     (const u32*)w->rp_pos, start, K, T, w->rp_res, w->rp_late, st);
+  if (exact) {
+    const u32 np = (u32)walk_events(ne);
+    const Walk wk = {w->rp_sp, w->rp_A, w->rp_off, w->rp_ev, w->rp_pred};
+    hipLaunchKernelGGL(k_rp_expand, dim3((np + G10_BLOCK - 1) / G10_BLOCK), dim3(G10_BLOCK), 0, s, (const u64*)keys, (u32)ne, np,
+                       (const g10_migration*)w->records, n, rbits, (const u32*)w->rp_pos, start, K, T, wk);
+    G10_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_replay, dim3(1), dim3(G10_WAVE), 0, s, wk, (np - WALK_PAD) / 64u, T, (double*)w->rp_res, w->rp_late, st);
+  } else
+    hipLaunchKernelGGL(k_replay_long, dim3(1), dim3(G10_WAVE), 0, s, (const u64*)keys, (u32)ne, (const g10_migration*)w->records, n, rbits,
+                       (const u32*)w->rp_pos, start, K, T, w->rp_res, w->rp_late, st);
   G10_HIP(hipGetLastError());
   ReplayStats hs;
   G10_HIP(hipMemcpyAsync(&hs, st, sizeof hs, hipMemcpyDeviceToHost, s));

@@ -61,3 +61,9 @@ def test_replay_of_many_events_at_one_point(g10, n):
         assert_plan_equal(h.plan(**a), p)
         both(h, p, (None, np.full(K, 1, np.uint64), np.full(K, 90_000, np.uint64)))
     h.close()
+
+
+@pytest.mark.parametrize("n", [63, 65, 128, 129, 191, 192, 193, 255, 256, 257, 320, 513])
+def test_replay_of_predecessors_at_every_distance(g10, n):
+    """n events between an event and the one it waits for: among the 64 events that are walked at a time, among the last 192, in memory."""
+    test_replay_of_many_events_at_one_point(g10, n)
