@@ -503,7 +503,7 @@ static void work_layout(PlanWork* w, Arena& ar) {
   ar.take(&w->pf_keys, C); ar.take(&w->pf_keys_alt, C);
   ar.take(&w->pf_order, C); ar.take(&w->pf_order_alt, C);
   ar.take(&w->pf_gained, C); ar.take(&w->pf_last, C);
-  ar.take(&w->pf_pressure, K);
+  ar.take(&w->pf_pressure, (u64)w->nch << w->shift_ch);
   ar.take(&w->pf_stats, 4);
   ar.take(&w->dur_own, K); ar.take(&w->start_own, (u64)K + 1);
   ar.take(&w->times_scratch, scan_scratch_elems(K)); ar.take(&w->times_stats, 16);

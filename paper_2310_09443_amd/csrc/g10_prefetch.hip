@@ -35,10 +35,21 @@ __device__ __forceinline__ u64 lane_value64(u64 v, u32 l) {      // lane l's v (
   return ((u64)hi << 32) | lo;
 }
 
+__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+
+// largest value over the lanes: the upper halves first, then the lower ones of the lanes that have it (a maximum of 64-bit
+// values in one go compares and selects at every step of the reduction)
+__device__ __forceinline__ u64 wave_max64(u64 v) {
+  const u32 hi = (u32)(v >> 32), top = wave_max(hi);
+  return ((u64)top << 32) | wave_max(hi == top ? (u32)v : 0u);
+}
+
 struct PfShared {
   u64 n_moved, slots;
 };
 
+// ONE: a chunk is one strip of 256 slots (timelines of up to 131 072 slots).  E holds nch chunks, zeros behind slot K - 1.
+template <bool ONE>
 __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ rec, const uint2* __restrict__ rec_ab,
                                              const u32* __restrict__ order, u32 n, u64* __restrict__ E, u32 K, u32 nch,
                                              u32 spt, u32 shift_ch, u64 cap, u32* __restrict__ gained,
@@ -47,16 +58,19 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
   u64* cmax = (u64*)smem;                          // [nch] largest pressure of the chunk (lazy add included)
   u64* ladd = cmax + nch;                          // [nch] added to every slot of the chunk, not yet in E
   PfShared* S = (PfShared*)(ladd + nch);
-  const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, CH = 1u << shift_ch;
+  const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, CH = 1u << shift_ch, strips = ONE ? 1u : spt;
 
-  for (u32 c = wave; c < nch; c += WG_WAVES) {           // chunk maxima
+  for (u32 c = wave; c < nch; c += WG_WAVES) {           // chunk maxima; the slots behind the timeline's end
     u64 m = 0;
-    for (u32 st = 0; st < spt; ++st) {
+    for (u32 st = 0; st < strips; ++st) {
       const u32 j0 = c * CH + st * 256u + lane * 4u;
 #pragma unroll
-      for (u32 i = 0; i < 4; ++i) if (j0 + i < K) { const u64 x = E[j0 + i]; m = x > m ? x : m; }
+      for (u32 i = 0; i < 4; ++i) {
+        if (j0 + i < K) { const u64 x = E[j0 + i]; m = x > m ? x : m; }
+        else E[j0 + i] = 0;
+      }
     }
-    m = wave_max(m);
+    m = wave_max64(m);
     if (lane == 0) { cmax[c] = m; ladd[c] = 0; }
   }
   if (tid == 0) { S->n_moved = 0; S->slots = 0; }
@@ -68,137 +82,144 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
   // of one slot; so 64 records are tested at once, one per lane, those before the first that passes are done - nothing
   // gained -, only that one takes the search, and the ones behind it are tested again with what its move adds to their
   // slots (kept in the lanes, not loaded anew).  (The records of the next 64 are on their way meanwhile.)
-  // A move is bound by its dependent trips to L2 (0.6 us each).  It takes one where the highest chunk that may refuse does:
-  // that chunk and the one at the end of the window are loaded together, whole, and the chunks cut are written back from
-  // those registers, without a wait - the accesses of one wavefront are served in order.  (Stress trace, 1226 moves: 3.4 ms;
-  // 6.2 with a trip for the test, one or more for the search, one per cut chunk and one for the stores to arrive, and with a
-  // look at every chunk of the timeline, seven a lane, in the search and in the update.)
+  // A move is bound by the instructions of the one wavefront, which it issues one after the other, and by a trip to L2: the
+  // chunk at the end of the window is asked for first, the highest chunk that may refuse as soon as the chunk maxima name it;
+  // both come whole, and are written back from those registers, without a wait - the accesses of one wavefront are served
+  // in order.  The chunks between them take a lazy add.  (Stress trace, 1226 moves: 6.2 ms with a trip for the test, one or
+  // more for the search, one per cut chunk and one for the stores to arrive; 3.3 with one trip, 6600 cycles a
+  // move, and a maximum of 64-bit values over the lanes for the search and for each cut chunk; 2.15 now.)
   if (wave == 0) {
     u64 n_moved = 0, slots = 0;
-    u32 nr = 0, na = 0, nb = 0;
+    // (the next 64 records and the numbers of those behind them; past the end the last one again)
+    auto number = [&](u32 at) -> u32 { return order[at < n ? at : n - 1u]; };
+    u32 nr = 0, nr2 = 0, na = 0, nb = 0;
     u64 nsz = 0;
-    if (lane < n) { nr = order[lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
-    u32 it = 0;                                    // first record of the 64
-    u64 todo = 0;                                  // lanes whose record is not done yet
-    u32 cr = 0, ca = 0, cb = 0, cbb = 0;           // this lane's record: its number, absent window, last absent slot
-    u64 csz = 0, val = 0;                          // ... size; pressure of that slot
+    if (n) { nr = number(lane); nr2 = number(64u + lane); nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
+    u32 it = 0;                                    // first record of the next 64
     struct Strip { u64 x[4]; };                    // a strip of 256 slots of a chunk, 64 apart in a lane
     auto load_strip = [&](u32 c, u32 st) -> Strip {
       Strip v;
+      const u64* at = E + (c * CH + st * 256u + lane);
 #pragma unroll
-      for (u32 i = 0; i < 4; ++i) { const u32 j = c * CH + st * 256u + i * 64u + lane; v.x[i] = E[j < K ? j : K - 1]; }
+      for (u32 i = 0; i < 4; ++i) v.x[i] = at[i * 64u];
       return v;
     };
-    while (true) {
-      if (!todo) {                                 // the next 64
-        if (it >= n) break;
-        const u32 cnt = n - it < 64u ? n - it : 64u;
-        todo = cnt == 64u ? ~0ull : (1ull << cnt) - 1ull;
-        cr = nr; ca = na; cb = nb; csz = nsz;
-        cbb = cb >= K ? cb - K : cb;
-        it += cnt;
-        if ((todo >> lane) & 1ull) val = E[cbb] + ladd[cbb >> shift_ch];
-        if (it + lane < n) { nr = order[it + lane]; nsz = rec[nr].size_bytes; const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
-      }
-      const bool mine = (todo >> lane) & 1ull;
-      const u64 pm = __ballot(mine && csz <= cap && val <= cap - csz);
-      const u32 f = pm ? (u32)__builtin_ctzll(pm) : 64u;       // the records before it stay where they are
-      if (mine && lane < f) { gained[cr] = 0u; last[cr] = cbb; }
-      if (!pm) { todo = 0; continue; }
-      todo &= f == 63u ? 0ull : ~0ull << (f + 1u);
-      const u32 r = (u32)__builtin_amdgcn_readlane((int)cr, (int)f), a = (u32)__builtin_amdgcn_readlane((int)ca, (int)f),
-                b = (u32)__builtin_amdgcn_readlane((int)cb, (int)f), bb = b >= K ? b - K : b;
-      const u64 s = lane_value64(csz, f);
+    while (it < n) {
+      // ---- the next 64 records -----------------------------------------------------------------------------------
+      const u32 cnt = n - it < 64u ? n - it : 64u;
+      const u32 cr = nr, ca = na, cb = nb, cbb = cb >= K ? cb - K : cb;      // this lane's record: its number, absent window, last absent slot
+      const u64 csz = nsz, climit = cap - csz;     // (a slot holds the tensor iff its pressure is not above this; a tensor above the capacity never moves)
+      u64 val = E[cbb] + ladd[cbb >> shift_ch];    // pressure of the last absent slot
+      u32 cg = 0;                                  // slots gained
+      u64 todo = ballot(lane < cnt && csz <= cap); // lanes whose record is not done yet
+      it += cnt;
+      nr = nr2; nsz = rec[nr].size_bytes;
+      { const uint2 ab = rec_ab[nr]; na = ab.x; nb = ab.y; }
+      nr2 = number(it + 64u + lane);
+      while (true) {
+        todo &= ballot(val <= climit);             // (the pressure only rises: a record that cannot move now does not move)
+        if (!todo) break;
+        const u32 f = (u32)__builtin_ctzll(todo);  // the records before it stay where they are
+        todo &= todo - 1;
+        const u32 a = (u32)__builtin_amdgcn_readlane((int)ca, (int)f), b = (u32)__builtin_amdgcn_readlane((int)cb, (int)f), bb = b >= K ? b - K : b;
+        const u64 s = lane_value64(csz, f), lim = cap - s;
+        const u32 c_end = bb >> shift_ch;          // the chunk at the end of the window
+        Strip v_end = {}, v_hit = {};
+        if (ONE) v_end = load_strip(c_end, 0);
 
-      // the earliest slot from which every slot up to b can hold the tensor: one past the last slot of [a, b]
-      // that cannot.  The window in pieces of chunks, from its end back - the part in the second iteration, then the one in
-      // the first -, a piece per lane: the chunk maxima say which piece may hold that slot, and that piece is scanned.
-      const u64 lim = cap - s;                     // a slot holds the tensor iff its pressure <= lim
-      const u32 c_end = bb >> shift_ch;            // the chunk at the end of the window
-      const u32 n2 = b >= K ? c_end + 1u - ((a > K ? a - K : 0u) >> shift_ch) : 0u;     // pieces of the second iteration
-      const u32 t1 = (b < K ? b : K - 1u) >> shift_ch, n1 = a < K ? t1 + 1u - (a >> shift_ch) : 0u;      // last chunk, pieces of the first
-      auto chunk_of = [&](u32 t) -> u32 { return t < n2 ? c_end - t : t1 - (t - n2); };
-      u32 p = a;
-      u32 c_seen = NONE32;                         // the chunk scanned last; its first strip and the end chunk's
-      Strip v_end = {}, v_seen = {};
-      bool end_loaded = false;
-      u32 t0 = 0, pieces = n1 + n2;                // (pieces from the end down to the one of p)
-      while (t0 < n1 + n2) {
-        const u32 t = t0 + lane;
-        const u64 hits = __ballot(t < n1 + n2 && cmax[t < n1 + n2 ? chunk_of(t) : 0u] > lim);
-        if (!hits) { t0 += 64u; continue; }
-        const u32 th = uniform(t0 + (u32)__builtin_ctzll(hits)), c = chunk_of(th), second = th < n2 ? K : 0u;
-        const u32 lo = c * CH + second > a ? c * CH + second : a, end_ = c * CH + CH < K ? c * CH + CH : K;
-        const u32 hi = end_ - 1u + second < b ? end_ - 1u + second : b;
-        u32 best = 0;                              // doubled coordinate + 1 of the last refusing slot of the piece
-        const u64 lz = ladd[c];
-        for (u32 st = 0; st < spt; ++st) {
-          const Strip v = load_strip(c, st);
-          if (!end_loaded) { v_end = c == c_end ? v : load_strip(c_end, 0); end_loaded = true; }
-          if (spt == 1u) { c_seen = c; v_seen = v; }
+        // the earliest slot from which every slot up to b can hold the tensor: one past the last slot of [a, b]
+        // that cannot.  The window in pieces of chunks, from its end back - the part in the second iteration, then the one in
+        // the first -, a piece per lane: the chunk maxima say which piece may hold that slot, and that piece is scanned.
+        const u32 n2 = b >= K ? c_end + 1u - ((a > K ? a - K : 0u) >> shift_ch) : 0u;     // pieces of the second iteration
+        const u32 t1 = (b < K ? b : K - 1u) >> shift_ch, n1 = a < K ? t1 + 1u - (a >> shift_ch) : 0u;      // last chunk, pieces of the first
+        auto chunk_of = [&](u32 t) -> u32 { return t < n2 ? c_end - t : t1 + n2 - t; };
+        u32 p = a, c_hit = NONE32, t0 = 0, pieces = n1 + n2;                // (pieces from the end down to the one of p)
+        while (t0 < n1 + n2) {
+          const u32 t = t0 + lane;
+          const u64 hits = ballot(t < n1 + n2 && cmax[t < n1 + n2 ? chunk_of(t) : 0u] > lim);
+          if (!hits) { t0 += 64u; continue; }
+          const u32 th = t0 + (u32)__builtin_ctzll(hits), c = chunk_of(th), second = th < n2 ? K : 0u;
+          const u32 lo = c * CH + second > a ? c * CH + second : a, end_ = c * CH + CH < K ? c * CH + CH : K;
+          const u32 hi = end_ - 1u + second < b ? end_ - 1u + second : b;
+          const u64 lz = uniform(ladd[c]), limz = lim - lz;
+          u32 best = 0;                            // doubled coordinate + 1 of the last refusing slot of the piece
+          for (u32 st = strips; st-- > 0 && !best;) {
+            const u32 j0 = c * CH + st * 256u + second;
+            u64 m[4];
+            auto refusing = [&](const Strip& v) {
 #pragma unroll
-          for (u32 i = 0; i < 4; ++i) {
-            const u32 j = c * CH + st * 256u + i * 64u + lane + second;
-            if (j >= lo && j <= hi && v.x[i] + lz > lim) best = j + 1;    // ascending: the last one stays
+              for (u32 i = 0; i < 4; ++i) m[i] = ballot(j0 + lane + i * 64u - lo <= hi - lo && (v.x[i] > limz || lz > lim));
+            };
+            if (ONE && c == c_end) refusing(v_end);        // (a copy of it would be waited for before the other load is made)
+            else { v_hit = load_strip(c, st); c_hit = c; refusing(v_hit); }
+            if (m[3]) best = j0 + 256u - (u32)__builtin_clzll(m[3]);
+            else if (m[2]) best = j0 + 192u - (u32)__builtin_clzll(m[2]);
+            else if (m[1]) best = j0 + 128u - (u32)__builtin_clzll(m[1]);
+            else if (m[0]) best = j0 + 64u - (u32)__builtin_clzll(m[0]);
           }
+          if (best) { p = best; pieces = best > hi ? th : th + 1u; break; }      // (one past the piece's end: the piece is not gained)
+          t0 = th + 1u;
         }
-        best = wave_max(best);
-        if (best) { p = best; pieces = best > hi ? th : th + 1u; break; }      // (one past the piece's end: the piece is not gained)
-        t0 = th + 1u;
-      }
-      const u32 g = b + 1 - p;
-      if (lane == 0) {
-        gained[r] = g;
-        const u32 nl = b - g;                      // last absent slot left (one before a if none)
-        last[r] = nl >= K ? nl - K : nl;
-      }
-      if (g) {                                     // the slots gained take the tensor
+        const u32 g = b + 1 - p;                   // (one at least: slot b can hold it)
+        if (lane == f) cg = g;
+        // ---- the slots gained take the tensor ----------------------------------------------------------------------
         n_moved += 1; slots += g;
-        if (mine && in_doubled(cbb, K, p, b) != NONE32) val += s;
-        // whole chunks lazily; the window cuts the first and the last piece at most (of one chunk, where it goes around)
-        u32 cut0 = NONE32, cut1 = NONE32;
-        for (u32 q = 0; q < pieces; q += 64u) {
-          const u32 t = q + lane;
-          bool cut = false;
-          u32 c = 0;
-          if (t < pieces) {
-            c = chunk_of(t);
-            const u32 second = t < n2 ? K : 0u, lo = c * CH + second, end_ = (c * CH + CH < K ? c * CH + CH : K) + second;
-            cut = lo < p || end_ > b + 1u;
-            if (!cut) { ladd[c] += s; cmax[c] += s; }
-          }
-          u64 cm = __ballot(cut);
-          if (cm && cut0 == NONE32) { cut0 = (u32)__builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(cm)); cm &= cm - 1; }
-          if (cm) cut1 = (u32)__builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(cm));
-        }
-        if (cut1 == cut0) cut1 = NONE32;
         // (slots in [p, b]: both less K where it lies in the second iteration, or all but the (b - K, p) between)
         const bool both = p < K && b >= K;
         const u32 rlo = both ? b - K + 1u : p >= K ? p - K : p, rn = both ? p - rlo : b - p + 1u;
-#pragma unroll 1
-        for (u32 w = 0; w < 2; ++w) {
-          const u32 cc = w ? cut1 : cut0;
-          if (cc == NONE32) continue;
-          const u64 lz = ladd[cc];
-          u64 m = 0;
-          for (u32 st = 0; st < spt; ++st) {
-            const u32 j0 = cc * CH + st * 256u + lane;          // (64 neighbouring slots per load and store)
-            Strip v;
-            if (cc == c_seen) v = v_seen;                       // (strips of a chunk of one strip only)
-            else if (spt == 1u && end_loaded && cc == c_end) v = v_end;
-            else v = load_strip(cc, st);
+        if ((cbb - rlo < rn) != both) val += s;
+        // the pieces between the first and the last lie inside the window
+        for (u32 t = 1u + lane; t + 1u < pieces; t += 64u) { const u32 c = chunk_of(t); ladd[c] += s; cmax[c] += s; }
+        // those two, slot by slot (one chunk, where the window goes around)
+        const u32 c_low = chunk_of(pieces - 1u);
+        if (ONE) {
+          const u64 lz0 = ladd[c_end], lz1 = ladd[c_low];
+          const u32 j0 = c_end * 256u + lane, j1 = c_low * 256u + lane;
+          if (c_low != c_hit) v_hit = load_strip(c_low, 0);
+          u64 m0 = 0, m1 = 0;
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i) {
+            const u32 j = j0 + i * 64u;
+            if ((j - rlo < rn) != both && j < K) { v_end.x[i] += s; E[j] = v_end.x[i]; }
+            m0 = v_end.x[i] > m0 ? v_end.x[i] : m0;
+          }
+          if (c_low != c_end) {
 #pragma unroll
             for (u32 i = 0; i < 4; ++i) {
-              const u32 j = j0 + i * 64u;
-              if ((j - rlo < rn) != both && j < K) { v.x[i] += s; E[j] = v.x[i]; }
-              const u64 x = j < K ? v.x[i] + lz : 0ull;
-              m = x > m ? x : m;
+              const u32 j = j1 + i * 64u;
+              if ((j - rlo < rn) != both && j < K) { v_hit.x[i] += s; E[j] = v_hit.x[i]; }
+              m1 = v_hit.x[i] > m1 ? v_hit.x[i] : m1;
             }
+            m1 = wave_max64(m1) + lz1;
+            if (lane == 0) cmax[c_low] = m1;
           }
-          m = wave_max(m);
-          if (lane == 0) cmax[cc] = m;
+          m0 = wave_max64(m0) + lz0;
+          if (lane == 0) cmax[c_end] = m0;
+        } else {
+#pragma unroll 1
+          for (u32 w = 0; w < (c_low != c_end ? 2u : 1u); ++w) {
+            const u32 c = w ? c_low : c_end;
+            u64 m = 0;
+            for (u32 st = 0; st < strips; ++st) {
+              const u32 j0 = c * CH + st * 256u + lane;
+              Strip v = load_strip(c, st);
+#pragma unroll
+              for (u32 i = 0; i < 4; ++i) {
+                const u32 j = j0 + i * 64u;
+                if ((j - rlo < rn) != both && j < K) { v.x[i] += s; E[j] = v.x[i]; }
+                m = v.x[i] > m ? v.x[i] : m;
+              }
+            }
+            m = wave_max64(m) + ladd[c];
+            if (lane == 0) cmax[c] = m;
+          }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next loads find what was just written (in order)
+      }
+      if (lane < cnt) {
+        gained[cr] = cg;
+        const u32 nl = cb - cg;                    // last absent slot left (one before a if none)
+        last[cr] = nl >= K ? nl - K : nl;
       }
     }
     if (lane == 0) { S->n_moved = n_moved; S->slots = slots; }
@@ -207,7 +228,7 @@ __global__ __launch_bounds__(WG) void k_eager(const g10_migration* __restrict__ 
   // the lazy adds into the slots; the peak
   u64 m = 0;
   for (u32 j = tid; j < K; j += WG) { const u64 x = E[j] + ladd[j >> shift_ch]; E[j] = x; m = x > m ? x : m; }
-  m = wave_max(m);
+  m = wave_max64(m);
   if (lane == 0) atomicMax((unsigned long long*)&stats[2], (unsigned long long)m);
   if (tid == 0) { stats[0] = S->n_moved; stats[1] = S->slots; }
 }
@@ -242,7 +263,7 @@ int prefetch_run(g10_plan_s* h, g10_prefetch_result* out) {
     G10_TRY(radix_sort_u64_pairs(&keys, &alt, &ord, &oalt, n, bits_for(2 * w->T), w->hist, s));
   }
   const size_t lds = ((size_t)2 * w->nch * 8 + sizeof(PfShared) + 15) & ~(size_t)15;
-  hipLaunchKernelGGL(k_eager, dim3(1), dim3(WG), lds, s, (const g10_migration*)w->records, (const uint2*)w->rec_ab,
+  hipLaunchKernelGGL((w->spt == 1 ? k_eager<true> : k_eager<false>), dim3(1), dim3(WG), lds, s, (const g10_migration*)w->records, (const uint2*)w->rec_ab,
                      (const u32*)ord, n, w->pf_pressure, K, w->nch, w->spt, w->shift_ch, w->plan_cap, w->pf_gained, w->pf_last,
                      w->pf_stats);
   G10_HIP(hipGetLastError());
