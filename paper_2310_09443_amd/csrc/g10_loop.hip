@@ -81,6 +81,13 @@ constexpr u32 MC_GUESS_SHIFT_MIN = 2;   // the widest margin of a pass's first t
 // fit the LDS beside chunks and tiles: 64 always do, 256 nearly always.  The picking wavefront holds 64, the best by bound.
 // (Ranking passes of a plan with 64 in all / with 256 and the choice: ResNet 240 / 25, decoder 186 / 70, stress 500 / 160.)
 constexpr u32 LIST_MIN = 64, LIST_MAX = 256, LIST_VECS = 8, LIST_ENTRY = LIST_VECS * 16 + 8;
+// A plan by the clipped area goes on in the form with lists once LISTS_AFTER winners in a row had their band as their area, shown by
+// the chunks alone, and LISTS_LEFT periods are left; it leaves that form after LISTS_VAIN lists in a row that gave one migration
+// at most, to come back after twice as many winners each time, but where LISTS_PAID lists had given several.  (Another launch is
+// 25 us, a list in vain 8; a pass of the form with lists without one takes 2 us more than one of the other: registers.  With one
+// form for both, lists tried less and less often, plans of 20 to 60 passes took 10 to 13 % more.  ResNet, 1638 migrations,
+// after 8 winners and 4 lists 4.3 ms, 10 and 3 5.5, 10 and 2 6.8; in the form with lists alone 3.4; one migration a pass 17.6.)
+constexpr u32 LISTS_AFTER = 8, LISTS_VAIN = 4, LISTS_PAID = 4, LISTS_MORE_MAX = 7, LISTS_LEFT = 128;
 static_assert(LIST_MIN == G10_WAVE && LIST_MAX % G10_WAVE == 0, "an entry a lane; strips of whole wavefronts");
 // LE_I's last word: host memory was found to have no room for the entry, at any later time neither, or to have room (as long
 // as nothing else goes there: Shared::probed).
@@ -118,7 +125,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 dests[2];               // the round's migrations to flash, to host
   u32 probed;                 // nothing has gone to host since the entries with E_ROOM were looked at
   u32 pick_max, next;         // migrations picked in a round at most; NX_*
-  unsigned char spare[136];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
+  unsigned char spare[104];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
@@ -128,6 +135,11 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 fast, pad1;             // the pass's migrations were picked from the list without an arg-max over all threads
   u32 lim, pad3;              // the plan has made as many passes as it may
   u32 Fkeep, more;            // the floor of the pass; another round of commits follows from the same list
+  // clipped area: the plan's passes make lists, so often it has stopped doing so; this pass does not; lists in vain in a row, or winners
+  // in a row whose area was their band by the chunks alone; migrations and refused candidates when the pass began
+  u32 lists, lists_ended, no_list, in_row;
+  u64 settled0;
+  u32 uneven, paid;           // a chunk of the winner's window has a slot over the capacity by less than its size; lists that gave several
   u64 more_rounds, list_rescored;   // such rounds made; list entries scored again for them (statistics)
   u64 hq;                     // host-capacity query: maximum over the period
   u64 acc[3];                 // clipped area being summed: bits 0..31, 32..63 and 64.. of the terms, added apart
@@ -267,15 +279,21 @@ __host__ __device__ __forceinline__ u32 list_cap(u32 nch, u32 nt) {
 
 // TIGHT: the form for plans whose host memory refuses candidates, several of which go in one round (probe_host).  A form of its
 // own because what it adds to the chunk test, the picks and the commit costs the others 3 to 4 % (18 us a round, 0.6 more).
-template <bool RATIO, bool CLIP, bool TIGHT>
+// LISTS: the form of the clipped area that commits several migrations a pass, for plans whose winners' areas are their bands
+// (LISTS_AFTER).
+template <bool RATIO, bool CLIP, bool TIGHT, bool LISTS>
 __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopArgs* __restrict__ plans) {
   constexpr u32 LB = loop_threads(RATIO, CLIP), LW = LB / G10_WAVE;    // threads and wavefronts of this form
-  // Several migrations per ranking pass (ranking by the benefit itself, band reading): after the
+  // Several migrations per ranking pass (ranking by the benefit itself): after the
   // winner, the next best candidates of the same pass are committed with it as long as it is
   // certain that each would have won the pass after the one before it - see "more migrations
-  // of the same pass" below.
-  constexpr bool MC = !RATIO && !CLIP;
-  static_assert(MC || !TIGHT, "several migrations a pass");
+  // of the same pass" below.  With the clipped area a pick stands for its band, which bounds every area, and is committed
+  // only where the chunks show that its area is the band: every slot over the capacity in the chunks that its absent window
+  // touches exceeds it by the tensor's size, behind what the picks before it take.  Where that fails for the first pick, the
+  // pass goes on to the arg-max and the areas summed slot by slot (settle).
+  constexpr bool MC = !RATIO && (!CLIP || LISTS);
+  static_assert((MC && !CLIP) || !TIGHT, "several migrations a pass");
+  static_assert((MC && CLIP) || !LISTS, "several migrations a pass");
   constexpr bool WIDE = RATIO && !CLIP;        // long scoring rounds may be left to the scoring kernel (see WideCtx)
   extern __shared__ __align__(16) unsigned char smem[];
   const LoopArgs a = in_global(plans[blockIdx.x]);   // one workgroup per plan
@@ -382,6 +400,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->pub = ctl->pub ? ctl->pub : PUB_START;      // (0: not set yet; a margin of 0 starts over)
     S->nl = 0; S->restL = NONE32; S->stale_hot = 0; S->pick_max = MAXM;
     S->stop = 0; S->t_start = wall_clock64();
+    S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->uneven = 0; S->paid = 0;   // (the launch opens a pass: no list in vain yet)
+    S->settled0 = ctl->n_mig + ctl->n_drop;
     S->mem[0].hi = 0; S->mem[0].lo = 0;
   }
   __syncthreads();
@@ -546,6 +566,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (r.strike0) a.cd.A[cur.p] = make_uint4(A.x, A.y, 1u, 0u);
       if (r.strike1) a.cd.B[cur.p] = make_uint4(1u, 0u, B.z, B.w);
       u32 exact = 0;
+      bool lowered = false;
       Score rr = r;
       if (CLIP && (rr.ok0 || rr.ok1)) {          // the band bounds the area; a value computed earlier bounds it closer
         const uint2 e = a.cd.ce[cur.p];
@@ -555,6 +576,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           const u32 vd = (e.y >> 1) & 1u, pd = rr.ok0 ? 0u : 1u;
           if (vd == 0u && rr.ok0 && gt128(rr.h0, rr.l0, vhi, vlo)) { rr.h0 = vhi; rr.l0 = vlo; }
           if (vd == 1u && rr.ok1 && gt128(rr.h1, rr.l1, vhi, vlo)) { rr.h1 = vhi; rr.l1 = vlo; }
+          lowered = true;
           exact = (vd == pd && e.x == (u32)S->n_iter) ? 1u : 0u;   // (the number of the pass stamps the values computed in it)
         }
       }
@@ -578,7 +600,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       if (MC) {
         // every candidate whose bound reaches the list's threshold goes on the list of the pass
         // with all a commit needs; the others count with their bound only (floor2)
-        const bool pub = kc >= thr_pub && kc != 0u;
+        // (a candidate whose area has been found below its band is not listed: picks stand for bands)
+        const bool pub = kc >= thr_pub && kc != 0u && !lowered;
         const u64 pm = __ballot(pub);
         u32 slot = NONE32;
         if (pm) {
@@ -1281,6 +1304,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       const u32 cv = cover(tid, CH, K, wa, wb, len);
       if (cv) {
         const u64 mo = minOver[tid];
+        if (mo != NONE64 && mo - cap < s) S->uneven = 1;
         if (cv == len && mo == NONE64) {
           // no slot of the chunk is over the capacity
         } else if (cv == len && mo - cap >= s) {
@@ -1294,18 +1318,25 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       }
     }
     __syncthreads();
-    run_jobs(0u, uniform(S->njobs), 0xffffu, 0u);
+    const bool even = !uniform(S->uneven);
+    if (!even) run_jobs(0u, uniform(S->njobs), 0xffffu, 0u);     // (else the area is the band: nothing is summed)
     __syncthreads();
     const u64 a0 = S->acc[0], a1 = S->acc[1], a2 = S->acc[2];
     const u64 vlo = a0 + (a1 << 32), vhi = a2 + (a1 >> 32) + (vlo < a0 ? 1ull : 0ull);
-    const bool same = vhi == S->mem[0].hi && vlo == S->mem[0].lo;
+    const bool same = even || (vhi == S->mem[0].hi && vlo == S->mem[0].lo);
     __syncthreads();                                   // everyone has read the sums and the bound
     if (tid == 0) {
       S->evals += 1;
       S->njobs = 0;
+      if (!RATIO && !S->lists) {
+        S->in_row = even ? S->in_row + 1u : 0u;
+        if (C - S->n_mig - S->n_drop >= LISTS_LEFT && S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX)) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
+      }
+      S->uneven = 0;
       if (same) S->mem[0].exact = 1;
       else {
         S->refused += 1;
+        S->no_list = 1;                                // (the tiles scored again are not listed again)
         a.cd.cv[S->mem[0].pos] = make_uint4((u32)vlo, (u32)(vlo >> 32), (u32)vhi, (u32)(vhi >> 32));
         a.cd.ce[S->mem[0].pos] = make_uint2((u32)S->n_iter, 1u | (S->mem[0].dest << 1));
         S->ntl = 0;
@@ -1338,6 +1369,18 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       S->mem[0].hi = 0; S->mem[0].lo = 0;
       S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->by_floor = 0;
       if (S->stale_hot) { S->restL = NONE32; S->stale_hot = 0; }
+      if (LISTS) {
+        const u64 settled = S->n_mig + S->n_drop;
+        if (S->lists) {
+          if (settled - S->settled0 > 1u) { S->in_row = 0; S->paid += 1; }
+          else S->in_row += 1;
+          if (S->in_row >= LISTS_VAIN) {                   // (the other form goes on)
+            S->lists = 0; S->in_row = 0; S->stop = 1;
+            S->lists_ended = S->paid >= LISTS_PAID ? 0u : S->lists_ended + 1u;
+          }
+        }
+        S->no_list = S->lists ? 0u : 1u; S->settled0 = settled;
+      }
       S->lim = max_iter && S->n_iter >= max_iter ? 1u : 0u;
       if (a.tick_budget && wall_clock64() - S->t_start > a.tick_budget) S->stop = 1;
     }
@@ -1463,7 +1506,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           pass_units += nu;
         } else {
           u32 low = thr;                           // the list's threshold
-          if (MC) {
+          if (LISTS && uniform(S->no_list)) low = NONE32;
+          else if (MC) {
             const long long at = (long long)thr - (int)uniform((u32)S->pub);
             low = at > (long long)rest ? (u32)at : rest + 1u;
           }
@@ -1474,7 +1518,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           if (tid == 0) wv.ctx->pending = 0;
         }
         ++rounds;
-        if (MC && picks) {
+        if (MC && picks && !(LISTS && uniform(S->no_list))) {
           // The winner is the best entry of the list if that clears every bound of what is not on the
           // list: then one wavefront takes it from there, and the next ones with it, while the others
           // bring the group bounds up to date, and no arg-max over the threads is needed (2.5 us a
@@ -1496,7 +1540,19 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
             group_bounds(wave);
           }
           __syncthreads();
-          if (uniform(S->fast)) { rest_final = rest; break; }
+          if (uniform(S->fast)) {
+            if (LISTS && tid < nch) {                        // is the first one's area its band? (step 2 asks the same for the others)
+              const u32 pk = S->pick[0], slot = pk & 0xffffu;
+              const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot);
+              const bool host = (pk >> 16) & 1u;
+              u32 len = 0;
+              const u64 mo = minOver[tid];
+              if (cover(tid, CH, K, host ? B.x : A.z, host ? B.y : A.w, len) && mo != NONE64 && mo - cap < (((u64)B.w << 32) | B.z)) S->no_list = 1;
+            }
+            if (LISTS) __syncthreads();
+            if (!LISTS || !uniform(S->no_list)) { rest_final = rest; break; }
+            if (tid == 0) S->fast = 0;                       // (the best by bound is settled slot by slot; read again behind two barriers)
+          }
         }
         reduce_best();
         if (WIDE && from_wide) {                  // the rest of the best one
@@ -1673,6 +1729,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         }
         // the earlier ones may have let a slot of its absent window drop (its own pressure falls behind its win)
         bool wait = nA > 0 && spare <= runP;
+        if (LISTS && picked) wait = wait || (nA > 0 && spare - runP < ms);
         const u64 sA = nA > 0 ? ms : 0ull;
         if (md == G10_HOST) {
           // host memory may not hold it on top of the earlier ones
@@ -1726,6 +1783,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       __syncthreads();                                   // (both may change from here on)
       if (!looked_up) { probe_host(); m = 0; }
     }
+    if (LISTS && m == 0u && uniform(S->next) == NX_RESCORE) break;    // (its area may lie under its band: the next ranking pass settles it)
     if (MC && m == 0u) {                                 // (not even the first stands: the list is scored again)
       __syncthreads();
       if (tid == 0) { S->njobs = 0; S->cut = MAXM; S->need_exact = 0; S->next = NX_RESCORE; }
@@ -1817,6 +1875,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         // where many candidates are nearly equal (a pass scored thousands) the margin halves; it
         // doubles when a pass ran out of candidates above the floor with little scored
         u32 gs = S->gshift;
+        const bool listed = MC && !(LISTS && S->no_list);
         if (!owed) {
           // (the margin adapts once per ranking pass)
         } else if (WIDE && a.wide_min) {
@@ -1824,13 +1883,13 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           // the margin doubles whenever a pass needed one, and narrows only now and then
           if (rounds > 1u) { if (gs > 2u) --gs; }
           else if ((S->n_iter & 31u) == 0u && gs < GUESS_SHIFT) ++gs;
-        } else if (pass_units > (MC ? 24u : 8u) && gs < GUESS_SHIFT_MAX) ++gs;
+        } else if (pass_units > (listed ? 24u : 8u) && gs < GUESS_SHIFT_MAX) ++gs;
         // (Where a pass commits one migration, lists over 8 units do not pay: 600 passes by the ratio key with equal costs, 130 000
         // candidates, 15.0 ms with 24, 14.1 with 8.)
-        else if (MC) { if ((S->by_floor || rounds > 1u) && pass_units <= 18u && gs > MC_GUESS_SHIFT_MIN) --gs; }
+        else if (listed) { if ((S->by_floor || rounds > 1u) && pass_units <= 18u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
-        if (MC && owed) {
+        if (listed && owed) {
           const u32 nl_ = S->nlist;
           const int pub = S->pub, mag = pub < 0 ? -pub : pub;
           int x = pub;
@@ -1848,7 +1907,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         S->thr_key = RATIO ? rkey_dn(ratio_approx(Z.hi, Z.lo, Z.cost) * (1.0 - 1.0 / (double)(1u << gs))) : upkey(ghi, nlo);
         if (!room) {
           S->n_drop = nd + 1; S->more = 0;
-          if (MC && !TIGHT && nd + 1 >= TIGHT_FROM) S->stop = 1;           // (the form for it goes on)
+          if (MC && !CLIP && !TIGHT && nd + 1 >= TIGHT_FROM) S->stop = 1;           // (the form for it goes on)
         }
         else {
           // the passes of Algorithm 1 this round stands for beyond the one the ranking pass counted
@@ -1859,11 +1918,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           if (TIGHT && hosts) S->probed = 0;
           // another round of commits from the same list: unless the picking ran out of entries above
           // the floor and every one it picked was committed
-          const bool more = MC && S->nlist > 1u && picks && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
+          const bool more = MC && S->nlist > 1u && picks && listed && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
           S->more = more ? 1u : 0u;
           // (where the chunks cut a round short the next one picks little more than went through)
           if (MC) { const u32 pm = S->pick_max; S->pick_max = m < m0 ? (m + 2u < MAXM ? m + 2u : MAXM) : m0 == pm ? (2u * pm < MAXM ? 2u * pm : MAXM) : pm; }
           if (!owed) S->more_rounds += 1;
+          if (LISTS && picked) S->evals += m;              // (areas shown to be their bands)
         }
       }
     }
@@ -1945,6 +2005,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     ctl->n_iter = S->n_iter; ctl->n_mig = S->n_mig; ctl->n_drop = S->n_drop; ctl->n_evals = S->n_evals;
     ctl->thr_key = S->thr_key; ctl->status = S->status; ctl->done = S->done;
     ctl->gshift = S->gshift; ctl->pub = S->pub;
+    if (CLIP) { ctl->lists = S->lists; ctl->lists_ended = S->lists_ended; }
     ctl->overtime_after = base[(u64)A_OT * nb1 + nch];
     if (WIDE && a.wide) {
       ctl->units_scored = units0 + S->units; ctl->second_rounds = second0 + S->second; ctl->jobs_run = jobs0 + S->jobs;
@@ -2107,10 +2168,10 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch) {
 }
 
 typedef void (*LoopKernel)(const LoopArgs*);
-static LoopKernel loop_kernel(u32 rank, u32 area, bool tight) {
-  if (area == G10_AREA_CLIPPED) return rank == G10_RANK_RATIO ? k_loop<true, true, false> : k_loop<false, true, false>;
-  if (rank == G10_RANK_RATIO) return k_loop<true, false, false>;
-  return tight ? k_loop<false, false, true> : k_loop<false, false, false>;
+static LoopKernel loop_kernel(u32 rank, u32 area, bool second) {
+  if (rank == G10_RANK_RATIO) return area == G10_AREA_CLIPPED ? k_loop<true, true, false, false> : k_loop<true, false, false, false>;
+  if (area == G10_AREA_CLIPPED) return second ? k_loop<false, true, false, true> : k_loop<false, true, false, false>;
+  return second ? k_loop<false, false, true, false> : k_loop<false, false, false, false>;
 }
 
 int loop_allow_large_lds() {                     // (once per device: the attribute belongs to the kernel, not to a handle)
@@ -2120,14 +2181,14 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
   if (dev >= 0 && dev < 64 && done[dev]) return G10_OK;
   for (u32 rank = 0; rank < 2; ++rank)
     for (u32 area = 0; area < 2; ++area)
-      for (u32 tight = 0; tight < 2; ++tight)
-        G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area, tight != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
+      for (u32 second = 0; second < 2; ++second)
+        G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area, second != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
   if (dev >= 0 && dev < 64) done[dev] = true;
   return G10_OK;
 }
 
-int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool tight, hipStream_t s) {
-  hipLaunchKernelGGL(loop_kernel(rank, area, tight), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
+int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, hipStream_t s) {
+  hipLaunchKernelGGL(loop_kernel(rank, area, second), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }

@@ -899,9 +899,9 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // still score.  A batch ends its launches by the clock as well, so that no plan waits long for
   // the slowest one.  (Loops re-tiled every 64 / 128 / 192 rounds: stress 21.6 / 22.1 / 23.8 ms, ragged stress 4.44 / 4.62 /
   // 5.19; a 20-plan capacity sweep of the stress trace 35 ms at 64, 39 at 256.)
-  // (The other readings make one migration a round: every 128, in a batch every 256.)
+  // (The other readings, but for the clipped area with lists, make one migration a round: every 128, in a batch every 256.)
   auto retile_after = [&](const Inst& x) -> u32 {
-    const bool several = x.p->rank == G10_RANK_BENEFIT && x.p->area == G10_AREA_BAND;
+    const bool several = x.p->rank == G10_RANK_BENEFIT && (x.p->area == G10_AREA_BAND || x.hc.lists);
     return several ? RETILE_PASSES : count == 1 ? 2 * RETILE_PASSES : 4 * RETILE_PASSES;
   };
   u32 longest = 0;
@@ -942,14 +942,14 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   if (clocked) { G10_HIP(hipStreamSynchronize(s)); phase_end(0); }
   while (n_active) {
     u32 na = 0, n_by_kind[4] = {0, 0, 0, 0};
-    bool tight[4] = {false, false, false, false};          // (one plan of a kind that refuses candidates: all of them in that form)
+    bool second[4] = {false, false, false, false};         // (one plan of a kind that refuses candidates, or makes lists: all of them in that form)
     size_t lds = 0;
     for (u32 pass = 0; pass < 4 * count; ++pass) {         // the plans of one ranking key and benefit reading side by side: one kernel each
       const u32 i = pass % count, kind = pass / count;
       Inst& x = I[i];
       if (x.hc.done || 2 * x.p->area + x.p->rank != kind) continue;
       ++n_by_kind[kind];
-      tight[kind] = tight[kind] || x.hc.n_drop >= TIGHT_FROM;
+      second[kind] = second[kind] || (x.p->area == G10_AREA_CLIPPED ? x.hc.lists != 0u : x.hc.n_drop >= TIGHT_FROM);
       // Every launch (with the scoring kernel: every round of launches) finishes a pass, and a pass commits or refuses a
       // candidate or ends the plan: that bounds the launches by the candidates, however much of a launch's budget a pass takes.
       if (x.idle > 3) return G10_EDEVICE;
@@ -998,13 +998,13 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       // nothing left to do), so about this many reach the round's last pass; one more launch ends the pass the last
       // pair may have left open
       for (u32 g = 0; g < hargs[0].pass_budget; ++g) {
-        G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, tight[1], s));
+        G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], s));
         G10_TRY(loop_wide_launch((const LoopArgs*)h->loop_args, hargs[0].memo != nullptr, s));
       }
-      G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, tight[1], s));
+      G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], s));
     } else
     for (u32 kind = 0, first = 0; kind < 4; first += n_by_kind[kind], ++kind)
-      if (n_by_kind[kind]) G10_TRY(loop_launch((const LoopArgs*)h->loop_args + first, n_by_kind[kind], lds, kind & 1u, kind >> 1, tight[kind], s));
+      if (n_by_kind[kind]) G10_TRY(loop_launch((const LoopArgs*)h->loop_args + first, n_by_kind[kind], lds, kind & 1u, kind >> 1, second[kind], s));
     if (na > 1) {
       hipLaunchKernelGGL(k_ctl_collect, dim3(na), dim3(G10_WAVE), 0, s, (const LoopArgs*)h->loop_args, ctl_side);
       G10_HIP(hipGetLastError());

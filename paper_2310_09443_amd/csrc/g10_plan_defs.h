@@ -47,6 +47,7 @@ struct Ctl {
   u32 thr_key;                // first threshold of the next pass (0: use the largest tile bound)
   u32 n_live;                 // candidates that could still score at the last re-scoring
   u32 gshift;                 // the guess: first threshold = last best * (1 - 2^-gshift); 0 stands for GUESS_SHIFT
+  u32 lists, lists_ended;     // clipped area: the plan goes on in the form with lists; so often it has left that form
   int pub;                    // the list's margin under the threshold, in key steps; 0: not set yet
   // statistics
   u64 units_scored, second_rounds, jobs_run, launches, passes;
@@ -437,4 +438,4 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candi
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
 int loop_wide_launch(const g10::LoopArgs* plans, bool kept, hipStream_t s);   // the scoring kernel for plans[0]; kept: with its memo
-int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool tight, hipStream_t s);   // all of one ranking key and benefit reading; tight: in the form for plans that refuse candidates
+int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, hipStream_t s);   // all of one ranking key and benefit reading; second: in the form for plans that refuse candidates, or (clipped area) with lists

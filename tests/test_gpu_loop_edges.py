@@ -92,3 +92,22 @@ def test_most_chunks_and_most_tiles(g10, K, n):
         assert_plan_equal(h.plan(**a), v.plan(**a))
         assert h._counters(0).score_full_cands == n
     h.close()
+
+
+@pytest.mark.parametrize("cap,host", [(0.15, 0.02), (0.3, 0.25), (0.6, 0.05), (0.85, 2.0)])
+@pytest.mark.parametrize("K,N", [(90, 300), (257, 1500), (600, 2600)])
+def test_clipped_areas_that_are_their_bands_and_others(g10, K, N, cap, host):
+    """Plans by the clipped area go to the form that commits several migrations a pass and back: excesses above and below the
+    tensors' sizes, refused candidates, limits in the middle of a round; alone and beside a plan that stays in the other form."""
+    w = traces.stress(K=K, N=N, seed=K + N)
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * cap), host_cap=int(v.peak * host), area=1)
+    p = v.plan(**a)
+    assert_plan_equal(h.plan(**a), p)
+    for limit in (9, 40, 77):
+        assert_plan_equal(h.plan(max_iters=limit, **a), v.plan(max_iters=limit, **a))
+    b = dict(a, gpu_cap=int(v.peak * 0.97))
+    rs = h.plan_batch([a, b])
+    assert_plan_equal(rs[0], p)
+    assert_plan_equal(rs[1], v.plan(**b))
+    h.close()
