@@ -88,6 +88,12 @@ constexpr u32 LIST_MIN = 64, LIST_MAX = 256, LIST_VECS = 8, LIST_ENTRY = LIST_VE
 // form for both, lists tried less and less often, plans of 20 to 60 passes took 10 to 13 % more.  ResNet, 1638 migrations,
 // after 8 winners and 4 lists 4.3 ms, 10 and 3 5.5, 10 and 2 6.8; in the form with lists alone 3.4; one migration a pass 17.6.)
 constexpr u32 LISTS_AFTER = 8, LISTS_VAIN = 4, LISTS_PAID = 4, LISTS_MORE_MAX = 7, LISTS_LEFT = 128;
+// Where the chunks are no more than four per wavefront (but the last one) and the picks many, the chunk test takes a row of 16 lanes per chunk and a
+// lane per migration, else a lane per chunk and the migrations one after the other.  (Steps of ResNet, 23 chunks and 12 picks a
+// round 2875 -> 2743 us, encoder 1298 -> 1273, ResNet by the clipped area 3.89 -> 3.44 ms.  With rows wherever 80 chunks fit two turns
+// of them decoder, 49 chunks and 4 picks, 3258 -> 3435, ragged stress, 79 and 12, 5663 -> 5824.)
+constexpr u32 ROW_CHUNKS = (LW_MAX - 1) * 4, ROW_PICKS = 8;
+static_assert(MAXM == 16, "a row of lanes per chunk");
 static_assert(LIST_MIN == G10_WAVE && LIST_MAX % G10_WAVE == 0, "an entry a lane; strips of whole wavefronts");
 // LE_I's last word: host memory was found to have no room for the entry, at any later time neither, or to have room (as long
 // as nothing else goes there: Shared::probed).
@@ -112,7 +118,7 @@ struct Floor {                // bound of the list's entries that the picking wa
 
 struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   Winner mem[MAXM];           // migrations of the pass in commit order; [0] is the winner of the ranking (hi = lo = 0: none)
-  Winner wave_win[LW_MAX];    // best of every wavefront
+  Winner wave_win[LW_MAX];    // best of every wavefront (between two rankings: what the chunk test finds, ROW_CHUNKS)
   double bw[8];               // bandwidths out 0, 1, in 0, 1, and their reciprocals
   // What the picking wavefront leaves: the migrations of the round (entry of the list, destination << 16; free times
   // before the eviction window's start and the prefetch window's end as the picks before left them), and its state
@@ -258,6 +264,17 @@ __device__ __forceinline__ u32 thread_here() {
   return t;
 }
 
+// inclusive sums inside each row of 16 lanes
+__device__ __forceinline__ u64 row_scan(u64 v) {
+  v += dpp_move<0x111, 0xf, 0xf>((u64)0, v);
+  v += dpp_move<0x112, 0xf, 0xf>((u64)0, v);
+  v += dpp_move<0x114, 0xf, 0xf>((u64)0, v);
+  v += dpp_move<0x118, 0xf, 0xf>((u64)0, v);
+  return v;
+}
+__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+__device__ __forceinline__ bool any(bool x) { return ballot(x) != 0; }
+
 template <bool RATIO>
 __device__ __forceinline__ u32 best_lane(u64 hi, u64 lo, u64 cost, u32 cand) {
   if (RATIO) return wave_best_lane_ratio(hi, lo, cost, cand);
@@ -294,6 +311,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   constexpr bool MC = !RATIO && (!CLIP || LISTS);
   static_assert((MC && !CLIP) || !TIGHT, "several migrations a pass");
   static_assert((MC && CLIP) || !LISTS, "several migrations a pass");
+  static_assert(sizeof(Winner) * LW_MAX >= ROW_CHUNKS * sizeof(uint4), "the chunk test's results");
   constexpr bool WIDE = RATIO && !CLIP;        // long scoring rounds may be left to the scoring kernel (see WideCtx)
   extern __shared__ __align__(16) unsigned char smem[];
   const LoopArgs a = in_global(plans[blockIdx.x]);   // one workgroup per plan
@@ -1686,6 +1704,64 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       else M.tau_i = tau;
     }
     if (tid == 0) { S->jnext = LW - 1; S->touched = 0; S->ot_changed = 0; }
+    const bool rows = MC && picked && nch <= ROW_CHUNKS && m0 >= ROW_PICKS;
+    uint4* const bits = (uint4*)S->wave_win;             // (free between two rankings) per chunk: allP | cutP << 16, eF | wF << 16, allH | cutH << 16, eH | wH << 16
+    if (rows && wave < LW - 1) {
+      // Few chunks: a row of 16 lanes per chunk, a migration per lane, over all wavefronts but the one that writes the picks out.
+      // (A chunk per lane takes one wavefront 0.2 us a migration.)
+      const u32 i = lane & 15u, r = lane >> 4;
+      u32 gL = 0, gR = 0, ga = 1, gb = 0, gd = 0;
+      u64 ms = 0;
+      if (i < m0) {
+        const u32 pk = S->pick[i], slot = pk & 0xffffu;
+        const uint4 A = list_at(LE_A, slot), B = list_at(LE_B, slot);
+        const u32 d = (pk >> 16) & 1u;
+        gd = TIGHT && d ? (pk >> 16) & 3u : d;
+        gL = A.x; gR = A.y; ga = d ? B.x : A.z; gb = d ? B.y : A.w; ms = ((u64)B.w << 32) | B.z;
+      }
+      const bool real = i < m0, host = real && gd == G10_HOST, flash = real && gd == G10_FLASH;     // (neither: refused, it changes nothing)
+      const bool wrap = any(gR > K), hosts = any(host);
+      u32 cut = MAXM;
+      if (wave * 4u < nch) {
+        const u32 c = wave * 4u + r;
+        const bool in = c < nch;
+        const u64 mo = in ? minOver[c] : NONE64, hm = in && hosts ? hmax[c] : 0ull;
+        const bool stale = in && (hpend[c] & 2u) != 0u;
+        const u32 c0 = in ? c * CH : 0u, c1 = in ? (c0 + CH < K ? c0 + CH : K) : 0u, len = c1 - c0;
+        const u64 spare = stale ? 0ull : mo == NONE64 ? NONE64 : mo - cap;
+        int nE = (int)((c1 < ga ? c1 : ga) - (c0 > gL ? c0 : gL)), nA = (int)((c1 < gb + 1 ? c1 : gb + 1) - (c0 > ga ? c0 : ga)),
+            nW = (int)((c1 < gR ? c1 : gR) - (c0 > gb + 1 ? c0 : gb + 1));
+        bool fP = gL <= c0 && c1 <= gR;
+        if (wrap && gR > K) {                            // (ends in the second iteration)
+          const u32 nP = covered(c0, c1, K, gL, gR);
+          nE = (int)covered(c0, c1, K, gL, ga); nA = (int)covered(c0, c1, K, ga, gb + 1); nW = (int)nP - nE - nA;
+          fP = nP != 0 && nP == len;
+        }
+        const bool tA = real && in && nA > 0, does = host || flash;
+        const u64 sA = tA && does ? ms : 0ull, runP = row_scan(sA) - sA;
+        bool wait = tA && (spare <= runP || (LISTS && spare - runP < ms));
+        u64 mAllH = 0, mTH = 0, mEH = 0, mWH = 0;
+        if (hosts) {
+          const bool tH = host && in && (nE > 0 || nA > 0 || nW > 0);
+          const u64 sH = tH ? ms : 0ull, runH = row_scan(sH) - sH, hroom = hm < host_cap ? host_cap - hm : 0ull;
+          const bool full = tH && runH + ms > hroom;
+          if (any(full && i == 0u) && lane == 0) S->need_exact = 1;
+          wait = wait || (full && i != 0u);
+          mTH = ballot(tH); mAllH = ballot(tH && fP); mEH = ballot(tH && nE > 0); mWH = ballot(tH && nW > 0);
+        }
+        const u64 wm = ballot(wait), mA = ballot(tA && does), mAll = ballot(tA && does && nA == (int)len), mE = ballot(flash && in && nE > 0), mW = ballot(flash && in && nW > 0);
+        const u32 w16 = (u32)(wm | wm >> 16 | wm >> 32 | wm >> 48) & 0xffffu;
+        if (w16 && (u32)__builtin_ctz(w16) < cut) cut = (u32)__builtin_ctz(w16);
+        if (i == 0u && in) {
+          const u32 sh = r * 16u;
+          const u32 a_ = (u32)(mA >> sh) & 0xffffu, all_ = (u32)(mAll >> sh) & 0xffffu, th_ = (u32)(mTH >> sh) & 0xffffu, allh_ = (u32)(mAllH >> sh) & 0xffffu;
+          bits[c] = make_uint4(all_ | (a_ & ~all_) << 16, ((u32)(mE >> sh) & 0xffffu) | (u32)(mW >> sh) << 16,
+                               allh_ | (th_ & ~allh_) << 16, ((u32)(mEH >> sh) & 0xffffu) | (u32)(mWH >> sh) << 16);
+        }
+      }
+      if (cut < MAXM && lane == 0) atomicMin(&S->cut, cut);
+    }
+    if (rows) __syncthreads();
     if (tid < ((nch + 63u) & ~63u)) {
       // migration i lies in lane i of every wavefront and is read from there into scalars: with a trip to
       // LDS for every migration this loop took 2.1 us a round on the stress trace
@@ -1708,7 +1784,22 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       const u64 spare = stale ? 0ull : mo == NONE64 ? NONE64 : mo - cap;
       const u64 hroom = hm < host_cap ? host_cap - hm : 0ull;
       u32 cut = MAXM;                                    // (of this wavefront's chunks: the migrations from there on wait)
-      for (u32 i = 0; i < m0; ++i) {
+      if (rows) {
+        const uint4 b = in ? bits[tid] : make_uint4(0u, 0u, 0u, 0u);
+        allP = b.x & 0xffffu; cutP = b.x >> 16; eF = b.y & 0xffffu; wF = b.y >> 16;
+        allH = b.z & 0xffffu; cutH = b.z >> 16; eH = b.w & 0xffffu; wH = b.w >> 16;
+        const u32 tP = allP | cutP, tH = allH | cutH;
+        for (u32 i = 0; i < m0; ++i) {
+          const u64 ms = read_lane64(gs, i);
+          runP += (tP >> i) & 1u ? ms : 0ull;
+        }
+        if (any(tH != 0u))
+          for (u32 i = 0; i < m0; ++i) {
+            const u64 ms = read_lane64(gs, i);
+            runH += (tH >> i) & 1u ? ms : 0ull;
+            lzH += (allH >> i) & 1u ? ms : 0ull;
+          }
+      } else for (u32 i = 0; i < m0; ++i) {
         const u32 mL1 = (u32)__builtin_amdgcn_readlane((int)gL, (int)i), mR = (u32)__builtin_amdgcn_readlane((int)gR, (int)i);
         const u32 ma = (u32)__builtin_amdgcn_readlane((int)ga, (int)i), mb = (u32)__builtin_amdgcn_readlane((int)gb, (int)i);
         const u32 md = (u32)__builtin_amdgcn_readlane((int)gd, (int)i), bit = 1u << i;

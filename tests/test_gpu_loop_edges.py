@@ -111,3 +111,16 @@ def test_clipped_areas_that_are_their_bands_and_others(g10, K, N, cap, host):
     assert_plan_equal(rs[0], p)
     assert_plan_equal(rs[1], v.plan(**b))
     h.close()
+
+
+@pytest.mark.parametrize("host", [0.02, 0.4])
+@pytest.mark.parametrize("K,N,max_chunks", [(1024, 9000, 0), (1025, 9000, 0), (11264, 14000, 0), (11265, 14000, 0), (3000, 20000, 3)])
+def test_chunk_test_of_few_and_many_chunks(g10, K, N, max_chunks, host):
+    """Up to 44 chunks a round of eight picks or more is tested a row of lanes per chunk: rows left over, one chunk more, both destinations."""
+    w = traces.stress(K=K, N=N, seed=K)
+    h, v, args = run_both(g10, w)
+    for cap in (0.3, 0.7):
+        a = dict(args, gpu_cap=int(v.peak * cap), host_cap=int(v.peak * host))
+        p = v.plan(max_iters=600, **a)
+        assert_plan_equal(h.plan(max_iters=600, max_chunks=max_chunks, **a), p)
+    h.close()
