@@ -143,18 +143,19 @@ __global__ __launch_bounds__(G10_BLOCK) void k_pack(const uint4* __restrict__ pe
 // ---------------------------------------------------------------------------
 // timelines before any eviction: slot arrays, chunk-local prefixes, chunk totals
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, const u64* __restrict__ pressure0, const Ctl* ctl,
+// (c0: the plan's parameters, which go up with the launch)
+__global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, const u64* __restrict__ pressure0, const Ctl c0, Ctl* ctl,
                                                              u64* __restrict__ g_tot, u64* __restrict__ g_lazyP,
                                                              u64* __restrict__ g_minOver, u64* __restrict__ g_lazyH,
                                                              u64* __restrict__ g_hmax, u32* __restrict__ g_hmat,
                                                              u32* __restrict__ g_hpend, u64* __restrict__ peak, u64* __restrict__ wide) {
   if (blockIdx.x == 0) {                       // the peak after the plan; no pass left open
-    if (threadIdx.x == 0) *peak = 0;
+    if (threadIdx.x == 0) { *peak = 0; *ctl = c0; }
     if (threadIdx.x < 8) wide[threadIdx.x] = 0;
   }
   __shared__ u64 tmp[2 * G10_WAVES];
   __shared__ u64 mins[G10_WAVES];
-  const u64 cap = ctl->gpu_cap;
+  const u64 cap = c0.gpu_cap;
   const u32 chunk = blockIdx.x, ch = G10_BLOCK * tl.spt, K = tl.K;
   const u32 j0 = chunk * ch + threadIdx.x * tl.spt;
   u64 v[2] = {0, 0};
@@ -193,33 +194,30 @@ __global__ __launch_bounds__(G10_BLOCK) void k_init_timelines(Timelines tl, cons
   }
 }
 
-// level 1 of the over-capacity time before any eviction, for the full scoring
-// pass; also the "fits already" test
-__global__ __launch_bounds__(WG) void k_level1_init(const u64* __restrict__ g_tot, u32 nch, u64* __restrict__ base0, Ctl* ctl) {
-  __shared__ u64 scr[WG_WAVES];
-  const u32 tid = threadIdx.x;
-  const u64 v = tid < nch ? g_tot[(u64)A_OT * nch + tid] : 0ull;
-  const u64 inc = wave_scan_incl(v);
-  if (lane_id() == G10_WAVE - 1) scr[wave_id()] = inc;
-  __syncthreads();
-  u64 b = 0, t = 0;
-  for (u32 w = 0; w < WG_WAVES; ++w) { const u64 x = scr[w]; if (w < wave_id()) b += x; t += x; }
-  if (tid < nch) base0[tid] = b + inc - v;
-  if (tid == 0) {
-    base0[nch] = t;
-    ctl->overtime_before = t;
-    ctl->overtime_after = t;
-    if (t == 0) { ctl->done = 1; ctl->status = G10_FITS; }
+// over-capacity time before every slot, before any eviction: ot[j] for j in [0, K], chunk-local prefix + the chunks before,
+// in place; also the "fits already" test, and the candidates kept (pos: their scan, or null) for the host.  A workgroup adds the totals of
+// the chunks before its own up itself (two loads a thread at most): a launch for them alone, and a copy of their own for
+// the number of candidates, the parameters and the final peak, took 23 us of the 358 of the smallest trace's step.
+__global__ __launch_bounds__(G10_BLOCK) void k_ot_full(u64* __restrict__ ot, const u64* __restrict__ g_tot, u32 K, u32 nch,
+                                                      u32 shift_ch, const u32* __restrict__ pos, u32 C, Ctl* ctl) {
+  __shared__ u64 tmp[G10_WAVES + 1];
+  const u32 j = blockIdx.x * G10_BLOCK + threadIdx.x, chunk = (blockIdx.x * G10_BLOCK) >> shift_ch;      // (a workgroup's slots lie in one chunk)
+  u64 before = 0, all = 0;
+  for (u32 c = threadIdx.x; c < nch; c += G10_BLOCK) {
+    const u64 x = g_tot[(u64)A_OT * nch + c];
+    all += x;
+    if (c < chunk) before += x;
   }
-}
-
-// over-capacity time before every slot, before any eviction: ot[j] for j in [0, K], chunk-local
-// prefix + chunk base, in place
-__global__ __launch_bounds__(G10_BLOCK) void k_ot_full(u64* __restrict__ ot, const u64* __restrict__ base0, u32 K, u32 nch,
-                                                      u32 shift_ch) {
-  const u32 j = blockIdx.x * G10_BLOCK + threadIdx.x;
-  if (j < K) ot[j] += base0[j >> shift_ch];
-  else if (j == K) ot[K] = base0[nch];
+  before = block_sum(before, tmp);
+  all = block_sum(all, tmp);
+  if (j < K) ot[j] += before;
+  else if (j == K) ot[K] = all;
+  if (j == 0) {
+    ctl->overtime_before = all;
+    ctl->overtime_after = all;
+    if (all == 0) { ctl->done = 1; ctl->status = G10_FITS; }
+    ctl->n_cand = pos ? pos[C] : 0u;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -243,9 +241,10 @@ __device__ __forceinline__ u32 bound_of_sort_key(u32 sk) { return (0x7fffffu - s
 template <bool RATIO, bool PACKED>
 __global__ __launch_bounds__(G10_BLOCK) void k_score_full(const uint4* __restrict__ fw, const u64* __restrict__ fs, u32 n,
                                                          const u64* __restrict__ ot, u32 K,
-                                                         u32* __restrict__ sortkeys, const Ctl* __restrict__ ctl) {
+                                                         u32* __restrict__ sortkeys, const Ctl* __restrict__ ctl, u32* __restrict__ tkeys, u32 nt) {
   const u32 p = blockIdx.x * G10_BLOCK + threadIdx.x;
   if (p >= n) return;
+  if (p < nt) tkeys[p] = 0;                   // (the bounds of the tiles, which the gathering raises)
   uint4 W = fw[p];                            // {a0, b0, a1, b1}
   u64 s;
   if (PACKED) unpack_windows(W, W, s);
@@ -487,13 +486,12 @@ static void work_layout(PlanWork* w, Arena& ar) {
   }
   ar.take(&w->P, K); ar.take(&w->fre, (u64)4 * w->Kp); ar.take(&w->H, K);
   ar.take(&w->px, (u64)PX * w->Kp); ar.take(&w->otc, (u64)K + 1);
-  ar.take(&w->base0, (u64)w->nch + 1);
   ar.take(&w->g_base, (u64)N_ARR * (w->nch + 1));
   ar.take(&w->g_tot, (u64)N_ARR * w->nch);
   ar.take(&w->g_lazyP, w->nch); ar.take(&w->g_minOver, w->nch);
   ar.take(&w->g_lazyH, w->nch); ar.take(&w->g_hmax, w->nch);
-  ar.take(&w->pressure_after, K);
-  ar.take(&w->peak_after, 1);
+  ar.take(&w->pressure_after, (u64)K + 1);         // (the peak behind it: one copy takes both)
+  if (ar.base) w->peak_after = w->pressure_after + K;
   ar.take(&w->ctl, 1);
   ar.take(&w->records, C);
   ar.take(&w->rec_ab, C);
@@ -572,7 +570,7 @@ static PlanWork** work_slot(g10_plan_s* h, u32 i) { return i == 0 ? &h->work : &
 // `count` plans on one analysed trace.  The streaming kernels of the plans run one after the
 // other (each fills the chip); the greedy loops run side by side, one workgroup per plan, in
 // one launch per round; between rounds the long candidate lists are put back into score order.
-typedef void (*ScoreFullKernel)(const uint4*, const u64*, u32, const u64*, u32, u32*, const Ctl*);
+typedef void (*ScoreFullKernel)(const uint4*, const u64*, u32, const u64*, u32, u32*, const Ctl*, u32*, u32);
 static ScoreFullKernel score_full_kernel(u32 rank, bool packed) {
   if (packed) return rank == G10_RANK_RATIO ? k_score_full<true, true> : k_score_full<false, true>;
   return rank == G10_RANK_RATIO ? k_score_full<true, false> : k_score_full<false, false>;
@@ -615,7 +613,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // what goes up to and comes back from the device in small pieces lies in pinned memory: copies to and
   // from it are queued like kernels, a copy to pageable memory makes the host wait twice (grown before anything
   // is made that a return from here would have to free)
-  const size_t staging = (size_t)count * (sizeof(LoopArgs) + 2 * sizeof(Ctl) + sizeof(u64) + sizeof(u32));
+  const size_t staging = (size_t)count * (sizeof(LoopArgs) + sizeof(Ctl));
   if (h->pin_bytes < staging) {
     mem_host_free(h->pin);
     h->pin = nullptr; h->pin_bytes = 0;
@@ -624,9 +622,6 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   }
   LoopArgs* const hargs = (LoopArgs*)h->pin;
   Ctl* const hctl = (Ctl*)(hargs + count);                                    // progress blocks: after the preparation, and of a launch
-  Ctl* const hctl0 = hctl + count;                                            // ... as they go up
-  u64* const peaks = (u64*)(hctl0 + count);                                   // the plans' final peaks
-  u32* const hn = (u32*)(peaks + count);                                      // candidates kept
   Inst* I = new (std::nothrow) Inst[count];
   u32* who = (u32*)malloc((size_t)count * sizeof(u32));                       // the plan of every entry of a launch
   SortJob* hsj = (SortJob*)malloc((size_t)count * sizeof(SortJob));
@@ -724,15 +719,11 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     hc.rank = p->rank; hc.area = p->area;
     hc.C = C;
     hc.smax = h->max_size;
-    hctl0[i] = hc;
-    G10_HIP(hipMemcpyAsync(w->ctl, &hctl0[i], sizeof hc, hipMemcpyHostToDevice, q));
     Timelines& tl = x.tl;
     tl.dur = w->dur; tl.P = w->P; tl.fre = w->fre; tl.H = w->H; tl.px = w->px; tl.otc = w->otc;
     tl.K = K; tl.Kp = w->Kp; tl.nch = w->nch; tl.spt = w->spt; tl.shift_ch = w->shift_ch;
     hipLaunchKernelGGL(k_init_timelines, dim3(w->nch), dim3(G10_BLOCK), 0, q, tl, (const u64*)(h->pressure_buf + 1),
-                       (const Ctl*)w->ctl, w->g_tot, w->g_lazyP, w->g_minOver, w->g_lazyH, w->g_hmax, w->g_hmat, w->g_hpend, w->peak_after, (u64*)w->wide);
-    hipLaunchKernelGGL(k_level1_init, dim3(1), dim3(WG), 0, q, (const u64*)w->g_tot, w->nch, w->base0, w->ctl);
-    hipLaunchKernelGGL(k_ot_full, dim3(K / G10_BLOCK + 1), dim3(G10_BLOCK), 0, q, w->otc, (const u64*)w->base0, K, w->nch, w->shift_ch);
+                       hc, w->ctl, w->g_tot, w->g_lazyP, w->g_minOver, w->g_lazyH, w->g_hmax, w->g_hmat, w->g_hpend, w->peak_after, (u64*)w->wide);
     G10_HIP(hipGetLastError());
     x.lead = i;
     for (u32 j = 0; j < i; ++j) {
@@ -745,12 +736,14 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
                          (const Ctl*)w->ctl, w->win, w->keep);
       G10_HIP(hipGetLastError());
       G10_TRY(scan_excl_u32(w->keep, w->keep, C, w->scratch32, q));
-      G10_HIP(hipMemcpyAsync(&hn[i], w->keep + C, sizeof(u32), hipMemcpyDeviceToHost, q));
     }
+    hipLaunchKernelGGL(k_ot_full, dim3(K / G10_BLOCK + 1), dim3(G10_BLOCK), 0, q, w->otc, (const u64*)w->g_tot, K, w->nch, w->shift_ch,
+                       C && x.lead == i ? (const u32*)w->keep : (const u32*)nullptr, C, w->ctl);
+    G10_HIP(hipGetLastError());
     G10_HIP(hipMemcpyAsync(&hctl[i], w->ctl, sizeof hc, hipMemcpyDeviceToHost, q));
   }
   G10_TRY(sync_all());
-  for (u32 i = 0; i < count; ++i) { I[i].hc = hctl[i]; I[i].n = C ? hn[I[i].lead] : 0u; }
+  for (u32 i = 0; i < count; ++i) { I[i].hc = hctl[i]; I[i].n = I[I[i].lead].hc.n_cand; }
 
   // the candidate buffers of a plan; the value cache only where the plan reads the benefit as the clipped area
   auto cands_of = [](const Inst& x, int which) {
@@ -777,7 +770,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       const u32 gn = (n + G10_BLOCK - 1) / G10_BLOCK;
       // the two events take the kernel's own begin and end time stamps
       hipExtLaunchKernelGGL(score_full_kernel(x.p->rank, packed), dim3(gn), dim3(G10_BLOCK), 0, q, w->ev[2], w->ev[3], 0, (const uint4*)w->fw,
-                            (const u64*)w->fs, n, (const u64*)w->otc, K, w->keys, (const Ctl*)w->ctl);
+                            (const u64*)w->fs, n, (const u64*)w->otc, K, w->keys, (const Ctl*)w->ctl, w->tkeys, x.nt);
       x.timed_full = true;
     } else {
       u32 gn = (n + G10_BLOCK - 1) / G10_BLOCK;
@@ -796,7 +789,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     u32 *keys = w->keys, *alt = w->keys_alt;
     u32 *from = w->sv, *from_alt = w->sv_alt;          // where every candidate of the new order stood in the old one
     G10_TRY(radix_sort_u32_pairs(&keys, &alt, &from, &from_alt, n, SCORE_SORT_BITS, w->hist, q, true));
-    G10_HIP(hipMemsetAsync(w->tkeys, 0, (u64)NT_MAX * 4, q));
+    if (!first) G10_HIP(hipMemsetAsync(w->tkeys, 0, (u64)x.nt * 4, q));
     hipLaunchKernelGGL(k_tile_gather, dim3(x.n_pad / G10_BLOCK), dim3(G10_BLOCK), 0, q, (const u32*)keys, (const u32*)from, n, x.n_pad,
                        cands_of(x, x.cur), cands_of(x, x.cur ^ 1), 8 + x.tsh, w->tkeys);
     G10_HIP(hipGetLastError());
@@ -874,7 +867,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
         const u32 gn = (x.n + G10_BLOCK - 1) / G10_BLOCK;
         if (!writes_fw) G10_HIP(hipStreamWaitEvent(stream_of(i), lw->ev[2], 0));         // (recorded when an earlier plan wrote the copy)
         hipLaunchKernelGGL(score_full_kernel(x.p->rank, packed), dim3(gn), dim3(G10_BLOCK), 0, stream_of(i), (const uint4*)lw->fw, (const u64*)lw->fs, x.n,
-                           (const u64*)w->otc, K, w->keys, (const Ctl*)w->ctl);
+                           (const u64*)w->otc, K, w->keys, (const Ctl*)w->ctl, (u32*)nullptr, 0u);
         G10_HIP(hipGetLastError());
         fill_jobs(x, nj0, max0);
         ++nj0;
@@ -921,8 +914,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     hipLaunchKernelGGL(k_finish, dim3(K / G10_BLOCK / 4 + 1), dim3(G10_BLOCK), 0, q, x.tl, (const u64*)w->g_lazyP, w->pressure_after,
                        w->peak_after);
     G10_HIP(hipGetLastError());
-    G10_HIP(hipMemcpyAsync(&peaks[i], w->peak_after, 8, hipMemcpyDeviceToHost, q));
-    const size_t need = (size_t)K * 8 + hc.n_mig * sizeof(g10_migration) + hc.n_drop * sizeof(g10_dropped);
+    const size_t need = ((size_t)K + 1) * 8 + hc.n_mig * sizeof(g10_migration) + hc.n_drop * sizeof(g10_dropped);
     if (need > w->h_block_bytes) {
       if (w->h_block) { mem_host_free(w->h_block); w->h_block = nullptr; w->h_block_bytes = 0; }
       const size_t want = need + need / 4 + 4096;
@@ -930,11 +922,11 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       w->h_block_bytes = want;
     }
     w->h_pressure = (u64*)w->h_block;
-    w->h_records = (g10_migration*)(w->h_pressure + K);
+    w->h_records = (g10_migration*)(w->h_pressure + K + 1);
     w->h_dropped = (g10_dropped*)(w->h_records + hc.n_mig);
     if (hc.n_mig) G10_HIP(hipMemcpyAsync(w->h_records, w->records, hc.n_mig * sizeof(g10_migration), hipMemcpyDeviceToHost, q));
     if (hc.n_drop) G10_HIP(hipMemcpyAsync(w->h_dropped, w->dropped, hc.n_drop * sizeof(g10_dropped), hipMemcpyDeviceToHost, q));
-    G10_HIP(hipMemcpyAsync(w->h_pressure, w->pressure_after, (u64)K * 8, hipMemcpyDeviceToHost, q));
+    G10_HIP(hipMemcpyAsync(w->h_pressure, w->pressure_after, ((u64)K + 1) * 8, hipMemcpyDeviceToHost, q));
     return G10_OK;
   };
 
@@ -1074,7 +1066,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     memset(out, 0, sizeof *out);
     out->status = (int32_t)hc.status;
     out->n_migrations = hc.n_mig; out->n_iterations = hc.n_iter; out->n_dropped = hc.n_drop; out->n_cand_evals = hc.n_evals;
-    out->peak_before = h->peak; out->peak_after = peaks[i];
+    out->peak_before = h->peak; out->peak_after = w->h_pressure[K];
     out->overtime_before_ns = x.overtime_before; out->overtime_after_ns = hc.overtime_after;
     out->migrations = w->h_records; out->dropped = w->h_dropped; out->pressure_after = w->h_pressure;
     out->plan_ms = ms;

@@ -45,6 +45,7 @@ struct Ctl {
   u64 n_iter, n_mig, n_drop, n_evals;
   u64 overtime_before, overtime_after;
   u32 thr_key;                // first threshold of the next pass (0: use the largest tile bound)
+  u32 n_cand;                 // candidates with a window at the start
   u32 n_live;                 // candidates that could still score at the last re-scoring
   u32 gshift;                 // the guess: first threshold = last best * (1 - 2^-gshift); 0 stands for GUESS_SHIFT
   u32 lists, lists_ended;     // clipped area: the plan goes on in the form with lists; so often it has left that form
@@ -380,7 +381,7 @@ struct PlanWork {
   u32 *keys = nullptr, *keys_alt = nullptr;   // the keys of the score sort
   u32 *sv = nullptr, *sv_alt = nullptr;   // the values of the score sort: old positions
   g10::Cands cd[2] = {};
-  u64 *P = nullptr, *fre = nullptr, *H = nullptr, *px = nullptr, *otc = nullptr, *base0 = nullptr, *g_tot = nullptr,
+  u64 *P = nullptr, *fre = nullptr, *H = nullptr, *px = nullptr, *otc = nullptr, *g_tot = nullptr,
       *g_lazyP = nullptr, *g_minOver = nullptr, *g_lazyH = nullptr, *g_hmax = nullptr, *g_base = nullptr,
       *pressure_after = nullptr,
       *peak_after = nullptr;
