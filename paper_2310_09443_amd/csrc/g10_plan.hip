@@ -789,7 +789,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     u32 *keys = w->keys, *alt = w->keys_alt;
     u32 *from = w->sv, *from_alt = w->sv_alt;          // where every candidate of the new order stood in the old one
     G10_TRY(radix_sort_u32_pairs(&keys, &alt, &from, &from_alt, n, SCORE_SORT_BITS, w->hist, q, true));
-    if (!first) G10_HIP(hipMemsetAsync(w->tkeys, 0, (u64)x.nt * 4, q));
+    if (!first) G10_HIP(hipMemsetAsync(w->tkeys, 0, (u64)NT_MAX * 4, q));
     hipLaunchKernelGGL(k_tile_gather, dim3(x.n_pad / G10_BLOCK), dim3(G10_BLOCK), 0, q, (const u32*)keys, (const u32*)from, n, x.n_pad,
                        cands_of(x, x.cur), cands_of(x, x.cur ^ 1), 8 + x.tsh, w->tkeys);
     G10_HIP(hipGetLastError());
