@@ -69,6 +69,9 @@ __device__ __forceinline__ T dpp_move(T identity, T v) {
   }
 }
 
+// The lanes for which x holds, straight from the comparison (__ballot() takes an integer: a 0 or 1 per lane, compared again).
+__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+
 struct OpAdd { template <class T> static __device__ __forceinline__ T f(T a, T b) { return a + b; } };
 struct OpMax { template <class T> static __device__ __forceinline__ T f(T a, T b) { return a > b ? a : b; } };
 struct OpMin { template <class T> static __device__ __forceinline__ T f(T a, T b) { return a < b ? a : b; } };

@@ -272,7 +272,6 @@ __device__ __forceinline__ u64 row_scan(u64 v) {
   v += dpp_move<0x118, 0xf, 0xf>((u64)0, v);
   return v;
 }
-__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
 __device__ __forceinline__ bool any(bool x) { return ballot(x) != 0; }
 
 template <bool RATIO>

@@ -35,8 +35,6 @@ __device__ __forceinline__ u64 lane_value64(u64 v, u32 l) {      // lane l's v (
   return ((u64)hi << 32) | lo;
 }
 
-__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
-
 // largest value over the lanes: the upper halves first, then the lower ones of the lanes that have it (a maximum of 64-bit
 // values in one go compares and selects at every step of the reduction)
 __device__ __forceinline__ u64 wave_max64(u64 v) {

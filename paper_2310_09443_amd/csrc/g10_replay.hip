@@ -320,7 +320,6 @@ __device__ __forceinline__ double scan_max(double v) {
 __device__ __forceinline__ double scan_sum(double v) { return __longlong_as_double((long long)wave_scan_dpp<OpAddF>((u64)__double_as_longlong(v), (u64)0)); }
 __device__ __forceinline__ double lane_getf(double v, u32 l) { return __longlong_as_double((long long)lane_get((u64)__double_as_longlong(v), l)); }
 __device__ __forceinline__ double lane_anyf(double v, u32 l) { return __longlong_as_double((long long)lane_any((u64)__double_as_longlong(v), l)); }
-__device__ __forceinline__ u64 ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
 // (at: four times the lane)
 __device__ __forceinline__ double lane_at(double v, u32 at) {
   const u64 x = (u64)__double_as_longlong(v);
