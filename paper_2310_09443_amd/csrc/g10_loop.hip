@@ -12,7 +12,7 @@ namespace {
 // Threads of the loop workgroup: a chunk job takes a wavefront, and most rounds have more jobs than seven wavefronts
 // take at once beside the one that picks, so twelve (loops with eight / twelve: ResNet 2.85 / 2.65 ms, ragged stress
 // 4.7 / 4.25, stress 23.6 / 21.3, decoder 3.2 / 3.1, encoder 1.20 / 1.16).  Twelve leave 168 registers each, and the
-// benefit key in the band reading spills four; sixteen leave 128.  The ratio key in the band reading commits one migration
+// benefit key in the band reading spills four (with ROWS seven, with TIGHT six); sixteen leave 128.  The ratio key in the band reading commits one migration
 // a pass, four jobs: eight (its passes with the scoring kernel take 5 % longer with twelve).
 constexpr u32 LOOP_MIN = 512, LOOP_MAX = 768, LW_MAX = LOOP_MAX / G10_WAVE;   // ... least and most, and the most wavefronts
 constexpr u32 loop_threads(bool ratio, bool clip) { return ratio && !clip ? LOOP_MIN : LOOP_MAX; }
@@ -91,7 +91,9 @@ constexpr u32 LISTS_AFTER = 8, LISTS_VAIN = 4, LISTS_PAID = 4, LISTS_MORE_MAX = 
 // Where the chunks are no more than four per wavefront (but the last one) and the picks many, the chunk test takes a row of 16 lanes per chunk and a
 // lane per migration, else a lane per chunk and the migrations one after the other.  (Steps of ResNet, 23 chunks and 12 picks a
 // round 2875 -> 2743 us, encoder 1298 -> 1273, ResNet by the clipped area 3.89 -> 3.44 ms.  With rows wherever 80 chunks fit two turns
-// of them decoder, 49 chunks and 4 picks, 3258 -> 3435, ragged stress, 79 and 12, 5663 -> 5824.)
+// of them decoder, 49 chunks and 4 picks, 3258 -> 3435, ragged stress, 79 and 12, 5663 -> 5824.)  Forms of their own (ROWS), taken where
+// rows can be: in the one form for all, plans that never take them paid for it (plans of one migration a pass: 16.97 -> 16.65 ms on 20 011
+// slots, 7.16 -> 7.03 on the decoder trace).
 constexpr u32 ROW_CHUNKS = (LW_MAX - 1) * 4, ROW_PICKS = 8;
 static_assert(MAXM == 16, "a row of lanes per chunk");
 static_assert(LIST_MIN == G10_WAVE && LIST_MAX % G10_WAVE == 0, "an entry a lane; strips of whole wavefronts");
@@ -128,9 +130,17 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   double all[4];              // free time of each channel behind the picks
   Floor left;
   u32 sel[G10_WAVE], nsel;    // the entries of the list it holds
-  u32 dests[2];               // the round's migrations to flash, to host
   u32 probed;                 // nothing has gone to host since the entries with E_ROOM were looked at
   u32 pick_max, next;         // migrations picked in a round at most; NX_*
+  u32 dests[2];               // the round's migrations to flash, to host
+  // (what the forms with lists added lies here, in place of words that were spare: before the counters below, where the
+  // words that every round uses moved by 32 bytes, the benefit key spilled three registers more: decoder
+  // 3.09 ms instead of 3.08, plans of one migration a pass 7.03 instead of 6.87)
+  // clipped area: the plan's passes make lists, so often it has stopped doing so; this pass does not; lists in vain in a row, or winners
+  // in a row whose area was their band by the chunks alone; migrations and refused candidates when the pass began
+  u32 lists, lists_ended, no_list, in_row;
+  u64 settled0;
+  u32 uneven, paid;           // a chunk of the winner's window has a slot over the capacity by less than its size; lists that gave several
   unsigned char spare[104];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
@@ -141,11 +151,6 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 fast, pad1;             // the pass's migrations were picked from the list without an arg-max over all threads
   u32 lim, pad3;              // the plan has made as many passes as it may
   u32 Fkeep, more;            // the floor of the pass; another round of commits follows from the same list
-  // clipped area: the plan's passes make lists, so often it has stopped doing so; this pass does not; lists in vain in a row, or winners
-  // in a row whose area was their band by the chunks alone; migrations and refused candidates when the pass began
-  u32 lists, lists_ended, no_list, in_row;
-  u64 settled0;
-  u32 uneven, paid;           // a chunk of the winner's window has a slot over the capacity by less than its size; lists that gave several
   u64 more_rounds, list_rescored;   // such rounds made; list entries scored again for them (statistics)
   u64 hq;                     // host-capacity query: maximum over the period
   u64 acc[3];                 // clipped area being summed: bits 0..31, 32..63 and 64.. of the terms, added apart
@@ -297,7 +302,8 @@ __host__ __device__ __forceinline__ u32 list_cap(u32 nch, u32 nt) {
 // own because what it adds to the chunk test, the picks and the commit costs the others 3 to 4 % (18 us a round, 0.6 more).
 // LISTS: the form of the clipped area that commits several migrations a pass, for plans whose winners' areas are their bands
 // (LISTS_AFTER).
-template <bool RATIO, bool CLIP, bool TIGHT, bool LISTS>
+// ROWS: with the chunk test by rows of lanes (ROW_CHUNKS).
+template <bool RATIO, bool CLIP, bool TIGHT, bool LISTS, bool ROWS>
 __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopArgs* __restrict__ plans) {
   constexpr u32 LB = loop_threads(RATIO, CLIP), LW = LB / G10_WAVE;    // threads and wavefronts of this form
   // Several migrations per ranking pass (ranking by the benefit itself): after the
@@ -310,6 +316,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   constexpr bool MC = !RATIO && (!CLIP || LISTS);
   static_assert((MC && !CLIP) || !TIGHT, "several migrations a pass");
   static_assert((MC && CLIP) || !LISTS, "several migrations a pass");
+  static_assert(MC || !ROWS, "rows of lanes take a list's migrations");
   static_assert(sizeof(Winner) * LW_MAX >= ROW_CHUNKS * sizeof(uint4), "the chunk test's results");
   constexpr bool WIDE = RATIO && !CLIP;        // long scoring rounds may be left to the scoring kernel (see WideCtx)
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1627,7 +1634,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     // from the list scored again.  (A further round's picking took 4 to 5 us for two or three migrations while it
     // stopped at the first window that met another; now 5 to 9 for eight to twelve, half of them beside the jobs.)
     bool opened = false;                                 // the next pass's state is made
-    bool owed = true;                                    // no migration or refused candidate stands for the pass yet
+    bool owed = true;                                    // no migration or refused candidate stands for the pass yet (kept by TIGHT; the other forms commit in a pass's first round)
     PrefixView pv; pv.px = tl.px; pv.base = base; pv.K = K; pv.nch = nch; pv.shift_ch = tl.shift_ch;
     for (u32 cround = 0;; ++cround) {
     const u32 tid = thread_here(), lane = tid & 63u;
@@ -1648,7 +1655,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         const Entry e = load_entry(slot);
         const u32 m = pick(e, slot, fl, F, allowed, true, cround & 1u);
         if (lane == 0) S->left = fl;
-        if (m == 0u) open_pass(owed);                    // (nothing on the list clears the floor, or the bounds left out: the pass is over)
+        if (m == 0u) open_pass(TIGHT && owed);           // (nothing on the list clears the floor, or the bounds left out: the pass is over)
       }
       __syncthreads();
     } else if (MC && !cround && !uniform(S->fast)) {     // the winner of the arg-max alone; the list goes on in the next round
@@ -1703,7 +1710,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       else M.tau_i = tau;
     }
     if (tid == 0) { S->jnext = LW - 1; S->touched = 0; S->ot_changed = 0; }
-    const bool rows = MC && picked && nch <= ROW_CHUNKS && m0 >= ROW_PICKS;
+    const bool rows = ROWS && picked && m0 >= ROW_PICKS;
     uint4* const bits = (uint4*)S->wave_win;             // (free between two rankings) per chunk: allP | cutP << 16, eF | wF << 16, allH | cutH << 16, eH | wH << 16
     if (rows && wave < LW - 1) {
       // Few chunks: a row of 16 lanes per chunk, a migration per lane, over all wavefronts but the one that writes the picks out.
@@ -1881,7 +1888,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       continue;
     }
     if (MC && !TIGHT && cround && need_exact) break;     // (the exact host-memory test is left to the next ranking pass)
-    if (!owed) ++used;                                   // (rounds that commit something: a launch's budget is bounded by the candidates)
+    const bool first = TIGHT ? owed : cround == 0u;
+    if (!first) ++used;                                  // (rounds that commit something: a launch's budget is bounded by the candidates)
     if (need_exact && !looked_up) {                   // the winner alone; host memory slot by slot where its period cuts a chunk
       m = 1;
       const u64 s = S->mem[0].s;
@@ -1945,7 +1953,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           lkey[M.slot] = 0u; list_ot(M.slot, 0) = NONE64; list_ot(M.slot, 1) = NONE64;
         }
         if (refused) {
-          g10_dropped dr; dr.iteration = S->n_iter - (owed ? 1u : 0u) + lane; dr.cand = M.cand; dr.reserved = 0;
+          g10_dropped dr; dr.iteration = S->n_iter - (first ? 1u : 0u) + lane; dr.cand = M.cand; dr.reserved = 0;
           a.dropped[at_d] = dr;
         } else {
           g10_migration mg;
@@ -1966,7 +1974,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         // doubles when a pass ran out of candidates above the floor with little scored
         u32 gs = S->gshift;
         const bool listed = MC && !(LISTS && S->no_list);
-        if (!owed) {
+        if (!first) {
           // (the margin adapts once per ranking pass)
         } else if (WIDE && a.wide_min) {
           // with the scoring kernel a longer list costs little and a second round a pair of launches:
@@ -1979,7 +1987,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         else if (listed) { if ((S->by_floor || rounds > 1u) && pass_units <= 18u && gs > MC_GUESS_SHIFT_MIN) --gs; }
         else if (rounds > 1u && pass_units <= 2u && gs > GUESS_SHIFT) --gs;
         S->gshift = gs;
-        if (listed && owed) {
+        if (listed && first) {
           const u32 nl_ = S->nlist;
           const int pub = S->pub, mag = pub < 0 ? -pub : pub;
           int x = pub;
@@ -2002,9 +2010,9 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         else {
           // the passes of Algorithm 1 this round stands for beyond the one the ranking pass counted
           // at its top (a later round: all of its own), each with one live candidate fewer to rank
-          const u64 x = owed ? m - 1 : m, live = C - nm - nd;
+          const u64 x = first ? m - 1 : m, live = C - nm - nd;
           S->n_mig = nm + m - (u32)__popc(drops); S->n_drop = nd + (u32)__popc(drops); S->n_iter += x;
-          S->n_evals += owed ? x * live - x * (x + 1) / 2 : x * live - x * (x - 1) / 2;
+          S->n_evals += first ? x * live - x * (x + 1) / 2 : x * live - x * (x - 1) / 2;
           if (TIGHT && hosts) S->probed = 0;
           // another round of commits from the same list: unless the picking ran out of entries above
           // the floor and every one it picked was committed
@@ -2012,12 +2020,12 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           S->more = more ? 1u : 0u;
           // (where the chunks cut a round short the next one picks little more than went through)
           if (MC) { const u32 pm = S->pick_max; S->pick_max = m < m0 ? (m + 2u < MAXM ? m + 2u : MAXM) : m0 == pm ? (2u * pm < MAXM ? 2u * pm : MAXM) : pm; }
-          if (!owed) S->more_rounds += 1;
+          if (!first) S->more_rounds += 1;
           if (LISTS && picked) S->evals += m;              // (areas shown to be their bands)
         }
       }
     }
-    owed = false;
+    if (TIGHT) owed = false;
     if (!room) { __syncthreads(); break; }
     if (MC && wave == LW - 1) {
       // Beside the jobs the last wavefront picks the next round's migrations: it knows the channels as this round leaves
@@ -2080,7 +2088,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     }                                                    // (rounds of commits of one ranking pass)
     if (!opened) {                                       // (a refused candidate, or a test left to the next pass)
       __syncthreads();
-      if (wave == LW - 1) open_pass(owed);
+      if (wave == LW - 1) open_pass(TIGHT && owed);
       __syncthreads();
     }
   }
@@ -2258,10 +2266,14 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch) {
 }
 
 typedef void (*LoopKernel)(const LoopArgs*);
-static LoopKernel loop_kernel(u32 rank, u32 area, bool second) {
-  if (rank == G10_RANK_RATIO) return area == G10_AREA_CLIPPED ? k_loop<true, true, false, false> : k_loop<true, false, false, false>;
-  if (area == G10_AREA_CLIPPED) return second ? k_loop<false, true, false, true> : k_loop<false, true, false, false>;
-  return second ? k_loop<false, false, true, false> : k_loop<false, false, false, false>;
+static LoopKernel loop_kernel(u32 rank, u32 area, bool second, bool rows) {
+  if (rank == G10_RANK_RATIO) return area == G10_AREA_CLIPPED ? k_loop<true, true, false, false, false> : k_loop<true, false, false, false, false>;
+  if (area == G10_AREA_CLIPPED) {
+    if (!second) return k_loop<false, true, false, false, false>;
+    return rows ? k_loop<false, true, false, true, true> : k_loop<false, true, false, true, false>;
+  }
+  if (second) return rows ? k_loop<false, false, true, false, true> : k_loop<false, false, true, false, false>;
+  return rows ? k_loop<false, false, false, false, true> : k_loop<false, false, false, false, false>;
 }
 
 int loop_allow_large_lds() {                     // (once per device: the attribute belongs to the kernel, not to a handle)
@@ -2271,14 +2283,17 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
   if (dev >= 0 && dev < 64 && done[dev]) return G10_OK;
   for (u32 rank = 0; rank < 2; ++rank)
     for (u32 area = 0; area < 2; ++area)
-      for (u32 second = 0; second < 2; ++second)
-        G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area, second != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
+      for (u32 form = 0; form < (rank == G10_RANK_RATIO ? 1u : 4u); ++form)
+        G10_HIP(hipFuncSetAttribute((const void*)loop_kernel(rank, area, (form & 1u) != 0, (form & 2u) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
   if (dev >= 0 && dev < 64) done[dev] = true;
   return G10_OK;
 }
 
-int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, hipStream_t s) {
-  hipLaunchKernelGGL(loop_kernel(rank, area, second), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
+// (a plan whose largest tensor is beyond PICK_EXACT commits one migration a pass and never takes rows)
+bool loop_rows(u32 nch, u64 smax) { return nch <= ROW_CHUNKS && smax < PICK_EXACT / 1000; }
+
+int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, bool rows, hipStream_t s) {
+  hipLaunchKernelGGL(loop_kernel(rank, area, second, rows), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);
   G10_HIP(hipGetLastError());
   return G10_OK;
 }

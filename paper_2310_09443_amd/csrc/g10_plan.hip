@@ -901,6 +901,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   for (u32 i = 0; i < count; ++i) longest = I[i].n_valid > longest ? I[i].n_valid : longest;
   const u64 batch_ticks = longest > BATCH_LONG_LIST ? 2 * BATCH_LAUNCH_TICKS : BATCH_LAUNCH_TICKS;
   const bool timed_loop = n_active != 0;
+  const bool rows = loop_rows(I[0].w->nch, h->max_size);   // (the same for all plans of a handle)
   // The results of a finished plan: the pressure with the lazy adds applied and its peak, then the
   // copies to one block of pinned host memory (so that they run as plain DMA), grown when a plan
   // needs more.  In a batch they go out on the plan's own stream as soon as the plan is done, beside
@@ -990,13 +991,13 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
       // nothing left to do), so about this many reach the round's last pass; one more launch ends the pass the last
       // pair may have left open
       for (u32 g = 0; g < hargs[0].pass_budget; ++g) {
-        G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], s));
+        G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], false, s));
         G10_TRY(loop_wide_launch((const LoopArgs*)h->loop_args, hargs[0].memo != nullptr, s));
       }
-      G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], s));
+      G10_TRY(loop_launch((const LoopArgs*)h->loop_args, 1, lds, 1u, 0u, second[1], false, s));
     } else
     for (u32 kind = 0, first = 0; kind < 4; first += n_by_kind[kind], ++kind)
-      if (n_by_kind[kind]) G10_TRY(loop_launch((const LoopArgs*)h->loop_args + first, n_by_kind[kind], lds, kind & 1u, kind >> 1, second[kind], s));
+      if (n_by_kind[kind]) G10_TRY(loop_launch((const LoopArgs*)h->loop_args + first, n_by_kind[kind], lds, kind & 1u, kind >> 1, second[kind], rows, s));
     if (na > 1) {
       hipLaunchKernelGGL(k_ctl_collect, dim3(na), dim3(G10_WAVE), 0, s, (const LoopArgs*)h->loop_args, ctl_side);
       G10_HIP(hipGetLastError());

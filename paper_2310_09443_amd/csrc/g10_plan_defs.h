@@ -439,4 +439,6 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candi
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
 int loop_wide_launch(const g10::LoopArgs* plans, bool kept, hipStream_t s);   // the scoring kernel for plans[0]; kept: with its memo
-int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, hipStream_t s);   // all of one ranking key and benefit reading; second: in the form for plans that refuse candidates, or (clipped area) with lists
+bool loop_rows(u32 nch, u64 smax);                            // a plan of nch chunks and tensors of up to smax bytes goes in a form with the chunk test by rows of lanes
+// plans of one ranking key and benefit reading; second: in the form for plans that refuse candidates, or (clipped area) with lists
+int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, bool rows, hipStream_t s);
