@@ -111,6 +111,10 @@ enum { LE_A = 0, LE_B = 1, LE_I = 2, LE_OT = 3, LE_O0 = 4, LE_I0 = 5, LE_O1 = 6,
 // traces (many candidates of a repeated layer lie within the eighth under the last benefit).
 constexpr int PUB_START = 1 << 22, PUB_MIN = -(1 << 23), PUB_MAX = 1 << 30;
 
+// Beside the number of jobs, while an area is settled: some chunk has a slot over the capacity by less than the tensor's size.
+constexpr u32 UNEVEN = 1u << 16;
+static_assert(6 * NCH_MAX + 8 < UNEVEN, "the jobs of a round");
+
 enum { NX_RESCORE = 0, NX_PICKED = 1 };   // how a further round of a pass begins: the list scored again; its migrations picked already
 
 struct Floor {                // bound of the list's entries that the picking wavefront does not hold (see choose)
@@ -140,7 +144,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   // in a row whose area was their band by the chunks alone; migrations and refused candidates when the pass began
   u32 lists, lists_ended, no_list, in_row;
   u64 settled0;
-  u32 uneven, paid;           // a chunk of the winner's window has a slot over the capacity by less than its size; lists that gave several
+  u32 paid, pad2;             // lists that gave several
   unsigned char spare[104];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
@@ -424,8 +428,9 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->pub = ctl->pub ? ctl->pub : PUB_START;      // (0: not set yet; a margin of 0 starts over)
     S->nl = 0; S->restL = NONE32; S->stale_hot = 0; S->pick_max = MAXM;
     S->stop = 0; S->t_start = wall_clock64();
-    S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->uneven = 0; S->paid = 0;   // (the launch opens a pass: no list in vain yet)
+    S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->paid = 0;   // (the launch opens a pass: no list in vain yet)
     S->settled0 = ctl->n_mig + ctl->n_drop;
+    S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0;
     S->mem[0].hi = 0; S->mem[0].lo = 0;
   }
   __syncthreads();
@@ -1315,20 +1320,17 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
   // size x over-capacity time, the others are summed slot by slot.  Returns true when the
   // winner stands (or nothing is left).  If the area comes out below the bound it is
   // remembered with the candidate and false is returned: the tiles scored in this pass are
-  // then listed again (alist) and must be ranked once more.
-  auto settle = [&]() -> bool {
-    __syncthreads();
+  // then listed again (alist) and must be ranked once more.  (Four barriers; with three more, and words of their own for
+  // what the number of jobs carries, an area cost 0.3 us more, 3 % of plans in which most come out below.)
+  auto settle = [&]() -> bool {                        // (called behind the barrier that ends reduce_best, or a later one)
     if ((S->mem[0].hi | S->mem[0].lo) == 0 || S->mem[0].exact) return true;
     const u32 wa = S->mem[0].a, wb = S->mem[0].b;
     const u64 s = S->mem[0].s;
-    if (tid == 0) { S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0; S->njobs = 0; S->jnext = LW - 1; }
-    __syncthreads();
-    if (tid < nch) {
+    if (tid < nch) {                                   // (no job is listed and the sums are zero: open_pass, and below)
       u32 len = 0;
       const u32 cv = cover(tid, CH, K, wa, wb, len);
       if (cv) {
         const u64 mo = minOver[tid];
-        if (mo != NONE64 && mo - cap < s) S->uneven = 1;
         if (cv == len && mo == NONE64) {
           // no slot of the chunk is over the capacity
         } else if (cv == len && mo - cap >= s) {
@@ -1337,36 +1339,37 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           atomicAdd((unsigned long long*)&S->acc[1], (unsigned long long)(lo >> 32));
           atomicAdd((unsigned long long*)&S->acc[2], (unsigned long long)__umul64hi(s, t));
         } else {
-          jobs[atomicAdd(&S->njobs, 1u)] = ((u64)J_CLIP << 16) | tid;
+          const u32 one = mo != NONE64 && mo - cap < s ? 1u | UNEVEN : 1u;
+          jobs[atomicAdd(&S->njobs, one) & (UNEVEN - 1u)] = ((u64)J_CLIP << 16) | tid;
         }
       }
     }
     __syncthreads();
-    const bool even = !uniform(S->uneven);
-    if (!even) run_jobs(0u, uniform(S->njobs), 0xffffu, 0u);     // (else the area is the band: nothing is summed)
+    const u32 nj = uniform(S->njobs);
+    const bool even = nj < UNEVEN;                     // (the area is the band: nothing is summed)
+    if (!even) run_jobs(0u, nj & (UNEVEN - 1u), 0xffffu, 0u);
     __syncthreads();
     const u64 a0 = S->acc[0], a1 = S->acc[1], a2 = S->acc[2];
     const u64 vlo = a0 + (a1 << 32), vhi = a2 + (a1 >> 32) + (vlo < a0 ? 1ull : 0ull);
     const bool same = even || (vhi == S->mem[0].hi && vlo == S->mem[0].lo);
-    __syncthreads();                                   // everyone has read the sums and the bound
-    if (tid == 0) {
+    if (tid == 0) {                                    // (words that nobody reads before the next barrier)
       S->evals += 1;
-      S->njobs = 0;
-      if (!RATIO && !S->lists) {
-        S->in_row = even ? S->in_row + 1u : 0u;
-        if (C - S->n_mig - S->n_drop >= LISTS_LEFT && S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX)) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
+      S->njobs = 0; S->jnext = LW - 1;
+      if (!RATIO && (!LISTS || !S->lists)) {
+        if (!even) S->in_row = 0;
+        else if (++S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX) && C - S->n_mig - S->n_drop >= LISTS_LEFT) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
       }
-      S->uneven = 0;
       if (same) S->mem[0].exact = 1;
       else {
         S->refused += 1;
-        S->no_list = 1;                                // (the tiles scored again are not listed again)
+        if (LISTS) S->no_list = 1;                     // (the tiles scored again are not listed again)
         a.cd.cv[S->mem[0].pos] = make_uint4((u32)vlo, (u32)(vlo >> 32), (u32)vhi, (u32)(vhi >> 32));
         a.cd.ce[S->mem[0].pos] = make_uint2((u32)S->n_iter, 1u | (S->mem[0].dest << 1));
         S->ntl = 0;
       }
     }
-    __syncthreads();
+    __syncthreads();                                   // everyone has read the sums
+    if (tid == 0) { S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0; }
     if (same) return true;
     for (u32 g = tid; g < ns; g += LB) {               // every tile scored in this pass, once more
       u64 m = smark[g];
@@ -1390,6 +1393,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     if (lane == 0) {
       if (TIGHT && undo) { S->n_iter -= 1; S->n_evals -= C - S->n_mig - S->n_drop; }
       S->hq = 0; S->njobs = 0; S->ntl = 0; S->filt = 0;
+      if (CLIP) S->jnext = LW - 1;
       S->mem[0].hi = 0; S->mem[0].lo = 0;
       S->nlist = 0; S->F2 = 0; S->fast = 0; S->cut = MAXM; S->need_exact = 0; S->by_floor = 0;
       if (S->stale_hot) { S->restL = NONE32; S->stale_hot = 0; }
