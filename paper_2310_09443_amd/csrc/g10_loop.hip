@@ -82,12 +82,16 @@ constexpr u32 MC_GUESS_SHIFT_MIN = 2;   // the widest margin of a pass's first t
 // (Ranking passes of a plan with 64 in all / with 256 and the choice: ResNet 240 / 25, decoder 186 / 70, stress 500 / 160.)
 constexpr u32 LIST_MIN = 64, LIST_MAX = 256, LIST_VECS = 8, LIST_ENTRY = LIST_VECS * 16 + 8;
 // A plan by the clipped area goes on in the form with lists once LISTS_AFTER winners in a row had their band as their area, shown by
-// the chunks alone, and LISTS_LEFT periods are left; it leaves that form after LISTS_VAIN lists in a row that gave one migration
-// at most, to come back after twice as many winners each time, but where LISTS_PAID lists had given several.  (Another launch is
-// 25 us, a list in vain 8; a pass of the form with lists without one takes 2 us more than one of the other: registers.  With one
-// form for both, lists tried less and less often, plans of 20 to 60 passes took 10 to 13 % more.  ResNet, 1638 migrations,
-// after 8 winners and 4 lists 4.3 ms, 10 and 3 5.5, 10 and 2 6.8; in the form with lists alone 3.4; one migration a pass 17.6.)
-constexpr u32 LISTS_AFTER = 8, LISTS_VAIN = 4, LISTS_PAID = 4, LISTS_MORE_MAX = 7, LISTS_LEFT = 128;
+// the chunks alone; it leaves that form after LISTS_VAIN lists in a row that gave one migration at most, to come back after twice
+// as many winners each time, but where LISTS_PAID lists had given several.  (Another launch is 25 us, a list in vain 8; a pass of
+// the form with lists without one takes 2 us more than one of the other, and an area settled in it 0.4: registers.  With one form
+// for both, lists tried less and less often, plans of 20 to 60 passes took 10 to 13 % more.  ResNet, 1622 migrations, after 8
+// winners and 4 lists 3.4 ms, one migration a pass 17.8.)
+// It stays where LISTS_LEFT periods - with a window or without one - are not left, which keeps the smallest traces out, and where its
+// limit leaves it less than LISTS_PASSES passes.  (Twelve passes gain 120 us if the lists pay, and a change that does not costs 80.
+// Plans of 20 passes that changed with less left / stay: ResNet at 0.6 of its peak 882 / 865 us, 90 slots 335 / 306, 2000 slots
+// 510 / 492.)
+constexpr u32 LISTS_AFTER = 8, LISTS_VAIN = 4, LISTS_PAID = 4, LISTS_MORE_MAX = 7, LISTS_LEFT = 128, LISTS_PASSES = 12;
 // Where the chunks are no more than four per wavefront (but the last one) and the picks many, the chunk test takes a row of 16 lanes per chunk and a
 // lane per migration, else a lane per chunk and the migrations one after the other.  (Steps of ResNet, 23 chunks and 12 picks a
 // round 2875 -> 2743 us, encoder 1298 -> 1273, ResNet by the clipped area 3.89 -> 3.44 ms.  With rows wherever 80 chunks fit two turns
@@ -1357,7 +1361,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       S->njobs = 0; S->jnext = LW - 1;
       if (!RATIO && (!LISTS || !S->lists)) {
         if (!even) S->in_row = 0;
-        else if (++S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX) && C - S->n_mig - S->n_drop >= LISTS_LEFT) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
+        else if (++S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX) && C - S->n_mig - S->n_drop >= LISTS_LEFT && (!max_iter || max_iter - S->n_iter >= LISTS_PASSES)) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
       }
       if (same) S->mem[0].exact = 1;
       else {

@@ -124,3 +124,19 @@ def test_chunk_test_of_few_and_many_chunks(g10, K, N, max_chunks, host):
         p = v.plan(max_iters=600, **a)
         assert_plan_equal(h.plan(max_iters=600, max_chunks=max_chunks, **a), p)
     h.close()
+
+
+def test_no_change_of_form_near_the_limit(g10):
+    """A plan by the clipped area whose limit leaves it a few passes stays in the form it is in (a change is another launch)."""
+    w = traces.stress(K=90, N=300)
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * 0.3), host_cap=int(v.peak * 0.25), bw_out=(12000, 25000), bw_in=(12000, 25000), area=1)
+    p = v.plan(**a)
+    r = h.plan(**a)
+    assert_plan_equal(r, p)
+    assert r.loop_launches > 1 and r.loop_more_rounds > 0          # it changes where nothing limits it
+    for limit in (10, 13, 16):
+        r = h.plan(max_iters=limit, **a)
+        assert_plan_equal(r, v.plan(max_iters=limit, **a))
+        assert r.n_iterations == limit and r.loop_launches == 1
+    h.close()
