@@ -148,7 +148,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   // in a row whose area was their band by the chunks alone; migrations and refused candidates when the pass began
   u32 lists, lists_ended, no_list, in_row;
   u64 settled0;
-  u32 paid, pad2;             // lists that gave several
+  u32 paid, alone;            // lists that gave several; a change of form ends the launch (LoopArgs)
   unsigned char spare[104];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->pub = ctl->pub ? ctl->pub : PUB_START;      // (0: not set yet; a margin of 0 starts over)
     S->nl = 0; S->restL = NONE32; S->stale_hot = 0; S->pick_max = MAXM;
     S->stop = 0; S->t_start = wall_clock64();
-    S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->paid = 0;   // (the launch opens a pass: no list in vain yet)
+    S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->paid = 0; S->alone = a.alone;   // (the launch opens a pass: no list in vain yet)
     S->settled0 = ctl->n_mig + ctl->n_drop;
     S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0;
     S->mem[0].hi = 0; S->mem[0].lo = 0;
@@ -1361,7 +1361,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
       S->njobs = 0; S->jnext = LW - 1;
       if (!RATIO && (!LISTS || !S->lists)) {
         if (!even) S->in_row = 0;
-        else if (++S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX) && C - S->n_mig - S->n_drop >= LISTS_LEFT && (!max_iter || max_iter - S->n_iter >= LISTS_PASSES)) { S->lists = 1; S->in_row = 0; if (!LISTS) S->stop = 1; }
+        else if (++S->in_row >= LISTS_AFTER << (S->lists_ended < LISTS_MORE_MAX ? S->lists_ended : LISTS_MORE_MAX) && C - S->n_mig - S->n_drop >= LISTS_LEFT && (!max_iter || max_iter - S->n_iter >= LISTS_PASSES)) { S->lists = 1; S->in_row = 0; if (!LISTS && S->alone) S->stop = 1; }
       }
       if (same) S->mem[0].exact = 1;
       else {
@@ -1407,8 +1407,9 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           if (settled - S->settled0 > 1u) { S->in_row = 0; S->paid += 1; }
           else S->in_row += 1;
           if (S->in_row >= LISTS_VAIN) {                   // (the other form goes on)
-            S->lists = 0; S->in_row = 0; S->stop = 1;
-            S->lists_ended = S->paid >= LISTS_PAID ? 0u : S->lists_ended + 1u;
+            S->lists = 0; S->in_row = 0;
+            if (S->alone) S->stop = 1;
+            S->lists_ended = S->paid >= LISTS_PAID ? 0u : S->lists_ended + 1u; S->paid = 0;
           }
         }
         S->no_list = S->lists ? 0u : 1u; S->settled0 = settled;
@@ -2013,7 +2014,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         S->thr_key = RATIO ? rkey_dn(ratio_approx(Z.hi, Z.lo, Z.cost) * (1.0 - 1.0 / (double)(1u << gs))) : upkey(ghi, nlo);
         if (!room) {
           S->n_drop = nd + 1; S->more = 0;
-          if (MC && !CLIP && !TIGHT && nd + 1 >= TIGHT_FROM) S->stop = 1;           // (the form for it goes on)
+          if (MC && !CLIP && !TIGHT && nd + 1 >= TIGHT_FROM && S->alone) S->stop = 1;           // (the form for it goes on)
         }
         else {
           // the passes of Algorithm 1 this round stands for beyond the one the ranking pass counted

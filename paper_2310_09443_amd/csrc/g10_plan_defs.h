@@ -299,6 +299,7 @@ struct LoopArgs {
   g10_dropped* dropped;
   u32 pass_budget;            // the launch ends after this many passes,
   u64 tick_budget;            // or (if not 0) after this many ticks of the 100 MHz wall clock,
+  u32 alone;                  // or (if not 0) where the plan goes on better in another form of the kernel,
   u64 pass_stop;              // or (if not 0) once the plan has made this many passes over all its launches
   // Scoring rounds left to all compute units (ranking by benefit / cost, band reading; else null):
   // the block of loop_wide_bytes() bytes the loop kernel and the scoring kernel talk through, and

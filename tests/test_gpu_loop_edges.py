@@ -140,3 +140,35 @@ def test_no_change_of_form_near_the_limit(g10):
         assert_plan_equal(r, v.plan(max_iters=limit, **a))
         assert r.n_iterations == limit and r.loop_launches == 1
     h.close()
+
+
+def test_change_of_form_in_a_batch(g10):
+    """Beside other plans a plan ends its launch for the first change of form only: it is not held at every one until theirs end."""
+    w = traces.stress(K=600, N=2600)
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * 0.4), host_cap=int(v.peak * 0.25), bw_out=(12000, 25000), bw_in=(12000, 25000), area=1)
+    p = v.plan(**a)
+    r = h.plan(**a)
+    assert_plan_equal(r, p)
+    assert r.loop_launches > 2                         # (alone: a launch for every change)
+    for r in h.plan_batch([a, a]):
+        assert_plan_equal(r, p)
+        assert r.loop_launches == 2                    # (1.5 ms; a launch may take 2)
+    h.close()
+
+
+def test_batch_of_all_forms(g10):
+    """Both keys, both readings, plans that refuse candidates and plans with lists: launches side by side, several of each."""
+    w = traces.encoder12()
+    h, v, args = run_both(g10, w)
+    tight = dict(args, gpu_cap=int(v.peak * 0.3), host_cap=int(v.peak * 0.004), bw_out=(400, 25000), bw_in=(400, 25000))
+    clip = dict(args, gpu_cap=int(v.peak * 0.6), area=1)
+    ps = [clip, tight, dict(args), dict(args, rank=1, max_iters=300), dict(clip, rank=1, max_iters=40), dict(clip, gpu_cap=int(v.peak * 0.9), max_iters=40),
+          dict(tight, host_cap=0), dict(tight, area=1, max_iters=30)]
+    want = [v.plan(**dict(a, max_iters=a.get("max_iters", 2 ** 64 - 1))) for a in ps]
+    for _ in range(2):
+        rs = h.plan_batch(ps)
+        for r, p in zip(rs, want):
+            assert_plan_equal(r, p)
+    assert rs[1].loop_launches > 1 and rs[1].loop_passes < len(want[1].records) + len(want[1].null_cands)      # (it refuses several a round)
+    h.close()
