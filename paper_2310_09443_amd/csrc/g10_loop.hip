@@ -149,7 +149,9 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u32 lists, lists_ended, no_list, in_row;
   u64 settled0;
   u32 paid, alone;            // lists that gave several; a change of form ends the launch (LoopArgs)
-  unsigned char spare[104];   // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
+  u64 tight_at;               // refused candidates from which the plan goes on in the form for them (Ctl)
+  u32 calm, pad2;             // rounds in a row of that form without one
+  unsigned char spare[88];    // (free: with it 7899 tiles fill the LDS beside 512 chunks, see loop_tile_shift)
   u32 wave_f2[LW_MAX];        // per wavefront: largest bound among the candidates its threads scored but do not hold
   u32 F2, pad0;               // ... over the workgroup
   u32 nlist, m0, cut, need_exact;   // list length; migrations selected; how many of them may be committed; the winner's
@@ -434,6 +436,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     S->stop = 0; S->t_start = wall_clock64();
     S->lists = CLIP ? ctl->lists : 0u; S->lists_ended = ctl->lists_ended; S->no_list = LISTS && S->lists ? 0u : 1u; S->in_row = LISTS && S->lists ? NONE32 : 0u; S->paid = 0; S->alone = a.alone;   // (the launch opens a pass: no list in vain yet)
     S->settled0 = ctl->n_mig + ctl->n_drop;
+    if (TIGHT) { S->tight_at = ctl->tight_at; S->calm = ctl->calm; }
     S->acc[0] = 0; S->acc[1] = 0; S->acc[2] = 0;
     S->mem[0].hi = 0; S->mem[0].lo = 0;
   }
@@ -2014,7 +2017,8 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
         S->thr_key = RATIO ? rkey_dn(ratio_approx(Z.hi, Z.lo, Z.cost) * (1.0 - 1.0 / (double)(1u << gs))) : upkey(ghi, nlo);
         if (!room) {
           S->n_drop = nd + 1; S->more = 0;
-          if (MC && !CLIP && !TIGHT && nd + 1 >= TIGHT_FROM && S->alone) S->stop = 1;           // (the form for it goes on)
+          if (TIGHT) S->calm = 0;
+          else if (picks && !CLIP && nd + 1 >= TIGHT_FROM && S->alone) S->stop = 1;           // (the form for it goes on)
         }
         else {
           // the passes of Algorithm 1 this round stands for beyond the one the ranking pass counted
@@ -2023,6 +2027,14 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
           S->n_mig = nm + m - (u32)__popc(drops); S->n_drop = nd + (u32)__popc(drops); S->n_iter += x;
           S->n_evals += first ? x * live - x * (x + 1) / 2 : x * live - x * (x - 1) / 2;
           if (TIGHT && hosts) S->probed = 0;
+          if (TIGHT) {
+            const u32 calm = drops ? 0u : S->calm + 1u;
+            S->calm = calm;
+            if (calm >= TIGHT_CALM && S->tight_at <= nd) {                          // (the other form goes on)
+              S->tight_at = nd + 1; S->calm = 0;
+              if (S->alone) S->stop = 1;
+            }
+          }
           // another round of commits from the same list: unless the picking ran out of entries above
           // the floor and every one it picked was committed
           const bool more = MC && S->nlist > 1u && picks && listed && (!S->by_floor || m < m0) && !(max_iter && S->n_iter >= max_iter);
@@ -2113,6 +2125,7 @@ __global__ __launch_bounds__(loop_threads(RATIO, CLIP)) void k_loop(const LoopAr
     ctl->thr_key = S->thr_key; ctl->status = S->status; ctl->done = S->done;
     ctl->gshift = S->gshift; ctl->pub = S->pub;
     if (CLIP) { ctl->lists = S->lists; ctl->lists_ended = S->lists_ended; }
+    if (TIGHT) { ctl->tight_at = S->tight_at; ctl->calm = S->calm; }
     ctl->overtime_after = base[(u64)A_OT * nb1 + nch];
     if (WIDE && a.wide) {
       ctl->units_scored = units0 + S->units; ctl->second_rounds = second0 + S->second; ctl->jobs_run = jobs0 + S->jobs;
@@ -2298,8 +2311,9 @@ int loop_allow_large_lds() {                     // (once per device: the attrib
   return G10_OK;
 }
 
-// (a plan whose largest tensor is beyond PICK_EXACT commits one migration a pass and never takes rows)
-bool loop_rows(u32 nch, u64 smax) { return nch <= ROW_CHUNKS && smax < PICK_EXACT / 1000; }
+// A plan whose largest tensor is beyond PICK_EXACT commits one migration a pass: it never takes rows, nor refuses several candidates a round.
+bool loop_picks(u64 smax) { return smax < PICK_EXACT / 1000; }
+bool loop_rows(u32 nch, u64 smax) { return nch <= ROW_CHUNKS && loop_picks(smax); }
 
 int loop_launch(const LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, bool rows, hipStream_t s) {
   hipLaunchKernelGGL(loop_kernel(rank, area, second, rows), dim3(n_plans), dim3(loop_threads(rank == G10_RANK_RATIO, area == G10_AREA_CLIPPED)), lds, s, plans);

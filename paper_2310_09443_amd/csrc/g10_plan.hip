@@ -718,6 +718,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
     }
     hc.max_iter = p->max_iterations;
     hc.rank = p->rank; hc.area = p->area;
+    hc.tight_at = loop_picks(h->max_size) ? TIGHT_FROM : ~0ull;
     hc.C = C;
     hc.smax = h->max_size;
     Timelines& tl = x.tl;
@@ -906,7 +907,7 @@ int plan_batch_run(g10_plan_s* h, const g10_params* params, u32 count, g10_resul
   // 12 000 tensors on 2000 slots 2.46 / 1.85, and 2.88 where no change ends a launch.)
   auto loop_form = [](const Inst& x) -> u32 {
     const bool clipped = x.p->area == G10_AREA_CLIPPED;
-    const bool second = x.p->rank == G10_RANK_BENEFIT && (clipped ? x.hc.lists != 0u : x.hc.n_drop >= TIGHT_FROM);
+    const bool second = x.p->rank == G10_RANK_BENEFIT && (clipped ? x.hc.lists != 0u : x.hc.n_drop >= x.hc.tight_at);
     return 4 * x.p->area + 2 * x.p->rank + (second ? 1u : 0u);
   };
   u32 longest = 0;

@@ -19,9 +19,12 @@ constexpr u32 UNIT = 256;              // candidates scored by four wavefronts a
 constexpr u32 NCH_MAX = 512;           // chunks (level-1 arrays live in LDS)
 constexpr u32 NT_MAX = 8192;           // tiles  (their bounds live in LDS)
 constexpr size_t LDS_MAX = 160 * 1024; // LDS of a compute unit (both limits together are over it: loop_tile_shift)
-// A plan goes on in the loop kernel's form for little host memory from this many refused candidates on: the launch that ends for it
-// costs 25 us, a refused candidate 12 to 15 us in the general form and 1 to 6 in the other.
-constexpr u32 TIGHT_FROM = 8;
+// A plan goes on in the loop kernel's form for little host memory from TIGHT_FROM refused candidates on, leaves it after TIGHT_CALM rounds
+// in a row without one and comes back for the next: the launch that ends for a change costs 25 us, a refused candidate 12 to 15 us
+// in the general form and 1 to 6 in the other, a round 2 to 4 % more in the other.  (A plan of 1275 rounds with twelve refused
+// candidates, all among the first: in the other form to its end 13.65 ms, so 13.35, in the general form alone 13.2.  A plan that
+// commits one migration a pass gains nothing there: 45 000 passes, 31 000 refused, 521 ms there and 501 in the general form.)
+constexpr u32 TIGHT_FROM = 8, TIGHT_CALM = 256;
 constexpr u32 GUESS_SHIFT = 7;                 // first threshold of a pass: last benefit * (1 - 2^-shift), to begin with
 constexpr u32 GUESS_SHIFT_MAX = 24;            // the keys resolve no finer steps
 static_assert(WG >= NCH_MAX, "a thread per chunk");
@@ -48,6 +51,8 @@ struct Ctl {
   u32 n_cand;                 // candidates with a window at the start
   u32 n_live;                 // candidates that could still score at the last re-scoring
   u32 gshift;                 // the guess: first threshold = last best * (1 - 2^-gshift); 0 stands for GUESS_SHIFT
+  u64 tight_at;               // band reading, ranked by benefit: refused candidates from which the plan goes on in the form for them
+  u32 calm, pad0;             // ... rounds in a row of that form without one
   u32 lists, lists_ended;     // clipped area: the plan goes on in the form with lists; so often it has left that form
   int pub;                    // the list's margin under the threshold, in key steps; 0: not set yet
   // statistics
@@ -440,6 +445,7 @@ u32 loop_tile_shift(u64 n, u32 max_tiles, u32 nch);           // tile of n candi
 int loop_allow_large_lds();                                   // more than 64 KB of LDS for the kernel
 size_t loop_wide_bytes();                                     // device memory a plan's loop and the scoring kernel talk through
 int loop_wide_launch(const g10::LoopArgs* plans, bool kept, hipStream_t s);   // the scoring kernel for plans[0]; kept: with its memo
+bool loop_picks(u64 smax);                                    // may a plan with tensors of up to smax bytes commit several migrations a round?
 bool loop_rows(u32 nch, u64 smax);                            // a plan of nch chunks and tensors of up to smax bytes goes in a form with the chunk test by rows of lanes
 // plans of one ranking key and benefit reading; second: in the form for plans that refuse candidates, or (clipped area) with lists
 int loop_launch(const g10::LoopArgs* plans, u32 n_plans, size_t lds, u32 rank, u32 area, bool second, bool rows, hipStream_t s);
