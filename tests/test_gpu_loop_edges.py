@@ -97,8 +97,8 @@ def test_most_chunks_and_most_tiles(g10, K, n):
 @pytest.mark.parametrize("cap,host", [(0.15, 0.02), (0.3, 0.25), (0.6, 0.05), (0.85, 2.0)])
 @pytest.mark.parametrize("K,N", [(90, 300), (257, 1500), (600, 2600)])
 def test_clipped_areas_that_are_their_bands_and_others(g10, K, N, cap, host):
-    """Plans by the clipped area go to the form that commits several migrations a pass and back: excesses above and below the
-    tensors' sizes, refused candidates, limits in the middle of a round; alone and beside a plan that stays in the other form."""
+    """Plans by the clipped area, in the form that commits several migrations a pass where their areas are bands: excesses above and
+    below the tensors' sizes, limits in the middle of a round; alone and beside a plan that stays in the other form."""
     w = traces.stress(K=K, N=N, seed=K + N)
     h, v, args = run_both(g10, w)
     a = dict(args, gpu_cap=int(v.peak * cap), host_cap=int(v.peak * host), area=1)
@@ -123,6 +123,17 @@ def test_chunk_test_of_few_and_many_chunks(g10, K, N, max_chunks, host):
         a = dict(args, gpu_cap=int(v.peak * cap), host_cap=int(v.peak * host))
         p = v.plan(max_iters=600, **a)
         assert_plan_equal(h.plan(max_iters=600, max_chunks=max_chunks, **a), p)
+    h.close()
+
+
+def test_rounds_of_many_picks_on_few_chunks(g10):
+    """23 chunks and, on average, more than the eight migrations a round from which rows of lanes test the chunks."""
+    w = traces.resnet152()
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * 0.4), host_cap=int(v.peak * 0.25), bw_out=(12000, 25000), bw_in=(12000, 25000))
+    r = h.plan(**a)
+    assert_plan_equal(r, v.plan(**a))
+    assert r.n_migrations > 8 * (r.loop_passes + r.loop_more_rounds)
     h.close()
 
 
@@ -171,4 +182,21 @@ def test_batch_of_all_forms(g10):
         for r, p in zip(rs, want):
             assert_plan_equal(r, p)
     assert rs[1].loop_launches > 1 and rs[1].loop_passes < len(want[1].records) + len(want[1].null_cands)      # (it refuses several a round)
+    h.close()
+
+
+@pytest.mark.parametrize("N,flash,host,limit", [(14000, 800, 0.005, 60), (8000, 32000, 0.25, 120)])
+def test_lists_of_the_clipped_area_on_many_chunks(g10, N, flash, host, limit):
+    """46 chunks, more than rows of lanes take: candidates that host memory refuses while the plan makes lists; lists that commit several."""
+    w = traces.stress(K=11600, N=N)
+    h, v, args = run_both(g10, w)
+    a = dict(args, gpu_cap=int(v.peak * 0.3), host_cap=int(v.peak * host), bw_out=(flash, 25000), bw_in=(flash, 25000), area=1, max_iters=limit)
+    p = v.plan(**a)
+    r = h.plan(**a)
+    assert_plan_equal(r, p)
+    assert r.loop_launches >= 3                        # (into the form with lists and out of it)
+    if host < 0.01:
+        assert len(p.null_iters) > 40
+    else:
+        assert r.loop_more_rounds > 0 and r.loop_passes < r.n_iterations
     h.close()

@@ -22,13 +22,27 @@ def test_many_refusals(g10, trace, cap, host, flash):
     a = _args(args, v, cap, host, flash)
     p = v.plan(**a)
     assert len(p.null_cands) > 40
-    assert_plan_equal(h.plan(**a), p)
+    r = h.plan(**a)
+    assert_plan_equal(r, p)
+    assert r.loop_launches > 1 and 2 * r.loop_passes < len(p.records) + len(p.null_cands)      # (in the form for it, several a round)
     # chunks of several strips of 256 slots; one tile
     assert_plan_equal(h.plan(max_tiles=1, max_chunks=2, **a), p)
     # ends in the middle of a round, before and behind the change of form
     first = int(p.null_iters[0])
     for limit in (first + 1, first + 8, first + 9, first + 37):
         assert_plan_equal(h.plan(max_iters=limit, **a), v.plan(max_iters=limit, **a))
+    h.close()
+
+
+def test_many_refusals_on_many_chunks(g10):
+    """46 chunks: room looked up by more chunks than there are wavefronts, periods over all of them."""
+    w = traces.stress(K=11600, N=14000)
+    h, v, args = run_both(g10, w)
+    a = _args(args, v, 0.3, 0.01, 300)
+    p = v.plan(max_iters=1500, **a)
+    r = h.plan(max_iters=1500, **a)
+    assert_plan_equal(r, p)
+    assert len(p.null_cands) > 1000 and 2 * r.loop_passes < 1500
     h.close()
 
 
