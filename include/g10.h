@@ -172,7 +172,7 @@ typedef struct {
                                   have risen                                              */
   uint64_t loop_second_rounds; /* passes that needed a second scoring round            */
   uint64_t loop_chunk_jobs;    /* timeline chunks rewritten slot by slot               */
-  uint64_t loop_area_evals;    /* G10_AREA_CLIPPED: clipped areas summed exactly       */
+  uint64_t loop_area_evals;    /* G10_AREA_CLIPPED: clipped areas found exactly - summed, or shown by the chunks to be their bands */
   uint64_t loop_area_refused;  /* ... of which came out below the bound (ranked again) */
   uint64_t loop_wide_rounds;   /* G10_RANK_RATIO, one plan: scoring rounds of a pass left to the scoring
                                   kernel on all compute units (their candidates count in loop_cands_scored) */

@@ -164,7 +164,7 @@ struct alignas(16) Shared {   // small per-pass state of the loop workgroup
   u64 more_rounds, list_rescored;   // such rounds made; list entries scored again for them (statistics)
   u64 hq;                     // host-capacity query: maximum over the period
   u64 acc[3];                 // clipped area being summed: bits 0..31, 32..63 and 64.. of the terms, added apart
-  u64 evals, refused;         // clipped areas computed; of those, how many came out below the bound
+  u64 evals, refused;         // clipped areas found exactly, summed or shown to be bands; of those, how many came out below the bound
   u32 nl, restL;              // hot list: length; bound of the tiles outside it
   u32 ntl, filt;              // current round: tiles to score; bound of the hot tiles left out
   u32 njobs, jnext, ot_changed, stale_hot;   // jobs listed; the next one that a wavefront takes after its first
@@ -309,7 +309,8 @@ __host__ __device__ __forceinline__ u32 list_cap(u32 nch, u32 nt) {
 }
 
 // TIGHT: the form for plans whose host memory refuses candidates, several of which go in one round (probe_host).  A form of its
-// own because what it adds to the chunk test, the picks and the commit costs the others 3 to 4 % (18 us a round, 0.6 more).
+// own because what it adds to the chunk test, the picks and the commit costs plans without any 1.4 to 2 % (20.93 ms instead of 20.65 on
+// the stress trace), those that commit one migration a pass 3 to 4.  The clipped area and the ratio key refuse one candidate a pass.
 // LISTS: the form of the clipped area that commits several migrations a pass, for plans whose winners' areas are their bands
 // (LISTS_AFTER).
 // ROWS: with the chunk test by rows of lanes (ROW_CHUNKS).
