@@ -32,9 +32,9 @@ BYTES_PER_CAND_MOVED = 20      # what k_score_full itself streams per candidate:
 # HBM traffic of the loop kernel on config 5 from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, scaled by what the
 # same counters read for a 256 MiB copy): profiles/loop_stress_hbm_counters.md has the commands and the sums.  The
 # figures hold for the kernel they were taken on: reported only while the kernel's sources hash to what they did then.
-LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "8acc4cfb5eea55077a87eb112f852ea57f948defd4cc390d2522984930c29f79",
-                           "g10_plan_defs.h": "0c25d5b7de273e7ae90d70be831d9a27fb6c2cb9af69f3557e356914ea7a13c3"},
-                "workload": "config 5", "fetch_bytes_per_plan": 61.8e6, "write_bytes_per_plan": 44.6e6, "launches_per_plan": 12.0}
+LOOP_TRAFFIC = {"sha256": {"g10_loop.hip": "bb00930fef21739f62e5d4f8e6b3520cd74eb69810fb139d07392c6cd0918f02",
+                           "g10_plan_defs.h": "748c436c7beff5ba66cee52c357adf5a77838385680fbf3f43870b1e911d5225"},
+                "workload": "config 5", "fetch_bytes_per_plan": 61.7e6, "write_bytes_per_plan": 44.5e6, "launches_per_plan": 12.0}
 
 
 def loop_traffic_per_launch(config):

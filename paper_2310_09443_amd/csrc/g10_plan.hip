@@ -570,7 +570,7 @@ static PlanWork** work_slot(g10_plan_s* h, u32 i) { return i == 0 ? &h->work : &
 
 // `count` plans on one analysed trace.  The streaming kernels of the plans run one after the
 // other (each fills the chip); the greedy loops run side by side, one workgroup per plan, in
-// one launch per round; between rounds the long candidate lists are put back into score order.
+// one launch per round and form of the kernel; between rounds the long candidate lists are put back into score order.
 typedef void (*ScoreFullKernel)(const uint4*, const u64*, u32, const u64*, u32, u32*, const Ctl*, u32*, u32);
 static ScoreFullKernel score_full_kernel(u32 rank, bool packed) {
   if (packed) return rank == G10_RANK_RATIO ? k_score_full<true, true> : k_score_full<false, true>;
